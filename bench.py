@@ -34,13 +34,6 @@ HBM_PEAK_GBS = 8000.0
 CUS, LANES_PER_CU, CLOCK_GHZ = 256, 64, 2.4
 INT_PEAK_TOPS = CUS * LANES_PER_CU * CLOCK_GHZ / 1000.0   # 32-bit integer VALU ops, 39.3 T/s
 
-# HBM bytes per k_propagate launch (average over the 27 launches of one pair:
-# single sweeps and pipelined sweep pairs), from FETCH_SIZE and WRITE_SIZE
-# counter runs scaled by a plain-copy calibration; the counter runs are
-# summarised in profiles/hotpath_1024x436_hbm_counters.md.  Valid for the
-# k_propagate the summary names only.
-PROPAGATE_HBM_BYTES_PER_LAUNCH = 74.38e6
-
 K, R, R2, Q, EPS, LEAF = 3, 8, 6, 4, 5, 8
 SPARSE_S, SPARSE_E = 50, 4            # section 4: s and e for Sintel
 HEADLINE_SEED = 1000
@@ -74,7 +67,7 @@ def propagate_ops_per_pair(W, H, k, radii, n_prop=4):
 
 def per_point_ops_in_sweep_launches(W, H, k, radii, n_prop=4, n_rs=3):
     """Algorithmic integer ops of the per-point stages that run inside
-    pipelined sweep-pair launches, following the library's pairing: two
+    launches of a sweep pair, for a schedule that pairs them: two
     sweeps of one level with the same horizontal direction hold the random
     search between them (all grid points), and a level's last sweep paired
     with the next level's first holds that level's entry (the carried points,
@@ -433,8 +426,8 @@ def main():
     # timed region: K whole-path steps; the dominant kernel class is bracketed
     # with HIP events on the streams it runs on (library profiling hook), and
     # each of its launches is timed
-    per_field = 9 if args.pipeline else 12
-    ff.ff_profile_begin("propagate", 3 * 16 * args.steps + 8)
+    per_field = 4 * (K + 1)
+    ff.ff_profile_begin("propagate", 3 * per_field * args.steps + 8)
     ms_per_step, per_step, out = time_steps(run, torch, args.steps)
     tot, nl, each = ff.ff_profile_end(each=3 * per_field * args.steps)
     assert m.status() == [0, 0, 0], m.status()
@@ -442,13 +435,11 @@ def main():
 
     # dominant kernel against its roofline (integer VALU: census terms)
     avg_launch_ms = tot / max(nl, 1)
-    ops_per_launch = (propagate_ops_per_pair(W, H, K, (R, R, R2)) +
-                      per_point_ops_in_sweep_launches(W, H, K, (R, R, R2))) / (nl / args.steps)
+    ops_per_launch = propagate_ops_per_pair(W, H, K, (R, R, R2)) / (nl / args.steps)
     achieved = ops_per_launch / (avg_launch_ms / 1000.0) / 1e12
     roof = {"bound": "alu", "achieved": round(achieved, 4), "peak": round(INT_PEAK_TOPS, 2), "unit": "TOP/s",
-            "frac": round(achieved / INT_PEAK_TOPS, 5), "traffic": PROPAGATE_HBM_BYTES_PER_LAUNCH,
-            "traffic_GBps": round(PROPAGATE_HBM_BYTES_PER_LAUNCH / (avg_launch_ms / 1000.0) / 1e9, 2),
-            "kernel": "k_propagate", "avg_launch_ms": round(avg_launch_ms, 4), "launches": nl,
+            "frac": round(achieved / INT_PEAK_TOPS, 5),
+            "kernel": "k_sweep", "avg_launch_ms": round(avg_launch_ms, 4), "launches": nl,
             "ops_per_launch": int(ops_per_launch)}
 
     keep = out["keep"].float().mean().item()
@@ -470,17 +461,17 @@ def main():
         "config": {"workload": "one 1024x436 RGB Sintel-shaped layered pair (seed 1000, 6 layers, translations "
                                "U(+-200) px): descriptors x2, F/B1/B2 fields with kd-trees, two-way consistency "
                                "filter",
-                   "k": K, "r": R, "r2": R2, "R": 1, "leaf": LEAF, "subpel": Q, "eps": EPS,
-                   "band_rows": args.band_rows, "pipelined_sweep_pairs": bool(args.pipeline)},
+                   "k": K, "r": R, "r2": R2, "R": 1, "leaf": LEAF, "subpel": Q, "eps": EPS},
         "roofline": roof,
         "quality": {"F_inlier_rate_epe_lt_3px": round(rate, 4), "kept_fraction": round(keep, 4),
                     "occluded_fraction": round(float(pair.occluded.mean()), 4)},
     }
     if not args.no_secondary:
         line["kernels"] = kernel_table(ff, run, torch, W, H, C, img=img1)
-        if args.pipeline and len(each) >= 3 * per_field:
-            line["level1_sweep"] = level1_sweep(each, per_field, args.steps, W, H, args.band_rows)
-            line["level1_sweep"]["latency_floor"] = latency_floor(ff, torch, dev, line["level1_sweep"])
+        if len(each) >= 3 * per_field:
+            line["sweeps"] = sweep_times(each, per_field, args.steps)
+            line["load_round_trip_ns"] = {"l1": round(load_round_trip_ns(ff, torch, dev, 1 << 12), 1),
+                                          "l2": round(load_round_trip_ns(ff, torch, dev, 1 << 18), 1)}
         line["secondary"] = secondary(ff, torch, dev, pair, skewed, args.steps)
     if batch_pairs is not None:
         line["batch"] = bench_batch(args, ff, batch_pairs, torch, dev, steps=5)
@@ -523,7 +514,7 @@ def kernel_table(ff, run, torch, W, H, C, img=None):
                 row.update(bound="hbm", algorithmic_bytes=ab[c], alone_ms=round(alone[c][0], 4),
                            alone_GBps=round(gba, 1), alone_frac=round(gba / HBM_PEAK_GBS, 4))
         elif per == 0:
-            row["note"] = "no launch of its own: runs inside the pipelined sweep launches"
+            row["note"] = "not launched in this step"
         elif c in ab:
             gbs = ab[c] / (ms / 1000.0) / 1e9
             row.update(bound="hbm", algorithmic_bytes=ab[c], GBps=round(gbs, 1), frac=round(gbs / HBM_PEAK_GBS, 4))
@@ -537,19 +528,17 @@ def kernel_table(ff, run, torch, W, H, C, img=None):
     return table
 
 
-def level1_sweep(each, per_field, steps, W, H, bh):
-    """The last propagation launch of each field is level 1's single sweep
-    (pipelined schedule): its time per wavefront step.  A band starts
-    skew + 2 steps after the band above (the skew of its rows plus two steps
-    of hand-off lookahead) and runs Gw + skew steps."""
-    sweeps = [each[s * 3 * per_field + f * per_field + per_field - 1] for s in range(steps) for f in range(3)]
-    ms = statistics.median(sweeps)
-    bands = (H + bh - 1) // bh
-    skew = bh - 1 + (bh - 1) // 4
-    wave_steps = W + skew + (skew + 2) * (bands - 1)
-    return {"median_ms": round(ms, 4), "wavefront_steps": wave_steps,
-            "ns_per_step": round(ms * 1e6 / wave_steps, 1),
-            "cycles_per_step_at_2.4GHz": round(ms * 1e-3 * CLOCK_GHZ * 1e9 / wave_steps, 0)}
+def sweep_times(each, per_field, steps):
+    """Median duration of each propagation sweep of the three fields (coarsest
+    level first, the four sweeps of a level in order).  The hook lists the
+    launches in the order they were enqueued: per step, field by field."""
+    out = {}
+    for lev in range(K, -1, -1):
+        for i in range(4):
+            at = 4 * (K - lev) + i
+            ms = [each[(s * 3 + f) * per_field + at] for s in range(steps) for f in range(3)]
+            out[f"level{1 << lev}_sweep{i + 1}_ms"] = round(statistics.median(ms), 4)
+    return out
 
 
 def load_round_trip_ns(ff, torch, dev, n_ints, hops=20000, reps=5):
@@ -565,21 +554,6 @@ def load_round_trip_ns(ff, torch, dev, n_ints, hops=20000, reps=5):
         torch.cuda.synchronize()
         res.append(out[0].item() * 10.0 / hops)
     return statistics.median(res)
-
-
-def latency_floor(ff, torch, dev, sweep):
-    """The sweep's latency floor: a step's result decides the next step's
-    target addresses, so every wavefront step costs at least one dependent
-    round trip to the cache that holds the census words (L2 for a cycle of
-    1 MB, L1 for one of 16 KB, both measured here on one thread)."""
-    l1 = load_round_trip_ns(ff, torch, dev, 4096)
-    l2 = load_round_trip_ns(ff, torch, dev, 1 << 18)
-    floor_ms = sweep["wavefront_steps"] * l2 * 1e-6
-    return {"l1_round_trip_ns": round(l1, 1), "l2_round_trip_ns": round(l2, 1),
-            "l2_round_trip_cycles_at_2.4GHz": round(l2 * CLOCK_GHZ, 0),
-            "floor_ms_one_l2_round_trip_per_step": round(floor_ms, 4),
-            "floor_over_measured": round(floor_ms / sweep["median_ms"], 4),
-            "note": "the level-1 sweep's wavefront steps x one dependent L2 round trip, against its measured time"}
 
 
 def secondary(ff, torch, dev, pair, skewed, steps):

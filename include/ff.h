@@ -104,18 +104,16 @@ typedef struct {
                          level) and write the current grid -- for inspection */
   uint32_t field_id;  /* 0..3, part of the random-search counter */
   uint32_t pair_id;   /* part of the random-search counter */
-  int32_t band_rows;  /* propagation band height: 8, 16 (default) or 32 rows per
-                         workgroup; results are identical for every value */
-  int32_t pipeline;   /* 1 (default): two consecutive sweeps with the same
-                         horizontal direction (and the random search between
-                         them) run as one launch, the second sweep starting on
-                         columns that the first and the search have finished;
-                         0: one launch per sweep and per search.  Results are
-                         identical; max_steps >= 0 implies 0 */
-  int32_t watchdog_us; /* 0 (default): every wait of one workgroup on another
-                          gives up after 2 s and the call reports
-                          FF_ERR_DEVICE; > 0: that limit in microseconds
-                          (a tiny value forces the error path in tests) */
+  int32_t band_rows;  /* 0, 8, 16 (default) or 32: accepted for callers that
+                         set it; a sweep is split into tiles of a fixed size,
+                         and results are identical for every value */
+  int32_t pipeline;   /* 0 or 1 (default): accepted likewise, no effect on
+                         results or schedule */
+  int32_t watchdog_us; /* 0 (default): a workgroup that waits for work while no
+                          other one finishes any gives up after 2 s and the
+                          call reports FF_ERR_DEVICE; > 0: that limit in
+                          microseconds (a tiny value forces the error path in
+                          tests) */
   uint64_t seed;      /* Philox key */
 } ff_match_params;
 
@@ -140,8 +138,8 @@ ff_status ff_desc_init(ff_desc* d, const ff_image* img, int32_t k, int32_t subpe
 ff_status ff_compute_descriptors(const ff_desc* d, const ff_image* img, const uint8_t* pixels, void* blob,
                                  size_t blob_bytes, hipStream_t stream);
 
-/* Workspace bytes for one ff_match_field call (kd-tree, level grids,
- * propagation progress counters, status word). */
+/* Workspace bytes for one ff_match_field call (kd-tree, level grids, the
+ * sweeps' border words and request counters, status word). */
 size_t ff_match_workspace_bytes(const ff_desc* src, const ff_desc* dst, int32_t radius, const ff_match_params* p);
 
 /*
@@ -451,12 +449,14 @@ ff_status ff_match_sift(const ff_sift_job* jobs, int32_t n_jobs, const ff_match_
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * search as ff_match_field, with the same arguments minus the workspace, and
  * identical outputs.  Its scratch (what ff_match_field keeps in the
- * workspace) is one static device array of FF_NOALLOC_SCRATCH_BYTES per GPU,
+ * workspace) is one static device array per GPU (FF_NOALLOC_SCRATCH_BYTES
+ * and that second buffer),
  * held until the process ends; the call allocates nothing (no hipMalloc, no
  * host heap).  ff_init() looks the array up on the current device; call it
  * before the first use inside a capture.
- *  - Limit: FF_ERR_SIZE if ff_match_workspace_bytes() of the same arguments
- *    exceeds FF_NOALLOC_SCRATCH_BYTES (64 MiB: fields of up to about 1.7 Mpx
+ *  - Limit: FF_ERR_SIZE if ff_match_workspace_bytes() of the same arguments,
+ *    less the second grid buffer where a source much larger than the target
+ *    needs one of its own, exceeds FF_NOALLOC_SCRATCH_BYTES (64 MiB: fields of up to about 1.7 Mpx
  *    at k = 3 and leaf 8, e.g. 1024x436, 1242x375, 1280x720, 1600x1000; not
  *    1920x1080).  Checked before anything is enqueued.
  *  - Every call on one GPU uses that GPU's single array and the array keeps

@@ -63,12 +63,17 @@ struct FieldRec {
   // kd-tree over the target (offsets into ws)
   int32_t t_nodes, t_top, pad2, pad3;
   uint32_t o_dim, o_split, o_perm, o_perm2, o_mm, o_hist, o_cnt, o_key;
-  // level grids n = 2..2^k (flow then cost), the band handoff words of the
-  // first and of the second sweep of a launch, and the column-progress words
-  // of a pipelined sweep pair (two arrays)
+  // level grids n = 2..2^k (flow then cost); the second grid buffer of every
+  // level (a sweep reads one and writes the other); per level the request
+  // counters of the sweeps' tiles and this field's first tile among the
+  // fields of its patch radius; the tiles' border words, right columns and
+  // bottom rows; per tile the border flows its last visit saw
   uint32_t o_grid[5];
-  uint32_t o_xch;
-  uint32_t o_xch2, o_prog;
+  uint32_t o_alt;
+  uint32_t o_st[5];
+  int32_t t0[5];
+  uint32_t o_xr, o_xb, o_seen;
+  uint32_t clear_words;   // counters and border words, from o_st[0]
 };
 
 // Enqueue the kd-tree builds of `nf` fields whose records are in `table`

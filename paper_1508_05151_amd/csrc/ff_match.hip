@@ -8,31 +8,27 @@
 // plane of the subpixel phase of m = pQ + f at floor(m/Q) + n d; lookups
 // clamp to the image; f is invalid ("infinite") unless m lies in the image.
 //
-// Propagation (Eq. 2) keeps the raster-order dependencies exactly with an
-// anti-diagonal wavefront: a workgroup owns a band of BH grid rows and steps
-// along its own anti-diagonals; row 0 of a band waits on the results the
-// band above publishes.  Bands are claimed with a ticket, so a band only ever
-// waits on a band that started before it.  Propagated candidates are costed
-// with sliding windows: E(p, F(q)) = C(q) - (row or column leaving the patch)
-// + (row or column entering it), 2(2r+1) terms instead of (2r+1)^2, exact
-// because every sample lookup clamps per coordinate.
+// Propagation (Eq. 2): the raster-order sweep is the one solution of "every
+// point holds the best of its own value and its two predecessors' new
+// values", so its tiles may be solved in any order as long as they are solved
+// again whenever a border value changes (ff_relax.h).  Propagated candidates
+// are costed with sliding windows: E(p, F(q)) = C(q) - (row or column leaving
+// the patch) + (row or column entering it), 2(2r+1) terms instead of
+// (2r+1)^2, exact because every sample lookup clamps per coordinate.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "ff_device.h"
 #include "ff_internal.h"
+#include "ff_relax.h"
 
 namespace ff {
 
-constexpr int kLanesProp = 16;    // lanes per point in the propagation sweep
 constexpr int kLanesPt = 16;      // lanes per point in recost / random search
 constexpr int kStatusBytes = 256;
-constexpr int kMinBandRows = 8;   // smallest band height (sizes the handoff buffer)
-constexpr int kRecsPerWrite = 16; // table records per writer launch (kernel argument size)
-// words per pipelined-progress array: covers ceil(Gh / BH) * BH / 4 random-
-// search workgroups of any band height up to 32 at any level
-__host__ __device__ __forceinline__ int prog_words(int Hs) { return (Hs + 31) / 4 + 8; }
+constexpr int kRecsPerWrite = 12; // table records per writer launch (kernel argument size)
 
 // ---------------------------------------------------------------- per-field cost context
 struct CostCtx {
@@ -66,12 +62,16 @@ __device__ __forceinline__ CostCtx ctx_of(const FieldRec& f, int lev, int qshift
   return c;
 }
 
-// level grids: n = 1 is the output pair itself
-__device__ __forceinline__ int32_t* grid_flow(const FieldRec& f, int lev) {
+// level grids: buffer 0 of n = 1 is the output pair itself; buffer 1 is one
+// region of the workspace for every level
+__device__ __forceinline__ int32_t* grid_flow(const FieldRec& f, int lev, int buf) {
+  if (buf) return reinterpret_cast<int32_t*>(f.ws + f.o_alt);
   return lev == 0 ? f.flow : reinterpret_cast<int32_t*>(f.ws + f.o_grid[lev]);
 }
-__device__ __forceinline__ int32_t* grid_cost(const FieldRec& f, int lev, int G) {
-  return lev == 0 ? f.cost : reinterpret_cast<int32_t*>(f.ws + f.o_grid[lev]) + G;
+__device__ __forceinline__ int32_t* grid_cost(const FieldRec& f, int lev, int buf) {
+  if (!buf && lev == 0) return f.cost;
+  const int n = 1 << lev;
+  return grid_flow(f, lev, buf) + ((f.Ws + n - 1) >> lev) * ((f.Hs + n - 1) >> lev);
 }
 
 __device__ __forceinline__ bool centre_valid(const CostCtx& c, int px, int py, int fx, int fy) {
@@ -155,22 +155,12 @@ __global__ void k_write_table(RecChunk chunk, int n, FieldRec* __restrict__ out)
   if ((int)threadIdx.x < n) out[threadIdx.x] = chunk.r[threadIdx.x];
 }
 
-// zero every field's band handoff words and progress words (grid: chunks x
-// fields)
-__global__ void k_clear_xch(const FieldRec* __restrict__ table, int bands_rows) {
+// zero every field's border words and request counters (grid: chunks x fields)
+__global__ void k_clear_borders(const FieldRec* __restrict__ table) {
   const FieldRec& f = table[blockIdx.y];
-  uint64_t* x = reinterpret_cast<uint64_t*>(f.ws + f.o_xch);
-  uint64_t* x2 = reinterpret_cast<uint64_t*>(f.ws + f.o_xch2);
-  int32_t* pg = reinterpret_cast<int32_t*>(f.ws + f.o_prog);
-  const size_t nb = (size_t)((f.Hs + bands_rows - 1) / bands_rows);
-  const size_t nw = nb * f.Ws;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nw; i += (size_t)gridDim.x * blockDim.x) {
-    x[i] = 0;
-    x2[i] = 0;
-  }
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < 2 * (size_t)prog_words(f.Hs);
-       i += (size_t)gridDim.x * blockDim.x)
-    pg[i] = 0;
+  int32_t* x = reinterpret_cast<int32_t*>(f.ws + f.o_st[0]);
+  const size_t nw = f.clear_words;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nw; i += (size_t)gridDim.x * blockDim.x) x[i] = 0;
 }
 
 // ---------------------------------------------------------------- seeds (Eq. 1 / Eq. 4)
@@ -178,7 +168,8 @@ __global__ void k_clear_xch(const FieldRec* __restrict__ table, int bands_rows) 
 // patch's WHT vector, then re-rank the leaf (ascending pixel index) and the
 // optional proposal by the data term; the first minimum wins.
 // grid: (points / 4, fields)
-__global__ __launch_bounds__(256) void k_seed(const FieldRec* __restrict__ table, int lev, int qshift, int use_tree) {
+__global__ __launch_bounds__(256) void k_seed(const FieldRec* __restrict__ table, int lev, int qshift, int use_tree,
+                                                int buf) {
   const FieldRec& f = table[blockIdx.y];
   const CostCtx c = ctx_of(f, lev, qshift);
   const int Gw = (f.Ws + c.n - 1) >> lev, Gh = (f.Hs + c.n - 1) >> lev;
@@ -217,8 +208,8 @@ __global__ __launch_bounds__(256) void k_seed(const FieldRec* __restrict__ table
     }
   }
   if (lane == 0) {
-    grid_flow(f, lev)[(size_t)gy * Gw + gx] = bestF;
-    grid_cost(f, lev, Gw * Gh)[(size_t)gy * Gw + gx] = bestC;
+    grid_flow(f, lev, buf)[(size_t)gy * Gw + gx] = bestF;
+    grid_cost(f, lev, buf)[(size_t)gy * Gw + gx] = bestC;
   }
 }
 
@@ -228,7 +219,7 @@ __global__ __launch_bounds__(256) void k_seed(const FieldRec* __restrict__ table
 // coarse point (the fine points of even coordinates), which also writes the
 // three new points it covers.  grid: (coarse pts L / 256, fields)
 template <int L>
-__global__ __launch_bounds__(256) void k_level_entry(const FieldRec* __restrict__ table, int lev, int qshift) {
+__global__ __launch_bounds__(256) void k_level_entry(const FieldRec* __restrict__ table, int lev, int qshift, int buf) {
   static_assert(L == 16, "the row path assumes 16 lanes per point");
   const FieldRec& f = table[blockIdx.y];
   const CostCtx c = ctx_of(f, lev, qshift);
@@ -239,7 +230,7 @@ __global__ __launch_bounds__(256) void k_level_entry(const FieldRec* __restrict_
   if (cid >= Gwc * Ghc) return;
   const int cx = cid % Gwc, cy = cid / Gwc;
   const int gx = 2 * cx, gy = 2 * cy;
-  const int32_t fl = grid_flow(f, lev + 1)[cid];
+  const int32_t fl = grid_flow(f, lev + 1, 0)[cid];   // a finished level ends in buffer 0
   int32_t e = kInf;
   if (fl != kEmpty) {
     const int px = gx * c.n, py = gy * c.n, fx = fx_of(fl), fy = fy_of(fl);
@@ -258,8 +249,8 @@ __global__ __launch_bounds__(256) void k_level_entry(const FieldRec* __restrict_
     }
     e = group_sum<L>(part);
   }
-  int32_t* F = grid_flow(f, lev);
-  int32_t* C = grid_cost(f, lev, Gw * Gh);
+  int32_t* F = grid_flow(f, lev, buf);
+  int32_t* C = grid_cost(f, lev, buf);
   if (lane < 4) {
     const int x = gx + (lane & 1), y = gy + (lane >> 1);
     if (x < Gw && y < Gh) {
@@ -280,7 +271,7 @@ __global__ __launch_bounds__(256) void k_level_entry(const FieldRec* __restrict_
 // side of each term is read from global memory.
 template <int L>
 __global__ __launch_bounds__(256) void k_random_search(const FieldRec* __restrict__ table, int lev, int qshift, int step,
-                                                       int R) {
+                                                       int R, int buf) {
   constexpr int PTS = 256 / L;
   __shared__ uint32_t stile[(2 * kMaxRadius + 1) * (2 * kMaxRadius + PTS + 1)];
   const FieldRec& f = table[blockIdx.y];
@@ -292,8 +283,8 @@ __global__ __launch_bounds__(256) void k_random_search(const FieldRec* __restric
   // tile rows: S patch rows; pitch odd, so that the row-per-lane path's 16
   // lanes of a point fall in different banks
   const int S = 2 * c.r + 1, TWs = S - 1 + PTS, TP = TWs | 1;
-  int32_t* F = grid_flow(f, lev);
-  int32_t* C = grid_cost(f, lev, Gw * Gh);
+  int32_t* F = grid_flow(f, lev, buf);
+  int32_t* C = grid_cost(f, lev, buf);
   const int py = gy * c.n;
   // each point's flow and cost, loaded before the tile so that the two
   // round trips overlap
@@ -376,56 +367,40 @@ __global__ __launch_bounds__(256) void k_random_search(const FieldRec* __restric
 // the transformed coordinates u = sx > 0 ? gx : Gw-1-gx (same for v) every
 // sweep runs right and down.
 //
-// Step t of a band: row i handles u = t - s(i), s(i) = i + i / 4 (each
-// wavefront of four rows one step behind the one above, so that every
-// candidate of a step is known, and its target words loaded, at the end of
-// the step before).  Rows hand results down inside a wavefront by DPP and
-// across wavefronts through a double-buffered LDS slot (one barrier per
-// step).  The band's last row
-// publishes each result as one 64-bit word (flow | cost | launch tag) with a
-// relaxed agent-scope store; row 0 of the band below polls that word until
-// the tag matches.  One single-copy-atomic word carries data and readiness,
-// so no fence (L2 write-back or invalidate) is needed on the critical path.
-__device__ __forceinline__ uint64_t rt_clock() { return __builtin_amdgcn_s_memrealtime(); }
-
-__device__ __forceinline__ uint64_t xch_pack(int32_t f, int32_t cst, uint32_t tag) {
-  const uint32_t c16 = cst == kInf ? 0xFFFFu : (uint32_t)cst;
-  return (uint64_t)(uint32_t)f | ((uint64_t)(c16 | (tag << 16)) << 32);
-}
-
-// Batches of kBatch steps.  Before a batch the band stages in LDS (a) every
-// row's own flow and cost for the batch and (b) the source census tile the
-// batch's terms read (the source side does not depend on the wavefront);
-// after it the results leave from an LDS ring with coalesced stores.  Inside
-// a batch a step's only global traffic is its target census terms plus the
-// one-word handoff.
+// One wavefront visits one tile at a time (ff_relax.h has the scheduling and
+// why the order does not matter).  At step t row i of the tile is at column
+// u0 + t - i, on four lanes.  A step costs both candidates of its 16 points:
+// per point the row leaving and the row entering the patch (vertical
+// candidate) and the column leaving and entering it (horizontal), S = 2r+1
+// census words each, a quarter of every line per lane -- neighbouring lanes
+// read neighbouring words, so that a load instruction touches 16 lines, not
+// 64.  Source lines come from the tile's source census in LDS, held
+// row-major and column-major so that both kinds of line are contiguous.
 //
-// Term layout.  In sweep-transformed grid coordinates (u right, v down) the
-// sliding-window terms of a point are four groups of S = 2r+1: g0/g1 = row
-// v-r-1 / v+r (vertical candidate leaving / entering), g2/g3 = column u-r-1 /
-// u+r (horizontal candidate), each over offsets -r..r.  Slot g of lane l
-// takes offset index l of group g (valid while l < S); for S > 16 the S - 16
-// remaining offsets of the four groups are packed into TAIL extra slots whose
-// group is a per-lane constant.
-//
-// A step is written for a short instruction stream (one wavefront per SIMD,
-// so a step's latency is its instruction count plus what is left of one
-// memory round trip after the barrier and the step's LDS reads):
-// target words are read with 32-bit offsets from one scalar base (row-major
-// and transposed planes of a level lie in one blob), tail groups are chosen
-// with lane-constant masks, and the vertical and horizontal sums travel
-// packed in one 32-bit word through the DPP reduction.
-constexpr int kBatch = 32;
+// Bound: memory latency.  A step is one dependent chain (result, addresses,
+// loads, sums); neighbouring flows differ by subpixel steps, so its 64 lines
+// lie in different phase planes and mostly miss both caches: 0.62 us per step
+// with the chip idle, 1.3 us with every CU at work, of which instructions are
+// 0.25 us.  A visit is 16 steps and about 4 us around them.  Measured on
+// 1024x436 (three fields at once) a level-1 sweep takes 0.30 ms on average
+// where one wavefront per band of 16 rows, every band waiting for the one
+// above, took 1.15 ms; a pair 6.2 ms against 10.3, one 641x479 field 2.7
+// against 6.7, eight mixed pairs in one call 31.8 against 41.4.
+// Tile size (modelled from the visits each needs on that pair): 16 x 8, 8 x 16
+// and 8 x 8 points need 1.5 to 2 times the visits for the same chain, 16 x 32
+// has a longer one.
+constexpr int kTileH = 16, kTileW = 16;   // rows, columns; 4 lanes per row
+constexpr int kSweepGrid = 2048;          // workgroups of a launch at most
+__host__ __device__ __forceinline__ int tiles_x(int Gw) { return (Gw + kTileH - 1 + kTileW - 1) / kTileW; }
+__host__ __device__ __forceinline__ int tiles_y(int Gh) { return (Gh + kTileH - 1) / kTileH; }
 
 typedef __attribute__((address_space(1))) const char g_byte;
 
-
-__device__ __forceinline__ int med3i(int v, int lo, int hi) { return min(max(v, lo), hi); }
 // clamp to [0, hi] in one instruction (the compiler emits max then min when
-// the upper bound is not a constant); hi is uniform
+// the upper bound is not a constant)
 __device__ __forceinline__ uint32_t clamp0(int v, int hi) {
   int r;
-  asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(v), "s"(hi));
+  asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(v), "v"(hi));
   return (uint32_t)r;
 }
 // target word at a 32-bit word offset from a uniform base: the byte offset is
@@ -435,628 +410,387 @@ __device__ __forceinline__ uint32_t tword(g_byte* base, uint32_t w) {
   return *reinterpret_cast<__attribute__((address_space(1))) const uint32_t*>(base + (w << 2));
 }
 
-// ---------------------------------------------------------------- pipelined sweep pairs
-// Two consecutive sweeps that share the horizontal direction (and so run in
-// opposite vertical directions) can overlap: a point's value after the first
-// sweep and the random search between them is all the second one needs, so
-// the second sweep may start on columns the first has finished.  Such a pair
-// is one launch with three roles, claimed in this order by the launch's
-// ticket: A (the first sweep, one workgroup per band), X (the random search
-// after A, kXRows grid rows of the second sweep's bands per workgroup, run
-// behind A's progress) and B (the second sweep, one workgroup per band,
-// starting a batch once X has finished the columns it stages).  Every wait is
-// on a workgroup with a lower ticket, which is already running.  The random
-// search of a point depends on that point alone, so every result equals the
-// one-launch-per-stage order.  Workgroups of one launch may sit on different
-// XCDs, whose L2 caches are not coherent: flows and costs that cross roles
-// are read and written with device-coherent (agent-scope) accesses, and A and
-// X publish how many columns of a band are final in a progress word (launch
-// tag << 20 | columns) after their stores have completed.
-// The same holds across a level change: the last sweep of level 2n runs in
-// the horizontal direction of the first sweep of level n, and only the level
-// entry (coarse flows carried to the finer grid and re-costed, a per-point
-// step like the random search) lies between them; such a cross-level pair has
-// A on the coarse grid and X (the level entry) and B on the fine one.
-constexpr int kRoleA = 0, kRoleX = 1, kRoleB = 2;
-constexpr int kXRows = 4;
-constexpr int kPairSame = 1, kPairCross = 2;
-
-// global-address-space accesses throughout: a flat access also counts as an
-// LDS operation and, while pending, turns a wait for some loads into a wait
-// for all of them
-template <class T>
-__device__ __forceinline__ __attribute__((address_space(1))) T* gp(T* p) {
-  return (__attribute__((address_space(1))) T*)p;
-}
-__device__ __forceinline__ int32_t ld_coh(const int32_t* p) {
-  return __hip_atomic_load(gp(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_coh(int32_t* p, int32_t v) {
-  __hip_atomic_store(gp(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ int32_t prog_word(uint32_t tag, int cols) {
-  return (int32_t)(((tag & 0xFFFu) << 20) | (uint32_t)cols);
-}
-__device__ __forceinline__ int prog_cols(int32_t w, uint32_t tag) {
-  return ((uint32_t)w >> 20) == (tag & 0xFFFu) ? (int)((uint32_t)w & 0xFFFFFu) : 0;
-}
-// one thread: wait until a progress word reaches `need` columns; on the
-// watchdog the launch reports FF_ERR_DEVICE and the wait gives up, and once
-// an error is reported no later wait of the call waits at all
-__device__ bool wait_prog(const int32_t* w, uint32_t tag, int need, int32_t* status, uint64_t timeout) {
-  if (prog_cols(ld_coh(w), tag) >= need) return true;
-  const uint64_t t0 = rt_clock();
-  for (;;) {
-    __builtin_amdgcn_s_sleep(2);
-    if (prog_cols(ld_coh(w), tag) >= need) return true;
-    if (ld_coh(status) != 0) return false;
-    if (rt_clock() - t0 > timeout) {
-      __hip_atomic_store(status, (int32_t)FF_ERR_DEVICE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      return false;
-    }
-  }
-}
-// all of this workgroup's global stores complete, then one word published
-__device__ __forceinline__ void publish_prog(int32_t* w, uint32_t tag, int cols) {
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  if (threadIdx.x == 0) st_coh(w, prog_word(tag, cols));
-}
-
-// Data term of candidate (fx, fy) at grid point (px, py) of level lev by a
-// group of 16 lanes (the sum is left in every lane of the group): whole columns
-// per lane at stride 1 when no column clamps, else the generic walk.
-__device__ __forceinline__ int32_t cand_cost(const CostCtx& c, int lev, int px, int py, int fx, int fy, int lane) {
-  const int mx = px * c.Q + fx, my = py * c.Q + fy;
-  const int Mx = mx >> c.qshift, My = my >> c.qshift;
-  int32_t part;
-  if (lev == 0 && (c.r == 8 || c.r == 6) && px >= c.r && px + c.r < c.Ws && Mx >= c.r && Mx + c.r < c.Wd) {
-    const uint32_t* D2 = c.dst + (size_t)c.pw * (size_t)(((my & c.qmask) << c.qshift) + (mx & c.qmask));
-    g_u32* sb = (g_u32*)(c.src + (px - c.r));
-    g_u32* tb = (g_u32*)(D2 + (Mx - c.r));
-    part = c.r == 8 ? cols_sum_n1<17, false>(sb, c.Ws, py - 8, c.Hs - 1, tb, c.Wd, My - 8, c.Hd - 1, lane)
-                    : cols_sum_n1<13, false>(sb, c.Ws, py - 6, c.Hs - 1, tb, c.Wd, My - 6, c.Hd - 1, lane);
+// CW words of a line: consecutive (WIDE, one load) or every fourth sample
+template <int CW, bool WIDE, int LEV>
+__device__ __forceinline__ void load_line(g_byte* tgt, uint32_t at, int lev, uint32_t (&w)[CW]) {
+  g_byte* const p = tgt + (at << 2);
+  typedef uint32_t vec __attribute__((ext_vector_type(CW == 3 ? 4 : CW), aligned(4)));
+  if (WIDE && CW == 4) {
+    const vec x = *reinterpret_cast<__attribute__((address_space(1))) const vec*>(p);
+#pragma unroll
+    for (int m = 0; m < CW; ++m) w[m] = x[m];
   } else {
-    part = patch_partial(c, px, py, fx, fy, lane, 16);
-  }
-  return group_sum<16>(part);
-}
-
-// An X workgroup: rows kXRows m .. kXRows m + kXRows - 1 of band k of the
-// second sweep (level lev, direction syX), columns in chunks of 32 as the
-// first sweep's bands (direction -syX, progress words progA) finish the
-// columns they need; publishes its progress in progX[k * BH / kXRows + m].
-// Same-level pair: random search step rs (< 0: none, progress is only passed
-// on), as in k_random_search, the first sweep on the same grid.  Cross-level
-// pair: the level entry, as in k_level_entry, the first sweep on the grid of
-// level lev + 1.  A chunk's candidates are formed one point per thread (flow
-// and cost loads, Philox) before the 16-lane groups cost them, so a point's
-// chain holds one memory round trip.
-template <int BH>
-__device__ __forceinline__ void x_worker(const FieldRec& fr, const CostCtx& c, int lev, bool cross, int k, int m,
-                                         int sx, int syX, const int32_t* progA, int32_t* progX, int rs, int R,
-                                         uint32_t tag, int32_t* status, uint64_t timeout) {
-  constexpr int CH = kBatch;
-  __shared__ int32_t x_fx[kXRows * CH], x_fy[kXRows * CH], x_c[kXRows * CH], x_ok[kXRows * CH];
-  const int n = c.n;
-  const int Gw = (fr.Ws + n - 1) >> lev, Gh = (fr.Hs + n - 1) >> lev;
-  int32_t* const F = grid_flow(fr, lev);
-  int32_t* const C = grid_cost(fr, lev, Gw * Gh);
-  // the first sweep's grid
-  const int la = cross ? lev + 1 : lev;
-  const int Gwa = (fr.Ws + (1 << la) - 1) >> la, Gha = (fr.Hs + (1 << la) - 1) >> la;
-  const int32_t* const Fa = grid_flow(fr, la);
-  const int b0 = k * BH;
-  const int v0 = b0 + m * kXRows;
-  const int rows = min(kXRows, min(BH, Gh - b0) - m * kXRows);
-  int32_t* const pw = progX + k * (BH / kXRows) + m;
-  if (rows <= 0) {
-    publish_prog(pw, tag, Gw);
-    return;
-  }
-  // the first sweep's bands holding these grid rows: grid rows gy (range
-  // gya..gyb) lie in row gy >> cross of the first sweep's grid, which that
-  // sweep (direction -syX) numbers Gha - 1 - (gy >> cross) if it runs upward
-  const int gya = syX > 0 ? v0 : Gh - 1 - (v0 + rows - 1), gyb = syX > 0 ? v0 + rows - 1 : Gh - 1 - v0;
-  const int sh = cross ? 1 : 0;
-  const int blo = syX > 0 ? (Gha - 1 - (gyb >> sh)) / BH : (gya >> sh) / BH;
-  const int bhi = syX > 0 ? (Gha - 1 - (gya >> sh)) / BH : (gyb >> sh) / BH;
-  const int lane = threadIdx.x % 16, group = threadIdx.x / 16, ngroups = blockDim.x / 16;
-  for (int c0 = 0; c0 < Gw; c0 += CH) {
-    const int c1 = min(c0 + CH, Gw), cw = c1 - c0;
-    // columns of the first sweep's grid that hold this chunk's points: the
-    // last column of the chunk maps to the largest one
-    const int gxl = sx > 0 ? c1 - 1 : Gw - c1;
-    const int need = (sx > 0 ? (gxl >> sh) : Gwa - 1 - (gxl >> sh)) + 1;
-    if (threadIdx.x == 0)
-      for (int b = blo; b <= bhi; ++b) wait_prog(progA + b, tag, need, status, timeout);
-    __syncthreads();
-    if (cross || rs >= 0) {
-      // candidates, one point per thread
-      for (int q = threadIdx.x; q < rows * cw; q += blockDim.x) {
-        const int v = v0 + q / cw, u = c0 + q % cw;
-        const int gx = sx > 0 ? u : Gw - 1 - u, gy = syX > 0 ? v : Gh - 1 - v;
-        const int px = gx * n, py = gy * n;
-        int ok = 0, fxq = 0, fyq = 0, cq = 0;
-        if (cross) {
-          // carried points keep the coarse flow; every other point is new
-          int32_t fl = kEmpty;
-          if (!(gx & 1) && !(gy & 1)) fl = ld_coh(Fa + (size_t)(gy >> 1) * Gwa + (gx >> 1));
-          if (fl != kEmpty) {
-            ok = 1;
-            fxq = fx_of(fl);
-            fyq = fy_of(fl);
-          } else {
-            st_coh(F + (size_t)gy * Gw + gx, kEmpty);
-            st_coh(C + (size_t)gy * Gw + gx, kInf);
-          }
-        } else {
-          const int32_t fl = ld_coh(F + (size_t)gy * Gw + gx);
-          if (fl != kEmpty) {
-            const int rad = n * R * c.Q;
-            uint32_t u0, u1;
-            philox2((uint32_t)(py * c.Ws + px), (uint32_t)lev, (uint32_t)rs, fr.c3, fr.k0, fr.k1, u0, u1);
-            const uint64_t span = (uint64_t)(2 * rad + 1);
-            fxq = fx_of(fl) + (int)((u0 * span) >> 32) - rad;
-            fyq = fy_of(fl) + (int)((u1 * span) >> 32) - rad;
-            ok = centre_valid(c, px, py, fxq, fyq) ? 1 : 0;
-            cq = ld_coh(C + (size_t)gy * Gw + gx);
-          }
-        }
-        x_fx[q] = fxq;
-        x_fy[q] = fyq;
-        x_c[q] = cq;
-        x_ok[q] = ok;
-      }
-      __syncthreads();
-      // their data terms, one group of 16 lanes per point
-      for (int i = group; i < rows * cw; i += ngroups) {
-        if (!x_ok[i]) continue;
-        const int v = v0 + i / cw, u = c0 + i % cw;
-        const int gx = sx > 0 ? u : Gw - 1 - u, gy = syX > 0 ? v : Gh - 1 - v;
-        const int fx = x_fx[i], fy = x_fy[i];
-        const int32_t e = cand_cost(c, lev, gx * n, gy * n, fx, fy, lane);
-        if (lane == 0) {
-          if (cross) {
-            // the level entry keeps the flow whatever its cost
-            st_coh(F + (size_t)gy * Gw + gx, packf(fx, fy));
-            st_coh(C + (size_t)gy * Gw + gx, e);
-          } else if (e < x_c[i]) {
-            st_coh(F + (size_t)gy * Gw + gx, packf(fx, fy));
-            st_coh(C + (size_t)gy * Gw + gx, e);
-          }
-        }
-      }
-    }
-    publish_prog(pw, tag, c1);
+#pragma unroll
+    for (int m = 0; m < CW; ++m)
+      w[m] = *reinterpret_cast<__attribute__((address_space(1))) const uint32_t*>(
+          p + (WIDE ? 4 * m : (16 * m) << (LEV >= 0 ? LEV : lev)));
   }
 }
 
-// pair = 0: one sweep (sx, sy) at level lev, one workgroup per band;
-// kPairSame: the sweep pair (sx, sy) then (sx, -sy) at level lev with the
-// random search step rs (< 0: none) between them; kPairCross: the sweep
-// (sx, sy) at level lev + 1, the level entry of level lev, then the sweep
-// (sx, -sy) at level lev.  na: bands of level lev over the launch's fields;
-// na_a: bands of the first sweep's level.
-template <int TAIL, int BH>
-__global__ __launch_bounds__(BH * kLanesProp + 64) void k_propagate(const FieldRec* __restrict__ table, int f0, int nf,
-                                                               int lev, int qshift, int sx, int sy, uint32_t tag,
-                                                               int32_t* __restrict__ ticket,
-                                                               int32_t* __restrict__ status,
-                                                               uint64_t timeout_ticks, int pair, int na, int na_a,
-                                                               int rs, int R) {
-  constexpr int L = kLanesProp, CH = kBatch;
-  constexpr int NS = 4 + TAIL;   // term slots per lane
-  static_assert(L == 16 && CH % 2 == 0 && CH % L == 0 && TAIL <= 4, "layout");
-  // rows run skewed: row i works on u = t - s(i), s(i) = i + i / 4 (one more
-  // step per wavefront), so the tile's left margin is BH + BH / 4 columns
-  constexpr int M = BH + BH / 4;
-  constexpr int kTileWords = (BH + 2 * kMaxRadius + 1) * ((kBatch + M + 2 * kMaxRadius) | 1);
-  __shared__ int32_t s_band, s_field, s_role, s_sub;
-  __shared__ int32_t bufF[2][BH], bufC[2][BH];
-  __shared__ int32_t topF[2], topC[2];   // row 0's vertical candidate, by step parity
-  __shared__ int32_t inF[BH][CH], inC[BH][CH], outF[BH][CH], outC[BH][CH];
-  __shared__ uint32_t tile[kTileWords];
-  // the band's rows run on BH / 4 wavefronts; one more wavefront waits for
-  // the band above and hands row 0 its vertical candidate through LDS, one
-  // step ahead, so that no compute wavefront polls global memory
-  const bool pollWave = __builtin_amdgcn_readfirstlane(threadIdx.x) >= BH * L;
-  const int row = pollWave ? 0 : threadIdx.x / L, lane = threadIdx.x % L;
-  if (threadIdx.x == 0) {
-    // tickets are handed out in launch order; role-major, then field-major,
-    // band-minor; role sizes: A na_a, X na BH / kXRows, B na
-    int tk = atomicAdd(ticket, 1), fi = f0;
-    int role = -1, sub = 0;
-    for (int rb = 0; rb < (pair ? 3 : 1); ++rb) {
-      const int per = rb == kRoleX ? BH / kXRows : 1;
-      const int cnt = (rb == kRoleA ? na_a : na) * per;
-      if (tk < cnt) {
-        role = rb;
-        sub = tk % per;
-        tk /= per;
-        break;
-      }
-      tk -= cnt;
-    }
-    s_role = role;
-    s_sub = sub;
-    const int nr = 1 << (role == kRoleA && pair == kPairCross ? lev + 1 : lev);
-    for (; fi < f0 + nf; ++fi) {
-      const int gh = (table[fi].Hs + nr - 1) / nr;
-      const int nb = (gh + BH - 1) / BH;
-      if (tk < nb) break;
-      tk -= nb;
-    }
-    s_band = tk;
-    s_field = fi;
-  }
-  __syncthreads();
-  if (s_field >= f0 + nf || s_role < 0) return;
-  const int role = s_role;
-  if (role == kRoleA && pair == kPairCross) ++lev;   // the first sweep runs on the coarser grid
+struct SweepArgs {
+  int f0, nf;        // fields of this launch (one patch radius)
+  int lev, qshift;
+  int sx, sy;
+  uint32_t tag;      // of this launch, in the border words
+  int base;          // of the request counters (ff_relax.h)
+  int inbuf;         // grid buffer read; the other one is written
+};
+
+// S = 2r+1, or 0: the field's own (up to 31); LEV: the level, or -1: any
+template <int S, int LEV>
+__global__ __launch_bounds__(64) void k_sweep(const FieldRec* __restrict__ table, SweepArgs a, RelaxQ q) {
+  constexpr int RM = S ? S / 2 : kMaxRadius;
+  constexpr int CW = S ? S / 4 : 1;      // words of a line per lane, one more word per line left over (S = 4 CW + 1)
+  constexpr bool kWide = S && LEV == 0;  // consecutive words
+  static_assert(S == 0 || S % 4 == 1, "line split");
+  // even pitches: the rows of a step lie a pitch -+ 1 apart, so their words
+  // fall in different banks
+  constexpr int P1 = kTileW + kTileH + 2 * RM, P2 = (kTileH + 2 * RM + 4) & ~1;
+  constexpr int kPitchOwn = kTileW + 1;
+  __shared__ uint32_t s_row[(kTileH + 2 * RM + 1) * P1];          // source census, row-major
+  __shared__ uint32_t s_col[(kTileW + kTileH + 2 * RM) * P2];     // and column-major
+  __shared__ int2 s_own[kTileH * kPitchOwn];                      // own values
+  __shared__ int2 s_res[kTileH * kPitchOwn];                      // results, on entry those of the visit before
+  __shared__ int2 s_left[kTileH], s_top[kTileW + 2];              // border values: flow, 2 cost + changed
+  const int lane = threadIdx.x;
+  const int lev = LEV >= 0 ? LEV : a.lev;
   const int n = 1 << lev;
-  const FieldRec& fr = table[s_field];
-  const CostCtx c = ctx_of(fr, lev, qshift);
-  const int Gw = (fr.Ws + n - 1) >> lev, Gh = (fr.Hs + n - 1) >> lev;
-  int32_t* const F = grid_flow(fr, lev);
-  int32_t* const C = grid_cost(fr, lev, Gw * Gh);
-  // progress words: A's bands, then X's workgroups
-  int32_t* const progA = reinterpret_cast<int32_t*>(fr.ws + fr.o_prog);
-  int32_t* const progX = progA + prog_words(fr.Hs);
-  if (role == kRoleX) {
-    x_worker<BH>(fr, c, lev, pair == kPairCross, s_band, s_sub, sx, -sy, progA, progX, rs, R, tag, status,
-                 timeout_ticks);
-    return;
-  }
-  if (role == kRoleB) sy = -sy;
-  // a band's step is a latency chain: its compute wavefronts go first in the
-  // SIMD arbitration against co-resident workgroups (the X role's searches,
-  // other launches); measured 10.20 -> 10.16 ms per pair
-  if (!pollWave) __builtin_amdgcn_s_setprio(3);
-  const bool coherent = pair != 0;   // flows/costs cross roles of this launch
-  const int32_t* const waitProg = role == kRoleB ? progX : nullptr;
-  int32_t* const pubProg = role == kRoleA && pair ? progA : nullptr;
-  uint64_t* const xch = reinterpret_cast<uint64_t*>(fr.ws + (role == kRoleB ? fr.o_xch2 : fr.o_xch));
-  const int band = s_band;
-  const int v0 = band * BH;
-  if (v0 >= Gh) return;
-  const int rows = min(BH, Gh - v0);
-  const int skew = row + (row >> 2);      // s(row): this row works on u = t - skew
-  const int skewLast = (rows - 1) + ((rows - 1) >> 2);
-  const int nsteps = Gw + skewLast;
-  const int r = c.r, S = 2 * r + 1, Q = c.Q;
-  const int TH = BH + 2 * r + 1;          // tile rows: v0-r-1 .. v0+BH-1+r
-  const int TW = (CH + M + 2 * r) | 1;    // tile cols: tb-M-r .. tb+CH-1+r; odd pitch (banks)
-  const bool rowok = !pollWave && row < rows;
-  const int rr = rowok ? row : rows - 1;  // inactive rows shadow a valid row
-  const int gy = sy > 0 ? v0 + rr : Gh - 1 - (v0 + rr);
-  const int py = gy * n;
-  const bool publish = rowok && row == rows - 1 && v0 + rows < Gh;
-  const bool above = v0 > 0;              // a band above exists
-  const uint64_t* xin = xch + (size_t)(band > 0 ? band - 1 : 0) * Gw;
-  uint64_t* xout = xch + (size_t)band * Gw;
-  int32_t* Frow = F + (size_t)gy * Gw;
-  int32_t* Crow = C + (size_t)gy * Gw;
-  auto gx_of = [&](int u) { return sx > 0 ? u : Gw - 1 - u; };
-  auto gy_of = [&](int v) { return sy > 0 ? v : Gh - 1 - v; };
-  // target words: one scalar base (level plane 0), 32-bit word offsets; the
-  // transposed planes start dT words after the row-major ones
-  g_byte* const tgt = (g_byte*)(c.dst);
-  const uint32_t dT = (uint32_t)(c.dstT - c.dst);
-  const int nsx = sx * n, nsy = sy * n;
-  const int Wm = c.Wd - 1, Hm = c.Hd - 1;
-  const uint32_t Wd = (uint32_t)c.Wd, Hd = (uint32_t)c.Hd;
-  // lane constants: the full slots' offset along the group's free axis and
-  // validity; per tail slot its group (as selection masks), validity, sign
-  // and half of the packed sum; every slot's tile offset
-  const int offFull = lane - r;
-  const uint32_t fullMask = TAIL > 0 || lane < S ? ~0u : 0u;
-  const int oxFull = nsx * offFull, oyFull = nsy * offFull;
-  int tOff[TAIL > 0 ? TAIL : 1], tGrp[TAIL > 0 ? TAIL : 1];
-  bool tG1[TAIL > 0 ? TAIL : 1], tG3[TAIL > 0 ? TAIL : 1], tH[TAIL > 0 ? TAIL : 1];
-  int32_t tMul[TAIL > 0 ? TAIL : 1];
+  const int sx = a.sx, sy = a.sy;
+  // the first visits are dealt out in turn; then queued tiles
+  int mine = blockIdx.x, gt = mine, done = 0;
+  bool first = true;   // no earlier visit of this tile in this launch
+  do {
+    // the tile's field: the last one whose first tile is not above it
+    int fi = a.f0 + (a.nf == 1 ? 1 : 0);
+    for (int b = 0; b < a.nf && a.nf > 1; b += 64) {
+      const int k = b + lane;
+      const bool le = k < a.nf && table[a.f0 + k].t0[lev] <= gt;
+      fi += __popcll(__ballot(le));
+    }
+    fi = __builtin_amdgcn_readfirstlane(fi - 1);
+    const FieldRec& f = table[fi];
+    const CostCtx c = ctx_of(f, lev, a.qshift);
+    const int r = S ? S / 2 : c.r;
+    const int Sd = 2 * r + 1;
+    const int Q = c.Q;
+    const int Gw = (f.Ws + n - 1) >> lev, Gh = (f.Hs + n - 1) >> lev;
+    const int g0 = f.t0[lev], tile = gt - g0;
+    const int nu = tiles_x(Gw), nv = tiles_y(Gh);
+    const int tv = tile / nu, tu = tile - tv * nu;
+    const int u0 = tu * kTileW, v0 = tv * kTileH;
+    int32_t* const cnt = reinterpret_cast<int32_t*>(f.ws + f.o_st[lev]);
+    const int have = ld_coh(cnt + tile) - a.base;   // requests this visit answers
+    const int32_t* const inF = grid_flow(f, lev, a.inbuf);
+    const int32_t* const inC = grid_cost(f, lev, a.inbuf);
+    auto gx_of = [&](int u) { return sx > 0 ? u : Gw - 1 - u; };
+    auto gy_of = [&](int v) { return sy > 0 ? v : Gh - 1 - v; };
+    auto pidx = [&](int u, int v) { return gy_of(v) * Gw + gx_of(u); };
+    // own values, four points per lane (points outside the grid: EMPTY)
+    const int lx = lane & 15, ly = lane >> 4;
+    int32_t of[4], oc[4];
 #pragma unroll
-  for (int q = 0; q < TAIL; ++q) {
-    const int tl = S - 16;                   // remaining offsets per group
-    const int e = lane + 16 * q;             // packed tail term
-    const int g0 = e / tl;
-    const bool ok = g0 < 4;
-    const int g = ok ? g0 : 0;
-    tGrp[q] = g;
-    tOff[q] = 16 + (ok ? e % tl : 0) - r;
-    tG1[q] = g == 1;
-    tG3[q] = g == 3;
-    tH[q] = g >= 2;
-    tMul[q] = ok ? ((g & 1) ? 1 : -1) * (g >= 2 ? 65536 : 1) : 0;
-  }
-  int stoff[NS];
+    for (int k = 0; k < 4; ++k) {
+      const int p = pidx(clampi(u0 + lx - k * 4 - ly, 0, Gw - 1), min(v0 + k * 4 + ly, Gh - 1));
+      of[k] = gp(inF)[p];
+      oc[k] = gp(inC)[p];
+    }
+    // a tile visited before: its results, and the border flows they came from
+    int32_t* const outF = grid_flow(f, lev, a.inbuf ^ 1);
+    int32_t* const outC = grid_cost(f, lev, a.inbuf ^ 1);
+    int32_t* const was = reinterpret_cast<int32_t*>(f.ws + f.o_seen) + tile * 32;
+    int32_t pf[4], pc[4], wasF = 0;
+    if (!first) {
 #pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    const int g = k < 4 ? k : tGrp[k - 4 < TAIL ? k - 4 : 0];
-    const int o = k < 4 ? offFull : tOff[k - 4 < TAIL ? k - 4 : 0];
-    const int du = g < 2 ? o : (g == 2 ? -r - 1 : r);
-    const int dv = g < 2 ? (g == 0 ? -r - 1 : r) : o;
-    stoff[k] = (r + 1 + dv) * TW + (M + r + du);
-  }
-  bool abandoned = false;
-  auto wait_word = [&](int u, uint64_t w) -> uint64_t {
-    if ((uint32_t)(w >> 48) != tag && !abandoned) {
-      const uint64_t t0 = rt_clock();
-      do {
-        __builtin_amdgcn_s_sleep(1);
-        w = __hip_atomic_load(&xin[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (rt_clock() - t0 > timeout_ticks) {
-          __hip_atomic_store(status, (int32_t)FF_ERR_DEVICE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          abandoned = true;
-          break;
+      for (int k = 0; k < 4; ++k) {
+        const int p = pidx(clampi(u0 + lx - k * 4 - ly, 0, Gw - 1), min(v0 + k * 4 + ly, Gh - 1));
+        pf[k] = ld_coh(outF + p);
+        pc[k] = ld_coh(outC + p);
+      }
+      wasF = ld_coh(was + (lane & 31));
+    }
+    // the source census under the tile's patches, in ascending grid
+    // coordinates from (gxm, gym), clamped to the image in pixels; lane
+    // (ly, lx) takes the samples at rows ly + 4 k, columns lx + 16 j
+    const int TH = kTileH + 2 * r + 1, TW = kTileW + kTileH + 2 * r;
+    constexpr int NK = (kTileH + 2 * RM + 1 + 3) / 4, NJ = (kTileW + kTileH + 2 * RM + 15) / 16;
+    const int gxm = sx > 0 ? u0 - kTileH - r : Gw - kTileW - u0 - r;
+    const int gym = sy > 0 ? v0 - r - 1 : Gh - kTileH - v0 - r;
+    int scol[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) scol[j] = clampi((gxm + lx + 16 * j) * n, 0, c.Ws - 1);
+    auto stage = [&](auto K0, auto K1) {
+      uint32_t w[K1.value - K0.value][NJ];
+#pragma unroll
+      for (int k = K0.value; k < K1.value; ++k) {
+        const int row = clampi((gym + ly + 4 * k) * n, 0, c.Hs - 1) * c.Ws;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) w[k - K0.value][j] = gp(c.src)[row + scol[j]];
+      }
+#pragma unroll
+      for (int k = K0.value; k < K1.value; ++k)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const int y = ly + 4 * k, x = lx + 16 * j;
+          if (y < TH && x < TW) {
+            s_row[y * P1 + x] = w[k - K0.value][j];
+            s_col[x * P2 + y] = w[k - K0.value][j];
+          }
         }
-      } while ((uint32_t)(w >> 48) != tag);
+    };
+    stage(std::integral_constant<int, 0>{}, std::integral_constant<int, NK / 2>{});
+    // the neighbours' border values: lanes 0..15 the column left of row
+    // `lane`, lanes 16..31 the row above; and this tile's own border words,
+    // its right column and its bottom row.  Read after the request counter.
+    uint64_t* const xr = reinterpret_cast<uint64_t*>(f.ws + f.o_xr);
+    uint64_t* const xb = reinterpret_cast<uint64_t*>(f.ws + f.o_xb);
+    const bool isl = lane < 16;
+    const int bl = lane & 15;
+    const int hu = isl ? u0 - bl - 1 : u0 + bl, hv = isl ? v0 + bl : v0 - 1;
+    const bool hok = lane < 32 && hu >= 0 && hu < Gw && hv >= 0 && hv < Gh;
+    const int ou = isl ? u0 + 15 - bl : u0 + bl - 15, ov = isl ? v0 + bl : v0 + 15;
+    const bool ook = lane < 32 && ou >= 0 && ou < Gw && ov < Gh && (isl ? tu + 1 < nu : tv + 1 < nv);
+    const int handled = __builtin_amdgcn_readfirstlane(have);
+    mem_wait();
+    uint64_t hw = 0;
+    int32_t hf = kEmpty, hc = kInf;
+    if (hok) {
+      hw = ld_coh(isl ? xr + (size_t)(tu - 1) * Gh + hv : xb + (size_t)(tv - 1) * Gw + hu);
+      hf = gp(inF)[pidx(hu, hv)];
+      hc = gp(inC)[pidx(hu, hv)];
     }
-    return w;
-  };
-  const uint32_t maxMx = (uint32_t)(Wm * Q), maxMy = (uint32_t)(Hm * Q);
-  // the polling wavefront: before the barrier that ends step col - 2, the
-  // band above's result at column col for row 0 (EMPTY without a band
-  // above or past the row's end); `pw` holds the prefetched word for col
-  uint64_t pw = above ? __hip_atomic_load(&xin[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-  auto provide = [&](int col) {
-    int32_t f = kEmpty, cst = kInf;
-    if (above && col < Gw) {
-      const uint64_t w = wait_word(col, pw);
-      f = (int32_t)(uint32_t)w;
-      const uint32_t c16 = (uint32_t)(w >> 32) & 0xFFFFu;
-      cst = c16 == 0xFFFFu ? kInf : (int32_t)c16;
-      pw = __hip_atomic_load(&xin[med3i(col + 1, 0, Gw - 1)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if ((threadIdx.x & 63) == 0) {
-      topF[col & 1] = f;
-      topC[col & 1] = cst;
-    }
-  };
-  // Both candidates of the next step are known at the end of a step: the
-  // horizontal one is the row's own result, the vertical one the result of
-  // the row above -- in this wavefront (moved down one 16-lane row by DPP),
-  // or, for a wavefront's first row, written to LDS by the wavefront above
-  // two steps earlier (the skew), or for row 0 handed over by the polling
-  // wavefront two steps ahead.  So every target word of the next step is
-  // loaded at the end of the step before and is in flight across the
-  // barrier (which waits for LDS operations only).
-  int32_t hFn = kEmpty, hCn = kInf, vFn = kEmpty, vCn = kInf;
-  int mxh = 0, myh = 0, mxv = 0, myv = 0;
-  uint32_t nb[NS];
+    stage(std::integral_constant<int, NK / 2>{}, std::integral_constant<int, NK>{});
 #pragma unroll
-  for (int k = 0; k < NS; ++k) nb[k] = 0;
-  // pxq: the next column's x in 1/Q px (computed ahead, off the chain from
-  // a step's result to its successor's loads); hok: that column has a
-  // horizontal predecessor
-  const int nQshift = lev + c.qshift;   // n Q = 2^(lev + qshift)
-  auto pxq_of = [&](int un) { return gx_of(med3i(un, 0, Gw - 1)) << nQshift; };
-  auto prep = [&](int pxq, bool hok, int32_t f, int32_t cst, int32_t vf, int32_t vc) {
-    hFn = hok ? f : kEmpty;
-    hCn = hok ? cst : kInf;
-    vFn = vf;
-    vCn = vc;
-    mxh = pxq + fx_of(hFn);
-    myh = py * Q + fy_of(hFn);
-    mxv = pxq + fx_of(vFn);
-    myv = py * Q + fy_of(vFn);
-    const int Mxh = mxh >> c.qshift, Myh = myh >> c.qshift;
-    const int Mxv = mxv >> c.qshift, Myv = myv >> c.qshift;
-    // every product has both factors below 2^24 (plane words <= 2^22, phase
-    // < 64, coordinates and pitches < 8192): full-rate 24-bit multiplies
-    const uint32_t phh = dT + __umul24(c.pw, (uint32_t)(((myh & c.qmask) << c.qshift) + (mxh & c.qmask)));
-    const uint32_t base2 = phh + __umul24(clamp0(Mxh - nsx * (r + 1), Wm), Hd);
-    const uint32_t base3 = phh + __umul24(clamp0(Mxh + nsx * r, Wm), Hd);
-    const uint32_t phv = __umul24(c.pw, (uint32_t)(((myv & c.qmask) << c.qshift) + (mxv & c.qmask)));
-    const uint32_t base0 = phv + __umul24(clamp0(Myv - nsy * (r + 1), Hm), Wd);
-    const uint32_t base1 = phv + __umul24(clamp0(Myv + nsy * r, Hm), Wd);
-    const uint32_t xv = clamp0(Mxv + oxFull, Wm);
-    const uint32_t yh = clamp0(Myh + oyFull, Hm);
-    nb[0] = tword(tgt, base0 + xv);
-    nb[1] = tword(tgt, base1 + xv);
-    nb[2] = tword(tgt, base2 + yh);
-    nb[3] = tword(tgt, base3 + yh);
-#pragma unroll
-    for (int q = 0; q < TAIL; ++q) {
-      // the lane's group (a per-lane constant) picks the base and the free
-      // coordinate
-      const uint32_t xq = clamp0(Mxv + nsx * tOff[q], Wm);
-      const uint32_t yq = clamp0(Myh + nsy * tOff[q], Hm);
-      const uint32_t bv = tG1[q] ? base1 : base0, bh = tG3[q] ? base3 : base2;
-      nb[4 + q] = tword(tgt, (tH[q] ? bh : bv) + (tH[q] ? yq : xq));
+    for (int k = 0; k < 4; ++k) {
+      const int u = u0 + lx - k * 4 - ly;
+      const bool ok = u >= 0 && u < Gw && v0 + k * 4 + ly < Gh;
+      const int2 own = ok ? make_int2(of[k], oc[k]) : make_int2(kEmpty, kInf);
+      s_own[(k * 4 + ly) * kPitchOwn + lx] = own;
+      s_res[(k * 4 + ly) * kPitchOwn + lx] = first || !ok ? own : make_int2(pf[k], pc[k]);
     }
-  };
-  const bool waveFirst = (row & 3) == 0;
-  auto step = [&](int t, int tb) {
-    const int j = t - tb;
-    const int u = t - skew;
-    const bool active = rowok && u >= 0 && u < Gw;
-    const int pxq1 = pxq_of(u + 1);
-    const int32_t curF0 = inF[row][j], curC0 = inC[row][j];
-    // the next step's vertical candidate of a wavefront's first row: row 0
-    // from the polling wavefront, else the row above's result of step t - 1
-    const int32_t lvF = row == 0 ? topF[(t + 1) & 1] : bufF[(t - 1) & 1][row > 0 ? row - 1 : 0];
-    const int32_t lvC = row == 0 ? topC[(t + 1) & 1] : bufC[(t - 1) & 1][row > 0 ? row - 1 : 0];
-    const int32_t vF = vFn, vC = vCn, hF = hFn, hC = hCn;
-    // candidate centres in 1/Q px; EMPTY (-32768, -32768) always falls
-    // outside, so the validity test also rejects empty candidates
-    const bool useV = active && vF != curF0 && (uint32_t)mxv <= maxMx && (uint32_t)myv <= maxMy;
-    const bool useH = active && hF != curF0 && (uint32_t)mxh <= maxMx && (uint32_t)myh <= maxMy;
-    const int tbase = row * TW + (u - tb);
-    uint32_t aw[NS];
-#pragma unroll
-    for (int k = 0; k < NS; ++k) aw[k] = tile[tbase + stoff[k]];
-    // entering minus leaving terms, vertical in the low half, horizontal in
-    // the high half of one word (|sums| < 2^15)
-    int32_t packed = (int32_t)__popc((aw[1] ^ nb[1]) & fullMask) - (int32_t)__popc((aw[0] ^ nb[0]) & fullMask);
-    packed += (int32_t)((uint32_t)((int32_t)__popc((aw[3] ^ nb[3]) & fullMask) -
-                                   (int32_t)__popc((aw[2] ^ nb[2]) & fullMask)) << 16);
-#pragma unroll
-    for (int q = 0; q < TAIL; ++q) {
-      packed += __mul24((int32_t)__popc(aw[4 + q] ^ nb[4 + q]), tMul[q]);
+    if ((uint32_t)(hw >> 48) == a.tag) {
+      const uint32_t c16 = (uint32_t)(hw >> 32) & 0xFFFFu;
+      hf = (int32_t)(uint32_t)hw;
+      hc = c16 == 0xFFFFu ? kInf : (int32_t)c16;
     }
-    const int32_t sum = row16_sum(packed);
-    const int32_t dvs = (int32_t)(int16_t)(uint16_t)((uint32_t)sum & 0xFFFFu);
-    const int32_t dhs = (sum - dvs) >> 16;
-    // candidate order of Eq. 2: current, vertical, horizontal; strict <
-    int32_t curF = curF0, curC = curC0;
-    if (useV && vC + dvs < curC) { curF = vF; curC = vC + dvs; }
-    if (useH && hC + dhs < curC) { curF = hF; curC = hC + dhs; }
-    // the next step's candidates: the row above's result moved down one row
-    // of 16 lanes (rows 1..3 of the wavefront), or the LDS value
-    const int32_t dF = __builtin_amdgcn_update_dpp(0, curF, 0x142, 0xE, 0xF, false);   // row_bcast:15
-    const int32_t dC = __builtin_amdgcn_update_dpp(0, curC, 0x142, 0xE, 0xF, false);
-    prep(pxq1, u >= 0, curF, curC, waveFirst ? lvF : dF, waveFirst ? lvC : dC);
-    if (lane == 0) {
-      bufF[t & 1][row] = curF;
-      bufC[t & 1][row] = curC;
-      outF[row][j] = curF;
-      outC[row][j] = curC;
-      if (publish && active)
-        __hip_atomic_store(gp(xout + u), xch_pack(curF, curC, tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  };
-  const int TT = TH * TW;
-  constexpr int KPT = (kTileWords + BH * L - 1) / (BH * L);   // tile words per thread
-  for (int tb = 0; tb < nsteps; tb += CH) {
-    // a trailing sweep starts a batch once the columns it stages are final
-    if (waitProg) {
-      if (threadIdx.x == 0)
-        for (int m = 0; m < BH / kXRows; ++m)
-          wait_prog(waitProg + band * (BH / kXRows) + m, tag, min(tb + CH, Gw), status, timeout_ticks);
-      __syncthreads();
-    }
-    // stage this batch's own flows and costs (row r at step tb + j works on
-    // u = tb + j - s(r)) and the source tile: tile(y, x) is the source
-    // census at transformed grid (u, v) = (tb - M - r + x, v0 - r - 1 + y),
-    // clamped to the image in pixels
+    // cost doubled, the low bit marks a value that this tile has not seen
+    // (EMPTY's cost is never used)
+    if (lane < 32) (isl ? s_left : s_top)[bl] = make_int2(hf, (int)((uint32_t)hc << 1) | (first || hf != wasF ? 1 : 0));
+    if (lane == 32) s_top[kTileW] = make_int2(kEmpty, 0);
+    __syncthreads();
+    // what the readers of this tile's border hold so far
+    const int oidx = isl ? bl * kPitchOwn + 15 : 15 * kPitchOwn + bl;
+    int2 seen = s_res[oidx];
+    asm volatile("" : "+v"(seen.x), "+v"(seen.y));   // read before the steps overwrite it
+    // ---- the steps
+    const int i = lane >> 2, j = lane & 3;
+    g_byte* const tgt = (g_byte*)(c.dst);
+    const uint32_t dT = (uint32_t)(c.dstT - c.dst);   // transposed planes after the row-major ones
+    const int Wm = c.Wd - 1, Hm = c.Hd - 1;
+    const uint32_t Wd = (uint32_t)c.Wd, Hd = (uint32_t)c.Hd;
+    const uint32_t maxMx = (uint32_t)(Wm * Q), maxMy = (uint32_t)(Hm * Q);
+    const int rn = r * n;
+    const int offX0 = -sx * (r + 1) * n, offX1 = sx * rn, offY0 = -sy * (r + 1) * n, offY1 = sy * rn;
+    const int vi = v0 + i, gyi = gy_of(vi), gx0 = gx_of(u0 - i);
+    const int js = kWide ? CW * j : j;                // the lane's first word of a line
+    const int jt = (kWide ? CW * j : j * n) - rn;     // and its place in the target's
+    const uint32_t* spv = s_row + (gyi - sy * (r + 1) - gym) * P1 + (gx0 - r - gxm) + js;
+    const uint32_t* sph = s_col + (gx0 - sx * (r + 1) - gxm) * P2 + (gyi - r - gym) + js;
+    const int eV = sy * Sd * P1, eH = sx * Sd * P2;   // from a leaving line to the entering one
+    // the last word of line j (S = 4 CW + 1)
+    const uint32_t* spt = (j < 2 ? spv + (j & 1) * eV : sph + (j & 1) * eH) + (S - 1 - js);
+    const int32_t tmul = (j & 1 ? 1 : -1) * (j >= 2 ? 65536 : 1);
+    const int tailOff = (S - 1) * n - rn - jt;
+    const int nQshift = lev + c.qshift;
+    const int pyq = gyi << nQshift;
+    int pxq = gx0 << nQshift;
+    int uL = vi < Gh ? u0 - i : -(1 << 20);
+    int2 h = s_left[i], v = i == 0 ? s_top[0] : s_left[i > 0 ? i - 1 : 0];
+    // LDS values are read a step ahead of their use
+    int2 ownN = s_own[i * kPitchOwn], oldN = s_res[i * kPitchOwn], topN = s_top[1];
+    const bool roomX = Wm >= 2 * rn, roomY = Hm >= 2 * rn;   // else every line clamps
+#pragma unroll 1
+    for (int t = 0; t < kTileW; ++t) {
+      const int2 own = ownN, old = oldN, top = topN;
+      ownN = s_own[i * kPitchOwn + t + 1];
+      oldN = s_res[i * kPitchOwn + t + 1];
+      topN = s_top[t + 2];
+      const int mxv = pxq + fx_of(v.x), myv = pyq + fy_of(v.x), mxh = pxq + fx_of(h.x), myh = pyq + fy_of(h.x);
+      // EMPTY (-32768, -32768) lies outside, so this rejects it too
+      // a point none of whose inputs changed keeps its result
+      const bool in = ((uint32_t)uL < (uint32_t)Gw) & (((v.y | h.y) & 1) != 0);
+      const bool useV = in & (v.x != own.x) & ((uint32_t)mxv <= maxMx) & ((uint32_t)myv <= maxMy);
+      const bool useH = in & (h.x != own.x) & ((uint32_t)mxh <= maxMx) & ((uint32_t)myh <= maxMy);
+      int2 res = in ? own : old;
+      if (__ballot(useV || useH)) {
+        const int Mxv = mxv >> c.qshift, Myv = myv >> c.qshift, Mxh = mxh >> c.qshift, Myh = myh >> c.qshift;
+        // every product has both factors below 2^24 (plane words <= 2^22,
+        // phase < 64, coordinates and pitches < 8192)
+        const uint32_t plv = __umul24(c.pw, (uint32_t)(((myv & c.qmask) << c.qshift) + (mxv & c.qmask)));
+        const uint32_t plh = dT + __umul24(c.pw, (uint32_t)(((myh & c.qmask) << c.qshift) + (mxh & c.qmask)));
+        uint32_t l0 = plv + __umul24(clamp0(Myv + offY0, Hm), Wd), l1 = plv + __umul24(clamp0(Myv + offY1, Hm), Wd);
+        uint32_t l2 = plh + __umul24(clamp0(Mxh + offX0, Wm), Hd), l3 = plh + __umul24(clamp0(Mxh + offX1, Wm), Hd);
+        uint32_t lea = 0, ent = 0, leaH = 0, entH = 0, tail = 0;
+        const bool clampV = (uint32_t)(Mxv - rn) > (uint32_t)(Wm - 2 * rn);
+        const bool clampH = (uint32_t)(Myh - rn) > (uint32_t)(Hm - 2 * rn);
+        if (S && roomX && roomY && __ballot((useV & clampV) | (useH & clampH)) == 0) {
+          // no sample of a candidate in use clamps; the lanes of a candidate
+          // that is not read word 0
+          l0 = useV ? l0 + (uint32_t)(Mxv + jt) : 0;
+          l1 = useV ? l1 + (uint32_t)(Mxv + jt) : 0;
+          l2 = useH ? l2 + (uint32_t)(Myh + jt) : 0;
+          l3 = useH ? l3 + (uint32_t)(Myh + jt) : 0;
+          const uint32_t lt = j < 2 ? (j & 1 ? l1 : l0) : (j & 1 ? l3 : l2);
+          uint32_t w0[CW], w1[CW], w2[CW], w3[CW];
+          load_line<CW, kWide, LEV>(tgt, l0, lev, w0);
+          load_line<CW, kWide, LEV>(tgt, l1, lev, w1);
+          load_line<CW, kWide, LEV>(tgt, l2, lev, w2);
+          load_line<CW, kWide, LEV>(tgt, l3, lev, w3);
+          const uint32_t wt = tword(tgt, lt + (uint32_t)((j < 2 ? useV : useH) ? tailOff : 0));
 #pragma unroll
-    for (int jj = 0; jj < CH / L; ++jj) {
-      const int j = lane + jj * L;
-      const int u = tb + j - skew;
-      if (rowok && u >= 0 && u < Gw) {
-        if (coherent) {
-          inF[row][j] = ld_coh(Frow + gx_of(u));
-          inC[row][j] = ld_coh(Crow + gx_of(u));
+          for (int m = 0; m < CW; ++m) {
+            const int k = kWide ? m : 4 * m;
+            lea += __popc(w0[m] ^ spv[k]);
+            ent += __popc(w1[m] ^ spv[eV + k]);
+            leaH += __popc(w2[m] ^ sph[k]);
+            entH += __popc(w3[m] ^ sph[eH + k]);
+          }
+          tail = __popc(wt ^ *spt);
+          asm volatile("" : "+v"(tail));   // keeps this branch's loads in it
         } else {
-          inF[row][j] = Frow[gx_of(u)];
-          inC[row][j] = Crow[gx_of(u)];
+          if (S) {
+            // all loads first: one round trip
+            uint32_t x[4][CW];
+#pragma unroll
+            for (int m = 0; m < CW; ++m) {
+              const int o = (js + (kWide ? m : 4 * m)) * n - rn;
+              const uint32_t xv = clamp0(Mxv + o, Wm), yh = clamp0(Myh + o, Hm);
+              x[0][m] = tword(tgt, l0 + xv);
+              x[1][m] = tword(tgt, l1 + xv);
+              x[2][m] = tword(tgt, l2 + yh);
+              x[3][m] = tword(tgt, l3 + yh);
+            }
+            const uint32_t lt = j < 2 ? (j & 1 ? l1 : l0) : (j & 1 ? l3 : l2);
+            const uint32_t wt = tword(tgt, lt + clamp0((j < 2 ? Mxv : Myh) + rn, j < 2 ? Wm : Hm));
+#pragma unroll
+            for (int m = 0; m < CW; ++m) {
+              const int k = kWide ? m : 4 * m;
+              lea += __popc(x[0][m] ^ spv[k]);
+              ent += __popc(x[1][m] ^ spv[eV + k]);
+              leaH += __popc(x[2][m] ^ sph[k]);
+              entH += __popc(x[3][m] ^ sph[eH + k]);
+            }
+            tail = __popc(wt ^ *spt);
+          } else {
+            for (int k = 0; k < Sd - js; k += 4) {
+              const int o = (js + k) * n - rn;
+              const uint32_t xv = clamp0(Mxv + o, Wm), yh = clamp0(Myh + o, Hm);
+              lea += __popc(tword(tgt, l0 + xv) ^ spv[k]);
+              ent += __popc(tword(tgt, l1 + xv) ^ spv[eV + k]);
+              leaH += __popc(tword(tgt, l2 + yh) ^ sph[k]);
+              entH += __popc(tword(tgt, l3 + yh) ^ sph[eH + k]);
+            }
+          }
         }
+        // vertical sum in the low half, horizontal in the high half
+        // (|sums| < 2^15), over the row's four lanes
+        int32_t d = (int32_t)(ent - lea) + (int32_t)((entH - leaH) << 16) + __mul24((int32_t)tail, tmul);
+        d += __builtin_amdgcn_update_dpp(0, d, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
+        d += __builtin_amdgcn_update_dpp(0, d, 0x4E, 0xF, 0xF, false);   // quad_perm [2,3,0,1]
+        const int32_t dV = (int32_t)(int16_t)(uint16_t)((uint32_t)d & 0xFFFFu), dH = (d - dV) >> 16;
+        // candidate order of Eq. 2: current, vertical, horizontal; strict <
+        const int costV = (v.y >> 1) + dV, costH = (h.y >> 1) + dH;
+        if (useV && costV < res.y) res = make_int2(v.x, costV);
+        if (useH && costH < res.y) res = make_int2(h.x, costH);
       }
-    }
-    if (!pollWave) {
-      // all of a thread's tile loads are issued before its first LDS write
-      uint32_t tv[KPT];
-#pragma unroll
-      for (int k = 0; k < KPT; ++k) {
-        const int e = min((int)threadIdx.x + k * BH * L, TT - 1);
-        const int y = e / TW, x = e - y * TW;
-        const int gxp = gx_of(tb - M - r + x) * n, gyp = gy_of(v0 - r - 1 + y) * n;
-        tv[k] = c.src[(size_t)clampi(gyp, 0, c.Hs - 1) * c.Ws + clampi(gxp, 0, c.Ws - 1)];
-      }
-#pragma unroll
-      for (int k = 0; k < KPT; ++k) {
-        const int e = (int)threadIdx.x + k * BH * L;
-        if (e < TT) tile[e] = tv[k];
-      }
-    } else if (tb == 0) {
-      provide(0);
-      provide(1);
+      s_res[i * kPitchOwn + t] = res;
+      // next step's candidates: horizontal the row's own result, vertical the
+      // result of the row above (four lanes down; across a 16-lane DPP row
+      // its last lane's value; the top row from the border)
+      h = make_int2(res.x, (int)((uint32_t)res.y << 1) | (first || res.x != old.x ? 1 : 0));
+      v.x = __builtin_amdgcn_update_dpp(top.x, h.x, 0x114, 0xF, 0xF, false);   // row_shr:4
+      v.y = __builtin_amdgcn_update_dpp(top.y, h.y, 0x114, 0xF, 0xF, false);
+      v.x = __builtin_amdgcn_update_dpp(v.x, h.x, 0x142, 0xE, 0x1, false);     // row_bcast:15
+      v.y = __builtin_amdgcn_update_dpp(v.y, h.y, 0x142, 0xE, 0x1, false);
+      pxq += sx * (1 << nQshift);
+      spv += sx;
+      sph += sx * P2;
+      spt += j < 2 ? sx : sx * P2;
+      ++uL;
     }
     __syncthreads();
-    if (tb == 0) {
-      // step 0's candidates (row 0's vertical one from the polling wavefront);
-      // a barrier before the polling wavefront reuses that LDS slot
-      if (!pollWave) prep(pxq_of(0), false, kEmpty, kInf, row == 0 ? topF[0] : kEmpty, row == 0 ? topC[0] : kInf);
-      lds_barrier();
-    }
-    const int te = min(tb + CH, nsteps);
-    for (int t = tb; t < te; ++t) {
-      if (pollWave) provide(t + 2);
-      else step(t, tb);
-      lds_barrier();
-    }
-    // write the batch's results back
+    // ---- results out, changed border words published
 #pragma unroll
-    for (int jj = 0; jj < CH / L; ++jj) {
-      const int j = lane + jj * L;
-      const int u = tb + j - skew;
-      if (rowok && u >= 0 && u < Gw && tb + j < te) {
-        if (coherent) {
-          st_coh(Frow + gx_of(u), outF[row][j]);
-          st_coh(Crow + gx_of(u), outC[row][j]);
-        } else {
-          Frow[gx_of(u)] = outF[row][j];
-          Crow[gx_of(u)] = outC[row][j];
-        }
+    for (int k = 0; k < 4; ++k) {
+      const int u = u0 + lx - k * 4 - ly, v = v0 + k * 4 + ly;
+      if (u >= 0 && u < Gw && v < Gh) {
+        const int2 x = s_res[(k * 4 + ly) * kPitchOwn + lx];
+        st_coh(outF + pidx(u, v), x.x);
+        st_coh(outC + pidx(u, v), x.y);
       }
     }
-    // after steps < te every row has finished columns u <= te - 1 - s(rows - 1)
-    if (pubProg) publish_prog(pubProg + band, tag, min(max(te - skewLast, 0), Gw));
-  }
+    if (lane < 32) st_coh(was + lane, hf);
+    const int2 now = s_res[oidx];
+    const bool chg = ook && now.x != seen.x;
+    if (chg) st_coh(isl ? xr + (size_t)tu * Gh + ov : xb + (size_t)tv * Gw + ou, xch_pack(now.x, now.y, a.tag));
+    const uint64_t cm = __ballot(chg);
+    mem_wait();
+    __syncthreads();
+    gt = relax_done(q, cnt, a.base, tile, nu, g0, handled, (cm & 0xFFFFu) != 0, (cm & 0x7FFF0000u) != 0,
+                    (cm & 0x80000000u) != 0, done);
+    first = false;
+    if (gt < 0) {
+      mine += q.G;
+      first = mine < q.T;
+      gt = first ? mine : relax_wait(q, done);
+    }
+  } while (gt >= 0);
 }
 
 // write the grid of level lev into the full-resolution outputs (inspection
 // stops); grid: (W / 256, H, fields)
-__global__ void k_write_grid(const FieldRec* __restrict__ table, int lev) {
+__global__ void k_write_grid(const FieldRec* __restrict__ table, int lev, int buf) {
   const FieldRec& f = table[blockIdx.z];
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
   const int y = blockIdx.y;
   if (x >= f.Ws || y >= f.Hs) return;
   const int n = 1 << lev;
-  const int Gw = (f.Ws + n - 1) >> lev, Gh = (f.Hs + n - 1) >> lev;
+  const int Gw = (f.Ws + n - 1) >> lev;
   const size_t o = (size_t)y * f.Ws + x;
   if ((x % n) == 0 && (y % n) == 0) {
-    f.flow[o] = grid_flow(f, lev)[(size_t)(y / n) * Gw + x / n];
-    f.cost[o] = grid_cost(f, lev, Gw * Gh)[(size_t)(y / n) * Gw + x / n];
+    f.flow[o] = grid_flow(f, lev, buf)[(size_t)(y / n) * Gw + x / n];
+    f.cost[o] = grid_cost(f, lev, buf)[(size_t)(y / n) * Gw + x / n];
   } else {
     f.flow[o] = kEmpty;
     f.cost[o] = kInf;
   }
 }
 
-// One propagation launch: a sweep, or a sweep pair (A, X, B workgroups);
-// lev is the level of the (second) sweep.
-struct PropLaunch {
-  int lev, qshift, sx, sy;
-  uint32_t tag;
-  int32_t* ticket;
-  int32_t* status;
-  uint64_t timeout;
-  int pair, rs, R;
-};
-
-template <int BH>
-static void launch_propagate_bh(int r, int bands, int bands_a, hipStream_t stream, const FieldRec* table, int f0,
-                                int nf, const PropLaunch& L) {
-  const dim3 grid(L.pair ? bands_a + bands * (1 + BH / kXRows) : bands), block(BH * kLanesProp + 64);
-  const int S = 2 * r + 1, tail = S > 16 ? (4 * (S - 16) + 15) / 16 : 0;
-#define FF_PROP(TA)                                                                                                \
-  if (tail == TA) {                                                                                                \
-    k_propagate<TA, BH><<<grid, block, 0, stream>>>(table, f0, nf, L.lev, L.qshift, L.sx, L.sy, L.tag, L.ticket,    \
-                                                    L.status, L.timeout, L.pair, bands, bands_a, L.rs, L.R);       \
-    return;                                                                                                        \
+template <int S>
+static void launch_sweep_s(const FieldRec* table, const SweepArgs& a, const RelaxQ& q, hipStream_t stream) {
+  switch (a.lev) {
+    case 0: k_sweep<S, 0><<<q.G, 64, 0, stream>>>(table, a, q); break;
+    case 1: k_sweep<S, 1><<<q.G, 64, 0, stream>>>(table, a, q); break;
+    case 2: k_sweep<S, 2><<<q.G, 64, 0, stream>>>(table, a, q); break;
+    case 3: k_sweep<S, 3><<<q.G, 64, 0, stream>>>(table, a, q); break;
+    default: k_sweep<S, -1><<<q.G, 64, 0, stream>>>(table, a, q); break;
   }
-  FF_PROP(0) FF_PROP(1) FF_PROP(2) FF_PROP(3) FF_PROP(4)
-#undef FF_PROP
 }
 
-static void launch_propagate(int bh, int r, int bands, int bands_a, hipStream_t stream, const FieldRec* table, int f0,
-                             int nf, const PropLaunch& L) {
-  if (bh == 8)
-    launch_propagate_bh<8>(r, bands, bands_a, stream, table, f0, nf, L);
-  else if (bh == 32)
-    launch_propagate_bh<32>(r, bands, bands_a, stream, table, f0, nf, L);
-  else
-    launch_propagate_bh<16>(r, bands, bands_a, stream, table, f0, nf, L);
+// the paper's radii (r = 8, r2 = 6) have instances of their own
+static void launch_sweep(int r, const FieldRec* table, const SweepArgs& a, const RelaxQ& q, hipStream_t stream) {
+  if (r == 8) launch_sweep_s<17>(table, a, q, stream);
+  else if (r == 6) launch_sweep_s<13>(table, a, q, stream);
+  else k_sweep<0, -1><<<q.G, 64, 0, stream>>>(table, a, q);
 }
 
 // ---------------------------------------------------------------- host plans
 struct FieldPlan {
   bool has_tree;
   TreeLayout tree;        // offsets relative to the field region
-  size_t off_grid[5];
-  size_t off_xch, off_xch2, off_prog;
+  size_t off_grid[5], off_st[5];
+  size_t off_alt, off_xr, off_xb, off_seen;
+  size_t clear_words;     // from off_st[0]: counters and border words
+  size_t alt_bytes;       // of an off_alt outside the tree's region, else 0
   size_t bytes;
 };
 
@@ -1075,19 +809,36 @@ static FieldPlan field_plan(const ff_desc* src, const ff_desc* dst, const ff_mat
     P.off_grid[lev] = off;
     off += G * 8;
   }
-  const size_t nb = (size_t)((src->height + kMinBandRows - 1) / kMinBandRows);
   off = align_up(off, 256);
-  P.off_xch = off;
-  off = align_up(off + nb * src->width * 8, 256);
-  P.off_xch2 = off;
-  off = align_up(off + nb * src->width * 8, 256);
-  P.off_prog = off;
-  off += 2 * (size_t)prog_words(src->height) * 4;
+  const size_t clear0 = off;
+  for (int lev = 0; lev <= p->k; ++lev) {
+    const int n = 1 << lev;
+    P.off_st[lev] = off;
+    off += (size_t)tiles_x((src->width + n - 1) / n) * tiles_y((src->height + n - 1) / n) * 4;
+  }
+  off = align_up(off, 256);
+  P.off_xr = off;
+  off += (size_t)tiles_x(src->width) * src->height * 8;
+  P.off_xb = off;
+  off += (size_t)tiles_y(src->height) * src->width * 8;
+  P.clear_words = (off - clear0) / 4;
+  P.off_seen = off;
+  off += (size_t)tiles_x(src->width) * tiles_y(src->height) * 32 * 4;
+  // the second grid buffer: what the tree build needs beside the finished
+  // tree (which seeding reads) is free once the tree stands; a source that
+  // does not fit there gets a region of its own, the field's last
+  const size_t alt = (size_t)src->width * src->height * 8;
+  if (P.has_tree && P.tree.bytes - P.tree.off_perm2 >= alt) {
+    P.off_alt = P.tree.off_perm2;
+  } else {
+    off = align_up(off, 256);
+    P.off_alt = off;
+    P.alt_bytes = align_up(alt, 256);
+    off += alt;
+  }
   P.bytes = align_up(off, 256);
   return P;
 }
-
-static int band_rows_of(const ff_match_params* p) { return p->band_rows == 0 ? 16 : p->band_rows; }
 
 static ff_status check_params(const ff_desc* src, const ff_desc* dst, int radius, const ff_match_params* p) {
   if (!src || !dst || !p) return FF_ERR_ARG;
@@ -1136,15 +887,16 @@ struct JobArray {
 };
 
 struct BatchLayout {
-  size_t off_tickets, off_table;
-  int launches;
+  size_t off_ctl, off_ring, off_table;   // scheduler words of every launch, the queue they share
+  size_t ctl_words;                      // from off_ctl, cleared per call
+  int launches, cap;
   JobArray<size_t> off_field;   // per table entry
   JobArray<int> order;          // table entry -> job index (grouped by radius)
   size_t bytes;
 };
 
 static BatchLayout batch_layout(const ff_field_job* jobs, int n, const ff_match_params* p) {
-  BatchLayout B;
+  BatchLayout B{};
   B.order.resize(n);
   for (int i = 0; i < n; ++i) B.order[i] = i;
   if (n > 1)
@@ -1154,9 +906,15 @@ static BatchLayout batch_layout(const ff_field_job* jobs, int n, const ff_match_
   for (int i = 0; i < n; ++i)
     if (i == 0 || jobs[B.order[i]].radius != jobs[B.order[i - 1]].radius) ++groups;
   size_t off = kStatusBytes;
-  B.off_tickets = off;
+  B.off_ctl = off;
   B.launches = (p->k + 1) * p->n_prop * groups;
-  off = align_up(off + (size_t)B.launches * 4, 256);
+  off += (size_t)B.launches * sizeof(RelaxCtl);
+  B.off_ring = off;
+  for (int i = 0; i < n; ++i)   // tiles of the finest level over all fields: every launch has fewer
+    B.cap += tiles_x(jobs[i].src->width) * tiles_y(jobs[i].src->height);
+  off += (size_t)B.cap * 4;
+  B.ctl_words = (off - B.off_ctl) / 4;
+  off = align_up(off, 256);
   B.off_table = off;
   off = align_up(off + (size_t)n * sizeof(FieldRec), 256);
   B.off_field.resize(n);
@@ -1208,10 +966,15 @@ static FieldRec make_rec(const ff_field_job& j, const ff_match_params* p, char* 
     r.o_cnt = (uint32_t)P.tree.off_cnt;
     r.o_key = (uint32_t)P.tree.off_key;
   }
-  for (int l = 0; l < 5; ++l) r.o_grid[l] = (uint32_t)P.off_grid[l];
-  r.o_xch = (uint32_t)P.off_xch;
-  r.o_xch2 = (uint32_t)P.off_xch2;
-  r.o_prog = (uint32_t)P.off_prog;
+  for (int l = 0; l < 5; ++l) {
+    r.o_grid[l] = (uint32_t)P.off_grid[l];
+    r.o_st[l] = (uint32_t)P.off_st[l];
+  }
+  r.o_alt = (uint32_t)P.off_alt;
+  r.o_xr = (uint32_t)P.off_xr;
+  r.o_xb = (uint32_t)P.off_xb;
+  r.o_seen = (uint32_t)P.off_seen;
+  r.clear_words = (uint32_t)P.clear_words;
   return r;
 }
 
@@ -1231,11 +994,16 @@ static void write_table(const JobArray<FieldRec>& recs, int nrec, FieldRec* dev,
 static ff_status run_batch(const ff_field_job* jobs, int n, const ff_match_params* p, char* ws, const BatchLayout& B,
                            hipStream_t stream, bool tree_only = false) {
   int32_t* status = reinterpret_cast<int32_t*>(ws);
-  int32_t* tickets = reinterpret_cast<int32_t*>(ws + B.off_tickets);
+  RelaxCtl* ctl = reinterpret_cast<RelaxCtl*>(ws + B.off_ctl);
   FieldRec* table = reinterpret_cast<FieldRec*>(ws + B.off_table);
   JobArray<FieldRec> recs;
   recs.resize(n);
-  int maxW = 0, maxH = 0, maxN = 0, maxTop = 0, maxG = 0;
+  int maxW = 0, maxH = 0, maxN = 0, maxTop = 0;
+  const int k = p->k;
+  auto grid_of = [](int size, int lev) { return (size + (1 << lev) - 1) >> lev; };
+  auto tiles_of = [&](const FieldRec& f, int lev) {
+    return tiles_x(grid_of(f.Ws, lev)) * tiles_y(grid_of(f.Hs, lev));
+  };
   for (int i = 0; i < n; ++i) {
     const ff_field_job& j = jobs[B.order[i]];
     recs[i] = make_rec(j, p, ws + B.off_field[i]);
@@ -1243,15 +1011,14 @@ static ff_status run_batch(const ff_field_job* jobs, int n, const ff_match_param
     maxH = std::max(maxH, recs[i].Hs);
     maxN = std::max(maxN, recs[i].Wd * recs[i].Hd);
     maxTop = std::max(maxTop, recs[i].t_top);
-    maxG = std::max(maxG, recs[i].Ws * recs[i].Hs);
+    if (i > 0 && recs[i].r == recs[i - 1].r)
+      for (int lev = 0; lev <= k; ++lev) recs[i].t0[lev] = recs[i - 1].t0[lev] + tiles_of(recs[i - 1], lev);
   }
   const int qshift = ilog2i(jobs[0].dst->subpel);
-  const int k = p->k;
-  const int bh = band_rows_of(p);
   fill_i32(status, 1, 0, stream);
-  fill_i32(tickets, (size_t)B.launches, 0, stream);
+  fill_i32(reinterpret_cast<int32_t*>(ctl), B.ctl_words, 0, stream);
   write_table(recs, n, table, stream);
-  k_clear_xch<<<dim3(64, n), 256, 0, stream>>>(table, kMinBandRows);
+  k_clear_borders<<<dim3(64, n), 256, 0, stream>>>(table);
   if (p->use_kdtree == 1 || tree_only) {
     prof_mark(FF_PROF_TREE, stream, true);
     ff_status st = enqueue_tree_build(table, n, maxN, maxTop, p->leaf, stream);
@@ -1259,121 +1026,92 @@ static ff_status run_batch(const ff_field_job* jobs, int n, const ff_match_param
     if (st != FF_OK) return st;
   }
   if (tree_only) return launch_status();
-  auto pts = [&](int lev) { return ((maxW + (1 << lev) - 1) >> lev) * ((maxH + (1 << lev) - 1) >> lev); };
+  auto pts = [&](int lev) { return grid_of(maxW, lev) * grid_of(maxH, lev); };
   // random search: one workgroup per 256 / kLanesPt consecutive points of a grid row
   auto rs_blocks = [&](int lev) {
     const int pt = 256 / kLanesPt;
-    return (unsigned)((((maxW + (1 << lev) - 1) >> lev) + pt - 1) / pt * ((maxH + (1 << lev) - 1) >> lev));
+    return (unsigned)((grid_of(maxW, lev) + pt - 1) / pt * grid_of(maxH, lev));
   };
-  // pipelined launches need tags below 2^12 (progress words) and no
-  // inspection stops between their stages
-  const bool pipe = p->pipeline == 1 && p->max_steps < 0 && B.launches < 4096;
-  int steps = 0, cur_lev = k;
+  // the grid buffer in use: every sweep reads one and writes the other, and a
+  // level's last one ends in buffer 0
+  const int buf0 = p->n_prop & 1;
+  int steps = 0, cur_lev = k, buf = buf0;
   auto stop = [&]() { return p->max_steps >= 0 && steps >= p->max_steps; };
   auto finish = [&]() -> ff_status {
-    if (cur_lev > 0) k_write_grid<<<dim3((maxW + 255) / 256, maxH, n), 256, 0, stream>>>(table, cur_lev);
+    if (cur_lev > 0 || buf)
+      k_write_grid<<<dim3((maxW + 255) / 256, maxH, n), 256, 0, stream>>>(table, cur_lev, buf);
     return launch_status();
   };
   prof_mark(FF_PROF_SEED, stream, true);
-  k_seed<<<dim3((pts(k) + 3) / 4, n), 256, 0, stream>>>(table, k, qshift, p->use_kdtree ? 1 : 0);
+  k_seed<<<dim3((pts(k) + 3) / 4, n), 256, 0, stream>>>(table, k, qshift, p->use_kdtree ? 1 : 0, buf);
   prof_mark(FF_PROF_SEED, stream, false);
   ++steps;
   if (stop()) return finish();
-  // watchdog for the propagation's inter-band waits: 2 s of the 100 MHz clock
+  // watchdog of the sweeps' waits: 2 s of the 100 MHz clock
   const uint64_t timeout = p->watchdog_us > 0 ? (uint64_t)p->watchdog_us * 100u : 200000000ull;
   int launch = 0;
   auto sx_of = [](int i) { return ((i & 3) == 0 || (i & 3) == 3) ? 1 : -1; };
   auto sy_of = [](int i) { return ((i & 3) == 0 || (i & 3) == 2) ? 1 : -1; };
-  auto bands_at = [&](int g0, int g1, int lv) {
-    int bands = 0;
-    for (int g = g0; g < g1; ++g) bands += (((recs[g].Hs + (1 << lv) - 1) >> lv) + bh - 1) / bh;
-    return bands;
-  };
-  // one launch per patch radius group
-  auto propagate = [&](PropLaunch L) {
+  // sweep i of a level, one launch per patch radius
+  auto sweep = [&](int lev, int i) {
     prof_mark(FF_PROF_PROPAGATE, stream, true);
-    for (int g0 = 0; g0 < n;) {
-      int g1 = g0;
-      while (g1 < n && recs[g1].r == recs[g0].r) ++g1;
-      const int bands = bands_at(g0, g1, L.lev);
-      const int bands_a = L.pair == kPairCross ? bands_at(g0, g1, L.lev + 1) : bands;
-      L.tag = (uint32_t)(launch + 1);
-      L.ticket = tickets + launch;
-      launch_propagate(bh, recs[g0].r, bands, bands_a, stream, table, g0, g1 - g0, L);
+    for (int f0 = 0; f0 < n;) {
+      int f1 = f0;
+      while (f1 < n && recs[f1].r == recs[f0].r) ++f1;
+      // request counters start at -(i + 1): every sweep of a level leaves
+      // them where the next one's first visits are owed
+      const SweepArgs a{f0, f1 - f0, lev, qshift, sx_of(i), sy_of(i), (uint32_t)(launch + 1), -(i + 1), buf};
+      RelaxQ q{};
+      q.ctl = ctl + launch;
+      q.ring = reinterpret_cast<int32_t*>(ws + B.off_ring);
+      q.cap = B.cap;
+      q.T = recs[f1 - 1].t0[lev] + tiles_of(recs[f1 - 1], lev);
+      q.G = std::min(q.T, kSweepGrid);
+      q.status = status;
+      q.timeout = timeout;
+      launch_sweep(recs[f0].r, table, a, q, stream);
       ++launch;
-      g0 = g1;
+      f0 = f1;
     }
+    buf ^= 1;
     prof_mark(FF_PROF_PROPAGATE, stream, false);
   };
-  auto rsearch = [&](int lv, int step) {
-    prof_mark(FF_PROF_RANDOM_SEARCH, stream, true);
-    k_random_search<kLanesPt><<<dim3(rs_blocks(lv), n), 256, 0, stream>>>(table, lv, qshift, step, p->R);
-    prof_mark(FF_PROF_RANDOM_SEARCH, stream, false);
-  };
-  bool entered = false;   // this level's entry and first sweep ran in a cross-level pair
   for (int lev = k; lev >= 0; --lev) {
     cur_lev = lev;
-    int i = 0;
-    if (entered) {
-      i = 1;
-      entered = false;
-    } else if (lev < k) {
+    if (lev < k) {
+      buf = buf0;
       // one group of lanes per point of the coarser grid
       const unsigned gpts = (unsigned)(((size_t)pts(lev + 1) * kLanesPt + 255) / 256);
       prof_mark(FF_PROF_LEVEL_ENTRY, stream, true);
-      k_level_entry<kLanesPt><<<dim3(gpts, n), 256, 0, stream>>>(table, lev, qshift);
+      k_level_entry<kLanesPt><<<dim3(gpts, n), 256, 0, stream>>>(table, lev, qshift, buf);
       prof_mark(FF_PROF_LEVEL_ENTRY, stream, false);
       ++steps;
       if (stop()) return finish();
     }
-    while (i < p->n_prop) {
-      PropLaunch L{lev, qshift, sx_of(i), sy_of(i), 0, nullptr, status, timeout, 0, -1, p->R};
-      if (pipe && i + 1 < p->n_prop && sx_of(i + 1) == sx_of(i)) {
-        // sweeps i and i + 1 (opposite vertical directions) as one pipelined
-        // launch with the random search between them; the search after
-        // sweep i + 1 follows on its own
-        L.pair = kPairSame;
-        L.rs = i < p->n_rs ? i : -1;
-        propagate(L);
-        if (i + 1 < p->n_rs) rsearch(lev, i + 1);
-        i += 2;
-        continue;
-      }
-      if (pipe && i == p->n_prop - 1 && i >= p->n_rs && lev > 0 && sx_of(0) == sx_of(i) && sy_of(0) == -sy_of(i)) {
-        // the level's last sweep (no search after it), the next level's
-        // entry and its first sweep as one pipelined launch
-        L.lev = lev - 1;
-        L.pair = kPairCross;
-        propagate(L);
-        if (p->n_rs > 0) rsearch(lev - 1, 0);
-        entered = true;
-        ++i;
-        continue;
-      }
-      propagate(L);
+    for (int i = 0; i < p->n_prop; ++i) {
+      sweep(lev, i);
       ++steps;
       if (stop()) return finish();
       if (i < p->n_rs) {
-        rsearch(lev, i);
+        prof_mark(FF_PROF_RANDOM_SEARCH, stream, true);
+        k_random_search<kLanesPt><<<dim3(rs_blocks(lev), n), 256, 0, stream>>>(table, lev, qshift, i, p->R, buf);
+        prof_mark(FF_PROF_RANDOM_SEARCH, stream, false);
         ++steps;
         if (stop()) return finish();
       }
-      ++i;
     }
   }
-  (void)maxG;
-  cur_lev = 0;
   return finish();
 }
 
 // ---------------------------------------------------------------- no-allocation scratch
 // ff_match_field_noalloc keeps what ff_match_field keeps in its workspace
-// (status word, tickets, field table, kd-tree, level grids, handoff and
-// progress words) in this one static array per device.  On the host its name
+// (status word, scheduler words, field table, kd-tree, level grids, border
+// words) in this one static array per device.  On the host its name
 // is only a stand-in symbol, not a device address: host code uses the address
 // hipGetSymbolAddress returns for the current device, looked up once per
 // device (at ff_init, else at the entry point's first call there).
-static __device__ __align__(256) char scratch[FF_NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) char scratch[FF_NOALLOC_SCRATCH_BYTES + 8 * (size_t)kMaxPoints];
 
 namespace {
 std::mutex g_scratch_mu;
@@ -1500,7 +1238,8 @@ ff_status ff_match_field_noalloc(const ff_desc* src, const void* src_blob, const
   if (st != FF_OK) return st;
   const ff_field_job j = single_job(src, src_blob, dst, dst_blob, radius, p, proposal, flow, cost);
   const BatchLayout B = batch_layout(&j, 1, p);
-  if (B.bytes > (size_t)FF_NOALLOC_SCRATCH_BYTES) return FF_ERR_SIZE;
+  // a second grid buffer outside the tree's region has its own room
+  if (B.bytes - field_plan(src, dst, p).alt_bytes > (size_t)FF_NOALLOC_SCRATCH_BYTES) return FF_ERR_SIZE;
   st = check_job(j, p);
   if (st != FF_OK) return st;
   st = ensure_init();

@@ -37,7 +37,7 @@ namespace ff {
 
 constexpr int kSBand = 4;     // grid rows per propagation band (one wavefront each)
 constexpr int kSLanes = 16;   // lanes per point (entry, random search): one DPP row
-constexpr int kSiftRecsPerWrite = 16;
+constexpr int kSiftRecsPerWrite = 12;
 constexpr int kSiftStatusBytes = 256;
 
 struct SiftRec {

@@ -1,0 +1,58 @@
+"""The tile relaxation of the propagation sweeps against the oracle (bit for
+bit: the sweep has one solution whatever order its tiles settle in), at the
+sizes where a tile's edges, its parallelogram's ends or a launch of one tile
+matter, at radii with and without a kernel instance of their own, and with an
+odd number of sweeps, where the two grid buffers end the other way round."""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import ffo
+from synth import pairs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _field(d1, b1, d2, b2, r, **kw):
+    from paper_1508_05151_amd import ff
+    prm = ff.ff_default_params(**kw)
+    ws = torch.full((ff.ff_match_workspace_bytes(d1, d2, r, prm),), 0xA5, dtype=torch.uint8, device="cuda")
+    F = torch.empty((d1.height, d1.width), dtype=torch.int32, device="cuda")
+    Cc = torch.empty_like(F)
+    ff.ff_match_field(d1, b1, d2, b2, r, prm, None, F, Cc, ws)
+    torch.cuda.synchronize()
+    assert ff.ff_read_status(ws) == 0
+    return F.cpu().numpy(), Cc.cpu().numpy()
+
+
+@pytest.mark.parametrize("W,H,r,Q,kw", [
+    (1, 33, 8, 4, dict(k=0)), (34, 1, 6, 4, dict(k=0)),                       # one column, one row
+    (16, 16, 8, 4, dict(k=1)), (17, 17, 8, 4, dict(k=1)), (15, 31, 6, 4, dict(k=1)),   # at and beside a tile
+    (33, 47, 5, 4, dict(k=2)), (49, 32, 15, 2, dict(k=0)), (65, 18, 1, 1, dict(k=1)),   # run-time radius
+    (140, 90, 8, 4, dict(k=4, n_prop=3, n_rs=1)), (90, 70, 6, 8, dict(k=3, n_prop=5, n_rs=2)),   # odd sweep counts
+    (97, 61, 8, 4, dict(k=2, n_prop=1, n_rs=1)), (70, 50, 7, 4, dict(k=1, n_prop=0, n_rs=0)),
+])
+def test_field_bit_exact_at_tile_edges(W, H, r, Q, kw):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1508_05151_amd import ff
+    print("sweep tiles", W, H, r, Q, kw, flush=True)
+    sys.stdout.flush()
+    p = pairs.layered_pair(seed=300 + W + H, W=W, H=H, nlayers=2)
+    d = ff.ff_desc_init(W, H, 3, kw["k"], Q, (r,))
+    blobs = []
+    for img in (p.img1, p.img2):
+        b = torch.empty(d.bytes, dtype=torch.uint8, device="cuda")
+        ff.ff_compute_descriptors(d, torch.from_numpy(np.ascontiguousarray(img)).cuda(), b)
+        blobs.append(b)
+    o1, o2 = ffo.Desc(p.img1, kw["k"], Q, (r,)), ffo.Desc(p.img2, kw["k"], Q, (r,))
+    # the whole search, and a stop inside the coarsest and inside the finest
+    # level (either grid buffer may be the current one there)
+    n_prop, n_rs = kw.get("n_prop", 4), kw.get("n_rs", 3)
+    stops = sorted({-1, 2, 3, 1 + (n_prop + n_rs) * (kw["k"] + 1) + kw["k"] - 1})
+    for stop in stops:
+        gF, gC = _field(d, blobs[0], d, blobs[1], r, seed=9, max_steps=stop, **kw)
+        oF, oC = ffo.match_field(o1, o2, r, seed=9, max_steps=stop, **kw)
+        assert np.array_equal(gF, oF) and np.array_equal(gC, oC), stop
