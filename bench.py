@@ -230,10 +230,8 @@ def bench_sift(ff, torch, dev, workloads, steps):
         run()
         torch.cuda.synchronize()
         ptot, pn, each = ff.ff_profile_end(each=16)
-        # level 0's four sweeps are the last launches; a sweep runs about
-        # Gw + Gh wavefront steps (4-row bands, each one step behind per row)
+        # level 0's four sweeps are the last launches
         lvl0 = statistics.median(each[-4:])
-        wsteps = W + H
         # bytes the sweep's loads request per point: per candidate the two
         # sliding rows or columns of 2r+1 samples, 5 pixels each (source and
         # the bilinear target quad) of 2S bytes, for F, B1 and B2
@@ -242,12 +240,11 @@ def bench_sift(ff, torch, dev, workloads, steps):
             "Mpixel_per_s": round(W * H / ms / 1e3, 3), "ms_per_pair": round(ms, 4),
             "median_ms_per_pair": round(statistics.median(per), 4),
             "stages_ms_per_pair": {c: round(t[c][0] * t[c][1], 4) for c in classes},
-            "propagation": {"kernel": "k_sift_prop", "launches_per_pair": pn, "ms_per_pair": round(ptot, 4),
-                            "level0_sweep_ms": round(lvl0, 4), "wavefront_steps_level0": wsteps,
-                            "ns_per_wavefront_step": round(lvl0 * 1e6 / wsteps, 1),
+            "propagation": {"kernel": "k_sift_sweep", "launches_per_pair": pn, "ms_per_pair": round(ptot, 4),
+                            "level0_sweep_ms": round(lvl0, 4),
                             "requested_bytes_per_point_three_fields": req,
                             "requested_GBps_level0": round(req * W * H / (lvl0 / 1000.0) / 1e9, 1),
-                            "bound": "the sweep's dependency chain: one memory round trip per wavefront step"},
+                            "bound": "loads and integer work of the tiles' visits at level 0, their chains above"},
             "quality": {"F_inlier_rate_epe_lt_3px": round(pairs.inlier_rate(out["F"].cpu().numpy(), p, Q), 4),
                         "kept_after_filters": round(out["keep_region"].float().mean().item(), 4),
                         "filtered_inlier_rate_epe_lt_3px": round(

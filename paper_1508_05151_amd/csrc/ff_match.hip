@@ -389,11 +389,6 @@ __global__ __launch_bounds__(256) void k_random_search(const FieldRec* __restric
 // Tile size (modelled from the visits each needs on that pair): 16 x 8, 8 x 16
 // and 8 x 8 points need 1.5 to 2 times the visits for the same chain, 16 x 32
 // has a longer one.
-constexpr int kTileH = 16, kTileW = 16;   // rows, columns; 4 lanes per row
-constexpr int kSweepGrid = 2048;          // workgroups of a launch at most
-__host__ __device__ __forceinline__ int tiles_x(int Gw) { return (Gw + kTileH - 1 + kTileW - 1) / kTileW; }
-__host__ __device__ __forceinline__ int tiles_y(int Gh) { return (Gh + kTileH - 1) / kTileH; }
-
 typedef __attribute__((address_space(1))) const char g_byte;
 
 // clamp to [0, hi] in one instruction (the compiler emits max then min when

@@ -43,6 +43,11 @@
 
 namespace ff {
 
+constexpr int kTileH = 16, kTileW = 16;   // rows, columns
+__host__ __device__ __forceinline__ int tiles_x(int Gw) { return (Gw + kTileH - 1 + kTileW - 1) / kTileW; }
+__host__ __device__ __forceinline__ int tiles_y(int Gh) { return (Gh + kTileH - 1) / kTileH; }
+constexpr int kSweepGrid = 2048;          // workgroups of a launch at most
+
 constexpr int kRelaxIdle = 96;   // workgroups kept waiting for work; the rest leave
 
 __device__ __forceinline__ uint64_t rt_clock() { return __builtin_amdgcn_s_memrealtime(); }
@@ -76,7 +81,8 @@ __device__ __forceinline__ void mem_wait() {
 // One launch's scheduler words, all zero before it, each in a line of its own
 // (an operation on a word that every workgroup uses takes its turn at one
 // memory channel); one wavefront per workgroup calls the functions below,
-// every lane with the same arguments.
+// every lane with the same arguments (the other wavefronts' memory operations
+// have completed).
 struct RelaxCtl {
   int32_t head, pad0[31];   // tickets drawn for queued tiles
   int32_t tail, pad1[31];   // tiles queued

@@ -15,27 +15,20 @@
 // (Eq. 4); per level the alternating propagation sweeps (Eq. 2) and random
 // searches (R_n = R n), coarse flows seeding the next level.
 //
-// Propagation: one workgroup per band of 4 grid rows, one wavefront per row
-// (small bands: more of the chip at work, and each step waits on the
-// slowest of fewer memory round trips).
-// At step t, row i of the band handles column u = t - i (sweep-transformed
-// coordinates): its vertical candidate is row i - 1's result of step t - 1
-// (LDS), its horizontal candidate its own result of step t - 1; row 0 takes
-// the band above's last-row result from a 64-bit word (cost | flow) that the
-// band above stores with an agent-scope atomic.  A candidate is costed with
-// a sliding window: its predecessor's cost minus the row (column) leaving
-// the patch plus the one entering it, 2 (2r+1) samples, all loaded at once.
-// Bands are numbered by a ticket, so a band only ever waits on a band that
-// started before it.
+// Propagation: the sweep's tiles are solved in any order and again when a
+// border value changes (ff_relax.h), one workgroup per tile, one wavefront
+// per four tile rows.  A candidate is costed with a sliding window: its
+// predecessor's cost minus the row (column) leaving the patch plus the one
+// entering it, 2 (2r+1) samples.
 #include <algorithm>
 #include <vector>
 
 #include "ff_device.h"
 #include "ff_internal.h"
+#include "ff_relax.h"
 
 namespace ff {
 
-constexpr int kSBand = 4;     // grid rows per propagation band (one wavefront each)
 constexpr int kSLanes = 16;   // lanes per point (entry, random search): one DPP row
 constexpr int kSiftRecsPerWrite = 12;
 constexpr int kSiftStatusBytes = 256;
@@ -50,9 +43,12 @@ struct SiftRec {
   int32_t Ws, Hs, Wd, Hd;
   int32_t P, S, r, vstride;
   uint32_t k0, k1, c3, t_nodes;
-  uint32_t o_dim, o_split, o_perm, o_xch;
-  uint32_t o_grid[5];
-  uint32_t pad[3];
+  uint32_t o_dim, o_split, o_perm;
+  // as in FieldRec; border words per level, two buffers that the level's
+  // sweeps alternate, each right columns then bottom rows
+  uint32_t o_alt, o_seen, clear_words, ones_words;
+  uint32_t o_grid[5], o_st[5], o_x[5];
+  int32_t t0[5];
 };
 
 struct SCtx {
@@ -78,11 +74,14 @@ __device__ __forceinline__ SCtx sctx_of(const SiftRec& f, int lev, int qshift) {
   return c;
 }
 
-__device__ __forceinline__ int32_t* sgrid_flow(const SiftRec& f, int lev) {
+__device__ __forceinline__ int32_t* sgrid_flow(const SiftRec& f, int lev, int buf) {
+  if (buf) return reinterpret_cast<int32_t*>(f.ws + f.o_alt);
   return lev == 0 ? f.flow : reinterpret_cast<int32_t*>(f.ws + f.o_grid[lev]);
 }
-__device__ __forceinline__ int32_t* sgrid_cost(const SiftRec& f, int lev, int G) {
-  return lev == 0 ? f.cost : reinterpret_cast<int32_t*>(f.ws + f.o_grid[lev]) + G;
+__device__ __forceinline__ int32_t* sgrid_cost(const SiftRec& f, int lev, int buf) {
+  if (!buf && lev == 0) return f.cost;
+  const int n = 1 << lev;
+  return sgrid_flow(f, lev, buf) + ((f.Ws + n - 1) >> lev) * ((f.Hs + n - 1) >> lev);
 }
 
 __device__ __forceinline__ bool svalid(const SCtx& c, int px, int py, int32_t f) {
@@ -228,13 +227,14 @@ __global__ void k_tree_write_table(TreeChunk chunk, int n, FieldRec* __restrict_
   if ((int)threadIdx.x < n) out[threadIdx.x] = chunk.r[threadIdx.x];
 }
 
-// mark every field's first handoff buffer empty (grid: chunks x fields)
-__global__ void k_sift_clear_xch(const SiftRec* __restrict__ table) {
+// every field's request counters to zero, its border words to all ones
+// (empty); grid: chunks x fields
+__global__ void k_sift_clear(const SiftRec* __restrict__ table) {
   const SiftRec& f = table[blockIdx.y];
-  uint64_t* x = reinterpret_cast<uint64_t*>(f.ws + f.o_xch);
-  const size_t nw = (size_t)((f.Hs + kSBand - 1) / kSBand) * f.Ws;
+  int32_t* x = reinterpret_cast<int32_t*>(f.ws + f.o_st[0]);
+  const size_t n0 = f.clear_words, nw = n0 + f.ones_words;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nw; i += (size_t)gridDim.x * blockDim.x)
-    x[i] = ~0ull;
+    x[i] = i < n0 ? 0 : -1;
 }
 
 // ---------------------------------------------------------------- seeds (Eq. 1 / Eq. 4)
@@ -242,7 +242,7 @@ __global__ void k_sift_clear_xch(const SiftRec* __restrict__ table) {
 // WHT vector, re-rank the leaf (ascending pixel index) by the data term;
 // the first minimum wins.  grid: (points / 4, fields)
 template <int SG>
-__global__ __launch_bounds__(256) void k_sift_seed(const SiftRec* __restrict__ table, int lev, int qshift) {
+__global__ __launch_bounds__(256) void k_sift_seed(const SiftRec* __restrict__ table, int lev, int qshift, int buf) {
   const SiftRec& f = table[blockIdx.y];
   const SCtx c = sctx_of(f, lev, qshift);
   const int Gw = (f.Ws + c.n - 1) >> lev, Gh = (f.Hs + c.n - 1) >> lev;
@@ -281,8 +281,8 @@ __global__ __launch_bounds__(256) void k_sift_seed(const SiftRec* __restrict__ t
     }
   }
   if (lane == 0) {
-    sgrid_flow(f, lev)[(size_t)gy * Gw + gx] = bestF;
-    sgrid_cost(f, lev, Gw * Gh)[(size_t)gy * Gw + gx] = bestC;
+    sgrid_flow(f, lev, buf)[(size_t)gy * Gw + gx] = bestF;
+    sgrid_cost(f, lev, buf)[(size_t)gy * Gw + gx] = bestC;
   }
 }
 
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(256) void k_sift_seed(const SiftRec* __restrict__ t
 // this level's patch; new points start empty.  16 lanes per coarse point,
 // which also write the three new points it covers.
 template <int SG>
-__global__ __launch_bounds__(256) void k_sift_entry(const SiftRec* __restrict__ table, int lev, int qshift) {
+__global__ __launch_bounds__(256) void k_sift_entry(const SiftRec* __restrict__ table, int lev, int qshift, int buf) {
   const SiftRec& f = table[blockIdx.y];
   const SCtx c = sctx_of(f, lev, qshift);
   const int Gw = (f.Ws + c.n - 1) >> lev, Gh = (f.Hs + c.n - 1) >> lev;
@@ -300,14 +300,14 @@ __global__ __launch_bounds__(256) void k_sift_entry(const SiftRec* __restrict__ 
   const int lane = threadIdx.x % kSLanes;
   if (cid >= Gwc * Ghc) return;
   const int gx = 2 * (cid % Gwc), gy = 2 * (cid / Gwc);
-  const int32_t fl = sgrid_flow(f, lev + 1)[cid];
+  const int32_t fl = sgrid_flow(f, lev + 1, 0)[cid];   // a finished level ends in buffer 0
   int32_t e = kInf;
   if (fl != kEmpty) e = row16_sum(sift_partial<SG>(c, gx * c.n, gy * c.n, fl, lane, kSLanes));
   if (lane < 4) {
     const int x = gx + (lane & 1), y = gy + (lane >> 1);
     if (x < Gw && y < Gh) {
-      sgrid_flow(f, lev)[(size_t)y * Gw + x] = lane == 0 ? fl : kEmpty;
-      sgrid_cost(f, lev, Gw * Gh)[(size_t)y * Gw + x] = lane == 0 ? e : kInf;
+      sgrid_flow(f, lev, buf)[(size_t)y * Gw + x] = lane == 0 ? fl : kEmpty;
+      sgrid_cost(f, lev, buf)[(size_t)y * Gw + x] = lane == 0 ? e : kInf;
     }
   }
 }
@@ -318,15 +318,15 @@ __global__ __launch_bounds__(256) void k_sift_entry(const SiftRec* __restrict__ 
 // << 2); replace only on a strictly lower cost.  16 lanes per point.
 template <int SG>
 __global__ __launch_bounds__(256) void k_sift_rs(const SiftRec* __restrict__ table, int lev, int qshift, int step,
-                                                 int R) {
+                                                 int R, int buf) {
   const SiftRec& f = table[blockIdx.y];
   const SCtx c = sctx_of(f, lev, qshift);
   const int Gw = (f.Ws + c.n - 1) >> lev, Gh = (f.Hs + c.n - 1) >> lev;
   const int pid = (blockIdx.x * blockDim.x + threadIdx.x) / kSLanes;
   const int lane = threadIdx.x % kSLanes;
   if (pid >= Gw * Gh) return;
-  int32_t* F = sgrid_flow(f, lev);
-  int32_t* C = sgrid_cost(f, lev, Gw * Gh);
+  int32_t* F = sgrid_flow(f, lev, buf);
+  int32_t* C = sgrid_cost(f, lev, buf);
   const int32_t fl = F[pid];
   if (fl == kEmpty) return;
   const int px = (pid % Gw) * c.n, py = (pid / Gw) * c.n;
@@ -348,200 +348,347 @@ __global__ __launch_bounds__(256) void k_sift_rs(const SiftRec* __restrict__ tab
 // -sx (horizontal) and -sy (vertical).  Candidate order of Eq. 2: current,
 // vertical, horizontal, replaced only on a strictly lower cost; a candidate
 // equal to the current flow is not evaluated (it cannot win).
-__device__ __forceinline__ uint64_t rt_now() { return __builtin_amdgcn_s_memrealtime(); }
+//
+// One workgroup per tile, 16 lanes per row: four lanes for each of the lines
+// of samples that a step needs -- the row leaving and the row entering the
+// patch of the vertical candidate, the column leaving and the column entering
+// for the horizontal one: E(p, F(q)) = C(q) - leaving + entering, exact
+// because every lookup clamps per coordinate.  In the sweep direction
+// (sx, sy) the entering row is at sy r and the leaving one at -sy (r + 1)
+// (columns likewise with sx).  A lane takes samples q, q + 4 of its line (more
+// for r > 3), their five pixels' loads all in flight together; rows hand
+// results down through LDS, one barrier per step.
+// Bound: at level 0 the loads and integer work of the visits (2.7 visits per
+// tile), on coarser levels the chain of visits.  A colour pair is weighted
+// and summed by one packed dot product per weight.  Measured on the 1242x375
+// gray pair (F, B1, B2 in one launch): level-0 sweep 1.11 ms where bands of
+// 4 rows, each waiting for the one above, took 5.1; all 16 sweeps 8.0 ms
+// against 34, the pair 19.3 against 46.0; a 161x119 pair 5.6 against 9.1.
 
-// One signed sliding-window term of a propagated candidate: lane k of
-// 4 (2r+1) covers group k / (2r+1) -- 0 / 1: the row leaving / entering the
-// patch of the vertical candidate, 2 / 3: the column leaving / entering for
-// the horizontal one -- at free offset k mod (2r+1) - r.  In the sweep
-// direction (sx, sy) the entering row is at sy r and the leaving one at
-// -sy (r + 1) (columns likewise with sx): E(p, F(q)) = C(q) - leaving +
-// entering, exact because every lookup clamps per coordinate.
+// SG groups of four colours of one pixel, as packed int16 pairs
 template <int SG>
-__device__ __forceinline__ void slide_terms(const SCtx& c, int px, int py, int sx, int sy, bool useV, const Tgt& tv,
-                                            bool useH, const Tgt& th, int lane, int32_t& sV, int32_t& sH) {
-  const int Sd = 2 * c.r + 1, sgf = (c.S + 3) >> 2;
-  sV = 0;
-  sH = 0;
-  for (int k = lane; k < 4 * Sd; k += 64) {
-    const int grp = k / Sd, o = k - grp * Sd - c.r;
-    const bool vert = grp < 2, enter = (grp & 1) != 0;
-    const int across = vert ? sy : sx;
-    const int a = enter ? across * c.r : -across * (c.r + 1);
-    const int dx = (vert ? o : a) * c.n, dy = (vert ? a : o) * c.n;
-    const Tgt& t = vert ? tv : th;
-    const int sxp = clampi(px + dx, 0, c.Ws - 1), syp = clampi(py + dy, 0, c.Hs - 1);
-    const Px<SG> pa = load_px<SG>(c.src + pix_off(sxp, syp, c.Ws, c.P), sgf);
-    const Quad<SG> q = load_quad<SG>(c, clampi(t.Mx + dx, 0, c.Wd - 1), clampi(t.My + dy, 0, c.Hd - 1), sgf);
-    const int32_t d = dist_of<SG>(c, pa, q, t);
-    const int32_t sd = enter ? d : -d;
-    if (vert)
-      sV += useV ? sd : 0;
-    else
-      sH += useH ? sd : 0;
+struct Col {
+  uint32_t w[2 * SG];
+};
+template <int SG>
+__device__ __forceinline__ Col<SG> load_col(const int16_t* p) {
+  typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(8)));
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  Col<SG> r;
+#pragma unroll
+  for (int g = 0; g + 2 <= SG; g += 2) {
+    const u4 x = *(__attribute__((address_space(1))) const u4*)(p + 4 * g);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.w[2 * g + i] = x[i];
   }
+  if (SG & 1) {
+    const u2 x = *(__attribute__((address_space(1))) const u2*)(p + 4 * (SG - 1));
+    r.w[2 * SG - 2] = x[0];
+    r.w[2 * SG - 1] = x[1];
+  }
+  return r;
 }
 
-// Handoff words between bands: (cost << 32) | flow, all ones while not yet
-// written (no cost is 0xFFFFFFFF).  Launch L of a call reads and writes
-// buffer L & 1 and clears buffer (L + 1) & 1 for the next launch.
-constexpr uint64_t kXchEmpty = ~0ull;
+typedef short short2_t __attribute__((ext_vector_type(2)));
+// w * (the low or the high half of v) + acc, w in the matching half of wv
+__device__ __forceinline__ int32_t mad16(uint32_t v, uint32_t wv, int32_t acc) {
+  return __builtin_amdgcn_sdot2(__builtin_bit_cast(short2_t, v), __builtin_bit_cast(short2_t, wv), acc, false);
+}
 
+// floor(sqrt(v)), v < 2^40: the hardware root of the rounded v is off by less
+// than one, so one step either way corrects it
+__device__ __forceinline__ uint32_t isqrt40(uint64_t v) {
+  const float fv = fmaf((float)(uint32_t)(v >> 32), 4294967296.0f, (float)(uint32_t)v);
+  uint32_t k = (uint32_t)__builtin_amdgcn_sqrtf(fv);
+  k -= sq24(k) > v ? 1u : 0u;
+  k += sq24(k + 1) <= v ? 1u : 0u;
+  return k;
+}
+
+struct SiftSlide {
+  const int16_t* src;   // level's colour images
+  const int16_t* dst;
+  int Ws, Hs, Wd, Hd, P, S, r, n, Q, qshift;
+};
+
+// Signed share of a lane in its line's sum: samples q, q + 4, ... of the line
+// whose sample k lies at p + (dx0 + k kx, dy0 + k ky) around the source point
+// and the target centre alike.
 template <int SG>
-__global__ __launch_bounds__(kSBand * 64) void k_sift_prop(const SiftRec* __restrict__ table, int nf, int lev,
-                                                           int qshift, int sx, int sy, int parity,
-                                                           int32_t* __restrict__ ticket,
-                                                           int32_t* __restrict__ status, uint64_t timeout) {
-  __shared__ int32_t s_field, s_band, s_nb;
-  __shared__ int32_t resF[2][kSBand], resC[2][kSBand];
-  if (threadIdx.x == 0) {
-    int tk = atomicAdd(ticket, 1), fi = 0, nb = 0;
-    for (; fi < nf; ++fi) {
-      const int gh = (table[fi].Hs + (1 << lev) - 1) >> lev;
-      nb = (gh + kSBand - 1) / kSBand;
-      if (tk < nb) break;
-      tk -= nb;
+__device__ __forceinline__ int32_t slide_line(const SiftSlide& c, int px, int py, int mx, int my, int dx0, int dy0,
+                                              int kx, int ky, int q) {
+  const int Mx = mx >> c.qshift, My = my >> c.qshift, a = mx & (c.Q - 1), b = my & (c.Q - 1);
+  const int QQ = c.Q * c.Q;
+  // the five weights, negated for the target's; low half, and shifted to the high half
+  const uint32_t wl[5] = {(uint32_t)QQ, (uint32_t)(uint16_t)(-(c.Q - a) * (c.Q - b)),
+                          (uint32_t)(uint16_t)(-a * (c.Q - b)), (uint32_t)(uint16_t)(-(c.Q - a) * b),
+                          (uint32_t)(uint16_t)(-a * b)};
+  const int Sd = 2 * c.r + 1;
+  int32_t sum = 0;
+  for (int k0 = q; k0 < Sd; k0 += 8) {
+    Col<SG> p[2][5];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int k = min(k0 + 4 * s, Sd - 1), dx = dx0 + k * kx, dy = dy0 + k * ky;
+      const int X = clampi(Mx + dx, 0, c.Wd - 1), Y = clampi(My + dy, 0, c.Hd - 1);
+      const int X1 = min(X + 1, c.Wd - 1), Y1 = min(Y + 1, c.Hd - 1);
+      p[s][0] = load_col<SG>(c.src + pix_off(clampi(px + dx, 0, c.Ws - 1), clampi(py + dy, 0, c.Hs - 1), c.Ws, c.P));
+      p[s][1] = load_col<SG>(c.dst + pix_off(X, Y, c.Wd, c.P));
+      p[s][2] = load_col<SG>(c.dst + pix_off(X1, Y, c.Wd, c.P));
+      p[s][3] = load_col<SG>(c.dst + pix_off(X, Y1, c.Wd, c.P));
+      p[s][4] = load_col<SG>(c.dst + pix_off(X1, Y1, c.Wd, c.P));
     }
-    s_field = fi;
-    s_band = tk;
-    s_nb = nb;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      int64_t ss = 0;
+#pragma unroll
+      for (int g = 0; g < SG; ++g)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          int32_t e = 0;
+#pragma unroll
+          for (int t = 0; t < 5; ++t) e = mad16(p[s][t].w[2 * g + (i >> 1)], i & 1 ? wl[t] << 16 : wl[t], e);
+          // the last group's channels past S (only there: 4 SG - S < 4)
+          if (g == SG - 1 && i > 0) e = 4 * g + i < c.S ? e : 0;
+          ss += (int64_t)e * e;
+        }
+      const uint64_t v = c.qshift <= 2 ? (uint64_t)ss << (8 - 4 * c.qshift) : (uint64_t)ss >> 4;
+      const int32_t d = (int32_t)isqrt40(v);
+      sum += k0 + 4 * s < Sd ? d : 0;
+    }
   }
-  __syncthreads();
-  if (s_field >= nf) return;
-  const SiftRec& f = table[s_field];
-  const SCtx c = sctx_of(f, lev, qshift);
-  const int n = c.n;
-  const int Gw = (f.Ws + n - 1) >> lev, Gh = (f.Hs + n - 1) >> lev;
-  const int band = s_band, v0 = band * kSBand;
-  const size_t xwords = (size_t)((f.Hs + kSBand - 1) / kSBand) * f.Ws;   // one buffer
-  uint64_t* const xbase = reinterpret_cast<uint64_t*>(f.ws + f.o_xch);
-  {
-    // this band's share of the next launch's buffer
-    uint64_t* nxt = xbase + (size_t)(parity ^ 1) * xwords;
-    const size_t per = (xwords + s_nb - 1) / s_nb;
-    const size_t e0 = (size_t)band * per, e1 = min(xwords, e0 + per);
-    for (size_t i = e0 + threadIdx.x; i < e1; i += blockDim.x) nxt[i] = kXchEmpty;
-  }
-  if (v0 >= Gh) return;
-  const int rows = min(kSBand, Gh - v0);
-  const int row = threadIdx.x >> 6, lane = threadIdx.x & 63;   // one wavefront per band row
-  const bool rowok = row < rows;
-  const int gy = sy > 0 ? v0 + row : Gh - 1 - (v0 + row);
-  const int py = gy * n;
-  int32_t* const F = sgrid_flow(f, lev);
-  int32_t* const C = sgrid_cost(f, lev, Gw * Gh);
-  uint64_t* const xch = xbase + (size_t)parity * xwords;
-  const uint64_t* const xin = xch + (size_t)(band > 0 ? band - 1 : 0) * Gw;
-  uint64_t* const xout = xch + (size_t)band * Gw;
-  const bool publish = rowok && row == rows - 1 && v0 + rows < Gh;
-  const int nsteps = Gw + rows - 1;
-  // this row's result of the previous step: its horizontal candidate
-  int32_t hF = kEmpty, hC = kInf;
-  bool abandoned = false;
-  // prefetched for the row's next column: its own flow and cost and, for row
-  // 0, the band above's word (each loaded one step ahead, before the barrier)
-  auto own_idx = [&](int uu) { return (size_t)gy * Gw + (sx > 0 ? uu : Gw - 1 - uu); };
-  int32_t nF = kEmpty, nC = kInf;
-  uint64_t nW = kXchEmpty;
-  if (row == 0) {
-    nF = F[own_idx(0)];
-    nC = C[own_idx(0)];
-    if (band > 0) nW = __hip_atomic_load(&xin[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  for (int t = 0; t < nsteps; ++t) {
-    const int u = t - row;
-    const bool active = rowok && u >= 0 && u < Gw;
-    if (rowok && u == 0 && row > 0) {
-      nF = F[own_idx(0)];
-      nC = C[own_idx(0)];
+  return sum;
+}
+
+struct STile {
+  int2 own[kTileH * (kTileW + 1)];   // own values
+  int2 res[kTileH * (kTileW + 1)];   // results, on entry those of the visit before
+  int2 left[kTileH], top[kTileW + 2];   // border values: flow, 2 cost + changed
+  int2 step[2][kTileH];              // rows' results of a step, by its parity
+};
+
+// the 16 steps of a visit (as the census sweep's: row i at column u0 + t - i)
+template <int SG>
+__device__ __forceinline__ void sift_steps(const SiftSlide& c, STile& s, int lev, int sx, int sy, int u0, int v0, int Gw,
+                                           int Gh, bool first) {
+  const int i = threadIdx.x >> 4, l = threadIdx.x & 15, line = l >> 2, q = l & 3;
+  const bool horiz = line >= 2, enter = (line & 1) != 0;
+  const int nQshift = lev + c.qshift;
+  const int gy = sy > 0 ? v0 + i : Gh - 1 - (v0 + i), py = gy * c.n;
+  const int gx0 = sx > 0 ? u0 - i : Gw - 1 - (u0 - i);
+  const uint32_t maxMx = (uint32_t)((c.Wd - 1) * c.Q), maxMy = (uint32_t)((c.Hd - 1) * c.Q);
+  const int across = (horiz ? sx : sy) * (enter ? c.r : -c.r - 1) * c.n, back = -c.r * c.n;
+  const int dx0 = horiz ? across : back, dy0 = horiz ? back : across;
+  const int kx = horiz ? 0 : c.n, ky = horiz ? c.n : 0;
+  int uL = v0 + i < Gh ? u0 - i : -(1 << 20);
+  int2 h = s.left[i], v = i == 0 ? s.top[0] : s.left[i > 0 ? i - 1 : 0];
+  constexpr int kPO = kTileW + 1;
+  for (int t = 0; t < kTileW; ++t) {
+    const int2 own = s.own[i * kPO + t], old = s.res[i * kPO + t];
+    const int px = (gx0 + sx * t) * c.n;
+    // this lane's candidate
+    const int2 cand = horiz ? h : v;
+    const int mx = (px << c.qshift) + fx_of(cand.x), my = (gy << nQshift) + fy_of(cand.x);
+    // a point none of whose inputs changed keeps its result; EMPTY lies outside
+    const bool in = ((uint32_t)uL < (uint32_t)Gw) & (((v.y | h.y) & 1) != 0);
+    const bool use = in & (cand.x != own.x) & ((uint32_t)mx <= maxMx) & ((uint32_t)my <= maxMy);
+    int32_t e = kInf;
+    if (__ballot(use)) {
+      int32_t d = 0;
+      if (use) d = slide_line<SG>(c, px, py, mx, my, dx0, dy0, kx, ky, q);
+      d = enter ? d : -d;
+      // over the candidate's eight lanes
+      d += __builtin_amdgcn_update_dpp(0, d, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
+      d += __builtin_amdgcn_update_dpp(0, d, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
+      d += __builtin_amdgcn_update_dpp(0, d, 0x141, 0xF, 0xF, false);   // row_half_mirror
+      if (use) e = (cand.y >> 1) + d;
     }
-    const int32_t curF0 = nF, curC0 = nC;
-    int32_t vF = kEmpty, vC = kInf;
-    if (row == 0) {
-      if (band > 0 && active) {
-        uint64_t w = nW;
-        if (w == kXchEmpty && !abandoned) {
-          const uint64_t t0 = rt_now();
-          do {
-            __builtin_amdgcn_s_sleep(1);
-            w = __hip_atomic_load(&xin[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (rt_now() - t0 > timeout) {
-              __hip_atomic_store(status, (int32_t)FF_ERR_DEVICE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              abandoned = true;
-              break;
-            }
-          } while (w == kXchEmpty);
-        }
-        if (w != kXchEmpty) {
-          vF = (int32_t)(uint32_t)w;
-          vC = (int32_t)(uint32_t)(w >> 32);
-        }
-      }
-    } else {
-      vF = resF[(t - 1) & 1][row - 1];
-      vC = resC[(t - 1) & 1][row - 1];
+    const int32_t oe = __builtin_amdgcn_update_dpp(0, e, 0x128, 0xF, 0xF, false);        // row_ror:8
+    const int32_t ofl = __builtin_amdgcn_update_dpp(0, cand.x, 0x128, 0xF, 0xF, false);
+    const int32_t eV = horiz ? oe : e, eH = horiz ? e : oe;
+    const int32_t fV = horiz ? ofl : cand.x, fH = horiz ? cand.x : ofl;
+    int2 res = in ? own : old;
+    if (eV < res.y) res = make_int2(fV, eV);
+    if (eH < res.y) res = make_int2(fH, eH);
+    h = make_int2(res.x, (int)((uint32_t)res.y << 1) | (first || res.x != old.x ? 1 : 0));
+    if (l == 0) {
+      s.res[i * kPO + t] = res;
+      s.step[t & 1][i] = h;
     }
-    int32_t outF = kEmpty, outC = kInf;
-    if (active) {
-      const size_t pi = own_idx(u);
-      const int px = (sx > 0 ? u : Gw - 1 - u) * n;
-      const bool useV = vF != curF0 && svalid(c, px, py, vF);
-      const bool useH = u > 0 && hF != curF0 && svalid(c, px, py, hF);
-      int32_t curF = curF0, curC = curC0;
-      if (useV || useH) {
-        const Tgt tv = tgt_of(c, px, py, useV ? vF : 0), th = tgt_of(c, px, py, useH ? hF : 0);
-        int32_t dV, dH;
-        slide_terms<SG>(c, px, py, sx, sy, useV, tv, useH, th, lane, dV, dH);
-        const int32_t eV = vC + wave_sum(dV), eH = hC + wave_sum(dH);
-        if (useV && eV < curC) {
-          curF = vF;
-          curC = eV;
-        }
-        if (useH && eH < curC) {
-          curF = hF;
-          curC = eH;
-        }
-      }
-      if (lane == 0 && curF != curF0) {
-        F[pi] = curF;
-        C[pi] = curC;
-      }
-      outF = curF;
-      outC = curC;
-      if (publish && lane == 0)
-        __hip_atomic_store(&xout[u], ((uint64_t)(uint32_t)outC << 32) | (uint32_t)outF, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-      hF = outF;
-      hC = outC;
-      if (u + 1 < Gw) {
-        nF = F[own_idx(u + 1)];
-        nC = C[own_idx(u + 1)];
-        if (row == 0 && band > 0) nW = __hip_atomic_load(&xin[u + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
-    if (lane == 0) {
-      resF[t & 1][row] = outF;
-      resC[t & 1][row] = outC;
-    }
-    // only the LDS results cross rows; each row's global stores touch its
-    // own points and the next column's prefetches stay in flight
     lds_barrier();
+    v = i == 0 ? s.top[t + 1] : s.step[t & 1][i > 0 ? i - 1 : 0];
+    ++uL;
   }
+}
+template <int SG>
+__device__ __forceinline__ void sift_steps_of(int sg, const SiftSlide& c, STile& s, int lev, int sx, int sy, int u0,
+                                              int v0, int Gw, int Gh, bool first) {
+  if constexpr (SG > 1) {
+    if (sg < SG) return sift_steps_of<SG - 1>(sg, c, s, lev, sx, sy, u0, v0, Gw, Gh, first);
+  }
+  sift_steps<SG>(c, s, lev, sx, sy, u0, v0, Gw, Gh, first);
+}
+
+struct SiftSweepArgs {
+  int nf, lev, qshift, sx, sy;
+  int base;    // of the request counters (ff_relax.h)
+  int par;     // border word buffer in use; the other one is emptied
+  int inbuf;   // grid buffer read; the other one is written
+};
+
+// SG: groups of four colours of the widest field of the call
+template <int SG>
+__global__ __launch_bounds__(256) void k_sift_sweep(const SiftRec* __restrict__ table, SiftSweepArgs a, RelaxQ q) {
+  __shared__ STile s;
+  __shared__ int s_next, s_first;
+  const int tid = threadIdx.x, lev = a.lev, n = 1 << lev, sx = a.sx, sy = a.sy;
+  constexpr int kPO = kTileW + 1;
+  int mine = blockIdx.x, gt = mine, done = 0;
+  bool first = true;   // no earlier visit of this tile in this launch
+  do {
+    // the tile's field: the last one whose first tile is not above it
+    int fi = 0;
+    for (int b = 0; b < a.nf; b += 64) {
+      const int k = b + (tid & 63);
+      const bool le = k < a.nf && table[k].t0[lev] <= gt;
+      fi += __popcll(__ballot(le));
+    }
+    fi = __builtin_amdgcn_readfirstlane(fi - 1);
+    const SiftRec& f = table[fi];
+    const int Gw = (f.Ws + n - 1) >> lev, Gh = (f.Hs + n - 1) >> lev;
+    const int g0 = f.t0[lev], tile = gt - g0;
+    const int nu = tiles_x(Gw), nv = tiles_y(Gh);
+    const int tv = tile / nu, tu = tile - tv * nu;
+    const int u0 = tu * kTileW, v0 = tv * kTileH;
+    int32_t* const cnt = reinterpret_cast<int32_t*>(f.ws + f.o_st[lev]);
+    const int have = ld_coh(cnt + tile) - a.base;   // requests this visit answers
+    const int32_t* const inF = sgrid_flow(f, lev, a.inbuf);
+    const int32_t* const inC = sgrid_cost(f, lev, a.inbuf);
+    int32_t* const outF = sgrid_flow(f, lev, a.inbuf ^ 1);
+    int32_t* const outC = sgrid_cost(f, lev, a.inbuf ^ 1);
+    auto pidx = [&](int u, int v) { return (sy > 0 ? v : Gh - 1 - v) * Gw + (sx > 0 ? u : Gw - 1 - u); };
+    // one point per thread: its own value, and its result if the tile was visited before
+    const int pi = tid >> 4, pt = tid & 15, pu = u0 + pt - pi, pv = v0 + pi;
+    const bool pok = pu >= 0 && pu < Gw && pv < Gh;
+    const int pp = pidx(clampi(pu, 0, Gw - 1), min(pv, Gh - 1));
+    int2 own = make_int2(gp(inF)[pp], gp(inC)[pp]), old = own;
+    if (!first) old = make_int2(ld_coh(outF + pp), ld_coh(outC + pp));
+    if (!pok) own = old = make_int2(kEmpty, kInf);
+    s.own[pi * kPO + pt] = own;
+    s.res[pi * kPO + pt] = old;
+    // border words: right columns (tile column major), bottom rows; the
+    // first 32 threads hold the column left of the tile and the row above it
+    const size_t xwords = (size_t)nu * Gh + (size_t)nv * Gw;
+    uint64_t* const xr = reinterpret_cast<uint64_t*>(f.ws + f.o_x[lev]) + (a.par ? xwords : 0);
+    uint64_t* const xb = xr + (size_t)nu * Gh;
+    int32_t* const was = reinterpret_cast<int32_t*>(f.ws + f.o_seen) + tile * 32;
+    const bool isl = tid < 16;
+    const int bl = tid & 15;
+    const int hu = isl ? u0 - bl - 1 : u0 + bl, hv = isl ? v0 + bl : v0 - 1;
+    const int ou = isl ? u0 + 15 - bl : u0 + bl - 15, ov = isl ? v0 + bl : v0 + 15;
+    const bool ook = tid < 32 && ou >= 0 && ou < Gw && ov < Gh && (isl ? tu + 1 < nu : tv + 1 < nv);
+    const ptrdiff_t oat = isl ? (ptrdiff_t)((size_t)tu * Gh + ov) : (ptrdiff_t)((size_t)nu * Gh + (size_t)tv * Gw + ou);
+    const int handled = __builtin_amdgcn_readfirstlane(have);
+    int32_t hf = kEmpty, hc = kInf;
+    if (tid < 64) {
+      mem_wait();   // the request counter is read before the borders
+      if (tid < 32) {
+        int32_t wasF = 0;
+        if (!first) wasF = ld_coh(was + tid);
+        if (hu >= 0 && hu < Gw && hv >= 0 && hv < Gh) {
+          const uint64_t w = ld_coh(isl ? xr + (size_t)(tu - 1) * Gh + hv : xb + (size_t)(tv - 1) * Gw + hu);
+          hf = gp(inF)[pidx(hu, hv)];
+          hc = gp(inC)[pidx(hu, hv)];
+          if (w != ~0ull) {
+            hf = (int32_t)(uint32_t)w;
+            hc = (int32_t)(uint32_t)(w >> 32);
+          }
+        }
+        // cost doubled, the low bit marks a value this tile has not seen
+        // (costs stay below 2^29; EMPTY's is never used)
+        const int2 b = make_int2(hf, (int)((uint32_t)hc << 1) | (first || hf != wasF ? 1 : 0));
+        if (isl)
+          s.left[bl] = b;
+        else
+          s.top[bl] = b;
+      }
+      if (tid == 32) s.top[kTileW] = make_int2(kEmpty, 0);
+    }
+    __syncthreads();
+    // what the readers of this tile's border hold so far
+    const int oidx = isl ? bl * kPO + 15 : 15 * kPO + bl;
+    int32_t seen = s.res[oidx < kTileH * kPO ? oidx : 0].x;
+    asm volatile("" : "+v"(seen));
+    __syncthreads();
+    SiftSlide c;
+    c.src = f.src + (size_t)lev * f.Ws * f.Hs * f.P;
+    c.dst = f.dst + (size_t)lev * f.Wd * f.Hd * f.P;
+    c.Ws = f.Ws;
+    c.Hs = f.Hs;
+    c.Wd = f.Wd;
+    c.Hd = f.Hd;
+    c.P = f.P;
+    c.S = f.S;
+    c.r = f.r;
+    c.n = n;
+    c.Q = 1 << a.qshift;
+    c.qshift = a.qshift;
+    sift_steps_of<SG>((f.S + 3) >> 2, c, s, lev, sx, sy, u0, v0, Gw, Gh, first);
+    __syncthreads();
+    // ---- results out, changed border words published
+    if (pok) {
+      const int2 x = s.res[pi * kPO + pt];
+      st_coh(outF + pp, x.x);
+      st_coh(outC + pp, x.y);
+    }
+    uint64_t cm = 0;
+    if (tid < 64) {
+      const int2 now = s.res[oidx < kTileH * kPO ? oidx : 0];
+      const bool chg = ook && now.x != seen;
+      if (tid < 32) {
+        st_coh(was + tid, hf);
+        // the buffer of the level's next sweep starts empty
+        if (first && ook) st_coh(reinterpret_cast<uint64_t*>(f.ws + f.o_x[lev]) + (a.par ? 0 : xwords) + oat, (uint64_t)~0ull);
+      }
+      if (chg) st_coh(xr + oat, ((uint64_t)(uint32_t)now.y << 32) | (uint32_t)now.x);
+      cm = __ballot(chg);
+    }
+    mem_wait();
+    __syncthreads();
+    if (tid < 64) {
+      int next = relax_done(q, cnt, a.base, tile, nu, g0, handled, (cm & 0xFFFFu) != 0, (cm & 0x7FFF0000u) != 0,
+                            (cm & 0x80000000u) != 0, done);
+      bool fresh = false;
+      if (next < 0) {
+        mine += q.G;
+        fresh = mine < q.T;
+        next = fresh ? mine : relax_wait(q, done);
+      }
+      if (tid == 0) {
+        s_next = next;
+        s_first = fresh;
+      }
+    }
+    __syncthreads();
+    gt = __builtin_amdgcn_readfirstlane(s_next);
+    first = s_first != 0;
+    __syncthreads();
+  } while (gt >= 0);
 }
 
 // write the grid of level lev into the full-resolution outputs (inspection
 // stops); grid: (W / 256, H, fields)
-__global__ void k_sift_write_grid(const SiftRec* __restrict__ table, int lev) {
+__global__ void k_sift_write_grid(const SiftRec* __restrict__ table, int lev, int buf) {
   const SiftRec& f = table[blockIdx.z];
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
   const int y = blockIdx.y;
   if (x >= f.Ws || y >= f.Hs) return;
   const int n = 1 << lev;
-  const int Gw = (f.Ws + n - 1) >> lev, Gh = (f.Hs + n - 1) >> lev;
+  const int Gw = (f.Ws + n - 1) >> lev;
   const size_t o = (size_t)y * f.Ws + x;
   if ((x % n) == 0 && (y % n) == 0) {
-    f.flow[o] = sgrid_flow(f, lev)[(size_t)(y / n) * Gw + x / n];
-    f.cost[o] = sgrid_cost(f, lev, Gw * Gh)[(size_t)(y / n) * Gw + x / n];
+    f.flow[o] = sgrid_flow(f, lev, buf)[(size_t)(y / n) * Gw + x / n];
+    f.cost[o] = sgrid_cost(f, lev, buf)[(size_t)(y / n) * Gw + x / n];
   } else {
     f.flow[o] = kEmpty;
     f.cost[o] = kInf;
@@ -551,8 +698,9 @@ __global__ void k_sift_write_grid(const SiftRec* __restrict__ table, int lev) {
 // ---------------------------------------------------------------- host
 struct SiftFieldPlan {
   TreeLayout tree;
-  size_t off_grid[5];
-  size_t off_xch;
+  size_t off_grid[5], off_st[5], off_x[5];
+  size_t off_alt, off_seen;
+  size_t clear_words, ones_words;   // from off_st[0]: request counters, then border words
   size_t bytes;
 };
 
@@ -561,33 +709,60 @@ static SiftFieldPlan sift_field_plan(const ff_sift_job& j, const ff_match_params
   const int Ws = j.src->width, Hs = j.src->height;
   P.tree = tree_layout(j.dst->width * j.dst->height, p->leaf, 0);
   size_t off = P.tree.bytes;
+  auto grid_of = [](int size, int lev) { return (size + (1 << lev) - 1) >> lev; };
   for (int lev = 1; lev <= p->k; ++lev) {
-    const int n = 1 << lev;
-    const size_t G = (size_t)((Ws + n - 1) / n) * ((Hs + n - 1) / n);
     off = align_up(off, 256);
     P.off_grid[lev] = off;
-    off += G * 8;
+    off += (size_t)grid_of(Ws, lev) * grid_of(Hs, lev) * 8;
   }
   off = align_up(off, 256);
-  P.off_xch = off;
-  off += 2 * (size_t)((Hs + kSBand - 1) / kSBand) * Ws * 8;
+  const size_t clear0 = off;
+  for (int lev = 0; lev <= p->k; ++lev) {
+    P.off_st[lev] = off;
+    off += (size_t)tiles_x(grid_of(Ws, lev)) * tiles_y(grid_of(Hs, lev)) * 4;
+  }
+  off = align_up(off, 8);
+  P.clear_words = (off - clear0) / 4;
+  for (int lev = 0; lev <= p->k; ++lev) {
+    const int Gw = grid_of(Ws, lev), Gh = grid_of(Hs, lev);
+    P.off_x[lev] = off;
+    off += 2 * ((size_t)tiles_x(Gw) * Gh + (size_t)tiles_y(Gh) * Gw) * 8;
+  }
+  P.ones_words = (off - clear0) / 4 - P.clear_words;
+  P.off_seen = off;
+  off += (size_t)tiles_x(Ws) * tiles_y(Hs) * 32 * 4;
+  // the second grid buffer: what the tree build needs beside the finished
+  // tree is free once the tree stands, if the source fits there
+  const size_t alt = (size_t)Ws * Hs * 8;
+  if (P.tree.bytes - P.tree.off_perm2 >= alt) {
+    P.off_alt = P.tree.off_perm2;
+  } else {
+    P.off_alt = off = align_up(off, 256);
+    off += alt;
+  }
   P.bytes = align_up(off, 256);
   return P;
 }
 
 struct SiftBatchLayout {
-  size_t off_tickets, off_table, off_ttable;
-  int launches;
+  size_t off_ctl, off_ring, off_table, off_ttable;   // scheduler words of every launch, the queue they share
+  size_t ctl_words;                                  // from off_ctl, cleared per call
+  int launches, cap;
   std::vector<size_t> off_field;
   size_t bytes;
 };
 
 static SiftBatchLayout sift_batch_layout(const ff_sift_job* jobs, int n, const ff_match_params* p) {
-  SiftBatchLayout B;
+  SiftBatchLayout B{};
   size_t off = kSiftStatusBytes;
-  B.off_tickets = off;
+  B.off_ctl = off;
   B.launches = (p->k + 1) * p->n_prop;
-  off = align_up(off + (size_t)B.launches * 4, 256);
+  off += (size_t)B.launches * sizeof(RelaxCtl);
+  B.off_ring = off;
+  for (int i = 0; i < n; ++i) B.cap += tiles_x(jobs[i].src->width) * tiles_y(jobs[i].src->height);
+  off += (size_t)B.cap * 4;
+  B.ctl_words = (off - B.off_ctl) / 4;
+  off = align_up(off, 256);
   B.off_table = off;
   off = align_up(off + (size_t)n * sizeof(SiftRec), 256);
   B.off_ttable = off;
@@ -648,8 +823,15 @@ static SiftRec make_sift_rec(const ff_sift_job& j, const SiftFieldPlan& P, char*
   r.o_dim = (uint32_t)P.tree.off_dim;
   r.o_split = (uint32_t)P.tree.off_split;
   r.o_perm = (uint32_t)P.tree.off_perm;
-  r.o_xch = (uint32_t)P.off_xch;
-  for (int l = 0; l < 5; ++l) r.o_grid[l] = (uint32_t)P.off_grid[l];
+  r.o_alt = (uint32_t)P.off_alt;
+  r.o_seen = (uint32_t)P.off_seen;
+  r.clear_words = (uint32_t)P.clear_words;
+  r.ones_words = (uint32_t)P.ones_words;
+  for (int l = 0; l < 5; ++l) {
+    r.o_grid[l] = (uint32_t)P.off_grid[l];
+    r.o_st[l] = (uint32_t)P.off_st[l];
+    r.o_x[l] = (uint32_t)P.off_x[l];
+  }
   return r;
 }
 
@@ -683,12 +865,16 @@ template <int SG>
 static ff_status run_sift_batch(const ff_sift_job* jobs, int n, const ff_match_params* p, char* ws,
                                 const SiftBatchLayout& B, hipStream_t stream) {
   int32_t* status = reinterpret_cast<int32_t*>(ws);
-  int32_t* tickets = reinterpret_cast<int32_t*>(ws + B.off_tickets);
+  RelaxCtl* ctl = reinterpret_cast<RelaxCtl*>(ws + B.off_ctl);
   SiftRec* table = reinterpret_cast<SiftRec*>(ws + B.off_table);
   FieldRec* ttable = reinterpret_cast<FieldRec*>(ws + B.off_ttable);
   std::vector<SiftRec> recs(n);
   std::vector<FieldRec> trecs(n);
   int maxW = 0, maxH = 0, maxN = 0, maxTop = 0;
+  auto tiles_of = [](const SiftRec& f, int lev) {
+    const int m = (1 << lev) - 1;
+    return tiles_x((f.Ws + m) >> lev) * tiles_y((f.Hs + m) >> lev);
+  };
   for (int i = 0; i < n; ++i) {
     const SiftFieldPlan P = sift_field_plan(jobs[i], p);
     recs[i] = make_sift_rec(jobs[i], P, ws + B.off_field[i]);
@@ -697,11 +883,12 @@ static ff_status run_sift_batch(const ff_sift_job* jobs, int n, const ff_match_p
     maxH = std::max(maxH, recs[i].Hs);
     maxN = std::max(maxN, recs[i].Wd * recs[i].Hd);
     maxTop = std::max(maxTop, trecs[i].t_top);
+    for (int lev = 0; lev <= p->k && i > 0; ++lev) recs[i].t0[lev] = recs[i - 1].t0[lev] + tiles_of(recs[i - 1], lev);
   }
   const int qshift = ilog2i(jobs[0].src->subpel);
   const int k = p->k;
   fill_i32(status, 1, 0, stream);
-  fill_i32(tickets, (size_t)B.launches, 0, stream);
+  fill_i32(reinterpret_cast<int32_t*>(ctl), B.ctl_words, 0, stream);
   for (int i = 0; i < n; i += kSiftRecsPerWrite) {
     SiftChunk sc{};
     TreeChunk tc{};
@@ -713,20 +900,24 @@ static ff_status run_sift_batch(const ff_sift_job* jobs, int n, const ff_match_p
     k_sift_write_table<<<1, kSiftRecsPerWrite, 0, stream>>>(sc, m, table + i);
     k_tree_write_table<<<1, kSiftRecsPerWrite, 0, stream>>>(tc, m, ttable + i);
   }
-  k_sift_clear_xch<<<dim3(64, n), 256, 0, stream>>>(table);
+  k_sift_clear<<<dim3(64, n), 256, 0, stream>>>(table);
   prof_mark(FF_PROF_TREE, stream, true);
   ff_status st = enqueue_tree_build(ttable, n, maxN, maxTop, p->leaf, stream);
   prof_mark(FF_PROF_TREE, stream, false);
   if (st != FF_OK) return st;
   auto pts = [&](int lev) { return ((maxW + (1 << lev) - 1) >> lev) * ((maxH + (1 << lev) - 1) >> lev); };
   auto groups = [&](int npts) { return (unsigned)(((size_t)npts * kSLanes + 255) / 256); };
-  int steps = 0, cur_lev = k;
+  // the grid buffer in use: every sweep reads one and writes the other, and a
+  // level's last one ends in buffer 0
+  const int buf0 = p->n_prop & 1;
+  int steps = 0, cur_lev = k, buf = buf0;
   auto stop = [&]() { return p->max_steps >= 0 && steps >= p->max_steps; };
   auto finish = [&]() -> ff_status {
-    if (cur_lev > 0) k_sift_write_grid<<<dim3((maxW + 255) / 256, maxH, n), 256, 0, stream>>>(table, cur_lev);
+    if (cur_lev > 0 || buf)
+      k_sift_write_grid<<<dim3((maxW + 255) / 256, maxH, n), 256, 0, stream>>>(table, cur_lev, buf);
     return launch_status();
   };
-  k_sift_seed<SG><<<dim3((pts(k) + 3) / 4, n), 256, 0, stream>>>(table, k, qshift);
+  k_sift_seed<SG><<<dim3((pts(k) + 3) / 4, n), 256, 0, stream>>>(table, k, qshift, buf);
   ++steps;
   if (stop()) return finish();
   const uint64_t timeout = p->watchdog_us > 0 ? (uint64_t)p->watchdog_us * 100u : 200000000ull;
@@ -736,28 +927,40 @@ static ff_status run_sift_batch(const ff_sift_job* jobs, int n, const ff_match_p
   for (int lev = k; lev >= 0; --lev) {
     cur_lev = lev;
     if (lev < k) {
-      k_sift_entry<SG><<<dim3(groups(pts(lev + 1)), n), 256, 0, stream>>>(table, lev, qshift);
+      buf = buf0;
+      k_sift_entry<SG><<<dim3(groups(pts(lev + 1)), n), 256, 0, stream>>>(table, lev, qshift, buf);
       ++steps;
       if (stop()) return finish();
     }
     for (int i = 0; i < p->n_prop; ++i) {
-      int bands = 0;
-      for (int g = 0; g < n; ++g) bands += (((recs[g].Hs + (1 << lev) - 1) >> lev) + kSBand - 1) / kSBand;
+      const SiftSweepArgs a{n, lev, qshift, sx_of(i), sy_of(i), -(i + 1), i & 1, buf};
+      RelaxQ q{};
+      q.ctl = ctl + launch;
+      q.ring = reinterpret_cast<int32_t*>(ws + B.off_ring);
+      q.cap = B.cap;
+      q.T = recs[n - 1].t0[lev] + tiles_of(recs[n - 1], lev);
+      q.G = std::min(q.T, kSweepGrid);
+      q.status = status;
+      q.timeout = timeout;
       prof_mark(FF_PROF_SIFT_PROPAGATE, stream, true);
-      k_sift_prop<SG><<<bands, kSBand * 64, 0, stream>>>(table, n, lev, qshift, sx_of(i), sy_of(i), launch & 1,
-                                                         tickets + launch, status, timeout);
+      if (SG <= 3)
+        k_sift_sweep<3><<<q.G, 256, 0, stream>>>(table, a, q);
+      else if (SG <= 5)
+        k_sift_sweep<5><<<q.G, 256, 0, stream>>>(table, a, q);
+      else
+        k_sift_sweep<8><<<q.G, 256, 0, stream>>>(table, a, q);
       prof_mark(FF_PROF_SIFT_PROPAGATE, stream, false);
+      buf ^= 1;
       ++launch;
       ++steps;
       if (stop()) return finish();
       if (i < p->n_rs) {
-        k_sift_rs<SG><<<dim3(groups(pts(lev)), n), 256, 0, stream>>>(table, lev, qshift, i, p->R);
+        k_sift_rs<SG><<<dim3(groups(pts(lev)), n), 256, 0, stream>>>(table, lev, qshift, i, p->R, buf);
         ++steps;
         if (stop()) return finish();
       }
     }
   }
-  cur_lev = 0;
   return finish();
 }
 

@@ -56,3 +56,47 @@ def test_field_bit_exact_at_tile_edges(W, H, r, Q, kw):
         gF, gC = _field(d, blobs[0], d, blobs[1], r, seed=9, max_steps=stop, **kw)
         oF, oC = ffo.match_field(o1, o2, r, seed=9, max_steps=stop, **kw)
         assert np.array_equal(gF, oF) and np.array_equal(gC, oC), stop
+
+
+@pytest.mark.parametrize("W,H,r,S,Sc,Q,kw", [
+    (1, 20, 3, 12, 12, 4, dict(k=0)), (16, 16, 2, 18, 18, 4, dict(k=1)), (17, 33, 3, 4, 12, 4, dict(k=1)),
+    (35, 17, 5, 7, 7, 2, dict(k=0)), (50, 34, 3, 1, 5, 4, dict(k=2, n_prop=3, n_rs=1)),   # odd sweep count
+    (48, 40, 1, 32, 32, 8, dict(k=1, n_prop=5, n_rs=2)), (33, 31, 3, 22, 24, 1, dict(k=1, n_prop=2, n_rs=2)),
+])
+def test_sift_field_bit_exact_at_tile_edges(W, H, r, S, Sc, Q, kw):
+    """The same with the SIFT-flow data term: line lengths below, at and above
+    one round of four lanes, channel counts that end inside a group of four
+    with and without stored channels behind them, the widest pixels."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1508_05151_amd import ff
+    print("sift sweep tiles", W, H, r, S, Sc, Q, kw, flush=True)
+    sys.stdout.flush()
+    k = kw["k"]
+    p = pairs.layered_pair(seed=400 + W + H, W=W, H=H, nlayers=2)
+    rng = np.random.default_rng(W * H)
+    codes = [rng.integers(-2047, 2048, (H, W, Sc)).astype(np.int16) for _ in range(2)]
+    d = ff.ff_desc_init(W, H, 3, k, Q, (r,))
+    ws = torch.empty(ff.ff_sift_workspace_bytes(W, H, W, H), dtype=torch.uint8, device="cuda")
+    blobs, levels, od, ol = [], [], [], []
+    for img, c in zip((p.img1, p.img2), codes):
+        b = torch.empty(d.bytes, dtype=torch.uint8, device="cuda")
+        ff.ff_compute_lab_wht(d, torch.from_numpy(np.ascontiguousarray(img)).cuda(), b)
+        lv = torch.empty((k + 1, H, W, ff.ff_sift_pitch(Sc)), dtype=torch.int16, device="cuda")
+        ff.ff_sift_levels(torch.from_numpy(c).cuda(), k, lv, ws)
+        blobs.append(b)
+        levels.append(lv)
+        od.append(ffo.Desc(img, k, Q, (r,)))
+        ol.append(ffo.SiftLevels(c, k))
+    for stop in (-1, 2, 3):
+        flow = torch.empty((H, W), dtype=torch.int32, device="cuda")
+        cost = torch.empty_like(flow)
+        prm = ff.ff_default_params(max_steps=stop, **kw)
+        job = ff.make_sift_job(d, blobs[0], d, blobs[1], levels[0], levels[1], S, k, r, flow, cost, 2, 5, 77)
+        mws = torch.full((ff.ff_match_sift_workspace_bytes([job], prm),), 0xA5, dtype=torch.uint8, device="cuda")
+        ff.ff_match_sift([job], prm, mws)
+        torch.cuda.synchronize()
+        assert ff.ff_read_status(mws) == 0
+        oF, oC = ffo.match_field_sift(od[0], od[1], ol[0], ol[1], r, S, max_steps=stop, seed=77, field_id=2, pair_id=5,
+                                      **kw)
+        assert np.array_equal(flow.cpu().numpy(), oF) and np.array_equal(cost.cpu().numpy(), oC), stop
