@@ -14,7 +14,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libff.so")
-SOURCES = ["ff_desc.hip", "ff_tree.hip", "ff_match.hip", "ff_filter.hip", "ff_net.hip", "ff_sift.hip",
+SOURCES = ["ff_desc.hip", "ff_tree.hip", "ff_match.hip", "ff_filter.hip", "ff_net.hip", "ff_sift.hip", "ff_pca.hip",
            "ff_sift_match.hip", "ff_api.cpp"]
 ARCH = os.environ.get("FF_OFFLOAD_ARCH", "gfx950")
 

@@ -103,6 +103,15 @@ size_t sift_levels_scratch_bytes(int W, int H, int S);
 void enqueue_sift_levels(const int16_t* codes, int W, int H, int S, int P, int k, int16_t* levels, int32_t* scratch,
                          hipStream_t stream);
 
+// PCA of SIFT vectors (ff_pca.hip): the mean, the eigenvalues (descending)
+// and the basis of the covariance of both images' 128-dimensional vectors
+// into out (128 + 128 + 128 x 128 doubles), and the projection of one image's
+// vectors on the first S basis columns as int16 codes
+constexpr int kSiftDim = 128;
+size_t pca_scratch_bytes();
+void enqueue_pca(const float* D1, int N1, const float* D2, int N2, double* scratch, double* out, hipStream_t stream);
+void enqueue_project(const float* D, int N, const double* pca, int S, int16_t* codes, hipStream_t stream);
+
 ff_status ensure_init();
 ff_status launch_status();   // maps hipGetLastError to FF_ERR_HIP
 
