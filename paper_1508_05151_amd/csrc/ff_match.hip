@@ -103,8 +103,13 @@ __device__ __forceinline__ int32_t patch_partial(const CostCtx& c, int px, int p
 
 template <int L>
 __device__ __forceinline__ int32_t group_sum(int32_t v) {
+  static_assert(L == 16 || L == 64, "rows of 16 lanes");
+  v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);    // lane ^ 1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);    // lane ^ 2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false);   // 7 - lane, within eight
+  v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false);   // 15 - lane
 #pragma unroll
-  for (int o = L / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, L);
+  for (int o = 16; o < L; o <<= 1) v += __shfl_xor(v, o, L);
   return v;
 }
 
@@ -116,26 +121,13 @@ __device__ __forceinline__ int32_t group_sum(int32_t v) {
 // column 0 in plane row 0 (sb, tb), its row pitch in words and the plane row
 // of patch row 0 (sy0, ty0); rows clamp to [0, ymax], columns are not
 // clamped, so the caller guarantees that both S-word row segments lie inside
-// their planes.  INSIDE: the source rows never clamp (sy0 = 0, symax = S - 1)
-// and a patch whose target rows all lie inside skips the clamps (kept out of
-// the sweep kernel, whose register count it would raise).
-// Measured against one row per lane (16-byte loads): random search 55.6 ->
-// 51.9 us per launch, pair 10.13 -> 10.02 ms.
+// their planes.
 typedef __attribute__((address_space(1))) const uint32_t g_u32;
 
-template <int S, bool INSIDE, typename SP>
-__device__ __forceinline__ int32_t cols_sum_n1(SP sb, int spw, int sy0, int symax, g_u32* tb, int tpw, int ty0,
+template <int S>
+__device__ __forceinline__ int32_t cols_sum_n1(g_u32* sb, int spw, int sy0, int symax, g_u32* tb, int tpw, int ty0,
                                                int tymax, int lane) {
   int32_t sum = 0;
-  if (INSIDE && ty0 >= 0 && ty0 + S - 1 <= tymax) {
-    g_u32* t0 = tb + ty0 * tpw;
-    if (lane < S) {
-#pragma unroll
-      for (int row = 0; row < S; ++row) sum += __popc(sb[row * spw + lane] ^ t0[row * tpw + lane]);
-    }
-    for (int row = lane; S > 16 && row < S; row += 16) sum += __popc(sb[row * spw + 16] ^ t0[row * tpw + 16]);
-    return sum;
-  }
   if (lane < S) {
 #pragma unroll
     for (int row = 0; row < S; ++row)
@@ -242,8 +234,8 @@ __global__ __launch_bounds__(256) void k_level_entry(const FieldRec* __restrict_
       const uint32_t* D2 = c.dst + (size_t)c.pw * (size_t)(((my & c.qmask) << c.qshift) + (mx & c.qmask));
       g_u32* sb = (g_u32*)(c.src + (px - c.r));
       g_u32* tb = (g_u32*)(D2 + (Mx - c.r));
-      part = c.r == 8 ? cols_sum_n1<17, false>(sb, c.Ws, py - 8, c.Hs - 1, tb, c.Wd, My - 8, c.Hd - 1, lane)
-                      : cols_sum_n1<13, false>(sb, c.Ws, py - 6, c.Hs - 1, tb, c.Wd, My - 6, c.Hd - 1, lane);
+      part = c.r == 8 ? cols_sum_n1<17>(sb, c.Ws, py - 8, c.Hs - 1, tb, c.Wd, My - 8, c.Hd - 1, lane)
+                      : cols_sum_n1<13>(sb, c.Ws, py - 6, c.Hs - 1, tb, c.Wd, My - 6, c.Hd - 1, lane);
     } else {
       part = patch_partial(c, px, py, fx, fy, lane, L);
     }
@@ -261,28 +253,70 @@ __global__ __launch_bounds__(256) void k_level_entry(const FieldRec* __restrict_
   (void)Ghc;
 }
 
+typedef __attribute__((address_space(1))) const char g_byte;
+
+// clamp to [0, hi] in one instruction (the compiler emits max then min when
+// the upper bound is not a constant)
+__device__ __forceinline__ uint32_t clamp0(int v, int hi) {
+  int r;
+  asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(v), "v"(hi));
+  return (uint32_t)r;
+}
+// target word at a 32-bit word offset from a uniform base: the byte offset is
+// formed in 32 bits so the load takes the scalar-base + 32-bit-offset form
+// (ff_desc_init refuses layouts whose largest offset would not fit)
+__device__ __forceinline__ uint32_t tword(g_byte* base, uint32_t w) {
+  return *reinterpret_cast<__attribute__((address_space(1))) const uint32_t*>(base + (w << 2));
+}
+
+// CW words of a line from byte offset at: consecutive (WIDE, one load) or every fourth sample
+template <int CW, bool WIDE, int LEV>
+__device__ __forceinline__ void load_line(g_byte* tgt, uint32_t at, int lev, uint32_t (&w)[CW]) {
+  g_byte* const p = tgt + at;
+  typedef uint32_t vec __attribute__((ext_vector_type(CW == 3 ? 4 : CW), aligned(4)));
+  if (WIDE && CW == 4) {
+    const vec x = *reinterpret_cast<__attribute__((address_space(1))) const vec*>(p);
+#pragma unroll
+    for (int m = 0; m < CW; ++m) w[m] = x[m];
+  } else {
+#pragma unroll
+    for (int m = 0; m < CW; ++m)
+      w[m] = *reinterpret_cast<__attribute__((address_space(1))) const uint32_t*>(
+          p + (WIDE ? 4 * m : (16 * m) << (LEV >= 0 ? LEV : lev)));
+  }
+}
+
 // ---------------------------------------------------------------- random search
 // Section 3.1 / 3.2: one uniform offset per point, per axis an integer in
 // [-nRQ, nRQ] 1/Q px, from Philox keyed by the seed with counter (pixel, level,
 // step, field | pair << 2); replace only on a strictly lower cost.
-// One workgroup = 256 / L consecutive points of one grid row.  Their source
-// patches overlap: the union (S rows x S - 1 + 256 / L columns, grid-aligned
-// samples clamped to the image) is staged in LDS once, so only the target
-// side of each term is read from global memory.
-template <int L>
-__global__ __launch_bounds__(256) void k_random_search(const FieldRec* __restrict__ table, int lev, int qshift, int step,
-                                                       int R, int buf) {
-  constexpr int PTS = 256 / L;
-  __shared__ uint32_t stile[(2 * kMaxRadius + 1) * (2 * kMaxRadius + PTS + 1)];
-  const FieldRec& f = table[blockIdx.y];
+// Bound: the texture addresser.  A candidate's rows lie at unrelated addresses,
+// so a patch is S cache lines or more however it is read, and three of four
+// candidates lose: both kernels add the patch up in thirds and drop a
+// candidate once its sum reaches the point's cost.
+//
+// All levels and radii: one workgroup = 16 consecutive points of one grid row,
+// 16 lanes per point.  Their source patches overlap: the union (grid-aligned
+// samples clamped to the image) is staged in LDS once.  A point's terms go
+// round its lanes, those of a third all in flight at once (S_ > 0).
+// 1024x436, levels 1-3: 28 us per launch with the patch in one go, 24 us in
+// thirds; eight pairs of 641x479 and below 295 and 270 us.
+constexpr int kSearchPts = 16;
+struct SearchSmem {
+  uint32_t src[(2 * kMaxRadius + 1) * (2 * kMaxRadius + kSearchPts + 1)];
+  int32_t f[kSearchPts], c[kSearchPts];
+};
+template <int S_>
+__device__ __forceinline__ void search_row(const FieldRec& f, SearchSmem& sm, int lev, int qshift, int step, int R, int buf) {
+  constexpr int L = 16, PTS = kSearchPts;
+  uint32_t* const stile = sm.src;
   const CostCtx c = ctx_of(f, lev, qshift);
   const int Gw = (f.Ws + c.n - 1) >> lev, Gh = (f.Hs + c.n - 1) >> lev;
   const int tilesX = (Gw + PTS - 1) / PTS;
   const int gy = blockIdx.x / tilesX, gx0 = (blockIdx.x % tilesX) * PTS;
   if (gy >= Gh) return;   // whole workgroup
-  // tile rows: S patch rows; pitch odd, so that the row-per-lane path's 16
-  // lanes of a point fall in different banks
-  const int S = 2 * c.r + 1, TWs = S - 1 + PTS, TP = TWs | 1;
+  // tile rows: S patch rows of an odd pitch
+  const int r = S_ ? S_ / 2 : c.r, S = 2 * r + 1, TWs = S - 1 + PTS, TP = TWs | 1;
   int32_t* F = grid_flow(f, lev, buf);
   int32_t* C = grid_cost(f, lev, buf);
   const int py = gy * c.n;
@@ -291,74 +325,279 @@ __global__ __launch_bounds__(256) void k_random_search(const FieldRec* __restric
   const int gq = gx0 + (int)threadIdx.x;
   int32_t fl = kEmpty, cq = 0;
   if (threadIdx.x < PTS && gq < Gw) {
-    fl = F[gy * Gw + gq];
-    cq = C[gy * Gw + gq];
+    fl = gp(F)[gy * Gw + gq];
+    cq = gp(C)[gy * Gw + gq];
   }
-  for (int e = threadIdx.x; e < S * TWs; e += 256) {
+  auto stage = [&](int e) {
     const int yy = e / TWs, xx = e - yy * TWs;
-    const int sy = clampi((gy + yy - c.r) * c.n, 0, c.Hs - 1), sx = clampi((gx0 + xx - c.r) * c.n, 0, c.Ws - 1);
-    stile[yy * TP + xx] = c.src[(size_t)sy * c.Ws + sx];
+    const int sy = clampi((gy + yy - r) * c.n, 0, c.Hs - 1), sx = clampi((gx0 + xx - r) * c.n, 0, c.Ws - 1);
+    stile[yy * TP + xx] = gp(c.src)[sy * c.Ws + sx];
+  };
+  if (S_) {
+#pragma unroll
+    for (int k = 0; k < (S_ * (S_ - 1 + PTS) + 255) / 256; ++k)
+      if ((int)threadIdx.x + 256 * k < S * TWs) stage(threadIdx.x + 256 * k);
+  } else {
+    for (int e = threadIdx.x; e < S * TWs; e += 256) stage(e);
   }
   // each point's candidate, once per point (one lane of the first wavefront
   // per point: the Philox rounds are quarter-rate multiplies)
-  __shared__ int32_t s_fx[PTS], s_fy[PTS], s_c[PTS], s_ok[PTS];
   if (threadIdx.x < PTS) {
-    int ok = 0, fxq = 0, fyq = 0;
-    if (gq < Gw) {
-      if (fl != kEmpty) {
-        const int pxq = gq * c.n;
-        const int rad = c.n * R * c.Q;
-        uint32_t u0, u1;
-        philox2((uint32_t)(py * c.Ws + pxq), (uint32_t)lev, (uint32_t)step, f.c3, f.k0, f.k1, u0, u1);
-        const uint64_t span = (uint64_t)(2 * rad + 1);
-        fxq = fx_of(fl) + (int)((u0 * span) >> 32) - rad;
-        fyq = fy_of(fl) + (int)((u1 * span) >> 32) - rad;
-        ok = centre_valid(c, pxq, py, fxq, fyq) ? 1 : 0;
-      }
+    int32_t fq = 0, bound = -1;
+    if (fl != kEmpty) {
+      const int pxq = gq * c.n;
+      const int rad = c.n * R * c.Q;
+      uint32_t u0, u1;
+      philox2((uint32_t)(py * c.Ws + pxq), (uint32_t)lev, (uint32_t)step, f.c3, f.k0, f.k1, u0, u1);
+      const uint64_t span = (uint64_t)(2 * rad + 1);
+      const int fx = fx_of(fl) + (int)((u0 * span) >> 32) - rad, fy = fy_of(fl) + (int)((u1 * span) >> 32) - rad;
+      fq = packf(fx, fy);
+      if (centre_valid(c, pxq, py, fx, fy)) bound = cq;
     }
-    s_fx[threadIdx.x] = fxq;
-    s_fy[threadIdx.x] = fyq;
-    s_c[threadIdx.x] = cq;
-    s_ok[threadIdx.x] = ok;
+    sm.f[threadIdx.x] = fq;
+    sm.c[threadIdx.x] = bound;
   }
   __syncthreads();
   const int i = threadIdx.x / L, lane = threadIdx.x % L;
-  const int gx = gx0 + i;
-  if (gx >= Gw || !s_ok[i]) return;
-  const int pid = gy * Gw + gx;
-  const int px = gx * c.n;
-  const int fx = s_fx[i], fy = s_fy[i];
-  // the patch sum, source terms from the tile
-  const int mx = px * c.Q + fx, my = py * c.Q + fy;
+  const int32_t bound = sm.c[i];
+  if (bound < 0) return;   // no such point, nothing to search around, or outside the image
+  const int gx = gx0 + i, px = gx * c.n;
+  const int32_t cand = sm.f[i];
+  const int mx = px * c.Q + fx_of(cand), my = py * c.Q + fy_of(cand);
   const int Mx = mx >> c.qshift, My = my >> c.qshift;
-  const uint32_t* D2 = c.dst + (size_t)c.pw * (size_t)(((my & c.qmask) << c.qshift) + (mx & c.qmask));
+  const uint32_t plane = __umul24(c.pw, (uint32_t)(((my & c.qmask) << c.qshift) + (mx & c.qmask)));
+  g_byte* const tgt = (g_byte*)c.dst;
+  const uint32_t* sp = stile + i;
   int32_t sum = 0;
-  if (L == 16 && lev == 0 && (c.r == 8 || c.r == 6) && Mx >= c.r && Mx + c.r < c.Wd) {
-    // stride 1 and no column clamp on the target side: whole columns per lane
-    // (the tile's rows are already clamped)
-    g_u32* tb = (g_u32*)(D2 + (Mx - c.r));
-    const uint32_t* sb = stile + i;
-    sum = c.r == 8 ? cols_sum_n1<17, true>(sb, TP, 0, S - 1, tb, c.Wd, My - 8, c.Hd - 1, lane)
-                   : cols_sum_n1<13, true>(sb, TP, 0, S - 1, tb, c.Wd, My - 6, c.Hd - 1, lane);
+  // term t = lane + 16 k of the patch, at (dx, dy)
+  int dy = lane / S, dx = lane - dy * S;
+  const int stepy = L / S, stepx = L - stepy * S;
+  auto at = [&] {
+    return plane + __umul24(clamp0(My + (dy - r) * c.n, c.Hd - 1), (uint32_t)c.Wd) +
+           clamp0(Mx + (dx - r) * c.n, c.Wd - 1);
+  };
+  auto next = [&] {
+    dx += stepx;
+    dy += stepy;
+    if (dx >= S) { dx -= S; ++dy; }
+  };
+  if (S_) {
+    // a third of the terms at a time; a candidate whose sum reaches the
+    // point's cost is out
+    constexpr int K = (S_ * S_ + L - 1) / L, T = S_ ? (K + 2) / 3 : 1;
+    int32_t total = 0;
+#pragma unroll
+    for (int k0 = 0; k0 < K; k0 += T) {
+      uint32_t w[T], a[T];
+#pragma unroll
+      for (int k = 0; k < T; ++k) {   // past the patch for some lanes at the end: read (rows clamp), not summed
+        if (k0 + k >= K) break;
+        w[k] = tword(tgt, at());
+        a[k] = sp[min(dy, S - 1) * TP + dx];
+        next();
+      }
+#pragma unroll
+      for (int k = 0; k < T; ++k)
+        if (k0 + k < K) sum += lane + L * (k0 + k) < S * S ? __popc(w[k] ^ a[k]) : 0;
+      total = group_sum<L>(sum);
+      if (total >= bound) return;
+    }
+    sum = total;
   } else {
-    int dy = lane / S, dx = lane - dy * S;
-    const int stepy = L / S, stepx = L - stepy * S;
-#pragma unroll 4
     for (int t = lane; t < S * S; t += L) {
-      const uint32_t a = stile[dy * TP + i + dx];
-      const uint32_t b = D2[(size_t)clampi(My + (dy - c.r) * c.n, 0, c.Hd - 1) * c.Wd +
-                            clampi(Mx + (dx - c.r) * c.n, 0, c.Wd - 1)];
-      sum += __popc(a ^ b);
-      dx += stepx;
-      dy += stepy;
-      if (dx >= S) { dx -= S; ++dy; }
+      sum += __popc(tword(tgt, at()) ^ sp[dy * TP + dx]);
+      next();
     }
   }
-  const int32_t e = group_sum<L>(sum);
-  if (lane == 0 && e < s_c[i]) {
-    F[pid] = packf(fx, fy);
-    C[pid] = e;
+  if (!S_) sum = group_sum<L>(sum);
+  if (lane == 0 && sum < bound) {
+    gp(F)[gy * Gw + gx] = cand;
+    gp(C)[gy * Gw + gx] = sum;
   }
+}
+
+__global__ __launch_bounds__(256) void k_random_search(const FieldRec* __restrict__ table, int lev, int qshift, int step,
+                                                       int R, int buf) {
+  __shared__ SearchSmem sm;
+  const FieldRec& f = table[blockIdx.y];
+  if (f.r == 8) search_row<17>(f, sm, lev, qshift, step, R, buf);
+  else if (f.r == 6) search_row<13>(f, sm, lev, qshift, step, R, buf);
+  else search_row<0>(f, sm, lev, qshift, step, R, buf);
+}
+
+// Level 0, r = 8 and 6: workgroups of 16 x 16 points.  A wavefront draws 64
+// candidates, one per lane, and costs them 16 at a time, four lanes per
+// point: a row of the patch is one load per lane (four words, or three of one
+// word), neighbouring lanes on neighbouring words, so that an instruction
+// reads whole row segments of 16 points; the row's last word is left to the
+// lane whose turn it is.  Row and word offsets are uniform and go into the
+// scalar base of the load.  Runs of adjacent tiles go to one XCD, whose L2
+// then serves their overlap.
+// Against 16 lanes per point, whole patches: eight pairs (641x479 and below)
+// 1,390 -> 793 us per launch; all four levels of eight pairs 6.9 -> 4.8 ms, of
+// 1024x436 0.56 -> 0.40 ms a field.  At levels 1-3 most patches clamp and
+// their samples lie 2 to 8 words apart, so that no row is one load, and the
+// grids are too small for four rounds per wavefront: this kernel took 59 us a
+// launch there (1024x436) against 24, and they keep the one above.
+struct TileSmem {
+  uint32_t src[32 * 32];
+  int32_t f[256], bound[256];
+};
+template <int S>
+__device__ __forceinline__ void search_tile(const FieldRec& f, TileSmem& sm, int qshift, int step, int R, int buf) {
+  constexpr int r = S / 2, CW = S / 4, TP = 16 + 2 * r;
+  static_assert(S % 4 == 1 && TP <= 32, "row split");
+  uint32_t* const s_src = sm.src;
+  int32_t *const s_f = sm.f, *const s_bound = sm.bound;
+  const CostCtx c = ctx_of(f, 0, qshift);
+  const int Gw = f.Ws, Gh = f.Hs;
+  const int tilesX = (Gw + 15) >> 4, nt = tilesX * ((Gh + 15) >> 4);
+  const int per = (nt + 7) >> 3, tile = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per || tile >= nt) return;   // whole workgroup
+  const int gy0 = tile / tilesX * 16, gx0 = tile % tilesX * 16;
+  int32_t* F = grid_flow(f, 0, buf);
+  int32_t* C = grid_cost(f, 0, buf);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  // this lane's point: its flow and cost, loaded before the tile so that the
+  // round trips overlap
+  const int pgx = gx0 + (lane & 15), pgy = gy0 + wave * 4 + (lane >> 4);
+  int32_t fl = kEmpty, bound = -1;
+  if (pgx < Gw && pgy < Gh) {
+    fl = gp(F)[pgy * Gw + pgx];
+    bound = gp(C)[pgy * Gw + pgx];
+  }
+  {
+    // rows lane / 16 + 4 wave + 16 k, columns lane % 16 + 16 j
+    constexpr int NK = (TP + 15) / 16;
+    uint32_t w[NK][NK];
+#pragma unroll
+    for (int k = 0; k < NK; ++k)
+#pragma unroll
+      for (int j = 0; j < NK; ++j) {
+        const int y = wave * 4 + (lane >> 4) + 16 * k, x = (lane & 15) + 16 * j;
+        w[k][j] = gp(c.src)[clampi(gy0 + y - r, 0, c.Hs - 1) * c.Ws + clampi(gx0 + x - r, 0, c.Ws - 1)];
+      }
+#pragma unroll
+    for (int k = 0; k < NK; ++k)
+#pragma unroll
+      for (int j = 0; j < NK; ++j) {
+        const int y = wave * 4 + (lane >> 4) + 16 * k, x = (lane & 15) + 16 * j;
+        if (y < TP && x < TP) s_src[y * TP + x] = w[k][j];
+      }
+  }
+  {
+    int32_t cand = 0;
+    if (fl != kEmpty) {
+      const int rad = R * c.Q;
+      uint32_t u0, u1;
+      philox2((uint32_t)(pgy * c.Ws + pgx), 0u, (uint32_t)step, f.c3, f.k0, f.k1, u0, u1);
+      const uint64_t span = (uint64_t)(2 * rad + 1);
+      const int fx = fx_of(fl) + (int)((u0 * span) >> 32) - rad, fy = fy_of(fl) + (int)((u1 * span) >> 32) - rad;
+      cand = packf(fx, fy);
+      if (!centre_valid(c, pgx, pgy, fx, fy)) bound = -1;
+    } else {
+      bound = -1;   // nothing to search around
+    }
+    s_f[threadIdx.x] = cand;
+    s_bound[threadIdx.x] = bound;
+  }
+  __syncthreads();
+  const int i = lane >> 2, j = lane & 3;
+  const int Wm = c.Wd - 1, Hm = c.Hd - 1;
+  const bool room = Wm >= 2 * r && Hm >= 2 * r;
+  g_byte* const tgt = (g_byte*)c.dst;
+  const uint32_t Wd = (uint32_t)c.Wd;
+  for (int it = 0; it < 4; ++it) {
+    const int q = wave * 64 + it * 16 + i, ly = wave * 4 + it;
+    const int32_t cand = s_f[q], bnd = s_bound[q];
+    bool use = bnd >= 0;
+    if (__ballot(use) == 0) continue;
+    const int mx = ((gx0 + i) << c.qshift) + fx_of(cand), my = ((gy0 + ly) << c.qshift) + fy_of(cand);
+    const int Mx = mx >> c.qshift, My = my >> c.qshift;
+    const uint32_t plane = __umul24(c.pw, (uint32_t)(((my & c.qmask) << c.qshift) + (mx & c.qmask)));
+    const uint32_t* sp = s_src + ly * TP + i;
+    int32_t sum = 0;
+    auto quad = [&](int32_t v) {   // over the point's four lanes
+      v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
+      return v + __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);   // quad_perm [2,3,0,1]
+    };
+    const bool clamps = ((uint32_t)(Mx - r) > (uint32_t)(Wm - 2 * r)) | ((uint32_t)(My - r) > (uint32_t)(Hm - 2 * r));
+    if (room && __ballot(use & clamps) == 0) {
+      // a third of the rows at a time; a candidate whose sum reaches the
+      // point's cost is out
+      const uint32_t at = plane + __umul24((uint32_t)(My - r), Wd) + (uint32_t)(Mx - r);
+      const uint32_t o = (at + (uint32_t)(CW * j)) << 2, ot = (at + __umul24((uint32_t)j, Wd)) << 2;
+      const size_t rowB = (size_t)c.Wd * 4;
+      constexpr int kThird = (S + 2) / 3;
+      int32_t total = 0;
+#pragma unroll
+      for (int y0 = 0; y0 < S; y0 += kThird) {
+        if (use) {
+          uint32_t w[kThird][CW], wt[(kThird + 3) / 4];
+#pragma unroll
+          for (int y = 0; y < kThird; ++y)
+            if (y0 + y < S) load_line<CW, true, 0>(tgt + (y0 + y) * rowB, o, 0, w[y]);
+#pragma unroll
+          for (int t = 0; t < kThird; t += 4)   // row y0 + t + j
+            if (t + 3 < kThird && y0 + t + 3 < S ? true : t + j < kThird && y0 + t + j < S)
+              wt[t / 4] = *reinterpret_cast<__attribute__((address_space(1))) const uint32_t*>(tgt + (y0 + t) * rowB +
+                                                                                              (S - 1) * 4 + ot);
+          sum = 0;
+#pragma unroll
+          for (int y = 0; y < kThird; ++y)
+            if (y0 + y < S) {
+#pragma unroll
+              for (int m = 0; m < CW; ++m) sum += __popc(w[y][m] ^ sp[(y0 + y) * TP + CW * j + m]);
+            }
+#pragma unroll
+          for (int t = 0; t < kThird; t += 4)
+            if (t + 3 < kThird && y0 + t + 3 < S ? true : t + j < kThird && y0 + t + j < S)
+              sum += __popc(wt[t / 4] ^ sp[(y0 + t + j) * TP + S - 1]);
+          total += quad(sum);
+          use = total < bnd;
+        }
+        if (y0 + kThird < S && __ballot(use) == 0) break;
+      }
+      sum = total;
+    } else if (use) {
+      // columns and rows clamp one by one; a lane takes every fourth word
+      uint32_t xo[CW];
+#pragma unroll
+      for (int m = 0; m < CW; ++m) xo[m] = plane + clamp0(Mx + j + 4 * m - r, Wm);
+      const uint32_t xt = plane + clamp0(Mx + r, Wm);
+      uint32_t w[S][CW], wt[(S + 3) / 4];
+#pragma unroll
+      for (int y = 0; y < S; ++y) {
+        const uint32_t row = __umul24(clamp0(My + y - r, Hm), Wd);
+#pragma unroll
+        for (int m = 0; m < CW; ++m) w[y][m] = tword(tgt, row + xo[m]);
+      }
+#pragma unroll
+      for (int t = 0; t < (S + 3) / 4; ++t)   // row 4 t + j (past the last one for some lanes: read, not summed)
+        wt[t] = tword(tgt, __umul24(clamp0(My + 4 * t + j - r, Hm), Wd) + xt);
+#pragma unroll
+      for (int y = 0; y < S; ++y)
+#pragma unroll
+        for (int m = 0; m < CW; ++m) sum += __popc(w[y][m] ^ sp[y * TP + j + 4 * m]);
+#pragma unroll
+      for (int t = 0; t < (S + 3) / 4; ++t)
+        if (4 * t + j < S) sum += __popc(wt[t] ^ sp[(4 * t + j) * TP + S - 1]);
+      sum = quad(sum);
+    }
+    if (j == 0 && use && sum < bnd) {
+      const int p = (gy0 + ly) * Gw + gx0 + i;
+      gp(F)[p] = cand;
+      gp(C)[p] = sum;
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void k_random_search_tile(const FieldRec* __restrict__ table, int qshift, int step, int R,
+                                                            int buf) {
+  __shared__ TileSmem sm;
+  const FieldRec& f = table[blockIdx.y];
+  if (f.r == 8) search_tile<17>(f, sm, qshift, step, R, buf);
+  else search_tile<13>(f, sm, qshift, step, R, buf);
 }
 
 // ---------------------------------------------------------------- propagation (Eq. 2)
@@ -389,39 +628,6 @@ __global__ __launch_bounds__(256) void k_random_search(const FieldRec* __restric
 // Tile size (modelled from the visits each needs on that pair): 16 x 8, 8 x 16
 // and 8 x 8 points need 1.5 to 2 times the visits for the same chain, 16 x 32
 // has a longer one.
-typedef __attribute__((address_space(1))) const char g_byte;
-
-// clamp to [0, hi] in one instruction (the compiler emits max then min when
-// the upper bound is not a constant)
-__device__ __forceinline__ uint32_t clamp0(int v, int hi) {
-  int r;
-  asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(v), "v"(hi));
-  return (uint32_t)r;
-}
-// target word at a 32-bit word offset from a uniform base: the byte offset is
-// formed in 32 bits so the load takes the scalar-base + 32-bit-offset form
-// (ff_desc_init refuses layouts whose largest offset would not fit)
-__device__ __forceinline__ uint32_t tword(g_byte* base, uint32_t w) {
-  return *reinterpret_cast<__attribute__((address_space(1))) const uint32_t*>(base + (w << 2));
-}
-
-// CW words of a line: consecutive (WIDE, one load) or every fourth sample
-template <int CW, bool WIDE, int LEV>
-__device__ __forceinline__ void load_line(g_byte* tgt, uint32_t at, int lev, uint32_t (&w)[CW]) {
-  g_byte* const p = tgt + (at << 2);
-  typedef uint32_t vec __attribute__((ext_vector_type(CW == 3 ? 4 : CW), aligned(4)));
-  if (WIDE && CW == 4) {
-    const vec x = *reinterpret_cast<__attribute__((address_space(1))) const vec*>(p);
-#pragma unroll
-    for (int m = 0; m < CW; ++m) w[m] = x[m];
-  } else {
-#pragma unroll
-    for (int m = 0; m < CW; ++m)
-      w[m] = *reinterpret_cast<__attribute__((address_space(1))) const uint32_t*>(
-          p + (WIDE ? 4 * m : (16 * m) << (LEV >= 0 ? LEV : lev)));
-  }
-}
-
 struct SweepArgs {
   int f0, nf;        // fields of this launch (one patch radius)
   int lev, qshift;
@@ -636,10 +842,10 @@ __global__ __launch_bounds__(64) void k_sweep(const FieldRec* __restrict__ table
           l3 = useH ? l3 + (uint32_t)(Myh + jt) : 0;
           const uint32_t lt = j < 2 ? (j & 1 ? l1 : l0) : (j & 1 ? l3 : l2);
           uint32_t w0[CW], w1[CW], w2[CW], w3[CW];
-          load_line<CW, kWide, LEV>(tgt, l0, lev, w0);
-          load_line<CW, kWide, LEV>(tgt, l1, lev, w1);
-          load_line<CW, kWide, LEV>(tgt, l2, lev, w2);
-          load_line<CW, kWide, LEV>(tgt, l3, lev, w3);
+          load_line<CW, kWide, LEV>(tgt, l0 << 2, lev, w0);
+          load_line<CW, kWide, LEV>(tgt, l1 << 2, lev, w1);
+          load_line<CW, kWide, LEV>(tgt, l2 << 2, lev, w2);
+          load_line<CW, kWide, LEV>(tgt, l3 << 2, lev, w3);
           const uint32_t wt = tword(tgt, lt + (uint32_t)((j < 2 ? useV : useH) ? tailOff : 0));
 #pragma unroll
           for (int m = 0; m < CW; ++m) {
@@ -993,6 +1199,7 @@ static ff_status run_batch(const ff_field_job* jobs, int n, const ff_match_param
   FieldRec* table = reinterpret_cast<FieldRec*>(ws + B.off_table);
   JobArray<FieldRec> recs;
   recs.resize(n);
+  bool paper_radii = true;
   int maxW = 0, maxH = 0, maxN = 0, maxTop = 0;
   const int k = p->k;
   auto grid_of = [](int size, int lev) { return (size + (1 << lev) - 1) >> lev; };
@@ -1002,6 +1209,7 @@ static ff_status run_batch(const ff_field_job* jobs, int n, const ff_match_param
   for (int i = 0; i < n; ++i) {
     const ff_field_job& j = jobs[B.order[i]];
     recs[i] = make_rec(j, p, ws + B.off_field[i]);
+    paper_radii &= recs[i].r == 8 || recs[i].r == 6;
     maxW = std::max(maxW, recs[i].Ws);
     maxH = std::max(maxH, recs[i].Hs);
     maxN = std::max(maxN, recs[i].Wd * recs[i].Hd);
@@ -1022,11 +1230,6 @@ static ff_status run_batch(const ff_field_job* jobs, int n, const ff_match_param
   }
   if (tree_only) return launch_status();
   auto pts = [&](int lev) { return grid_of(maxW, lev) * grid_of(maxH, lev); };
-  // random search: one workgroup per 256 / kLanesPt consecutive points of a grid row
-  auto rs_blocks = [&](int lev) {
-    const int pt = 256 / kLanesPt;
-    return (unsigned)((grid_of(maxW, lev) + pt - 1) / pt * grid_of(maxH, lev));
-  };
   // the grid buffer in use: every sweep reads one and writes the other, and a
   // level's last one ends in buffer 0
   const int buf0 = p->n_prop & 1;
@@ -1089,7 +1292,11 @@ static ff_status run_batch(const ff_field_job* jobs, int n, const ff_match_param
       if (stop()) return finish();
       if (i < p->n_rs) {
         prof_mark(FF_PROF_RANDOM_SEARCH, stream, true);
-        k_random_search<kLanesPt><<<dim3(rs_blocks(lev), n), 256, 0, stream>>>(table, lev, qshift, i, p->R, buf);
+        const unsigned Gw = (unsigned)grid_of(maxW, lev), Gh = (unsigned)grid_of(maxH, lev), wide = (Gw + 15) / 16;
+        if (lev == 0 && paper_radii)   // 16 x 16 points per workgroup, in eight runs of tiles
+          k_random_search_tile<<<dim3((wide * ((Gh + 15) / 16) + 7) / 8 * 8, n), 256, 0, stream>>>(table, qshift, i, p->R, buf);
+        else
+          k_random_search<<<dim3((Gw + kSearchPts - 1) / kSearchPts * Gh, n), 256, 0, stream>>>(table, lev, qshift, i, p->R, buf);
         prof_mark(FF_PROF_RANDOM_SEARCH, stream, false);
         ++steps;
         if (stop()) return finish();
