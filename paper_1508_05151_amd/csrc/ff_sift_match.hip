@@ -491,17 +491,26 @@ __device__ __forceinline__ void sift_steps(const SiftSlide& c, STile& s, int lev
     const int mx = (px << c.qshift) + fx_of(cand.x), my = (gy << nQshift) + fy_of(cand.x);
     // a point none of whose inputs changed keeps its result; EMPTY lies outside
     const bool in = ((uint32_t)uL < (uint32_t)Gw) & (((v.y | h.y) & 1) != 0);
-    const bool use = in & (cand.x != own.x) & ((uint32_t)mx <= maxMx) & ((uint32_t)my <= maxMy);
-    int32_t e = kInf;
-    if (__ballot(use)) {
+    // A cost depends on the point and the flow alone, so a candidate is read
+    // only if nothing tells its cost yet: not the horizontal one with the
+    // vertical one's flow; not the flow the last visit ended with; and not,
+    // where that was the point's own, an unchanged candidate, which lost then.
+    // 1242x375: 15.6 -> 15.1 ms a pair.  The census sweep has no such test:
+    // its steps are short of latency, not of bandwidth, and the longer chain
+    // cost a 128x96 pair 3 % for 0.6 % of eight pairs.
+    const bool use = in & (cand.x != own.x) & ((uint32_t)mx <= maxMx) & ((uint32_t)my <= maxMy) &
+                     !((old.x == own.x) & !(cand.y & 1)) & !(horiz & (h.x == v.x));
+    const bool ev = use & (cand.x != old.x);
+    int32_t e = use ? old.y : kInf;
+    if (__ballot(ev)) {
       int32_t d = 0;
-      if (use) d = slide_line<SG>(c, px, py, mx, my, dx0, dy0, kx, ky, q);
+      if (ev) d = slide_line<SG>(c, px, py, mx, my, dx0, dy0, kx, ky, q);
       d = enter ? d : -d;
       // over the candidate's eight lanes
       d += __builtin_amdgcn_update_dpp(0, d, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
       d += __builtin_amdgcn_update_dpp(0, d, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
       d += __builtin_amdgcn_update_dpp(0, d, 0x141, 0xF, 0xF, false);   // row_half_mirror
-      if (use) e = (cand.y >> 1) + d;
+      if (ev) e = (cand.y >> 1) + d;
     }
     const int32_t oe = __builtin_amdgcn_update_dpp(0, e, 0x128, 0xF, 0xF, false);        // row_ror:8
     const int32_t ofl = __builtin_amdgcn_update_dpp(0, cand.x, 0x128, 0xF, 0xF, false);
