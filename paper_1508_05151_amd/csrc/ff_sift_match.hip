@@ -29,7 +29,7 @@
 
 namespace ff {
 
-constexpr int kSLanes = 16;   // lanes per point (entry, random search): one DPP row
+constexpr int kSLanes = 16;   // lanes per point (entry): one DPP row
 constexpr int kSiftRecsPerWrite = 12;
 constexpr int kSiftStatusBytes = 256;
 
@@ -89,70 +89,64 @@ __device__ __forceinline__ bool svalid(const SCtx& c, int px, int py, int32_t f)
   return mx >= 0 && my >= 0 && mx <= (c.Wd - 1) * c.Q && my <= (c.Hd - 1) * c.Q;
 }
 
-// floor(sqrt(v)) for v < 2^46: a float estimate (from the two 32-bit
-// halves), corrected exactly; the root is below 2^23, so its squares are
-// full-rate 24-bit products
-__device__ __forceinline__ uint64_t sq24(uint32_t x) {
-  const uint32_t y = x & 0xFFFFFFu;   // no-op here: x < 2^24
-  return (uint64_t)y * y;
-}
-__device__ __forceinline__ uint32_t isqrt_u64(uint64_t v) {
-  const float fv = fmaf((float)(uint32_t)(v >> 32), 4294967296.0f, (float)(uint32_t)v);
-  uint32_t k = min((uint32_t)sqrtf(fv), 0x7FFFFFu);
-  while (sq24(k) > v) --k;
-  while (sq24(k + 1) <= v) ++k;
-  return k;
-}
-
-typedef short short4_t __attribute__((ext_vector_type(4)));
-
-// Bilinear target weights of a candidate and its integer target centre.
-struct Tgt {
-  int Mx, My, w00, w10, w01, w11;
-};
-
-__device__ __forceinline__ Tgt tgt_of(const SCtx& c, int px, int py, int32_t f) {
-  const int mx = px * c.Q + fx_of(f), my = py * c.Q + fy_of(f);
-  Tgt t;
-  t.Mx = mx >> c.qshift;
-  t.My = my >> c.qshift;
-  const int a = mx & (c.Q - 1), b = my & (c.Q - 1);
-  // weights <= Q^2 <= 64: the masks (no-ops) let the products with the
-  // colours compile to full-rate 24-bit multiplies
-  t.w00 = ((c.Q - a) * (c.Q - b)) & 0x7F;
-  t.w10 = (a * (c.Q - b)) & 0x7F;
-  t.w01 = ((c.Q - a) * b) & 0x7F;
-  t.w11 = (a * b) & 0x7F;
-  return t;
-}
-
-// The colours of one pixel as SG groups of 4 int16 (8-byte loads).  Groups
-// at or past the field's ceil(S/4) are not loaded (zero, and masked out by
-// the channel test).
+// SG groups of four colours of one pixel, as packed int16 pairs
 template <int SG>
-struct Px {
-  short4_t v[SG];
+struct Col {
+  uint32_t w[2 * SG];
 };
-
 template <int SG>
-__device__ __forceinline__ Px<SG> load_px(const int16_t* p, int sgf) {
-  Px<SG> r;
-  const short4_t* q = reinterpret_cast<const short4_t*>(p);
+__device__ __forceinline__ Col<SG> load_col(const int16_t* p) {
+  typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(8)));
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  Col<SG> r;
 #pragma unroll
-  for (int g = 0; g < SG; ++g) {
-    if (g < sgf)   // uniform: a field's channel count
-      r.v[g] = q[g];
-    else
-      r.v[g] = short4_t{0, 0, 0, 0};
+  for (int g = 0; g + 2 <= SG; g += 2) {
+    const u4 x = *(__attribute__((address_space(1))) const u4*)(p + 4 * g);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.w[2 * g + i] = x[i];
+  }
+  if (SG & 1) {
+    const u2 x = *(__attribute__((address_space(1))) const u2*)(p + 4 * (SG - 1));
+    r.w[2 * SG - 2] = x[0];
+    r.w[2 * SG - 1] = x[1];
   }
   return r;
 }
 
-// the target's four neighbours of (X, Y) (already clamped)
-template <int SG>
-struct Quad {
-  Px<SG> p00, p10, p01, p11;
-};
+typedef short short2_t __attribute__((ext_vector_type(2)));
+// w * (the low or the high half of v) + acc, w in the matching half of wv
+__device__ __forceinline__ int32_t mad16(uint32_t v, uint32_t wv, int32_t acc) {
+  return __builtin_amdgcn_sdot2(__builtin_bit_cast(short2_t, v), __builtin_bit_cast(short2_t, wv), acc, false);
+}
+
+// floor(sqrt(v)) of N values v < 2^46.  Below 2^40 (codes up to 2047, which is
+// what the projection gives) the hardware root of the rounded v is off by less
+// than one, so one step either way corrects it; above (a caller's own codes)
+// by up to three.  The root is below 2^23, so its squares are full-rate 24-bit
+// products.
+__device__ __forceinline__ uint64_t sq24(uint32_t x) {
+  const uint32_t y = x & 0xFFFFFFu;   // no-op here: x < 2^24
+  return (uint64_t)y * y;
+}
+template <int N>
+__device__ __forceinline__ void isqrt46(const uint64_t (&v)[N], uint32_t (&k)[N]) {
+  uint32_t top = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const float fv = fmaf((float)(uint32_t)(v[i] >> 32), 4294967296.0f, (float)(uint32_t)v[i]);
+    k[i] = (uint32_t)__builtin_amdgcn_sqrtf(fv);
+    k[i] -= sq24(k[i]) > v[i] ? 1u : 0u;
+    k[i] += sq24(k[i] + 1) <= v[i] ? 1u : 0u;
+    top |= (uint32_t)(v[i] >> 32);
+  }
+  if (top >= 256) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      while (sq24(k[i]) > v[i]) --k[i];
+      while (sq24(k[i] + 1) <= v[i]) ++k[i];
+    }
+  }
+}
 
 // int16 offset of pixel (x, y) in a plane of width w and pitch P: below
 // 2^27 (pixels < 2^22, P <= 32), so 32-bit full-rate 24-bit products
@@ -160,57 +154,82 @@ __device__ __forceinline__ uint32_t pix_off(int x, int y, int w, int P) {
   return __umul24(__umul24((uint32_t)y, (uint32_t)w) + (uint32_t)x, (uint32_t)P);
 }
 
-template <int SG>
-__device__ __forceinline__ Quad<SG> load_quad(const SCtx& c, int X, int Y, int sgf) {
-  const int X1 = min(X + 1, c.Wd - 1), Y1 = min(Y + 1, c.Hd - 1);
-  Quad<SG> q;
-  q.p00 = load_px<SG>(c.dst + pix_off(X, Y, c.Wd, c.P), sgf);
-  q.p10 = load_px<SG>(c.dst + pix_off(X1, Y, c.Wd, c.P), sgf);
-  q.p01 = load_px<SG>(c.dst + pix_off(X, Y1, c.Wd, c.P), sgf);
-  q.p11 = load_px<SG>(c.dst + pix_off(X1, Y1, c.Wd, c.P), sgf);
-  return q;
+// the five weights of a sample, negated for the target's four: source,
+// (0, 0), (1, 0), (0, 1), (1, 1); used in the low half, and shifted to the high
+struct Weights {
+  uint32_t w[5];
+};
+__device__ __forceinline__ Weights weights_of(const SCtx& c, int mx, int my) {
+  const int a = mx & (c.Q - 1), b = my & (c.Q - 1);
+  return {{(uint32_t)(c.Q * c.Q), (uint32_t)(uint16_t)(-(c.Q - a) * (c.Q - b)), (uint32_t)(uint16_t)(-a * (c.Q - b)),
+           (uint32_t)(uint16_t)(-(c.Q - a) * b), (uint32_t)(uint16_t)(-a * b)}};
 }
 
-// floor(sqrt(sum_s d_s^2 * 256 / Q^4)) of one sample.  Every factor fits 24
-// signed bits (weights and Q^2 <= 64, colours int16, |d_s| < 2^22), so the
-// products are full-rate 24-bit multiplies (the 64-bit square from its low
-// and high halves).
+// one sample's five pixels: offset (dx, dy) from the source point and from
+// the target centre alike
 template <int SG>
-__device__ __forceinline__ int32_t dist_of(const SCtx& c, const Px<SG>& a, const Quad<SG>& q, const Tgt& t) {
-  const int QQ = (c.Q * c.Q) & 0x7F;
-  uint64_t ss = 0;
+struct Sample {
+  Col<SG> p[5];
+};
+template <int SG>
+__device__ __forceinline__ Sample<SG> load_sample(const SCtx& c, int px, int py, int Mx, int My, int dx, int dy) {
+  const int X = clampi(Mx + dx, 0, c.Wd - 1), Y = clampi(My + dy, 0, c.Hd - 1);
+  const int X1 = min(X + 1, c.Wd - 1), Y1 = min(Y + 1, c.Hd - 1);
+  Sample<SG> s;
+  s.p[0] = load_col<SG>(c.src + pix_off(clampi(px + dx, 0, c.Ws - 1), clampi(py + dy, 0, c.Hs - 1), c.Ws, c.P));
+  s.p[1] = load_col<SG>(c.dst + pix_off(X, Y, c.Wd, c.P));
+  s.p[2] = load_col<SG>(c.dst + pix_off(X1, Y, c.Wd, c.P));
+  s.p[3] = load_col<SG>(c.dst + pix_off(X, Y1, c.Wd, c.P));
+  s.p[4] = load_col<SG>(c.dst + pix_off(X1, Y1, c.Wd, c.P));
+  return s;
+}
+
+// its squared distance, sum_s d_s^2 * 256 / Q^4: a colour pair is weighted and
+// summed by one packed dot product per weight
+template <int SG>
+__device__ __forceinline__ uint64_t sample_sq(const SCtx& c, const Sample<SG>& s, const Weights& wl) {
+  int64_t ss = 0;
 #pragma unroll
   for (int g = 0; g < SG; ++g)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int e = __mul24(QQ, (int)a.v[g][i]) -
-                    (__mul24(t.w00, (int)q.p00.v[g][i]) + __mul24(t.w10, (int)q.p10.v[g][i]) +
-                     __mul24(t.w01, (int)q.p01.v[g][i]) + __mul24(t.w11, (int)q.p11.v[g][i]));
-      const int em = g * 4 + i < c.S ? e : 0;
-      const int e24 = (int)((uint32_t)em << 8) >> 8;   // no-op: |em| < 2^23
-      ss += (uint64_t)((int64_t)e24 * e24);
+      int32_t e = 0;
+#pragma unroll
+      for (int t = 0; t < 5; ++t) e = mad16(s.p[t].w[2 * g + (i >> 1)], i & 1 ? wl.w[t] << 16 : wl.w[t], e);
+      // the last group's channels past S (only there: 4 SG - S < 4)
+      if (g == SG - 1 && i > 0) e = 4 * g + i < c.S ? e : 0;
+      ss += (int64_t)e * e;
     }
-  const uint64_t v = c.qshift <= 2 ? ss << (8 - 4 * c.qshift) : ss >> 4;
-  return (int32_t)isqrt_u64(v);
+  return c.qshift <= 2 ? (uint64_t)ss << (8 - 4 * c.qshift) : (uint64_t)ss >> 4;
 }
 
-// this lane's share (samples lane, lane + L, ...) of E for candidate f
+// f(the field's own group count, 1 .. SG, as a constant)
+template <int SG, typename F>
+__device__ __forceinline__ void with_groups(int sg, F&& f) {
+  if constexpr (SG > 1) {
+    if (sg < SG) return with_groups<SG - 1>(sg, static_cast<F&&>(f));
+  }
+  f(std::integral_constant<int, SG>{});
+}
+
+// this lane's share (samples lane, lane + L, ...) of E for candidate fl
 template <int SG>
-__device__ __forceinline__ int32_t sift_partial(const SCtx& c, int px, int py, int32_t f, int lane, int L) {
-  const Tgt t = tgt_of(c, px, py, f);
-  const int Sd = 2 * c.r + 1, sgf = (c.S + 3) >> 2;
+__device__ __forceinline__ int32_t sift_partial(const SCtx& c, int px, int py, int32_t fl, int lane, int L) {
+  const int mx = px * c.Q + fx_of(fl), my = py * c.Q + fy_of(fl);
+  const Weights wl = weights_of(c, mx, my);
+  const int Sd = 2 * c.r + 1;
   int32_t sum = 0;
   for (int k = lane; k < Sd * Sd; k += L) {
     const int iy = k / Sd, ix = k - iy * Sd;
-    const int dx = (ix - c.r) * c.n, dy = (iy - c.r) * c.n;
-    const int sx = clampi(px + dx, 0, c.Ws - 1), sy = clampi(py + dy, 0, c.Hs - 1);
-    const Px<SG> a = load_px<SG>(c.src + pix_off(sx, sy, c.Ws, c.P), sgf);
-    const Quad<SG> q = load_quad<SG>(c, clampi(t.Mx + dx, 0, c.Wd - 1), clampi(t.My + dy, 0, c.Hd - 1), sgf);
-    sum += dist_of<SG>(c, a, q, t);
+    const Sample<SG> s =
+        load_sample<SG>(c, px, py, mx >> c.qshift, my >> c.qshift, (ix - c.r) * c.n, (iy - c.r) * c.n);
+    const uint64_t v[1] = {sample_sq<SG>(c, s, wl)};
+    uint32_t d[1];
+    isqrt46(v, d);
+    sum += (int32_t)d[0];
   }
   return sum;
 }
-
 
 // ---------------------------------------------------------------- table, clears
 struct SiftChunk {
@@ -271,15 +290,17 @@ __global__ __launch_bounds__(256) void k_sift_seed(const SiftRec* __restrict__ t
     }
   }
   int32_t bestF = kEmpty, bestC = kInf;
-  for (int i = 0; i < cnt && start + i < Nd; ++i) {
-    const int id = perm[start + i];
-    const int32_t fl = packf((id % f.Wd - px) * c.Q, (id / f.Wd - py) * c.Q);
-    const int32_t e = wave_sum(sift_partial<SG>(c, px, py, fl, lane, 64));
-    if (e < bestC) {
-      bestC = e;
-      bestF = fl;
+  with_groups<SG>((c.S + 3) >> 2, [&](auto G) {
+    for (int i = 0; i < cnt && start + i < Nd; ++i) {
+      const int id = perm[start + i];
+      const int32_t fl = packf((id % f.Wd - px) * c.Q, (id / f.Wd - py) * c.Q);
+      const int32_t e = wave_sum(sift_partial<decltype(G)::value>(c, px, py, fl, lane, 64));
+      if (e < bestC) {
+        bestC = e;
+        bestF = fl;
+      }
     }
-  }
+  });
   if (lane == 0) {
     sgrid_flow(f, lev, buf)[(size_t)gy * Gw + gx] = bestF;
     sgrid_cost(f, lev, buf)[(size_t)gy * Gw + gx] = bestC;
@@ -302,7 +323,10 @@ __global__ __launch_bounds__(256) void k_sift_entry(const SiftRec* __restrict__ 
   const int gx = 2 * (cid % Gwc), gy = 2 * (cid / Gwc);
   const int32_t fl = sgrid_flow(f, lev + 1, 0)[cid];   // a finished level ends in buffer 0
   int32_t e = kInf;
-  if (fl != kEmpty) e = row16_sum(sift_partial<SG>(c, gx * c.n, gy * c.n, fl, lane, kSLanes));
+  if (fl != kEmpty)
+    with_groups<SG>((c.S + 3) >> 2, [&](auto G) {
+      e = row16_sum(sift_partial<decltype(G)::value>(c, gx * c.n, gy * c.n, fl, lane, kSLanes));
+    });
   if (lane < 4) {
     const int x = gx + (lane & 1), y = gy + (lane >> 1);
     if (x < Gw && y < Gh) {
@@ -315,32 +339,83 @@ __global__ __launch_bounds__(256) void k_sift_entry(const SiftRec* __restrict__ 
 // ---------------------------------------------------------------- random search
 // One offset per point, per axis an integer in [-nRQ, nRQ] 1/Q px from
 // Philox keyed by the seed with counter (pixel, level, step, field | pair
-// << 2); replace only on a strictly lower cost.  16 lanes per point.
+// << 2); replace only on a strictly lower cost.
+// A workgroup covers 32 x its points, a wavefront 8 x its of them: it draws
+// all its candidates at once, one per lane, and costs a row of eight at a
+// time, eight lanes per point, a sample per lane and round; a candidate whose
+// sum reaches the point's cost is out.  Runs of adjacent tiles go to one XCD.
+// Bound: the texture path and integer work alike (200 bytes and 200
+// instructions a sample).  Against 16 lanes per point, 8-byte loads and 24-bit
+// multiplies: 1242x375 gray (F, B1, B2) level 0 810 -> 436 us per launch, all
+// twelve launches 3.7 -> 2.2 ms.
+template <int SG>
+__device__ __forceinline__ void rs_rows(const SCtx& c, int32_t* F, int32_t* C, int Gw, int gx0, int gy0, int its,
+                                        int32_t cands, int32_t bounds) {
+  const int lane = threadIdx.x & 63, i = lane >> 3, j = lane & 7;
+  const int Sd = 2 * c.r + 1, n2 = Sd * Sd;
+  const uint32_t inv = 65536u / (uint32_t)Sd + 1;   // k / Sd = k inv >> 16 for k < 31 * 31
+  for (int it = 0; it < its; ++it) {
+    const int32_t cand = __shfl(cands, it * 8 + i), bound = __shfl(bounds, it * 8 + i);
+    bool use = bound >= 0;
+    const int px = (gx0 + i) * c.n, py = (gy0 + it) * c.n;
+    const int mx = px * c.Q + fx_of(cand), my = py * c.Q + fy_of(cand);
+    const Weights wl = weights_of(c, mx, my);
+    int32_t total = 0;
+    for (int k0 = 0; k0 < n2 && __ballot(use) != 0; k0 += 8) {
+      if (use) {
+        const int k = min(k0 + j, n2 - 1), iy = (int)(__umul24((uint32_t)k, inv) >> 16), ix = k - iy * Sd;
+        const Sample<SG> s =
+            load_sample<SG>(c, px, py, mx >> c.qshift, my >> c.qshift, (ix - c.r) * c.n, (iy - c.r) * c.n);
+        const uint64_t v[1] = {sample_sq<SG>(c, s, wl)};
+        uint32_t root[1];
+        isqrt46(v, root);
+        int32_t d = k0 + j < n2 ? (int32_t)root[0] : 0;
+        // over the point's eight lanes
+        d += __builtin_amdgcn_update_dpp(0, d, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
+        d += __builtin_amdgcn_update_dpp(0, d, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
+        d += __builtin_amdgcn_update_dpp(0, d, 0x141, 0xF, 0xF, false);   // row_half_mirror
+        total += d;
+        use = total < bound;
+      }
+    }
+    if (use && j == 0) {
+      const int p = (gy0 + it) * Gw + gx0 + i;
+      F[p] = cand;
+      C[p] = total;
+    }
+  }
+}
+
 template <int SG>
 __global__ __launch_bounds__(256) void k_sift_rs(const SiftRec* __restrict__ table, int lev, int qshift, int step,
-                                                 int R, int buf) {
+                                                 int R, int buf, int its) {
   const SiftRec& f = table[blockIdx.y];
   const SCtx c = sctx_of(f, lev, qshift);
   const int Gw = (f.Ws + c.n - 1) >> lev, Gh = (f.Hs + c.n - 1) >> lev;
-  const int pid = (blockIdx.x * blockDim.x + threadIdx.x) / kSLanes;
-  const int lane = threadIdx.x % kSLanes;
-  if (pid >= Gw * Gh) return;
+  const int tilesX = (Gw + 31) >> 5, nt = tilesX * ((Gh + its - 1) / its);
+  const int per = (nt + 7) >> 3, tile = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per || tile >= nt) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int gx0 = tile % tilesX * 32 + wave * 8, gy0 = tile / tilesX * its;
   int32_t* F = sgrid_flow(f, lev, buf);
   int32_t* C = sgrid_cost(f, lev, buf);
-  const int32_t fl = F[pid];
-  if (fl == kEmpty) return;
-  const int px = (pid % Gw) * c.n, py = (pid / Gw) * c.n;
-  uint32_t u0, u1;
-  philox2((uint32_t)(py * f.Ws + px), (uint32_t)lev, (uint32_t)step, f.c3, f.k0, f.k1, u0, u1);
-  const int rad = c.n * R * c.Q;
-  const uint64_t span = (uint64_t)(2 * rad + 1);
-  const int32_t cand = packf(fx_of(fl) + (int)((u0 * span) >> 32) - rad, fy_of(fl) + (int)((u1 * span) >> 32) - rad);
-  if (!svalid(c, px, py, cand)) return;
-  const int32_t e = row16_sum(sift_partial<SG>(c, px, py, cand, lane, kSLanes));
-  if (lane == 0 && e < C[pid]) {
-    F[pid] = cand;
-    C[pid] = e;
+  // this lane's point
+  const int gx = gx0 + (lane & 7), gy = gy0 + (lane >> 3);
+  int32_t cand = 0, bound = -1;
+  if (lane < 8 * its && gx < Gw && gy < Gh) {
+    const int32_t fl = F[gy * Gw + gx];
+    if (fl != kEmpty) {
+      const int px = gx * c.n, py = gy * c.n;
+      uint32_t u0, u1;
+      philox2((uint32_t)(py * f.Ws + px), (uint32_t)lev, (uint32_t)step, f.c3, f.k0, f.k1, u0, u1);
+      const int rad = c.n * R * c.Q;
+      const uint64_t span = (uint64_t)(2 * rad + 1);
+      cand = packf(fx_of(fl) + (int)((u0 * span) >> 32) - rad, fy_of(fl) + (int)((u1 * span) >> 32) - rad);
+      if (svalid(c, px, py, cand)) bound = C[gy * Gw + gx];
+    }
   }
+  with_groups<SG>((c.S + 3) >> 2,
+                  [&](auto G) { rs_rows<decltype(G)::value>(c, F, C, Gw, gx0, gy0, its, cand, bound); });
 }
 
 // ---------------------------------------------------------------- propagation (Eq. 2)
@@ -365,97 +440,29 @@ __global__ __launch_bounds__(256) void k_sift_rs(const SiftRec* __restrict__ tab
 // 4 rows, each waiting for the one above, took 5.1; all 16 sweeps 8.0 ms
 // against 34, the pair 19.3 against 46.0; a 161x119 pair 5.6 against 9.1.
 
-// SG groups of four colours of one pixel, as packed int16 pairs
-template <int SG>
-struct Col {
-  uint32_t w[2 * SG];
-};
-template <int SG>
-__device__ __forceinline__ Col<SG> load_col(const int16_t* p) {
-  typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(8)));
-  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-  Col<SG> r;
-#pragma unroll
-  for (int g = 0; g + 2 <= SG; g += 2) {
-    const u4 x = *(__attribute__((address_space(1))) const u4*)(p + 4 * g);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r.w[2 * g + i] = x[i];
-  }
-  if (SG & 1) {
-    const u2 x = *(__attribute__((address_space(1))) const u2*)(p + 4 * (SG - 1));
-    r.w[2 * SG - 2] = x[0];
-    r.w[2 * SG - 1] = x[1];
-  }
-  return r;
-}
-
-typedef short short2_t __attribute__((ext_vector_type(2)));
-// w * (the low or the high half of v) + acc, w in the matching half of wv
-__device__ __forceinline__ int32_t mad16(uint32_t v, uint32_t wv, int32_t acc) {
-  return __builtin_amdgcn_sdot2(__builtin_bit_cast(short2_t, v), __builtin_bit_cast(short2_t, wv), acc, false);
-}
-
-// floor(sqrt(v)), v < 2^40: the hardware root of the rounded v is off by less
-// than one, so one step either way corrects it
-__device__ __forceinline__ uint32_t isqrt40(uint64_t v) {
-  const float fv = fmaf((float)(uint32_t)(v >> 32), 4294967296.0f, (float)(uint32_t)v);
-  uint32_t k = (uint32_t)__builtin_amdgcn_sqrtf(fv);
-  k -= sq24(k) > v ? 1u : 0u;
-  k += sq24(k + 1) <= v ? 1u : 0u;
-  return k;
-}
-
-struct SiftSlide {
-  const int16_t* src;   // level's colour images
-  const int16_t* dst;
-  int Ws, Hs, Wd, Hd, P, S, r, n, Q, qshift;
-};
-
 // Signed share of a lane in its line's sum: samples q, q + 4, ... of the line
 // whose sample k lies at p + (dx0 + k kx, dy0 + k ky) around the source point
 // and the target centre alike.
 template <int SG>
-__device__ __forceinline__ int32_t slide_line(const SiftSlide& c, int px, int py, int mx, int my, int dx0, int dy0,
+__device__ __forceinline__ int32_t slide_line(const SCtx& c, int px, int py, int mx, int my, int dx0, int dy0,
                                               int kx, int ky, int q) {
-  const int Mx = mx >> c.qshift, My = my >> c.qshift, a = mx & (c.Q - 1), b = my & (c.Q - 1);
-  const int QQ = c.Q * c.Q;
-  // the five weights, negated for the target's; low half, and shifted to the high half
-  const uint32_t wl[5] = {(uint32_t)QQ, (uint32_t)(uint16_t)(-(c.Q - a) * (c.Q - b)),
-                          (uint32_t)(uint16_t)(-a * (c.Q - b)), (uint32_t)(uint16_t)(-(c.Q - a) * b),
-                          (uint32_t)(uint16_t)(-a * b)};
+  const int Mx = mx >> c.qshift, My = my >> c.qshift;
+  const Weights wl = weights_of(c, mx, my);
   const int Sd = 2 * c.r + 1;
   int32_t sum = 0;
   for (int k0 = q; k0 < Sd; k0 += 8) {
-    Col<SG> p[2][5];
+    Sample<SG> p[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      const int k = min(k0 + 4 * s, Sd - 1), dx = dx0 + k * kx, dy = dy0 + k * ky;
-      const int X = clampi(Mx + dx, 0, c.Wd - 1), Y = clampi(My + dy, 0, c.Hd - 1);
-      const int X1 = min(X + 1, c.Wd - 1), Y1 = min(Y + 1, c.Hd - 1);
-      p[s][0] = load_col<SG>(c.src + pix_off(clampi(px + dx, 0, c.Ws - 1), clampi(py + dy, 0, c.Hs - 1), c.Ws, c.P));
-      p[s][1] = load_col<SG>(c.dst + pix_off(X, Y, c.Wd, c.P));
-      p[s][2] = load_col<SG>(c.dst + pix_off(X1, Y, c.Wd, c.P));
-      p[s][3] = load_col<SG>(c.dst + pix_off(X, Y1, c.Wd, c.P));
-      p[s][4] = load_col<SG>(c.dst + pix_off(X1, Y1, c.Wd, c.P));
+      const int k = min(k0 + 4 * s, Sd - 1);
+      p[s] = load_sample<SG>(c, px, py, Mx, My, dx0 + k * kx, dy0 + k * ky);
     }
+    uint64_t v[2];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      int64_t ss = 0;
-#pragma unroll
-      for (int g = 0; g < SG; ++g)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          int32_t e = 0;
-#pragma unroll
-          for (int t = 0; t < 5; ++t) e = mad16(p[s][t].w[2 * g + (i >> 1)], i & 1 ? wl[t] << 16 : wl[t], e);
-          // the last group's channels past S (only there: 4 SG - S < 4)
-          if (g == SG - 1 && i > 0) e = 4 * g + i < c.S ? e : 0;
-          ss += (int64_t)e * e;
-        }
-      const uint64_t v = c.qshift <= 2 ? (uint64_t)ss << (8 - 4 * c.qshift) : (uint64_t)ss >> 4;
-      const int32_t d = (int32_t)isqrt40(v);
-      sum += k0 + 4 * s < Sd ? d : 0;
-    }
+    for (int s = 0; s < 2; ++s) v[s] = sample_sq<SG>(c, p[s], wl);
+    uint32_t d[2];
+    isqrt46(v, d);
+    sum += (int32_t)(d[0] + (k0 + 4 < Sd ? d[1] : 0u));
   }
   return sum;
 }
@@ -469,7 +476,7 @@ struct STile {
 
 // the 16 steps of a visit (as the census sweep's: row i at column u0 + t - i)
 template <int SG>
-__device__ __forceinline__ void sift_steps(const SiftSlide& c, STile& s, int lev, int sx, int sy, int u0, int v0, int Gw,
+__device__ __forceinline__ void sift_steps(const SCtx& c, STile& s, int lev, int sx, int sy, int u0, int v0, int Gw,
                                            int Gh, bool first) {
   const int i = threadIdx.x >> 4, l = threadIdx.x & 15, line = l >> 2, q = l & 3;
   const bool horiz = line >= 2, enter = (line & 1) != 0;
@@ -510,7 +517,7 @@ __device__ __forceinline__ void sift_steps(const SiftSlide& c, STile& s, int lev
       d += __builtin_amdgcn_update_dpp(0, d, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
       d += __builtin_amdgcn_update_dpp(0, d, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
       d += __builtin_amdgcn_update_dpp(0, d, 0x141, 0xF, 0xF, false);   // row_half_mirror
-      if (ev) e = (cand.y >> 1) + d;
+      if (ev) e = (int32_t)((uint32_t)cand.y >> 1) + d;
     }
     const int32_t oe = __builtin_amdgcn_update_dpp(0, e, 0x128, 0xF, 0xF, false);        // row_ror:8
     const int32_t ofl = __builtin_amdgcn_update_dpp(0, cand.x, 0x128, 0xF, 0xF, false);
@@ -529,15 +536,6 @@ __device__ __forceinline__ void sift_steps(const SiftSlide& c, STile& s, int lev
     ++uL;
   }
 }
-template <int SG>
-__device__ __forceinline__ void sift_steps_of(int sg, const SiftSlide& c, STile& s, int lev, int sx, int sy, int u0,
-                                              int v0, int Gw, int Gh, bool first) {
-  if constexpr (SG > 1) {
-    if (sg < SG) return sift_steps_of<SG - 1>(sg, c, s, lev, sx, sy, u0, v0, Gw, Gh, first);
-  }
-  sift_steps<SG>(c, s, lev, sx, sy, u0, v0, Gw, Gh, first);
-}
-
 struct SiftSweepArgs {
   int nf, lev, qshift, sx, sy;
   int base;    // of the request counters (ff_relax.h)
@@ -614,7 +612,7 @@ __global__ __launch_bounds__(256) void k_sift_sweep(const SiftRec* __restrict__ 
           }
         }
         // cost doubled, the low bit marks a value this tile has not seen
-        // (costs stay below 2^29; EMPTY's is never used)
+        // (costs stay below 2^31; EMPTY's is never used)
         const int2 b = make_int2(hf, (int)((uint32_t)hc << 1) | (first || hf != wasF ? 1 : 0));
         if (isl)
           s.left[bl] = b;
@@ -629,20 +627,9 @@ __global__ __launch_bounds__(256) void k_sift_sweep(const SiftRec* __restrict__ 
     int32_t seen = s.res[oidx < kTileH * kPO ? oidx : 0].x;
     asm volatile("" : "+v"(seen));
     __syncthreads();
-    SiftSlide c;
-    c.src = f.src + (size_t)lev * f.Ws * f.Hs * f.P;
-    c.dst = f.dst + (size_t)lev * f.Wd * f.Hd * f.P;
-    c.Ws = f.Ws;
-    c.Hs = f.Hs;
-    c.Wd = f.Wd;
-    c.Hd = f.Hd;
-    c.P = f.P;
-    c.S = f.S;
-    c.r = f.r;
-    c.n = n;
-    c.Q = 1 << a.qshift;
-    c.qshift = a.qshift;
-    sift_steps_of<SG>((f.S + 3) >> 2, c, s, lev, sx, sy, u0, v0, Gw, Gh, first);
+    const SCtx c = sctx_of(f, lev, a.qshift);
+    with_groups<SG>((f.S + 3) >> 2,
+                    [&](auto G) { sift_steps<decltype(G)::value>(c, s, lev, sx, sy, u0, v0, Gw, Gh, first); });
     __syncthreads();
     // ---- results out, changed border words published
     if (pok) {
@@ -952,19 +939,20 @@ static ff_status run_sift_batch(const ff_sift_job* jobs, int n, const ff_match_p
       q.status = status;
       q.timeout = timeout;
       prof_mark(FF_PROF_SIFT_PROPAGATE, stream, true);
-      if (SG <= 3)
-        k_sift_sweep<3><<<q.G, 256, 0, stream>>>(table, a, q);
-      else if (SG <= 5)
-        k_sift_sweep<5><<<q.G, 256, 0, stream>>>(table, a, q);
-      else
-        k_sift_sweep<8><<<q.G, 256, 0, stream>>>(table, a, q);
+      k_sift_sweep<SG><<<q.G, 256, 0, stream>>>(table, a, q);
       prof_mark(FF_PROF_SIFT_PROPAGATE, stream, false);
       buf ^= 1;
       ++launch;
       ++steps;
       if (stop()) return finish();
       if (i < p->n_rs) {
-        k_sift_rs<SG><<<dim3(groups(pts(lev)), n), 256, 0, stream>>>(table, lev, qshift, i, p->R, buf);
+        const int Gw = (maxW + (1 << lev) - 1) >> lev, Gh = (maxH + (1 << lev) - 1) >> lev, wide = (Gw + 31) / 32;
+        // rows of points per wavefront: eight, fewer where that leaves the
+        // chip short of wavefronts (16 per CU)
+        int its = 8;
+        while (its > 1 && (int64_t)wide * 4 * ((Gh + its - 1) / its) * n < 4096) its >>= 1;
+        const unsigned tiles = (unsigned)(wide * ((Gh + its - 1) / its));
+        k_sift_rs<SG><<<dim3((tiles + 7) / 8 * 8, n), 256, 0, stream>>>(table, lev, qshift, i, p->R, buf, its);
         ++steps;
         if (stop()) return finish();
       }
@@ -1004,16 +992,11 @@ ff_status ff_match_sift(const ff_sift_job* jobs, int32_t n_jobs, const ff_match_
   int sg = 1;
   for (int i = 0; i < n_jobs; ++i) sg = std::max(sg, (jobs[i].channels + 3) / 4);
   char* w = static_cast<char*>(workspace);
-  switch (sg) {
-    case 1: st = run_sift_batch<1>(jobs, n_jobs, p, w, B, stream); break;
-    case 2: st = run_sift_batch<2>(jobs, n_jobs, p, w, B, stream); break;
-    case 3: st = run_sift_batch<3>(jobs, n_jobs, p, w, B, stream); break;
-    case 4: st = run_sift_batch<4>(jobs, n_jobs, p, w, B, stream); break;
-    case 5: st = run_sift_batch<5>(jobs, n_jobs, p, w, B, stream); break;
-    case 6: st = run_sift_batch<6>(jobs, n_jobs, p, w, B, stream); break;
-    case 7: st = run_sift_batch<7>(jobs, n_jobs, p, w, B, stream); break;
-    default: st = run_sift_batch<8>(jobs, n_jobs, p, w, B, stream); break;
-  }
+  // instances by what their registers allow: a field's own group count picks
+  // the code inside
+  st = sg <= 3   ? run_sift_batch<3>(jobs, n_jobs, p, w, B, stream)
+       : sg <= 5 ? run_sift_batch<5>(jobs, n_jobs, p, w, B, stream)
+                 : run_sift_batch<8>(jobs, n_jobs, p, w, B, stream);
   prof_mark(FF_PROF_SIFT_MATCH, stream, false);
   return st;
 }

@@ -100,3 +100,67 @@ def test_sift_field_bit_exact_at_tile_edges(W, H, r, S, Sc, Q, kw):
         oF, oC = ffo.match_field_sift(od[0], od[1], ol[0], ol[1], r, S, max_steps=stop, seed=77, field_id=2, pair_id=5,
                                       **kw)
         assert np.array_equal(flow.cpu().numpy(), oF) and np.array_equal(cost.cpu().numpy(), oC), stop
+
+
+def _sift_jobs(W, H, r, S, Q, kw, codes, n):
+    """n fields (distinct counters) of one synthetic pair in one call."""
+    from paper_1508_05151_amd import ff
+    k = kw["k"]
+    p = pairs.layered_pair(seed=500 + W + H, W=W, H=H, nlayers=2)
+    d = ff.ff_desc_init(W, H, 3, k, Q, (r,))
+    ws = torch.empty(ff.ff_sift_workspace_bytes(W, H, W, H), dtype=torch.uint8, device="cuda")
+    blobs, levels = [], []
+    for img, c in zip((p.img1, p.img2), codes):
+        b = torch.empty(d.bytes, dtype=torch.uint8, device="cuda")
+        ff.ff_compute_lab_wht(d, torch.from_numpy(np.ascontiguousarray(img)).cuda(), b)
+        lv = torch.empty((k + 1, H, W, ff.ff_sift_pitch(S)), dtype=torch.int16, device="cuda")
+        ff.ff_sift_levels(torch.from_numpy(c).cuda(), k, lv, ws)
+        blobs.append(b)
+        levels.append(lv)
+    out = [(torch.empty((H, W), dtype=torch.int32, device="cuda"), torch.empty((H, W), dtype=torch.int32, device="cuda"))
+           for _ in range(n)]
+    jobs = [ff.make_sift_job(d, blobs[0], d, blobs[1], levels[0], levels[1], S, k, r, F, C, 2, i, 77)
+            for i, (F, C) in enumerate(out)]
+    prm = ff.ff_default_params(**kw)
+    mws = torch.full((ff.ff_match_sift_workspace_bytes(jobs, prm),), 0xA5, dtype=torch.uint8, device="cuda")
+    ff.ff_match_sift(jobs, prm, mws)
+    torch.cuda.synchronize()
+    assert ff.ff_read_status(mws) == 0
+    return p.img1, p.img2, [(F.cpu().numpy(), C.cpu().numpy()) for F, C in out]
+
+
+@pytest.mark.parametrize("W,H,n", [(70, 43, 20), (70, 43, 40), (33, 61, 150)])
+def test_sift_search_rows_per_wavefront(W, H, n):
+    """Enough fields in a call that the finest level's random search takes two,
+    four and eight rows of points per wavefront, whole and cut off at the
+    bottom and right; each of the first, a middle and the last field bit for
+    bit."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("sift search rows", W, H, n, flush=True)
+    r, S, Q, kw = 2, 6, 4, dict(k=1)
+    rng = np.random.default_rng(W * H)
+    codes = [rng.integers(-2047, 2048, (H, W, S)).astype(np.int16) for _ in range(2)]
+    img1, img2, got = _sift_jobs(W, H, r, S, Q, kw, codes, n)
+    od = [ffo.Desc(img, 1, Q, (r,)) for img in (img1, img2)]
+    ol = [ffo.SiftLevels(c, 1) for c in codes]
+    for i in (0, n // 2, n - 1):
+        oF, oC = ffo.match_field_sift(od[0], od[1], ol[0], ol[1], r, S, seed=77, field_id=2, pair_id=i, **kw)
+        assert np.array_equal(got[i][0], oF) and np.array_equal(got[i][1], oC), i
+
+
+@pytest.mark.parametrize("r,S,Q", [(3, 32, 8), (2, 32, 1), (3, 30, 2)])
+def test_sift_search_full_range_of_codes(r, S, Q):
+    """Colours at the ends of int16 (a caller's own codes): sums of squares up
+    to 2^45, where the float root is off by more than one."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("sift code range", r, S, Q, flush=True)
+    W, H, kw = 40, 33, dict(k=1)
+    rng = np.random.default_rng(r * S + Q)
+    codes = [(rng.choice([-1, 1], (H, W, S)) * rng.integers(32000, 32768, (H, W, S))).astype(np.int16) for _ in range(2)]
+    img1, img2, got = _sift_jobs(W, H, r, S, Q, kw, codes, 1)
+    od = [ffo.Desc(img, 1, Q, (r,)) for img in (img1, img2)]
+    ol = [ffo.SiftLevels(c, 1) for c in codes]
+    oF, oC = ffo.match_field_sift(od[0], od[1], ol[0], ol[1], r, S, seed=77, field_id=2, pair_id=0, **kw)
+    assert np.array_equal(got[0][0], oF) and np.array_equal(got[0][1], oC)
