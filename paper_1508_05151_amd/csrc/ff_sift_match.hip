@@ -543,9 +543,17 @@ struct SiftSweepArgs {
   int inbuf;   // grid buffer read; the other one is written
 };
 
+// Workgroups of a sweep, at most: those that the chip holds at once (three per
+// CU by registers, two with the widest pixels).  More only start when others
+// leave, with tiles whose neighbours have long been solved: 1242x375, all
+// sweeps of a pair with 256 / 512 / 768 / 1,024 / 2,048 of them: the pair takes
+// 13.9 / 11.9 / 11.7 / 12.1 / 12.9 ms.
+template <int SG>
+constexpr int kSiftSweepGrid = SG <= 5 ? 768 : 512;
+
 // SG: groups of four colours of the widest field of the call
 template <int SG>
-__global__ __launch_bounds__(256) void k_sift_sweep(const SiftRec* __restrict__ table, SiftSweepArgs a, RelaxQ q) {
+__global__ __launch_bounds__(256, SG <= 5 ? 3 : 2) void k_sift_sweep(const SiftRec* __restrict__ table, SiftSweepArgs a, RelaxQ q) {
   __shared__ STile s;
   __shared__ int s_next, s_first;
   const int tid = threadIdx.x, lev = a.lev, n = 1 << lev, sx = a.sx, sy = a.sy;
@@ -935,7 +943,7 @@ static ff_status run_sift_batch(const ff_sift_job* jobs, int n, const ff_match_p
       q.ring = reinterpret_cast<int32_t*>(ws + B.off_ring);
       q.cap = B.cap;
       q.T = recs[n - 1].t0[lev] + tiles_of(recs[n - 1], lev);
-      q.G = std::min(q.T, kSweepGrid);
+      q.G = std::min(q.T, kSiftSweepGrid<SG>);
       q.status = status;
       q.timeout = timeout;
       prof_mark(FF_PROF_SIFT_PROPAGATE, stream, true);
