@@ -11,17 +11,25 @@
 // master weights and Adam state are fp32.
 //
 // All three convolutions are implicit GEMMs on 16x16x32 MFMA tiles:
-//   forward        M = output pixels, N = Cout, K = 9 taps x Cin
-//   backward-data  M = input pixels,  N = Cin,  K = 9 taps x Cout
+//   forward        M = Cout, N = output pixels, K = 9 taps x Cin
+//   backward-data  M = Cin,  N = input pixels,  K = 9 taps x Cout (stride 2:
+//                  per parity of the pixel, the taps that reach it)
 //   backward-weight per tap: M = Cout, N = Cin, K = pixels, split over fixed
-//                  pixel chunks and reduced in a fixed order (deterministic)
+//                  runs of rows and reduced in a fixed order (deterministic)
 // Tensors are NHWC; Cin is padded to 8 (input) or 32 channels so that one
 // lane's 8 consecutive K values are 8 contiguous channels of one tap (one
 // 16-byte load).  Lane l of a 16x16x32 MFMA holds A[m = l % 16][k = 8 (l / 16)
 // .. + 7], B[k = 8 (l / 16) .. + 7][n = l % 16] and D[m = 4 (l / 16) + i][n =
-// l % 16], i = 0..3.  The forward and backward-data kernels stage the layer's
-// packed weight fragments (at most 18 KB) in LDS once per workgroup; every
-// wavefront then runs several 16-pixel tiles against them.
+// l % 16], i = 0..3.  A wavefront of the forward and backward-data kernels
+// keeps the layer's packed weight fragments in registers and runs 16-pixel
+// tiles against them; channels are dealt to the fragments' rows so that a lane
+// ends with eight neighbouring ones (one 16-byte store).
+//
+// A layer's launch is short (0.1 to 1.8 M pixels for 16 pairs of 1024x436), so
+// what a step does besides its contractions counts as much: weights and input
+// are packed in one launch, and one launch reduces every layer's weight
+// gradient and applies Adam.  16 x 1024x436: training step 1.78 -> 0.64 ms, forward
+// of two pairs 163 -> 41 us.
 #include <math.h>
 
 #include "ff_internal.h"
@@ -32,10 +40,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kNetLayers = 6;
-constexpr int kWChunks = 512;   // most backward-weight partials per layer
 constexpr int kKStep = 32;      // K per MFMA
-constexpr int kMaxKChunks = 9;  // 9 taps x 32 channels / 32
-constexpr int kTilesPerWave = 4;   // 16-pixel tiles per wavefront (forward, backward-data)
 
 struct NetLayer {
   int cin, cout, stride, dil, relu;
@@ -62,330 +67,563 @@ static int chunks_of(int cinp) { return (9 * cinp + kKStep - 1) / kKStep; }
 static int tiles_of(int c) { return (c + 15) / 16; }
 
 // ---------------------------------------------------------------- packing
-// forward B fragments, one 16-byte fragment per (chunk, tile, lane):
-// Wb[c][nt][g][n][i] = W[co = 16 nt + n][ci][tap] for K index
-// k = 32 c + 8 g + i = tap * cinp + ci (zero where out of range)
-__global__ void k_pack_fwd(const float* __restrict__ theta, int off, int cin, int cout, int cinp, int nchunks,
-                           int ntiles, uint16_t* __restrict__ wb) {
-  const int total = nchunks * ntiles * 64 * 8;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
-    const int i = e & 7, n = (e >> 3) & 15, g = (e >> 7) & 3, rest = e >> 9;
-    const int nt = rest % ntiles, c = rest / ntiles;
-    const int k = kKStep * c + 8 * g + i;
-    const int tap = k / cinp, ci = k % cinp, co = 16 * nt + n;
-    float w = 0.f;
-    if (tap < 9 && ci < cin && co < cout) w = theta[off + (co * cin + ci) * 9 + tap];
-    wb[e] = f2bf(w);
-  }
-}
+// What a step reads in another form than its caller has it, in one launch: the
+// images, the layers' weight fragments and, for training, the number of
+// labelled points (per block, summed by the loss kernel).
+//
+// Weight fragments, 16 bytes per (chunk, tile, lane): W[chunk c][tile t][g][row
+// r][i] for K index k = 32 c + 8 g + i = tap * cpad + channel (zero where out
+// of range); row r of tile t is channel 8 (r / 4) + 4 t + r % 4 of two tiles,
+// channel r of one.
+struct PackLayer {
+  int off, cin, cout;   // parameters
+  int cpad, tiles;      // padded K channels, row tiles
+  int bwd;              // rows are input channels, K runs over output channels
+  int end;              // elements up to and including this layer's
+  uint16_t* out;
+};
+struct PackArgs {
+  PackLayer l[2 * kNetLayers];
+  int n, blocks_in, blocks_w;   // layers; blocks of each role, the rest count labels
+  const uint8_t *i1, *i2;
+  size_t npx;
+  uint16_t* x;
+  const float* theta;
+  const int32_t* labels;
+  size_t nlabels;
+  int32_t* counts;
+};
+constexpr int kCountBlocks = 64;
 
-// backward-data B fragments: K index k = tap * coutp + co, N = ci
-__global__ void k_pack_bwd(const float* __restrict__ theta, int off, int cin, int cout, int coutp, int nchunks,
-                           int ntiles, uint16_t* __restrict__ wb) {
-  const int total = nchunks * ntiles * 64 * 8;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
-    const int i = e & 7, n = (e >> 3) & 15, g = (e >> 7) & 3, rest = e >> 9;
-    const int nt = rest % ntiles, c = rest / ntiles;
-    const int k = kKStep * c + 8 * g + i;
-    const int tap = k / coutp, co = k % coutp, ci = 16 * nt + n;
-    float w = 0.f;
-    if (tap < 9 && co < cout && ci < cin) w = theta[off + (co * cin + ci) * 9 + tap];
-    wb[e] = f2bf(w);
-  }
-}
-
-// u8 RGB pair (B x H x W x 3 each) -> bf16 NHWC with 8 channels:
-// RGB1/255 - 1/2, RGB2/255 - 1/2, 0, 0
-__global__ void k_pack_input(const uint8_t* __restrict__ i1, const uint8_t* __restrict__ i2, size_t npx,
-                             uint16_t* __restrict__ x) {
-  for (size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x; p < npx; p += (size_t)gridDim.x * blockDim.x) {
-    uint16_t v[8];
+__global__ __launch_bounds__(256) void k_pack(PackArgs a) {
+  __shared__ uint32_t s_tab[256];
+  const int blk = blockIdx.x;
+  if (blk < a.blocks_in) {
+    // u8 RGB pair (B x H x W x 3 each) -> bf16 NHWC with 8 channels:
+    // RGB1/255 - 1/2, RGB2/255 - 1/2, 0, 0
+    s_tab[threadIdx.x] = f2bf((float)threadIdx.x / 255.0f - 0.5f);
+    __syncthreads();
+    auto put = [&](size_t p, const uint32_t (&c)[6]) {
+      uint4 o;
+      o.x = s_tab[c[0]] | (s_tab[c[1]] << 16);
+      o.y = s_tab[c[2]] | (s_tab[c[3]] << 16);
+      o.z = s_tab[c[4]] | (s_tab[c[5]] << 16);
+      o.w = 0;
+      reinterpret_cast<uint4*>(a.x)[p] = o;
+    };
+    // four pixels, three words of each image, at a time where those are aligned
+    const bool words = (((uintptr_t)a.i1 | (uintptr_t)a.i2) & 3) == 0;
+    const size_t quads = words ? a.npx / 4 : 0;
+    const size_t tid = (size_t)blk * 256 + threadIdx.x, step = (size_t)a.blocks_in * 256;
+    for (size_t q = tid; q < quads; q += step) {
+      uint32_t w1[3], w2[3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      v[c] = f2bf((float)i1[p * 3 + c] / 255.0f - 0.5f);
-      v[3 + c] = f2bf((float)i2[p * 3 + c] / 255.0f - 0.5f);
+      for (int k = 0; k < 3; ++k) {
+        w1[k] = reinterpret_cast<const uint32_t*>(a.i1)[q * 3 + k];
+        w2[k] = reinterpret_cast<const uint32_t*>(a.i2)[q * 3 + k];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        uint32_t c[6];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          const int e = 3 * k + j;
+          c[j] = (w1[e >> 2] >> (8 * (e & 3))) & 0xFF;
+          c[3 + j] = (w2[e >> 2] >> (8 * (e & 3))) & 0xFF;
+        }
+        put(q * 4 + k, c);
+      }
     }
-    v[6] = v[7] = 0;
-    uint4 o;
-    o.x = v[0] | ((uint32_t)v[1] << 16);
-    o.y = v[2] | ((uint32_t)v[3] << 16);
-    o.z = v[4] | ((uint32_t)v[5] << 16);
-    o.w = v[6] | ((uint32_t)v[7] << 16);
-    reinterpret_cast<uint4*>(x)[p] = o;
+    for (size_t p = quads * 4 + tid; p < a.npx; p += step) {
+      const uint32_t c[6] = {a.i1[p * 3], a.i1[p * 3 + 1], a.i1[p * 3 + 2], a.i2[p * 3], a.i2[p * 3 + 1], a.i2[p * 3 + 2]};
+      put(p, c);
+    }
+  } else if (blk < a.blocks_in + a.blocks_w) {
+    const int at = (blk - a.blocks_in) * 256 + threadIdx.x;
+    int li = 0;
+    while (li < a.n && at >= a.l[li].end) ++li;
+    if (li == a.n) return;
+    const PackLayer& L = a.l[li];
+    const int e = at - (li ? a.l[li - 1].end : 0);
+    const int i = e & 7, r = (e >> 3) & 15, g = (e >> 7) & 3, rest = e >> 9;
+    const int t = rest % L.tiles, c = rest / L.tiles;
+    const int k = kKStep * c + 8 * g + i, tap = k / L.cpad, kc = k % L.cpad;
+    const int rc = L.tiles == 2 ? 8 * (r >> 2) + 4 * t + (r & 3) : r;
+    const int ci = L.bwd ? rc : kc, co = L.bwd ? kc : rc;
+    float w = 0.f;
+    if (tap < 9 && ci < L.cin && co < L.cout) w = a.theta[L.off + (co * L.cin + ci) * 9 + tap];
+    L.out[e] = f2bf(w);
+  } else {
+    const int b = blk - a.blocks_in - a.blocks_w;
+    int c = 0;
+    for (size_t i = (size_t)b * 256 + threadIdx.x; i < a.nlabels; i += (size_t)kCountBlocks * 256) c += a.labels[i] != kEmpty;
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+    if ((threadIdx.x & 63) == 0) s_tab[threadIdx.x >> 6] = (uint32_t)c;
+    __syncthreads();
+    if (threadIdx.x == 0) a.counts[b] = (int32_t)(s_tab[0] + s_tab[1] + s_tab[2] + s_tab[3]);
   }
 }
 
-// eight bf16 (16 bytes, 16-byte aligned) as an MFMA operand
-__device__ __forceinline__ bf16x8 ld_bf16x8(const uint16_t* p) {
-  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p));
-}
 __device__ __forceinline__ bf16x8 bf16x8_of(uint4 u) { return __builtin_bit_cast(bf16x8, u); }
 __device__ __forceinline__ f32x4 mfma32(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
+// eight floats as bf16, in order
+__device__ __forceinline__ uint4 pack8(const float (&v)[8]) {
+  uint32_t w[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) w[k] = f2bf(v[2 * k]) | ((uint32_t)f2bf(v[2 * k + 1]) << 16);
+  return make_uint4(w[0], w[1], w[2], w[3]);
+}
+// v * 1 where the bf16 activation is above zero, v * 0 elsewhere
+__device__ __forceinline__ void mask8(float (&v)[8], uint4 act) {
+  const uint32_t w[4] = {act.x, act.y, act.z, act.w};
+#pragma unroll
+  for (int k = 0; k < 8; ++k) v[k] *= bf2f((uint16_t)(w[k >> 1] >> (16 * (k & 1)))) > 0.f ? 1.f : 0.f;
+}
+// flow in px / 32 to packed 1/Q px (nearest even), clamped to int16
+__device__ __forceinline__ int32_t to_proposal(float x, float y, float q) {
+  const float fx = fminf(fmaxf(rintf(x * 32.f * q), -32767.f), 32767.f);
+  const float fy = fminf(fmaxf(rintf(y * 32.f * q), -32767.f), 32767.f);
+  return packf((int)fx, (int)fy);
+}
 
-// ---------------------------------------------------------------- forward
-// One wavefront = kTilesPerWave tiles of 16 output pixels x NT*16 output
-// channels, against the layer's weight fragments staged in LDS.  Epilogue
-// adds the bias, applies ReLU and stores bf16 (or fp32 for the last layer).
-template <int NT>
-__global__ __launch_bounds__(256) void k_conv_fwd(const uint16_t* __restrict__ x, int Bn, int H, int W, int cinp,
-                                                  int Ho, int Wo, int stride, int dil, int nchunks,
-                                                  const uint4* __restrict__ wb, const float* __restrict__ bias,
-                                                  int cout, int coutp, int relu, uint16_t* __restrict__ y,
-                                                  float* __restrict__ yf) {
-  __shared__ uint4 sW[kMaxKChunks * NT * 64];
-  for (int e = threadIdx.x; e < nchunks * NT * 64; e += blockDim.x) sW[e] = wb[e];
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const size_t npx = (size_t)Bn * Ho * Wo;
+// ---------------------------------------------------------------- forward, backward-data at stride 1
+// y[p] = sum over taps of W[tap] x[p * stride + (tap - centre) * dil], one
+// wavefront per run of 16-pixel tiles of output rows (p = 16 pixels of a row),
+// the next tile's loads in flight while one is multiplied.  Backward-data at
+// stride 1 is the same sum with -dil, and the producing layer's ReLU: stored
+// gradient = sum * (activation > 0).
+// Bound: at 0.4 M pixels and more the bytes, below them one round trip and the
+// launch.  A 14,080-pixel layer took 25 us with its weights staged through LDS
+// and four tiles of nine loads one after another; now 4 us.
+struct ConvArgs {
+  const uint16_t* x;
+  const uint4* wb;
+  const float* bias;       // forward
+  const uint16_t* aprev;   // backward: the activation at y's pixels
+  uint16_t* y;
+  float *yf, *flow;        // last layer: output as fp32, and a caller's copy
+  int32_t* prop;           // and its rounding
+  float q;
+  int rows, H, W, Ho, Wo, stride, dil, relu, cout;   // rows = batch * Ho
+};
+template <int CINP, int NT, bool BWD>
+__global__ __launch_bounds__(256) void k_conv(ConvArgs a) {
+  constexpr int NC = (9 * CINP + kKStep - 1) / kKStep;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = lane & 15, g = lane >> 4;
-  for (int ti = 0; ti < kTilesPerWave; ++ti) {
-    const size_t base = (((size_t)blockIdx.x * 4 + wave) * kTilesPerWave + ti) * 16;
-    if (base >= npx) break;
-    const size_t p = base + m;
-    const bool pv = p < npx;
-    const int ox = pv ? (int)(p % Wo) : 0;
-    const int oy = pv ? (int)((p / Wo) % Ho) : 0;
-    const int b = pv ? (int)(p / ((size_t)Wo * Ho)) : 0;
+  const int nxt = (a.Wo + 15) >> 4, ntile = a.rows * nxt, step = gridDim.x * 4;
+  int tile = blockIdx.x * 4 + wave;
+  if (tile >= ntile) return;
+  uint4 wf[NC][NT];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) wf[c][t] = a.wb[(c * NT + t) * 64 + lane];
+  float bias[4 * NT];
+#pragma unroll
+  for (int k = 0; k < 4 * NT; ++k) {
+    const int co = NT == 2 ? 8 * g + k : 4 * g + k;
+    bias[k] = !BWD && co < a.cout ? a.bias[co] : 0.f;
+  }
+  struct Tile {
+    uint4 v[NC], act;
+    uint32_t ok;   // taps inside the image
+    int row, ox;
+  };
+  auto load = [&](int t) {
+    Tile T;
+    T.row = t / nxt;
+    T.ox = (t - T.row * nxt) * 16 + m;
+    const int b = T.row / a.Ho, oy = T.row - b * a.Ho;
+    const uint16_t* img = a.x + (size_t)b * a.H * a.W * CINP;
+    T.ok = 0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int tap = CINP == 32 ? c : 4 * c + g;
+      const int iy = oy * a.stride + (tap / 3 - 1) * a.dil, ix = T.ox * a.stride + (tap % 3 - 1) * a.dil;
+      const bool ok = tap < 9 && (uint32_t)iy < (uint32_t)a.H && (uint32_t)ix < (uint32_t)a.W;
+      T.ok |= ok ? 1u << c : 0u;
+      const int cy = clampi(iy, 0, a.H - 1), cx = clampi(ix, 0, a.W - 1);
+      const uint16_t* at = CINP == 32 ? img + (size_t)cy * a.W * CINP + (uint32_t)(cx * CINP + 8 * g)
+                                      : img + (size_t)((uint32_t)cy * (uint32_t)a.W + (uint32_t)cx) * CINP;
+      T.v[c] = *reinterpret_cast<const uint4*>(at);
+    }
+    if (BWD) T.act = *reinterpret_cast<const uint4*>(a.aprev + ((size_t)T.row * a.Wo + min(T.ox, a.Wo - 1)) * 32 + 8 * g);
+    return T;
+  };
+  Tile T = load(tile);
+  for (;;) {
+    const int next = tile + step;
+    Tile N;
+    if (next < ntile) N = load(next);
     f32x4 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c < nchunks; ++c) {
-      const int k0 = kKStep * c + 8 * g;
-      const int tap = k0 / cinp, ci0 = k0 % cinp;
-      uint4 av = make_uint4(0, 0, 0, 0);
-      if (pv && tap < 9) {
-        const int iy = oy * stride - dil + (tap / 3) * dil, ix = ox * stride - dil + (tap % 3) * dil;
-        if (iy >= 0 && iy < H && ix >= 0 && ix < W)
-          av = *reinterpret_cast<const uint4*>(x + (((size_t)b * H + iy) * W + ix) * cinp + ci0);
-      }
-      const bf16x8 a = bf16x8_of(av);
 #pragma unroll
-      for (int t = 0; t < NT; ++t) acc[t] = mfma32(a, bf16x8_of(sW[(c * NT + t) * 64 + lane]), acc[t]);
+    for (int c = 0; c < NC; ++c) {
+      uint4 v = T.v[c];
+      if (!((T.ok >> c) & 1)) v = make_uint4(0, 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[t] = mfma32(bf16x8_of(wf[c][t]), bf16x8_of(v), acc[t]);
     }
-    // D[row = 4 g + i][col = m]: pixel base + 4 g + i, channel 16 t + m
+    if (T.ox < a.Wo) {
+      const size_t p = (size_t)T.row * a.Wo + T.ox;
+      if constexpr (NT == 2) {
+        // channels 8 g + 4 t + i
+        float v[8];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int co = 16 * t + m;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const size_t q = base + 4 * g + i;
-        if (q >= npx || co >= coutp) continue;
-        float v = co < cout ? acc[t][i] + bias[co] : 0.f;
-        if (relu) v = fmaxf(v, 0.f);
-        if (yf) {
-          if (co < cout) yf[q * cout + co] = v;
-        } else {
-          y[q * coutp + co] = f2bf(v);
+        for (int k = 0; k < 8; ++k) {
+          v[k] = acc[k >> 2][k & 3];
+          if (!BWD) v[k] += bias[k];
+          if (!BWD && a.relu) v[k] = fmaxf(v[k], 0.f);
         }
+        if (BWD) mask8(v, T.act);
+        *reinterpret_cast<uint4*>(a.y + p * 32 + 8 * g) = pack8(v);
+      } else if (g == 0) {
+        // the last layer's two channels
+        float v[2] = {acc[0][0] + bias[0], acc[0][1] + bias[1]};
+        if (a.relu) v[0] = fmaxf(v[0], 0.f), v[1] = fmaxf(v[1], 0.f);
+        a.yf[p * 2] = v[0];
+        a.yf[p * 2 + 1] = v[1];
+        if (a.flow) {
+          a.flow[p * 2] = v[0];
+          a.flow[p * 2 + 1] = v[1];
+        }
+        if (a.prop) a.prop[p] = to_proposal(v[0], v[1], a.q);
       }
     }
+    if (next >= ntile) break;
+    T = N;
+    tile = next;
   }
 }
 
-// ---------------------------------------------------------------- backward-data
-// dX[q][ci] = sum over taps and co of G[p(q, tap)][co] W[co][ci][tap], with
-// p = ((y + dil - ky dil) / s, (x + dil - kx dil) / s) where divisible and
-// inside; then the ReLU of the producing layer: stored gradient =
-// dX * (Aprev > 0), bf16.  Tiles and LDS staging as in the forward kernel.
-template <int NT>
-__global__ __launch_bounds__(256) void k_conv_bwd_data(const uint16_t* __restrict__ G, int Bn, int Ho, int Wo, int coutp,
-                                                       int H, int W, int stride, int dil, int nchunks,
-                                                       const uint4* __restrict__ wbt, int cinp,
-                                                       const uint16_t* __restrict__ aprev, uint16_t* __restrict__ gprev) {
-  __shared__ uint4 sW[kMaxKChunks * NT * 64];
-  for (int e = threadIdx.x; e < nchunks * NT * 64; e += blockDim.x) sW[e] = wbt[e];
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const size_t npx = (size_t)Bn * H * W;
+// ---------------------------------------------------------------- backward-data at stride 2
+// dX of the 2x2 input pixels around G's pixel (cy, cx), dilation 1: pixel
+// (2 cy + dy, 2 cx + dx) is reached by tap row 1 of G row cy where dy = 0, by
+// tap rows 0 of cy + 1 and 2 of cy where dy = 1, columns likewise: nine taps
+// for four pixels, where a sum over all nine for each multiplies three zeros
+// in four.  Then the producing layer's ReLU.  Bound: bytes.
+// 16 x 1024x436, 32 channels into 1.8 M pixels: 194 -> 55 us.
+__global__ __launch_bounds__(256) void k_conv_bwd2(const uint16_t* __restrict__ G, int rows, int Ho, int Wo, int H, int W,
+                                                   const uint4* __restrict__ wbt, const uint16_t* __restrict__ aprev,
+                                                   uint16_t* __restrict__ gprev) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = lane & 15, g = lane >> 4;
-  for (int ti = 0; ti < kTilesPerWave; ++ti) {
-    const size_t base = (((size_t)blockIdx.x * 4 + wave) * kTilesPerWave + ti) * 16;
-    if (base >= npx) break;
-    const size_t q = base + m;
-    const bool qv = q < npx;
-    const int x = qv ? (int)(q % W) : 0;
-    const int y = qv ? (int)((q / W) % H) : 0;
-    const int b = qv ? (int)(q / ((size_t)W * H)) : 0;
-    f32x4 acc[NT];
+  const int nxt = (Wo + 15) >> 4, ntile = rows * nxt, step = gridDim.x * 4;
+  int tile = blockIdx.x * 4 + wave;
+  if (tile >= ntile) return;
+  uint4 wf[9][2];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c < nchunks; ++c) {
-      const int k0 = kKStep * c + 8 * g;
-      const int tap = k0 / coutp, co0 = k0 % coutp;
-      uint4 av = make_uint4(0, 0, 0, 0);
-      if (qv && tap < 9) {
-        const int ty = y + dil - (tap / 3) * dil, tx = x + dil - (tap % 3) * dil;
-        if (ty >= 0 && tx >= 0 && ty % stride == 0 && tx % stride == 0) {
-          const int oy = ty / stride, ox = tx / stride;
-          if (oy < Ho && ox < Wo) av = *reinterpret_cast<const uint4*>(G + (((size_t)b * Ho + oy) * Wo + ox) * coutp + co0);
+  for (int c = 0; c < 9; ++c)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) wf[c][t] = wbt[(c * 2 + t) * 64 + lane];
+  struct Tile {
+    uint4 v[4], act[4];   // G at (cy + k / 2, cx + k % 2); activations at (2 cy + k / 2, 2 cx + k % 2)
+    int b, cy, cx;
+  };
+  auto load = [&](int t) {
+    Tile T;
+    const int row = t / nxt;
+    T.cx = (t - row * nxt) * 16 + m;
+    T.b = row / Ho;
+    T.cy = row - T.b * Ho;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int y = min(T.cy + (k >> 1), Ho - 1), x = min(T.cx + (k & 1), Wo - 1);
+      T.v[k] = *reinterpret_cast<const uint4*>(G + ((size_t)(T.b * Ho + y) * Wo + x) * 32 + 8 * g);
+      const int py = min(2 * T.cy + (k >> 1), H - 1), px = min(2 * T.cx + (k & 1), W - 1);
+      T.act[k] = *reinterpret_cast<const uint4*>(aprev + ((size_t)(T.b * H + py) * W + px) * 32 + 8 * g);
+    }
+    return T;
+  };
+  Tile T = load(tile);
+  for (;;) {
+    const int next = tile + step;
+    Tile N;
+    if (next < ntile) N = load(next);
+    const uint4 zero = make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (((k & 1) && T.cx + 1 >= Wo) || ((k & 2) && T.cy + 1 >= Ho)) T.v[k] = zero;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int dy = k >> 1, dx = k & 1;
+      f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+      for (int ty = dy ? 0 : 1; ty < 3; ty += dy ? 2 : 3)
+#pragma unroll
+        for (int tx = dx ? 0 : 1; tx < 3; tx += dx ? 2 : 3) {
+          const int src = (dy && ty == 0 ? 2 : 0) + (dx && tx == 0 ? 1 : 0), tap = 3 * ty + tx;
+#pragma unroll
+          for (int t = 0; t < 2; ++t) acc[t] = mfma32(bf16x8_of(wf[tap][t]), bf16x8_of(T.v[src]), acc[t]);
         }
-      }
-      const bf16x8 a = bf16x8_of(av);
+      const int py = 2 * T.cy + dy, px = 2 * T.cx + dx;
+      if (py < H && px < W) {
+        float v[8];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) acc[t] = mfma32(a, bf16x8_of(sW[(c * NT + t) * 64 + lane]), acc[t]);
-    }
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int ci = 16 * t + m;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const size_t r = base + 4 * g + i;
-        if (r >= npx || ci >= cinp) continue;
-        const float mask = bf2f(aprev[r * cinp + ci]) > 0.f ? 1.f : 0.f;
-        gprev[r * cinp + ci] = f2bf(acc[t][i] * mask);
+        for (int e = 0; e < 8; ++e) v[e] = acc[e >> 2][e & 3];
+        mask8(v, T.act[k]);
+        *reinterpret_cast<uint4*>(gprev + ((size_t)(T.b * H + py) * W + px) * 32 + 8 * g) = pack8(v);
       }
     }
+    if (next >= ntile) break;
+    T = N;
+    tile = next;
   }
 }
 
 // ---------------------------------------------------------------- backward-weight
-// Block = one fixed chunk of `chunk` output pixels (a multiple of 64, chosen
-// per layer so that a launch has up to kWChunks blocks); for every tap:
-// part[chunk][tap][co][ci] = sum_p G[p][co] X[p_in(p, tap)][ci] on MFMA
-// (A = G^T from LDS, B = X_tap from LDS, K = pixels, 8 per lane), bias
-// partial sum_p G[p][co].  Wave w handles taps w, w + 4, w + 8.  Staging
-// reads 8 channels (16 bytes) per load and transposes them into
-// channel-major LDS rows (pitch 72: rows start 16-byte aligned).
-constexpr int kWPitch = 64 + 8;
-__global__ __launch_bounds__(256) void k_conv_bwd_w(const uint16_t* __restrict__ G, int Bn, int Ho, int Wo, int coutp,
-                                                    const uint16_t* __restrict__ X, int H, int W, int cinp, int stride,
-                                                    int dil, int chunk, float* __restrict__ part,
-                                                    float* __restrict__ partb) {
-  __shared__ __align__(16) uint16_t sG[32][kWPitch];      // [co][pixel]
-  __shared__ __align__(16) uint16_t sX[9][32][kWPitch];   // [tap][ci][pixel]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// dW[tap][co][ci] = sum_p G[p][co] X[p_in(p, tap)][ci] with K = pixels, bias
+// gradient sum_p G[p][co].  A workgroup takes a run of 32-pixel pieces of
+// output rows, its wavefronts in turn, and every tap of them.  A lane's operand
+// is eight pixels of one channel: it loads channels 2m, 2m + 1 of its eight
+// pixels (16 lanes read a pixel's 64 bytes), and the low and the high halves
+// make the fragments of the even and of the odd channels -- the transposition
+// costs four byte permutes per fragment and no LDS.  Eight-channel tensors
+// fill the 16 columns with four taps at a time.  Sums stay in registers over
+// the run; the four wavefronts' are added in order at its end.
+// Bound: loads in flight (144 registers of sums leave two wavefronts per SIMD).
+// 16 x 1024x436, second layer 107 -> 61 us, the first 205 -> 211, against staging
+// 64 pixels of all taps through LDS with 2-byte writes.
+// Partials: [run][fragment (slot, mt, nt)][lane][4], slot = tap, or four taps.
+template <int CINP, int GCH>
+struct WGrad {
+  static constexpr int slots = CINP == 32 ? 9 : 3, mts = GCH == 32 ? 2 : 1;
+  static constexpr int frags = slots * mts * 2;
+};
+template <int CINP, int GCH, int STRIDE>
+__global__ __launch_bounds__(256, 2) void k_conv_bwd_w(const uint16_t* __restrict__ G, const uint16_t* __restrict__ X,
+                                                       int rows, int Ho, int Wo, int H, int W, int dil,
+                                                       float4* __restrict__ part, float* __restrict__ partb) {
+  using S = WGrad<CINP, GCH>;
+  __shared__ f32x4 s_red[S::frags * 64];
+  __shared__ float s_b[4][32];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = lane & 15, g = lane >> 4;
-  const size_t npx = (size_t)Bn * Ho * Wo;
-  const size_t c0 = (size_t)blockIdx.x * chunk;
-  const int MT = (coutp + 15) / 16, NTt = (cinp + 15) / 16;
-  f32x4 acc[3][2][2];
+  const int nxb = (Wo + 31) >> 5;
+  const int64_t units = (int64_t)rows * nxb;
+  const int u0 = (int)(units * blockIdx.x / gridDim.x), u1 = (int)(units * (blockIdx.x + 1) / gridDim.x);
+  f32x4 acc[S::slots][S::mts][2];
 #pragma unroll
-  for (int a = 0; a < 3; ++a)
+  for (int s = 0; s < S::slots; ++s)
 #pragma unroll
-    for (int b2 = 0; b2 < 2; ++b2)
+    for (int mt = 0; mt < S::mts; ++mt)
 #pragma unroll
-      for (int c2 = 0; c2 < 2; ++c2) acc[a][b2][c2] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float bsum = 0.f;   // thread t < coutp: bias partial of channel t
-  __shared__ int sPix[64][3];   // b, oy, ox of the 64 staged output pixels
-  // channel rows beyond the padded channel counts stay zero
-  for (int e = threadIdx.x; e < 32 * kWPitch; e += 256) (&sG[0][0])[e] = 0;
-  for (int e = threadIdx.x; e < 9 * 32 * kWPitch; e += 256) (&sX[0][0][0])[e] = 0;
-  const int gq = coutp / 8, xq = cinp / 8;   // 16-byte quads per pixel
-  for (size_t s0 = c0; s0 < c0 + chunk && s0 < npx; s0 += 64) {
-    if (threadIdx.x < 64) {
-      const size_t p = s0 + threadIdx.x;
-      sPix[threadIdx.x][0] = p < npx ? (int)(p / ((size_t)Wo * Ho)) : -1;
-      sPix[threadIdx.x][1] = (int)((p / Wo) % Ho);
-      sPix[threadIdx.x][2] = (int)(p % Wo);
+      for (int nt = 0; nt < 2; ++nt) acc[s][mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float bs[2] = {0.f, 0.f};
+  // the low (the high) halves of eight words, in order
+  auto halves = [](const uint32_t (&w)[8], uint32_t sel) {
+    return bf16x8_of(make_uint4(__builtin_amdgcn_perm(w[1], w[0], sel), __builtin_amdgcn_perm(w[3], w[2], sel),
+                                __builtin_amdgcn_perm(w[5], w[4], sel), __builtin_amdgcn_perm(w[7], w[6], sel)));
+  };
+  constexpr uint32_t kLow = 0x05040100u, kHigh = 0x07060302u;
+  for (int u = u0 + wave; u < u1; u += 4) {
+    const int row = u / nxb, xb = u - row * nxb, b = row / Ho, oy = row - b * Ho;
+    const int ox0 = 32 * xb + 8 * g;
+    const bool whole = 32 * xb + 32 <= Wo;
+    // G: channels 2m, 2m + 1 of pixels ox0 .. ox0 + 7 (eight-channel G: 0 and 1)
+    const uint16_t* gr = G + (size_t)row * Wo * GCH + (GCH == 32 ? 2 * m : 0);
+    uint32_t gd[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      gd[j] = *reinterpret_cast<const uint32_t*>(gr + (uint32_t)(min(ox0 + j, Wo - 1) * GCH));
+      if (!whole && ox0 + j >= Wo) gd[j] = 0;
+      if (GCH == 8 && m > 1) gd[j] = 0;
     }
-    for (int e = threadIdx.x; e < 64 * gq; e += 256) {
-      const int q = e % gq, px = e / gq;
-      const size_t p = s0 + px;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (p < npx) v = reinterpret_cast<const uint4*>(G + p * coutp)[q];
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int i = 0; i < 8; ++i) sG[8 * q + i][px] = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
+    bf16x8 A[S::mts];
+    if constexpr (GCH == 32) {
+      A[0] = halves(gd, kLow);
+      A[1] = halves(gd, kHigh);
+    } else {
+      A[0] = halves(gd, m == 0 ? kLow : kHigh);
     }
-    __syncthreads();
-    for (int e = threadIdx.x; e < 9 * 64 * xq; e += 256) {
-      const int q = e % xq, px = (e / xq) & 63, tap = e / (64 * xq);
-      const int b = sPix[px][0];
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (b >= 0) {
-        const int iy = sPix[px][1] * stride - dil + (tap / 3) * dil, ix = sPix[px][2] * stride - dil + (tap % 3) * dil;
-        if (iy >= 0 && iy < H && ix >= 0 && ix < W)
-          v = reinterpret_cast<const uint4*>(X + (((size_t)b * H + iy) * W + ix) * cinp)[q];
-      }
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-      for (int i = 0; i < 8; ++i) sX[tap][8 * q + i][px] = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
+    for (int j = 0; j < 8; ++j) {
+      bs[0] += bf2f((uint16_t)gd[j]);
+      bs[1] += bf2f((uint16_t)(gd[j] >> 16));
     }
-    __syncthreads();
-    if ((int)threadIdx.x < coutp)
-      for (int px = 0; px < 64; ++px) bsum += bf2f(sG[threadIdx.x][px]);
+    const uint16_t* img = X + (size_t)b * H * W * CINP;
+    const bool inside = whole && 32 * xb * STRIDE >= dil && (32 * xb + 31) * STRIDE + dil < W;
+    if constexpr (CINP == 32) {
 #pragma unroll
-    for (int ks = 0; ks < 64 / kKStep; ++ks) {
-      const int pk = kKStep * ks + 8 * g;   // this lane's 8 pixels
+      for (int ky = 0; ky < 3; ++ky) {
+        const int iy = oy * STRIDE + (ky - 1) * dil;
+        if ((uint32_t)iy >= (uint32_t)H) continue;
+        const uint16_t* xr = img + (size_t)iy * W * 32 + 2 * m;
+        uint32_t xd[3][8];
 #pragma unroll
-      for (int ti = 0; ti < 3; ++ti) {
-        const int tap = wave + 4 * ti;
-        if (tap >= 9) continue;
+        for (int kx = 0; kx < 3; ++kx) {
+          const int ix0 = ox0 * STRIDE + (kx - 1) * dil;
+          if (inside) {
+            const uint16_t* xp = xr + (uint32_t)(ix0 * 32);
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-          if (mt >= MT) continue;
-          const bf16x8 a = ld_bf16x8(&sG[16 * mt + m][pk]);
+            for (int j = 0; j < 8; ++j) xd[kx][j] = *reinterpret_cast<const uint32_t*>(xp + j * STRIDE * 32);
+          } else {
 #pragma unroll
-          for (int nt = 0; nt < 2; ++nt) {
-            if (nt >= NTt) continue;
-            acc[ti][mt][nt] = mfma32(a, ld_bf16x8(&sX[tap][16 * nt + m][pk]), acc[ti][mt][nt]);
+            for (int j = 0; j < 8; ++j) {
+              const int ix = ix0 + j * STRIDE;
+              const uint32_t w = *reinterpret_cast<const uint32_t*>(xr + (uint32_t)(clampi(ix, 0, W - 1) * 32));
+              xd[kx][j] = (uint32_t)ix < (uint32_t)W ? w : 0u;
+            }
           }
         }
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) {
+          const bf16x8 B[2] = {halves(xd[kx], kLow), halves(xd[kx], kHigh)};
+#pragma unroll
+          for (int mt = 0; mt < S::mts; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) acc[3 * ky + kx][mt][nt] = mfma32(A[mt], B[nt], acc[3 * ky + kx][mt][nt]);
+        }
+      }
+    } else {
+      uint32_t xd[3][8];
+#pragma unroll
+      for (int s = 0; s < 3; ++s) {
+        const int tap = 4 * s + (m >> 2), iy = oy * STRIDE + (tap / 3 - 1) * dil;
+        const int ix0 = ox0 * STRIDE + (tap % 3 - 1) * dil;
+        const bool ok = tap < 9 && (uint32_t)iy < (uint32_t)H;
+        const uint32_t base = (uint32_t)clampi(iy, 0, H - 1) * (uint32_t)W;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int ix = ix0 + j * STRIDE;
+          const uint32_t w =
+              *reinterpret_cast<const uint32_t*>(img + (size_t)(base + (uint32_t)clampi(ix, 0, W - 1)) * 8 + 2 * (m & 3));
+          xd[s][j] = ok && (uint32_t)ix < (uint32_t)W ? w : 0u;
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < 3; ++s) {
+        const bf16x8 B[2] = {halves(xd[s], kLow), halves(xd[s], kHigh)};
+#pragma unroll
+        for (int mt = 0; mt < S::mts; ++mt)
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt) acc[s][mt][nt] = mfma32(A[mt], B[nt], acc[s][mt][nt]);
       }
     }
+  }
+  // over the four wavefronts, in order
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    bs[k] += __shfl_xor(bs[k], 16);
+    bs[k] += __shfl_xor(bs[k], 32);
+    if (lane < 16) s_b[wave][2 * lane + k] = GCH == 32 || lane == 0 ? bs[k] : 0.f;
+  }
+  for (int w = 1; w < 4; ++w) {
     __syncthreads();
+    if (wave == w) {
+#pragma unroll
+      for (int f = 0; f < S::frags; ++f) s_red[f * 64 + lane] = acc[f / (2 * S::mts)][(f >> 1) % S::mts][f & 1];
+    }
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int f = 0; f < S::frags; ++f) acc[f / (2 * S::mts)][(f >> 1) % S::mts][f & 1] += s_red[f * 64 + lane];
+    }
   }
-  // D[row = co = 16 mt + 4 g + i][col = ci = 16 nt + m]
-  float* pc = part + (size_t)blockIdx.x * 9 * 32 * 32;
+  if (wave == 0) {
+    f32x4* const o = reinterpret_cast<f32x4*>(part) + (size_t)blockIdx.x * S::frags * 64;
 #pragma unroll
-  for (int ti = 0; ti < 3; ++ti) {
-    const int tap = wave + 4 * ti;
-    if (tap >= 9) continue;
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int co = 16 * mt + 4 * g + i, ci = 16 * nt + m;
-          pc[((size_t)tap * 32 + co) * 32 + ci] = (mt < MT && nt < NTt) ? acc[ti][mt][nt][i] : 0.f;
-        }
+    for (int f = 0; f < S::frags; ++f) o[f * 64 + lane] = acc[f / (2 * S::mts)][(f >> 1) % S::mts][f & 1];
   }
-  if (threadIdx.x < 32) partb[(size_t)blockIdx.x * 32 + threadIdx.x] = (int)threadIdx.x < coutp ? bsum : 0.f;
+  if (threadIdx.x < 32)
+    partb[(size_t)blockIdx.x * 32 + threadIdx.x] =
+        s_b[0][threadIdx.x] + s_b[1][threadIdx.x] + s_b[2][threadIdx.x] + s_b[3][threadIdx.x];
 }
 
-// fixed-order reduction of the partials into the parameter-layout gradient:
-// thread e owns partial slot e = (tap * 32 + co) * 32 + ci, so the threads
-// of a wavefront read consecutive words of each chunk's partials
-__global__ void k_reduce_w(const float* __restrict__ part, const float* __restrict__ partb, int nchunk, int cin,
-                           int cout, int off, float* __restrict__ grad) {
-  constexpr int kSlots = 9 * 32 * 32;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < kSlots + 32; e += gridDim.x * blockDim.x) {
-    if (e < kSlots) {
-      const int ci = e % 32, co = (e / 32) % 32, tap = e / (32 * 32);
-      if (ci >= cin || co >= cout) continue;
-      float s = 0.f;
-      for (int c = 0; c < nchunk; ++c) s += part[(size_t)c * kSlots + e];
-      grad[off + (co * cin + ci) * 9 + tap] = s;
+// ---------------------------------------------------------------- gradient sums, Adam
+// Every layer's gradient from its partials, and the update: 64 elements per
+// workgroup, a sixteenth of the partials per wavefront, added in a fixed order;
+// the last workgroup sums the loss.  Bound: the partials' bytes (49 MB at
+// 16 x 1024x436, 12 us).  One launch per layer with one thread per element took
+// 107 us each: a chain of 512 loads on 36 workgroups.
+struct StepLayer {
+  const float *part, *partb;
+  int runs, frags;      // partials; fragments of 256 floats in each
+  int off, cin, cout;   // parameters
+  int cinp, mts;
+  int end;              // workgroups up to and including this layer's
+};
+struct StepArgs {
+  StepLayer l[kNetLayers];
+  float *theta, *m, *v;   // m, v null: no update
+  float* grad_out;        // may be null, as loss_out
+  const float* lpart;
+  int lparts;
+  float* loss_out;
+  float lr, b1, b2, eps, c1, c2;
+};
+constexpr int kStepTpb = 1024;
+
+__global__ __launch_bounds__(kStepTpb) void k_grad_step(StepArgs a) {
+  __shared__ float s_sum[kStepTpb / 64][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = kStepTpb / 64;
+  int li = 0;
+  while (li < kNetLayers && (int)blockIdx.x >= a.l[li].end) ++li;
+  const float* src = a.lpart;
+  int n = a.lparts, pitch = 1, at = -1;   // terms, their distance, the parameter
+  float s = 0.f;
+  if (li == kNetLayers) {
+    for (int i = threadIdx.x; i < n; i += kStepTpb) s += src[i];
+  } else {
+    const StepLayer& L = a.l[li];
+    const int e = ((int)blockIdx.x - (li ? a.l[li - 1].end : 0)) * 64 + lane, nf = L.frags * 256;
+    n = L.runs;
+    if (e < nf) {
+      const int i = e & 3, fl = (e >> 2) & 63, f = e >> 8;
+      const int row = 4 * (fl >> 4) + i, col = fl & 15, nt = f & 1, mt = (f >> 1) % L.mts, slot = (f >> 1) / L.mts;
+      const int co = L.mts == 2 ? 2 * row + mt : row;
+      const int ci = L.cinp == 32 ? 2 * col + nt : 2 * (col & 3) + nt;
+      const int tap = L.cinp == 32 ? slot : 4 * slot + (col >> 2);
+      if (tap < 9 && co < L.cout && ci < L.cin) at = L.off + (co * L.cin + ci) * 9 + tap;
+      src = L.part + e;
+      pitch = nf;
     } else {
-      const int co = e - kSlots;
-      if (co >= cout) continue;
-      float s = 0.f;
-      for (int c = 0; c < nchunk; ++c) s += partb[(size_t)c * 32 + co];
-      grad[off + cout * cin * 9 + co] = s;
+      const int co = e - nf;
+      if (co < L.cout) at = L.off + L.cout * L.cin * 9 + co;
+      src = L.partb + (co & 31);
+      pitch = 32;
     }
+#pragma unroll 8
+    for (int c = w; c < n; c += nw) s += src[(size_t)c * pitch];
+  }
+  s_sum[w][lane] = s;
+  __syncthreads();
+  if (w) return;
+  float t = 0.f;
+#pragma unroll
+  for (int k = 0; k < kStepTpb / 64; ++k) t += s_sum[k][lane];
+  if (li == kNetLayers) {
+    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
+    if (lane == 0 && a.loss_out) *a.loss_out = t;
+    return;
+  }
+  if (at < 0) return;
+  if (a.grad_out) a.grad_out[at] = t;
+  if (a.m) {
+    const float mi = a.b1 * a.m[at] + (1.f - a.b1) * t;
+    const float vi = a.b2 * a.v[at] + (1.f - a.b2) * t * t;
+    a.m[at] = mi;
+    a.v[at] = vi;
+    a.theta[at] -= a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
   }
 }
 
 // ---------------------------------------------------------------- loss
 // masked L1 on the 1/8 grid: labels in 1/Q px (FF_EMPTY = none), output in
-// px / 32.  Count first (integer atomics), then per-element gradient
-// sign(out - t) / count into the bf16 gradient tensor (8 channels), and
-// per-block loss partials summed in a fixed order.
-__global__ void k_loss_count(const int32_t* __restrict__ labels, size_t n, int32_t* __restrict__ count) {
-  int c = 0;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    c += labels[i] != kEmpty;
-  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-  if ((threadIdx.x & 63) == 0 && c) atomicAdd(count, c);
-}
-
-__global__ void k_loss_grad(const float* __restrict__ out, const int32_t* __restrict__ labels, size_t n, float inv_q,
-                            const int32_t* __restrict__ count, uint16_t* __restrict__ g6, float* __restrict__ lpart) {
+// px / 32: per-element gradient sign(out - t) / count into the bf16 gradient
+// tensor (8 channels), and per-block loss partials summed in a fixed order.
+__global__ __launch_bounds__(256) void k_loss_grad(const float* __restrict__ out, const int32_t* __restrict__ labels,
+                                                   size_t n, float inv_q, const int32_t* __restrict__ counts,
+                                                   uint16_t* __restrict__ g6, float* __restrict__ lpart) {
   __shared__ float red[256];
-  const float inv_n = 1.f / (float)max(*count, 1);
+  int count = counts[threadIdx.x & (kCountBlocks - 1)];
+  static_assert(kCountBlocks == 64, "one count per lane");
+  for (int o = 32; o > 0; o >>= 1) count += __shfl_xor(count, o);
+  const float inv_n = 1.f / (float)max(count, 1);
   float ls = 0.f;
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) {
@@ -398,11 +636,7 @@ __global__ void k_loss_grad(const float* __restrict__ out, const int32_t* __rest
       gx = (dx > 0.f ? 1.f : (dx < 0.f ? -1.f : 0.f)) * inv_n;
       gy = (dy > 0.f ? 1.f : (dy < 0.f ? -1.f : 0.f)) * inv_n;
     }
-    uint16_t* o = g6 + i * 8;
-    o[0] = f2bf(gx);
-    o[1] = f2bf(gy);
-#pragma unroll
-    for (int c = 2; c < 8; ++c) o[c] = 0;
+    reinterpret_cast<uint4*>(g6)[i] = make_uint4(f2bf(gx) | ((uint32_t)f2bf(gy) << 16), 0, 0, 0);
   }
   red[threadIdx.x] = ls;
   __syncthreads();
@@ -413,45 +647,15 @@ __global__ void k_loss_grad(const float* __restrict__ out, const int32_t* __rest
   if (threadIdx.x == 0) lpart[blockIdx.x] = red[0] * inv_n;
 }
 
-__global__ void k_sum_fixed(const float* __restrict__ v, int n, float* __restrict__ out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    float s = 0.f;
-    for (int i = 0; i < n; ++i) s += v[i];
-    *out = s;
-  }
-}
-
-// ---------------------------------------------------------------- Adam
-__global__ void k_adam(float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v,
-                       const float* __restrict__ g, int n, float lr, float b1, float b2, float eps, float c1, float c2) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    theta[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-  }
-}
-
-// ---------------------------------------------------------------- proposal
-// round the network's flow to packed 1/Q px (nearest even), clamp to int16
-__global__ void k_to_proposal(const float* __restrict__ out, size_t n, float q, int32_t* __restrict__ prop) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const float fx = fminf(fmaxf(rintf(out[2 * i] * 32.f * q), -32767.f), 32767.f);
-    const float fy = fminf(fmaxf(rintf(out[2 * i + 1] * 32.f * q), -32767.f), 32767.f);
-    prop[i] = packf((int)fx, (int)fy);
-  }
-}
-
 // ---------------------------------------------------------------- workspace plan
 struct NetPlan {
   int H[kNetLayers + 1], W[kNetLayers + 1];   // tensor sizes: [0] input, [l+1] output of layer l
   size_t off_x[kNetLayers + 1];               // activations (bf16, padded channels); [6] = fp32 output
   size_t off_g[kNetLayers + 1];               // gradients w.r.t. pre-activation outputs (bf16)
   size_t off_wb[kNetLayers], off_wbt[kNetLayers];
-  size_t off_grad, off_part, off_partb, off_lpart, off_count, off_loss;
-  size_t part_chunks, lparts;
+  size_t off_part[kNetLayers], off_partb[kNetLayers], off_lpart, off_count;
+  int runs[kNetLayers], frags[kNetLayers];    // weight-gradient partials, fragments of each
+  size_t lparts;
   size_t bytes;
 };
 
@@ -476,49 +680,87 @@ static NetPlan net_plan(int Bn, int W, int H) {
     P.off_x[l] = take(l == kNetLayers ? px * 2 * 4 : px * ch * 2);
     P.off_g[l] = l == 0 ? 0 : take(px * (l == kNetLayers ? 8 : ch) * 2);
   }
-  size_t maxpx = 0;
   for (int l = 0; l < kNetLayers; ++l) {
     P.off_wb[l] = take((size_t)chunks_of(kNet[l].cinp) * tiles_of(kNet[l].cout) * 64 * 16);
     P.off_wbt[l] = take((size_t)chunks_of(kNet[l].coutp) * tiles_of(kNet[l].cin) * 64 * 16);
-    maxpx = std::max(maxpx, (size_t)Bn * P.H[l + 1] * P.W[l + 1]);
+    // runs of a weight gradient: two workgroups per CU at the first layer, whose
+    // partials are a third of the others', one at those (fixed for a given
+    // size: run-to-run identical sums)
+    const int64_t units = (int64_t)Bn * P.H[l + 1] * ((P.W[l + 1] + 31) / 32);
+    P.runs[l] = (int)std::min<int64_t>((units + 3) / 4, l == 0 ? 512 : 256);
+    P.frags[l] = l == 0                ? WGrad<8, 32>::frags
+                 : l == kNetLayers - 1 ? WGrad<32, 8>::frags
+                                       : WGrad<32, 32>::frags;
+    P.off_part[l] = take((size_t)P.runs[l] * P.frags[l] * 256 * 4);
+    P.off_partb[l] = take((size_t)P.runs[l] * 32 * 4);
   }
-  (void)maxpx;
-  P.part_chunks = kWChunks;
-  P.off_grad = take((size_t)param_total() * 4);
-  P.off_part = take(P.part_chunks * 9 * 32 * 32 * 4);
-  P.off_partb = take(P.part_chunks * 32 * 4);
   const size_t nout = (size_t)Bn * P.H[kNetLayers] * P.W[kNetLayers];
   P.lparts = (nout + 255) / 256;
   P.off_lpart = take(P.lparts * 4);
-  P.off_count = take(4);
-  P.off_loss = take(4);
+  P.off_count = take(kCountBlocks * 4);
   P.bytes = align_up(off, 256);
   return P;
 }
 
+// grid of a convolution launch: a wavefront per tile, and as many as the chip
+// holds at most (three to four wavefronts per SIMD by registers)
+static unsigned conv_blocks(int rows, int Wo) {
+  const int64_t tiles = (int64_t)rows * ((Wo + 15) / 16);
+  return (unsigned)std::min<int64_t>((tiles + 3) / 4, 1024);
+}
+
+// everything up to the network's output (fp32; flow, prop: see ConvArgs).
+// labels: of a training step, or null
 static void enqueue_forward(const NetPlan& P, int Bn, const float* theta, const uint8_t* i1, const uint8_t* i2, char* ws,
-                            hipStream_t s) {
-  const size_t npx0 = (size_t)Bn * P.H[0] * P.W[0];
-  k_pack_input<<<(unsigned)std::min<size_t>((npx0 + 255) / 256, 65535), 256, 0, s>>>(
-      i1, i2, npx0, reinterpret_cast<uint16_t*>(ws + P.off_x[0]));
+                            const int32_t* labels, float* flow, int32_t* prop, float q, hipStream_t s) {
+  PackArgs a{};
+  a.i1 = i1;
+  a.i2 = i2;
+  a.npx = (size_t)Bn * P.H[0] * P.W[0];
+  a.x = reinterpret_cast<uint16_t*>(ws + P.off_x[0]);
+  a.theta = theta;
+  int end = 0;
+  for (int bwd = 0; bwd < (labels ? 2 : 1); ++bwd)
+    for (int l = bwd; l < kNetLayers; ++l) {   // the first layer's input needs no gradient
+      const NetLayer& L = kNet[l];
+      const int cpad = bwd ? L.coutp : L.cinp, tiles = tiles_of(bwd ? L.cin : L.cout);
+      end += chunks_of(cpad) * tiles * 64 * 8;
+      a.l[a.n++] = {param_offset(l), L.cin, L.cout, cpad, tiles, bwd, end,
+                    reinterpret_cast<uint16_t*>(ws + (bwd ? P.off_wbt[l] : P.off_wb[l]))};
+    }
+  a.blocks_in = (int)std::min<size_t>((a.npx + 1023) / 1024, 8192);
+  a.blocks_w = (end + 255) / 256;
+  a.labels = labels;
+  a.nlabels = (size_t)Bn * P.H[kNetLayers] * P.W[kNetLayers];
+  a.counts = reinterpret_cast<int32_t*>(ws + P.off_count);
+  k_pack<<<a.blocks_in + a.blocks_w + (labels ? kCountBlocks : 0), 256, 0, s>>>(a);
   for (int l = 0; l < kNetLayers; ++l) {
     const NetLayer& L = kNet[l];
-    const int nch = chunks_of(L.cinp), nt = tiles_of(L.cout);
-    uint16_t* wb = reinterpret_cast<uint16_t*>(ws + P.off_wb[l]);
-    k_pack_fwd<<<64, 256, 0, s>>>(theta, param_offset(l), L.cin, L.cout, L.cinp, nch, nt, wb);
-    const float* bias = theta + param_offset(l) + L.cout * L.cin * 9;
-    const size_t npx = (size_t)Bn * P.H[l + 1] * P.W[l + 1];
-    const unsigned blocks = (unsigned)((npx + 64 * kTilesPerWave - 1) / (64 * kTilesPerWave));
-    const uint16_t* xin = reinterpret_cast<const uint16_t*>(ws + P.off_x[l]);
-    uint16_t* yout = l + 1 < kNetLayers ? reinterpret_cast<uint16_t*>(ws + P.off_x[l + 1]) : nullptr;
-    float* yf = l + 1 == kNetLayers ? reinterpret_cast<float*>(ws + P.off_x[l + 1]) : nullptr;
-    const uint4* wbv = reinterpret_cast<const uint4*>(wb);
-    if (nt == 2)
-      k_conv_fwd<2><<<blocks, 256, 0, s>>>(xin, Bn, P.H[l], P.W[l], L.cinp, P.H[l + 1], P.W[l + 1], L.stride, L.dil, nch,
-                                           wbv, bias, L.cout, L.coutp, L.relu, yout, yf);
-    else
-      k_conv_fwd<1><<<blocks, 256, 0, s>>>(xin, Bn, P.H[l], P.W[l], L.cinp, P.H[l + 1], P.W[l + 1], L.stride, L.dil, nch,
-                                           wbv, bias, L.cout, L.coutp, L.relu, yout, yf);
+    ConvArgs c{};
+    c.x = reinterpret_cast<const uint16_t*>(ws + P.off_x[l]);
+    c.wb = reinterpret_cast<const uint4*>(ws + P.off_wb[l]);
+    c.bias = theta + param_offset(l) + L.cout * L.cin * 9;
+    c.rows = Bn * P.H[l + 1];
+    c.H = P.H[l];
+    c.W = P.W[l];
+    c.Ho = P.H[l + 1];
+    c.Wo = P.W[l + 1];
+    c.stride = L.stride;
+    c.dil = L.dil;
+    c.relu = L.relu;
+    c.cout = L.cout;
+    const unsigned blocks = conv_blocks(c.rows, c.Wo);
+    if (l + 1 == kNetLayers) {
+      c.yf = reinterpret_cast<float*>(ws + P.off_x[l + 1]);
+      c.flow = flow;
+      c.prop = prop;
+      c.q = q;
+      k_conv<32, 1, false><<<blocks, 256, 0, s>>>(c);
+    } else {
+      c.y = reinterpret_cast<uint16_t*>(ws + P.off_x[l + 1]);
+      if (l == 0) k_conv<8, 2, false><<<blocks, 256, 0, s>>>(c);
+      else k_conv<32, 2, false><<<blocks, 256, 0, s>>>(c);
+    }
   }
 }
 
@@ -552,13 +794,8 @@ ff_status ff_proposal_forward(const float* params, const uint8_t* img1, const ui
   if (workspace_bytes < P.bytes) return FF_ERR_WORKSPACE;
   char* ws = static_cast<char*>(workspace);
   prof_mark(FF_PROF_PROPOSAL, stream, true);
-  enqueue_forward(P, batch, params, img1, img2, ws, stream);
-  const size_t n = (size_t)batch * P.H[kNetLayers] * P.W[kNetLayers];
-  const float* out = reinterpret_cast<const float*>(ws + P.off_x[kNetLayers]);
-  k_to_proposal<<<(unsigned)std::min<size_t>((n + 255) / 256, 65535), 256, 0, stream>>>(out, n, (float)subpel, proposal);
+  enqueue_forward(P, batch, params, img1, img2, ws, nullptr, flow_out, proposal, (float)subpel, stream);
   prof_mark(FF_PROF_PROPOSAL, stream, false);
-  if (flow_out && hipMemcpyAsync(flow_out, out, n * 2 * 4, hipMemcpyDeviceToDevice, stream) != hipSuccess)
-    return FF_ERR_HIP;
   return launch_status();
 }
 
@@ -576,62 +813,73 @@ ff_status ff_proposal_train_step(float* params, float* adam_m, float* adam_v, in
   if (workspace_bytes < P.bytes) return FF_ERR_WORKSPACE;
   char* ws = static_cast<char*>(workspace);
   prof_mark(FF_PROF_TRAIN, stream, true);
-  enqueue_forward(P, batch, params, img1, img2, ws, stream);
+  enqueue_forward(P, batch, params, img1, img2, ws, labels, nullptr, nullptr, 0.f, stream);
   // loss and dL/d(out)
   const size_t n6 = (size_t)batch * P.H[kNetLayers] * P.W[kNetLayers];
-  int32_t* count = reinterpret_cast<int32_t*>(ws + P.off_count);
   float* lpart = reinterpret_cast<float*>(ws + P.off_lpart);
-  fill_i32(count, 1, 0, stream);
-  k_loss_count<<<(unsigned)std::min<size_t>((n6 + 255) / 256, 1024), 256, 0, stream>>>(labels, n6, count);
   k_loss_grad<<<(unsigned)P.lparts, 256, 0, stream>>>(reinterpret_cast<const float*>(ws + P.off_x[kNetLayers]), labels,
-                                                     n6, 1.f / (float)subpel, count,
+                                                     n6, 1.f / (float)subpel, reinterpret_cast<int32_t*>(ws + P.off_count),
                                                      reinterpret_cast<uint16_t*>(ws + P.off_g[kNetLayers]), lpart);
-  k_sum_fixed<<<1, 64, 0, stream>>>(lpart, (int)P.lparts, reinterpret_cast<float*>(ws + P.off_loss));
   // backward, last layer first
-  float* grad = reinterpret_cast<float*>(ws + P.off_grad);
-  float* part = reinterpret_cast<float*>(ws + P.off_part);
-  float* partb = reinterpret_cast<float*>(ws + P.off_partb);
+  StepArgs a{};
+  int end = 0;
+  for (int l = 0; l < kNetLayers; ++l) {
+    const NetLayer& L = kNet[l];
+    end += (P.frags[l] * 256 + 32 + 63) / 64;
+    a.l[l] = {reinterpret_cast<const float*>(ws + P.off_part[l]), reinterpret_cast<const float*>(ws + P.off_partb[l]),
+              P.runs[l], P.frags[l], param_offset(l), L.cin, L.cout, L.cinp, l + 1 == kNetLayers ? 1 : 2, end};
+  }
   for (int l = kNetLayers - 1; l >= 0; --l) {
     const NetLayer& L = kNet[l];
     const uint16_t* G = reinterpret_cast<const uint16_t*>(ws + P.off_g[l + 1]);
     const uint16_t* X = reinterpret_cast<const uint16_t*>(ws + P.off_x[l]);
-    const int gch = l + 1 == kNetLayers ? 8 : L.coutp;
-    const size_t npx = (size_t)batch * P.H[l + 1] * P.W[l + 1];
-    // fixed chunking for a given size (run-to-run identical sums): chunks of
-    // a multiple of 64 pixels, at most kWChunks of them
-    const size_t chunk = std::max<size_t>(64, ((npx + kWChunks - 1) / kWChunks + 63) / 64 * 64);
-    const int nchunk = (int)((npx + chunk - 1) / chunk);
-    k_conv_bwd_w<<<nchunk, 256, 0, stream>>>(G, batch, P.H[l + 1], P.W[l + 1], gch, X, P.H[l], P.W[l], L.cinp, L.stride,
-                                             L.dil, (int)chunk, part, partb);
-    k_reduce_w<<<64, 256, 0, stream>>>(part, partb, nchunk, L.cin, L.cout, param_offset(l), grad);
-    if (l > 0) {
-      const int nchb = chunks_of(gch), ntb = tiles_of(L.cin);
-      uint16_t* wbt = reinterpret_cast<uint16_t*>(ws + P.off_wbt[l]);
-      k_pack_bwd<<<64, 256, 0, stream>>>(params, param_offset(l), L.cin, L.cout, gch, nchb, ntb, wbt);
-      const size_t nin = (size_t)batch * P.H[l] * P.W[l];
-      const unsigned blocks = (unsigned)((nin + 64 * kTilesPerWave - 1) / (64 * kTilesPerWave));
-      uint16_t* gprev = reinterpret_cast<uint16_t*>(ws + P.off_g[l]);
-      const uint16_t* aprev = X;
-      const uint4* wbtv = reinterpret_cast<const uint4*>(wbt);
-      if (ntb == 2)
-        k_conv_bwd_data<2><<<blocks, 256, 0, stream>>>(G, batch, P.H[l + 1], P.W[l + 1], gch, P.H[l], P.W[l], L.stride,
-                                                       L.dil, nchb, wbtv, L.cinp, aprev, gprev);
-      else
-        k_conv_bwd_data<1><<<blocks, 256, 0, stream>>>(G, batch, P.H[l + 1], P.W[l + 1], gch, P.H[l], P.W[l], L.stride,
-                                                       L.dil, nchb, wbtv, L.cinp, aprev, gprev);
+    const int H = P.H[l], W = P.W[l], Ho = P.H[l + 1], Wo = P.W[l + 1], rows = batch * Ho;
+    float4* part = reinterpret_cast<float4*>(ws + P.off_part[l]);
+    float* partb = reinterpret_cast<float*>(ws + P.off_partb[l]);
+    if (l == 0) k_conv_bwd_w<8, 32, 2><<<P.runs[l], 256, 0, stream>>>(G, X, rows, Ho, Wo, H, W, L.dil, part, partb);
+    else if (l + 1 == kNetLayers)
+      k_conv_bwd_w<32, 8, 1><<<P.runs[l], 256, 0, stream>>>(G, X, rows, Ho, Wo, H, W, L.dil, part, partb);
+    else if (L.stride == 2)
+      k_conv_bwd_w<32, 32, 2><<<P.runs[l], 256, 0, stream>>>(G, X, rows, Ho, Wo, H, W, L.dil, part, partb);
+    else
+      k_conv_bwd_w<32, 32, 1><<<P.runs[l], 256, 0, stream>>>(G, X, rows, Ho, Wo, H, W, L.dil, part, partb);
+    if (l == 0) break;
+    uint16_t* gprev = reinterpret_cast<uint16_t*>(ws + P.off_g[l]);
+    const uint4* wbt = reinterpret_cast<const uint4*>(ws + P.off_wbt[l]);
+    if (L.stride == 2) {   // dilation 1
+      k_conv_bwd2<<<conv_blocks(rows, Wo), 256, 0, stream>>>(G, rows, Ho, Wo, H, W, wbt, X, gprev);
+      continue;
     }
+    ConvArgs c{};
+    c.x = G;
+    c.wb = wbt;
+    c.aprev = X;
+    c.y = gprev;
+    c.rows = rows;
+    c.H = c.Ho = H;
+    c.W = c.Wo = W;
+    c.stride = 1;
+    c.dil = -L.dil;
+    if (l + 1 == kNetLayers) k_conv<8, 2, true><<<conv_blocks(rows, W), 256, 0, stream>>>(c);
+    else k_conv<32, 2, true><<<conv_blocks(rows, W), 256, 0, stream>>>(c);
   }
-  const int np = param_total();
+  a.grad_out = grad_out;
+  a.loss_out = loss_out;
+  a.lpart = lpart;
+  a.lparts = (int)P.lparts;
   if (update) {
-    const float b1 = 0.9f, b2 = 0.999f;
-    const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
-    k_adam<<<64, 256, 0, stream>>>(params, adam_m, adam_v, grad, np, lr, b1, b2, 1e-8f, c1, c2);
+    a.theta = params;
+    a.m = adam_m;
+    a.v = adam_v;
+    a.lr = lr;
+    a.b1 = 0.9f;
+    a.b2 = 0.999f;
+    a.eps = 1e-8f;
+    a.c1 = 1.f - powf(a.b1, (float)step);
+    a.c2 = 1.f - powf(a.b2, (float)step);
   }
+  k_grad_step<<<end + 1, kStepTpb, 0, stream>>>(a);
   prof_mark(FF_PROF_TRAIN, stream, false);
-  if (grad_out && hipMemcpyAsync(grad_out, grad, (size_t)np * 4, hipMemcpyDeviceToDevice, stream) != hipSuccess)
-    return FF_ERR_HIP;
-  if (loss_out && hipMemcpyAsync(loss_out, ws + P.off_loss, 4, hipMemcpyDeviceToDevice, stream) != hipSuccess)
-    return FF_ERR_HIP;
   return launch_status();
 }
 
