@@ -28,8 +28,8 @@
 // A layer's launch is short (0.1 to 1.8 M pixels for 16 pairs of 1024x436), so
 // what a step does besides its contractions counts as much: weights and input
 // are packed in one launch, and one launch reduces every layer's weight
-// gradient and applies Adam.  16 x 1024x436: training step 1.78 -> 0.64 ms, forward
-// of two pairs 163 -> 41 us.
+// gradient and applies Adam.  16 x 1024x436: training step 1.78 -> 0.40 ms, forward
+// of two pairs 163 -> 37 us.
 #include <math.h>
 
 #include "ff_internal.h"
@@ -56,6 +56,13 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
   return (uint16_t)(u >> 16);
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
+
+// LDS accesses of a wavefront before and after this point stay in order
+__device__ __forceinline__ void wave_lds_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+  asm volatile("" ::: "memory");
+}
 
 static int param_offset(int layer) {
   int o = 0;
@@ -97,25 +104,28 @@ constexpr int kCountBlocks = 64;
 
 __global__ __launch_bounds__(256) void k_pack(PackArgs a) {
   __shared__ uint32_t s_tab[256];
+  __shared__ uint4 s_px[4][64 * 5];   // four pixels per lane, a fifth place between
   const int blk = blockIdx.x;
   if (blk < a.blocks_in) {
     // u8 RGB pair (B x H x W x 3 each) -> bf16 NHWC with 8 channels:
     // RGB1/255 - 1/2, RGB2/255 - 1/2, 0, 0
     s_tab[threadIdx.x] = f2bf((float)threadIdx.x / 255.0f - 0.5f);
     __syncthreads();
-    auto put = [&](size_t p, const uint32_t (&c)[6]) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    auto of = [&](const uint32_t (&c)[6]) {
       uint4 o;
       o.x = s_tab[c[0]] | (s_tab[c[1]] << 16);
       o.y = s_tab[c[2]] | (s_tab[c[3]] << 16);
       o.z = s_tab[c[4]] | (s_tab[c[5]] << 16);
       o.w = 0;
-      reinterpret_cast<uint4*>(a.x)[p] = o;
+      return o;
     };
     // four pixels, three words of each image, at a time where those are aligned
     const bool words = (((uintptr_t)a.i1 | (uintptr_t)a.i2) & 3) == 0;
     const size_t quads = words ? a.npx / 4 : 0;
     const size_t tid = (size_t)blk * 256 + threadIdx.x, step = (size_t)a.blocks_in * 256;
-    for (size_t q = tid; q < quads; q += step) {
+    for (size_t q0 = tid - lane; q0 < quads; q0 += step) {
+      const size_t q = min(q0 + lane, quads - 1);
       uint32_t w1[3], w2[3];
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -131,12 +141,21 @@ __global__ __launch_bounds__(256) void k_pack(PackArgs a) {
           c[j] = (w1[e >> 2] >> (8 * (e & 3))) & 0xFF;
           c[3 + j] = (w2[e >> 2] >> (8 * (e & 3))) & 0xFF;
         }
-        put(q * 4 + k, c);
+        s_px[wave][lane * 5 + k] = of(c);
       }
+      // a wavefront's 256 pixels back in order, so that a store is 1 KB
+      wave_lds_order();
+      const size_t p0 = q0 * 4;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int e = 64 * k + lane;
+        if (p0 + e < quads * 4) reinterpret_cast<uint4*>(a.x)[p0 + e] = s_px[wave][(e >> 2) * 5 + (e & 3)];
+      }
+      wave_lds_order();
     }
     for (size_t p = quads * 4 + tid; p < a.npx; p += step) {
       const uint32_t c[6] = {a.i1[p * 3], a.i1[p * 3 + 1], a.i1[p * 3 + 2], a.i2[p * 3], a.i2[p * 3 + 1], a.i2[p * 3 + 2]};
-      put(p, c);
+      reinterpret_cast<uint4*>(a.x)[p] = of(c);
     }
   } else if (blk < a.blocks_in + a.blocks_w) {
     const int at = (blk - a.blocks_in) * 256 + threadIdx.x;
@@ -306,7 +325,7 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a) {
 // tap rows 0 of cy + 1 and 2 of cy where dy = 1, columns likewise: nine taps
 // for four pixels, where a sum over all nine for each multiplies three zeros
 // in four.  Then the producing layer's ReLU.  Bound: bytes.
-// 16 x 1024x436, 32 channels into 1.8 M pixels: 194 -> 55 us.
+// 16 x 1024x436, 32 channels into 1.8 M pixels: 194 -> 52 us.
 __global__ __launch_bounds__(256) void k_conv_bwd2(const uint16_t* __restrict__ G, int rows, int Ho, int Wo, int H, int W,
                                                    const uint4* __restrict__ wbt, const uint16_t* __restrict__ aprev,
                                                    uint16_t* __restrict__ gprev) {
@@ -378,160 +397,289 @@ __global__ __launch_bounds__(256) void k_conv_bwd2(const uint16_t* __restrict__ 
 // ---------------------------------------------------------------- backward-weight
 // dW[tap][co][ci] = sum_p G[p][co] X[p_in(p, tap)][ci] with K = pixels, bias
 // gradient sum_p G[p][co].  A workgroup takes a run of 32-pixel pieces of
-// output rows, its wavefronts in turn, and every tap of them.  A lane's operand
-// is eight pixels of one channel: it loads channels 2m, 2m + 1 of its eight
-// pixels (16 lanes read a pixel's 64 bytes), and the low and the high halves
-// make the fragments of the even and of the odd channels -- the transposition
-// costs four byte permutes per fragment and no LDS.  Eight-channel tensors
-// fill the 16 columns with four taps at a time.  Sums stay in registers over
-// the run; the four wavefronts' are added in order at its end.
-// Bound: loads in flight (144 registers of sums leave two wavefronts per SIMD).
-// 16 x 1024x436, second layer 107 -> 61 us, the first 205 -> 211, against staging
-// 64 pixels of all taps through LDS with 2-byte writes.
+// output rows.  A lane's operand is eight pixels (g, g + 4, ..) of one channel:
+// it loads channels 2m, 2m + 1 of its eight pixels (a wavefront's load is four
+// neighbouring pixels, 64 bytes each), and the low and the high halves make the
+// fragments of the even and of the odd channels -- the transposition costs four
+// byte permutes per fragment and no LDS.  Sums stay in registers over the run;
+// the wavefronts' are added pairwise in a fixed order at its end.
+// 32-channel X: three wavefronts per piece, one per tap row (a third of the
+// sums each: three to four wavefronts per SIMD instead of two), the next
+// piece's loads in flight while one is multiplied.
+// Eight-channel X (the images): four taps of eight channels fill the 16
+// columns; a pixel is 16 bytes, so its rows are staged in LDS, 65 pixels of
+// three rows per piece and wavefront, by 16-byte loads that are in flight over
+// the piece before, and read there in words.
+// Bound: bytes, and loads in flight at the small layers.
+// 16 x 1024x436, against staging 64 pixels of all taps through LDS with 2-byte
+// writes: first layer 205 -> 60 us, second 107 -> 43, the rest 34 -> 14 each.
 // Partials: [run][fragment (slot, mt, nt)][lane][4], slot = tap, or four taps.
 template <int CINP, int GCH>
 struct WGrad {
   static constexpr int slots = CINP == 32 ? 9 : 3, mts = GCH == 32 ? 2 : 1;
   static constexpr int frags = slots * mts * 2;
 };
-template <int CINP, int GCH, int STRIDE>
-__global__ __launch_bounds__(256, 2) void k_conv_bwd_w(const uint16_t* __restrict__ G, const uint16_t* __restrict__ X,
-                                                       int rows, int Ho, int Wo, int H, int W, int dil,
-                                                       float4* __restrict__ part, float* __restrict__ partb) {
-  using S = WGrad<CINP, GCH>;
-  __shared__ f32x4 s_red[S::frags * 64];
-  __shared__ float s_b[4][32];
+constexpr int kWGroups = 4;    // pieces at once in a workgroup, 32-channel X
+constexpr int kWWaves0 = 8;    // and eight-channel X
+
+// the low (the high) halves of eight words, in order
+constexpr uint32_t kLowHalf = 0x05040100u, kHighHalf = 0x07060302u;
+__device__ __forceinline__ bf16x8 halves(const uint32_t (&w)[8], uint32_t sel) {
+  return bf16x8_of(make_uint4(__builtin_amdgcn_perm(w[1], w[0], sel), __builtin_amdgcn_perm(w[3], w[2], sel),
+                              __builtin_amdgcn_perm(w[5], w[4], sel), __builtin_amdgcn_perm(w[7], w[6], sel)));
+}
+// G's channels 2m, 2m + 1 (eight-channel G: 0 and 1) of pixels 32 xb + g + 4 j
+// of a row, zero past its end
+template <int GCH>
+__device__ __forceinline__ void load_g(const uint16_t* G, int row, int xb, int Wo, int m, int g, uint32_t (&gd)[8]) {
+  const uint16_t* gr = G + (size_t)row * Wo * GCH + (GCH == 32 ? 2 * m : 0);
+  const int ox = 32 * xb + g;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const uint32_t w = *reinterpret_cast<const uint32_t*>(gr + (uint32_t)(min(ox + 4 * j, Wo - 1) * GCH));
+    gd[j] = ox + 4 * j < Wo && (GCH == 32 || m < 2) ? w : 0u;
+  }
+}
+template <int GCH, int MTS>
+__device__ __forceinline__ void g_frags(const uint32_t (&gd)[8], int m, bf16x8 (&A)[MTS]) {
+  if constexpr (GCH == 32) {
+    A[0] = halves(gd, kLowHalf);
+    A[1] = halves(gd, kHighHalf);
+  } else {
+    A[0] = halves(gd, m == 0 ? kLowHalf : kHighHalf);
+  }
+}
+
+template <int GCH, int STRIDE>
+__global__ __launch_bounds__(64 * 3 * kWGroups) void k_conv_bwd_w(const uint16_t* __restrict__ G,
+                                                                 const uint16_t* __restrict__ X, int rows, int Ho, int Wo,
+                                                                 int H, int W, int dil, float4* __restrict__ part,
+                                                                 float* __restrict__ partb) {
+  using S = WGrad<32, GCH>;
+  constexpr int FR = S::frags / 3;   // of one tap row
+  __shared__ f32x4 s_red[kWGroups / 2][3][FR * 64];
+  __shared__ float s_b[kWGroups][32];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = wave / 3, ky = wave - 3 * grp;
   const int m = lane & 15, g = lane >> 4;
   const int nxb = (Wo + 31) >> 5;
   const int64_t units = (int64_t)rows * nxb;
   const int u0 = (int)(units * blockIdx.x / gridDim.x), u1 = (int)(units * (blockIdx.x + 1) / gridDim.x);
-  f32x4 acc[S::slots][S::mts][2];
+  f32x4 acc[3][S::mts][2];
 #pragma unroll
-  for (int s = 0; s < S::slots; ++s)
+  for (int s = 0; s < 3; ++s)
 #pragma unroll
     for (int mt = 0; mt < S::mts; ++mt)
 #pragma unroll
       for (int nt = 0; nt < 2; ++nt) acc[s][mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
   float bs[2] = {0.f, 0.f};
-  // the low (the high) halves of eight words, in order
-  auto halves = [](const uint32_t (&w)[8], uint32_t sel) {
-    return bf16x8_of(make_uint4(__builtin_amdgcn_perm(w[1], w[0], sel), __builtin_amdgcn_perm(w[3], w[2], sel),
-                                __builtin_amdgcn_perm(w[5], w[4], sel), __builtin_amdgcn_perm(w[7], w[6], sel)));
+  struct Piece {
+    uint32_t gd[8], xd[3][8];
+    uint32_t ok[3];   // pixels of each tap inside the image (bit j)
   };
-  constexpr uint32_t kLow = 0x05040100u, kHigh = 0x07060302u;
-  for (int u = u0 + wave; u < u1; u += 4) {
+  auto load = [&](int u) {
+    Piece P;
     const int row = u / nxb, xb = u - row * nxb, b = row / Ho, oy = row - b * Ho;
-    const int ox0 = 32 * xb + 8 * g;
-    const bool whole = 32 * xb + 32 <= Wo;
-    // G: channels 2m, 2m + 1 of pixels ox0 .. ox0 + 7 (eight-channel G: 0 and 1)
-    const uint16_t* gr = G + (size_t)row * Wo * GCH + (GCH == 32 ? 2 * m : 0);
-    uint32_t gd[8];
+    load_g<GCH>(G, row, xb, Wo, m, g, P.gd);
+    const int iy = oy * STRIDE + (ky - 1) * dil;
+    const bool in = (uint32_t)iy < (uint32_t)H;
+    const uint16_t* xr = X + ((size_t)b * H + clampi(iy, 0, H - 1)) * W * 32 + 2 * m;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      gd[j] = *reinterpret_cast<const uint32_t*>(gr + (uint32_t)(min(ox0 + j, Wo - 1) * GCH));
-      if (!whole && ox0 + j >= Wo) gd[j] = 0;
-      if (GCH == 8 && m > 1) gd[j] = 0;
+    for (int kx = 0; kx < 3; ++kx) {
+      const int ix0 = (32 * xb + g) * STRIDE + (kx - 1) * dil;
+      P.ok[kx] = 0;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int ix = ix0 + 4 * j * STRIDE;
+        P.xd[kx][j] = *reinterpret_cast<const uint32_t*>(xr + (uint32_t)(clampi(ix, 0, W - 1) * 32));
+        P.ok[kx] |= in && (uint32_t)ix < (uint32_t)W ? 1u << j : 0u;
+      }
     }
+    return P;
+  };
+  int u = u0 + grp;
+  Piece P;
+  if (u < u1) P = load(u);
+  while (u < u1) {
+    const int next = u + kWGroups;
+    Piece N;
+    if (next < u1) N = load(next);
     bf16x8 A[S::mts];
-    if constexpr (GCH == 32) {
-      A[0] = halves(gd, kLow);
-      A[1] = halves(gd, kHigh);
-    } else {
-      A[0] = halves(gd, m == 0 ? kLow : kHigh);
-    }
+    g_frags<GCH>(P.gd, m, A);
+    if (ky == 0) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      bs[0] += bf2f((uint16_t)gd[j]);
-      bs[1] += bf2f((uint16_t)(gd[j] >> 16));
-    }
-    const uint16_t* img = X + (size_t)b * H * W * CINP;
-    const bool inside = whole && 32 * xb * STRIDE >= dil && (32 * xb + 31) * STRIDE + dil < W;
-    if constexpr (CINP == 32) {
-#pragma unroll
-      for (int ky = 0; ky < 3; ++ky) {
-        const int iy = oy * STRIDE + (ky - 1) * dil;
-        if ((uint32_t)iy >= (uint32_t)H) continue;
-        const uint16_t* xr = img + (size_t)iy * W * 32 + 2 * m;
-        uint32_t xd[3][8];
-#pragma unroll
-        for (int kx = 0; kx < 3; ++kx) {
-          const int ix0 = ox0 * STRIDE + (kx - 1) * dil;
-          if (inside) {
-            const uint16_t* xp = xr + (uint32_t)(ix0 * 32);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) xd[kx][j] = *reinterpret_cast<const uint32_t*>(xp + j * STRIDE * 32);
-          } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const int ix = ix0 + j * STRIDE;
-              const uint32_t w = *reinterpret_cast<const uint32_t*>(xr + (uint32_t)(clampi(ix, 0, W - 1) * 32));
-              xd[kx][j] = (uint32_t)ix < (uint32_t)W ? w : 0u;
-            }
-          }
-        }
-#pragma unroll
-        for (int kx = 0; kx < 3; ++kx) {
-          const bf16x8 B[2] = {halves(xd[kx], kLow), halves(xd[kx], kHigh)};
-#pragma unroll
-          for (int mt = 0; mt < S::mts; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) acc[3 * ky + kx][mt][nt] = mfma32(A[mt], B[nt], acc[3 * ky + kx][mt][nt]);
-        }
-      }
-    } else {
-      uint32_t xd[3][8];
-#pragma unroll
-      for (int s = 0; s < 3; ++s) {
-        const int tap = 4 * s + (m >> 2), iy = oy * STRIDE + (tap / 3 - 1) * dil;
-        const int ix0 = ox0 * STRIDE + (tap % 3 - 1) * dil;
-        const bool ok = tap < 9 && (uint32_t)iy < (uint32_t)H;
-        const uint32_t base = (uint32_t)clampi(iy, 0, H - 1) * (uint32_t)W;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int ix = ix0 + j * STRIDE;
-          const uint32_t w =
-              *reinterpret_cast<const uint32_t*>(img + (size_t)(base + (uint32_t)clampi(ix, 0, W - 1)) * 8 + 2 * (m & 3));
-          xd[s][j] = ok && (uint32_t)ix < (uint32_t)W ? w : 0u;
-        }
-      }
-#pragma unroll
-      for (int s = 0; s < 3; ++s) {
-        const bf16x8 B[2] = {halves(xd[s], kLow), halves(xd[s], kHigh)};
-#pragma unroll
-        for (int mt = 0; mt < S::mts; ++mt)
-#pragma unroll
-          for (int nt = 0; nt < 2; ++nt) acc[s][mt][nt] = mfma32(A[mt], B[nt], acc[s][mt][nt]);
+      for (int j = 0; j < 8; ++j) {
+        bs[0] += bf2f((uint16_t)P.gd[j]);
+        bs[1] += bf2f((uint16_t)(P.gd[j] >> 16));
       }
     }
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx) {
+      if (__ballot(P.ok[kx] != 0xFFu)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (!((P.ok[kx] >> j) & 1)) P.xd[kx][j] = 0;
+      }
+      const bf16x8 B[2] = {halves(P.xd[kx], kLowHalf), halves(P.xd[kx], kHighHalf)};
+#pragma unroll
+      for (int mt = 0; mt < S::mts; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) acc[kx][mt][nt] = mfma32(A[mt], B[nt], acc[kx][mt][nt]);
+    }
+    P = N;
+    u = next;
   }
-  // over the four wavefronts, in order
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     bs[k] += __shfl_xor(bs[k], 16);
     bs[k] += __shfl_xor(bs[k], 32);
-    if (lane < 16) s_b[wave][2 * lane + k] = GCH == 32 || lane == 0 ? bs[k] : 0.f;
+    if (ky == 0 && lane < 16) s_b[grp][2 * lane + k] = GCH == 32 || lane == 0 ? bs[k] : 0.f;
   }
-  for (int w = 1; w < 4; ++w) {
-    __syncthreads();
-    if (wave == w) {
+  for (int half = kWGroups / 2; half > 0; half >>= 1) {
+    if (grp >= half && grp < 2 * half) {
 #pragma unroll
-      for (int f = 0; f < S::frags; ++f) s_red[f * 64 + lane] = acc[f / (2 * S::mts)][(f >> 1) % S::mts][f & 1];
+      for (int f = 0; f < FR; ++f) s_red[grp - half][ky][f * 64 + lane] = acc[f / (2 * S::mts)][(f >> 1) % S::mts][f & 1];
     }
     __syncthreads();
-    if (wave == 0) {
+    if (grp < half) {
 #pragma unroll
-      for (int f = 0; f < S::frags; ++f) acc[f / (2 * S::mts)][(f >> 1) % S::mts][f & 1] += s_red[f * 64 + lane];
+      for (int f = 0; f < FR; ++f) acc[f / (2 * S::mts)][(f >> 1) % S::mts][f & 1] += s_red[grp][ky][f * 64 + lane];
     }
+    __syncthreads();
+  }
+  if (grp == 0) {
+    f32x4* const o = reinterpret_cast<f32x4*>(part) + ((size_t)blockIdx.x * 3 + ky) * FR * 64;
+#pragma unroll
+    for (int f = 0; f < FR; ++f) o[f * 64 + lane] = acc[f / (2 * S::mts)][(f >> 1) % S::mts][f & 1];
+  }
+  if (threadIdx.x < 32) {
+    float t = 0.f;
+#pragma unroll
+    for (int k = 0; k < kWGroups; ++k) t += s_b[k][threadIdx.x];
+    partb[(size_t)blockIdx.x * 32 + threadIdx.x] = t;
+  }
+}
+
+// the first layer: X of eight channels, 32-channel G, stride 2, dilation 1
+__global__ __launch_bounds__(64 * kWWaves0) void k_conv_bwd_w0(const uint16_t* __restrict__ G,
+                                                              const uint16_t* __restrict__ X, int rows, int Ho, int Wo,
+                                                              int H, int W, float4* __restrict__ part,
+                                                              float* __restrict__ partb) {
+  using S = WGrad<8, 32>;
+  constexpr int kCols = 65, kQuads = 3 * kCols, kLoads = (kQuads + 63) / 64;
+  union Smem {
+    uint4 x[kWWaves0][kQuads];                    // rows 2 oy - 1 .., columns 64 xb - 1 ..
+    f32x4 red[kWWaves0 / 2][S::frags * 64];
+  };
+  __shared__ Smem s;
+  __shared__ float s_b[kWWaves0][32];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = lane & 15, g = lane >> 4;
+  const int nxb = (Wo + 31) >> 5;
+  const int64_t units = (int64_t)rows * nxb;
+  const int u0 = (int)(units * blockIdx.x / gridDim.x), u1 = (int)(units * (blockIdx.x + 1) / gridDim.x);
+  f32x4 acc[S::slots][2][2];
+#pragma unroll
+  for (int i = 0; i < S::slots; ++i)
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt) acc[i][mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float bs[2] = {0.f, 0.f};
+  // this lane's words: tap 4 i + m / 4, channels 2 (m % 4), + 1
+  const uint32_t* word[S::slots];
+  bool tapok[S::slots];
+#pragma unroll
+  for (int i = 0; i < S::slots; ++i) {
+    const int tap = 4 * i + (m >> 2);
+    tapok[i] = tap < 9;
+    word[i] = reinterpret_cast<const uint32_t*>(&s.x[wave][min(tap, 8) / 3 * kCols + min(tap, 8) % 3 + 2 * g]) + (m & 3);
+  }
+  struct Piece {
+    uint32_t gd[8];
+    uint4 x[kLoads];
+  };
+  auto load = [&](int u) {
+    Piece P;
+    const int row = u / nxb, xb = u - row * nxb, b = row / Ho, oy = row - b * Ho;
+    load_g<32>(G, row, xb, Wo, m, g, P.gd);
+    const uint16_t* img = X + (size_t)b * H * W * 8;
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k) {
+      const int e = lane + 64 * k, r = e / kCols, iy = 2 * oy - 1 + r, ix = 64 * xb - 1 + e - r * kCols;
+      const uint4 v = *reinterpret_cast<const uint4*>(
+          img + (size_t)((uint32_t)clampi(iy, 0, H - 1) * (uint32_t)W + (uint32_t)clampi(ix, 0, W - 1)) * 8);
+      P.x[k] = (uint32_t)iy < (uint32_t)H && (uint32_t)ix < (uint32_t)W ? v : make_uint4(0, 0, 0, 0);
+    }
+    return P;
+  };
+  int u = u0 + wave;
+  Piece P;
+  if (u < u1) P = load(u);
+  while (u < u1) {
+    // this wavefront's own rows: no other one reads them
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k)
+      if (lane + 64 * k < kQuads) s.x[wave][lane + 64 * k] = P.x[k];
+    wave_lds_order();
+    const int next = u + kWWaves0;
+    Piece N;
+    if (next < u1) N = load(next);
+    bf16x8 A[2];
+    g_frags<32>(P.gd, m, A);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      bs[0] += bf2f((uint16_t)P.gd[j]);
+      bs[1] += bf2f((uint16_t)(P.gd[j] >> 16));
+    }
+#pragma unroll
+    for (int i = 0; i < S::slots; ++i) {
+      uint32_t xd[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {   // pixel g + 4 j, its tap's column 2 (g + 4 j) + kx
+        const uint32_t w = word[i][j * 8 * 4];
+        xd[j] = tapok[i] ? w : 0u;
+      }
+      const bf16x8 B[2] = {halves(xd, kLowHalf), halves(xd, kHighHalf)};
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) acc[i][mt][nt] = mfma32(A[mt], B[nt], acc[i][mt][nt]);
+    }
+    wave_lds_order();
+    P = N;
+    u = next;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    bs[k] += __shfl_xor(bs[k], 16);
+    bs[k] += __shfl_xor(bs[k], 32);
+    if (lane < 16) s_b[wave][2 * lane + k] = bs[k];
+  }
+  for (int half = kWWaves0 / 2; half > 0; half >>= 1) {
+    if (wave >= half && wave < 2 * half) {
+#pragma unroll
+      for (int f = 0; f < S::frags; ++f) s.red[wave - half][f * 64 + lane] = acc[f / 4][(f >> 1) & 1][f & 1];
+    }
+    __syncthreads();
+    if (wave < half) {
+#pragma unroll
+      for (int f = 0; f < S::frags; ++f) acc[f / 4][(f >> 1) & 1][f & 1] += s.red[wave][f * 64 + lane];
+    }
+    __syncthreads();
   }
   if (wave == 0) {
     f32x4* const o = reinterpret_cast<f32x4*>(part) + (size_t)blockIdx.x * S::frags * 64;
 #pragma unroll
-    for (int f = 0; f < S::frags; ++f) o[f * 64 + lane] = acc[f / (2 * S::mts)][(f >> 1) % S::mts][f & 1];
+    for (int f = 0; f < S::frags; ++f) o[f * 64 + lane] = acc[f / 4][(f >> 1) & 1][f & 1];
   }
-  if (threadIdx.x < 32)
-    partb[(size_t)blockIdx.x * 32 + threadIdx.x] =
-        s_b[0][threadIdx.x] + s_b[1][threadIdx.x] + s_b[2][threadIdx.x] + s_b[3][threadIdx.x];
+  if (threadIdx.x < 32) {
+    float t = 0.f;
+#pragma unroll
+    for (int k = 0; k < kWWaves0; ++k) t += s_b[k][threadIdx.x];
+    partb[(size_t)blockIdx.x * 32 + threadIdx.x] = t;
+  }
 }
 
 // ---------------------------------------------------------------- gradient sums, Adam
@@ -687,7 +835,8 @@ static NetPlan net_plan(int Bn, int W, int H) {
     // partials are a third of the others', one at those (fixed for a given
     // size: run-to-run identical sums)
     const int64_t units = (int64_t)Bn * P.H[l + 1] * ((P.W[l + 1] + 31) / 32);
-    P.runs[l] = (int)std::min<int64_t>((units + 3) / 4, l == 0 ? 512 : 256);
+    P.runs[l] = l == 0 ? (int)std::min<int64_t>((units + kWWaves0 - 1) / kWWaves0, 512)
+                       : (int)std::min<int64_t>((units + kWGroups - 1) / kWGroups, 256);
     P.frags[l] = l == 0                ? WGrad<8, 32>::frags
                  : l == kNetLayers - 1 ? WGrad<32, 8>::frags
                                        : WGrad<32, 32>::frags;
@@ -702,11 +851,11 @@ static NetPlan net_plan(int Bn, int W, int H) {
   return P;
 }
 
-// grid of a convolution launch: a wavefront per tile, and as many as the chip
-// holds at most (three to four wavefronts per SIMD by registers)
-static unsigned conv_blocks(int rows, int Wo) {
+// grid of a convolution launch: a wavefront per tile, and at most as many as
+// the chip holds (per_cu workgroups on a CU, by registers)
+static unsigned conv_blocks(int rows, int Wo, int per_cu) {
   const int64_t tiles = (int64_t)rows * ((Wo + 15) / 16);
-  return (unsigned)std::min<int64_t>((tiles + 3) / 4, 1024);
+  return (unsigned)std::min<int64_t>((tiles + 3) / 4, 256 * per_cu);
 }
 
 // everything up to the network's output (fp32; flow, prop: see ConvArgs).
@@ -749,7 +898,7 @@ static void enqueue_forward(const NetPlan& P, int Bn, const float* theta, const 
     c.dil = L.dil;
     c.relu = L.relu;
     c.cout = L.cout;
-    const unsigned blocks = conv_blocks(c.rows, c.Wo);
+    const unsigned blocks = conv_blocks(c.rows, c.Wo, l == 0 ? 5 : l + 1 == kNetLayers ? 3 : 2);
     if (l + 1 == kNetLayers) {
       c.yf = reinterpret_cast<float*>(ws + P.off_x[l + 1]);
       c.flow = flow;
@@ -836,18 +985,19 @@ ff_status ff_proposal_train_step(float* params, float* adam_m, float* adam_v, in
     const int H = P.H[l], W = P.W[l], Ho = P.H[l + 1], Wo = P.W[l + 1], rows = batch * Ho;
     float4* part = reinterpret_cast<float4*>(ws + P.off_part[l]);
     float* partb = reinterpret_cast<float*>(ws + P.off_partb[l]);
-    if (l == 0) k_conv_bwd_w<8, 32, 2><<<P.runs[l], 256, 0, stream>>>(G, X, rows, Ho, Wo, H, W, L.dil, part, partb);
+    constexpr int tpb = 64 * 3 * kWGroups;
+    if (l == 0) k_conv_bwd_w0<<<P.runs[l], 64 * kWWaves0, 0, stream>>>(G, X, rows, Ho, Wo, H, W, part, partb);
     else if (l + 1 == kNetLayers)
-      k_conv_bwd_w<32, 8, 1><<<P.runs[l], 256, 0, stream>>>(G, X, rows, Ho, Wo, H, W, L.dil, part, partb);
+      k_conv_bwd_w<8, 1><<<P.runs[l], tpb, 0, stream>>>(G, X, rows, Ho, Wo, H, W, L.dil, part, partb);
     else if (L.stride == 2)
-      k_conv_bwd_w<32, 32, 2><<<P.runs[l], 256, 0, stream>>>(G, X, rows, Ho, Wo, H, W, L.dil, part, partb);
+      k_conv_bwd_w<32, 2><<<P.runs[l], tpb, 0, stream>>>(G, X, rows, Ho, Wo, H, W, L.dil, part, partb);
     else
-      k_conv_bwd_w<32, 32, 1><<<P.runs[l], 256, 0, stream>>>(G, X, rows, Ho, Wo, H, W, L.dil, part, partb);
+      k_conv_bwd_w<32, 1><<<P.runs[l], tpb, 0, stream>>>(G, X, rows, Ho, Wo, H, W, L.dil, part, partb);
     if (l == 0) break;
     uint16_t* gprev = reinterpret_cast<uint16_t*>(ws + P.off_g[l]);
     const uint4* wbt = reinterpret_cast<const uint4*>(ws + P.off_wbt[l]);
     if (L.stride == 2) {   // dilation 1
-      k_conv_bwd2<<<conv_blocks(rows, Wo), 256, 0, stream>>>(G, rows, Ho, Wo, H, W, wbt, X, gprev);
+      k_conv_bwd2<<<conv_blocks(rows, Wo, 3), 256, 0, stream>>>(G, rows, Ho, Wo, H, W, wbt, X, gprev);
       continue;
     }
     ConvArgs c{};
@@ -860,8 +1010,8 @@ ff_status ff_proposal_train_step(float* params, float* adam_m, float* adam_v, in
     c.W = c.Wo = W;
     c.stride = 1;
     c.dil = -L.dil;
-    if (l + 1 == kNetLayers) k_conv<8, 2, true><<<conv_blocks(rows, W), 256, 0, stream>>>(c);
-    else k_conv<32, 2, true><<<conv_blocks(rows, W), 256, 0, stream>>>(c);
+    if (l + 1 == kNetLayers) k_conv<8, 2, true><<<conv_blocks(rows, W, 5), 256, 0, stream>>>(c);
+    else k_conv<32, 2, true><<<conv_blocks(rows, W, 2), 256, 0, stream>>>(c);
   }
   a.grad_out = grad_out;
   a.loss_out = loss_out;
