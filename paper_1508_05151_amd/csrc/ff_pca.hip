@@ -214,13 +214,17 @@ __device__ __forceinline__ double rcp_f64(double q) {
 
 // Householder reduction to tridiagonal form.  Thread (r, s) holds row r,
 // columns s + 8 m of the matrix in registers; a step's column (a row, the
-// matrix being symmetric) and the product with the reflector go through LDS,
-// two barriers per step; every wavefront forms the norms and dot products it
-// needs by itself.  Bound: the chain of 126 steps.
+// matrix being symmetric), the reflector's scalars and the product with it go
+// through LDS, three barriers per step.  Step k leaves columns below 8 (k / 8) and rows up to k as
+// they are (nothing reads them again): a wavefront whose eight rows are done
+// only keeps the barriers.  Bound: the chain of 126 steps.  260 us with
+// every column and wavefront in every step and the scalars in each of them,
+// 187 without the finished ones, 182 now.
 __global__ __launch_bounds__(1024) void k_eig_tri(const double* __restrict__ raw, double* __restrict__ scratch) {
-  __shared__ double xs[2][kDim], ps[kDim];
+  __shared__ double xs[2][kDim], ps[kDim], part[16], par[2];
   const EigScratch S = eig_scratch(scratch);
   const int tid = threadIdx.x, r = tid >> 3, s = tid & 7, lane = tid & 63;
+  const int rlast = __builtin_amdgcn_readfirstlane(r | 7);   // of this wavefront
   const double* mean = raw + kMat;
   if (tid < 3) S.mx[tid] = 0ull;
   double a[16];
@@ -240,51 +244,70 @@ __global__ __launch_bounds__(1024) void k_eig_tri(const double* __restrict__ raw
       if (s == sk) x[r] = a[mk];
       __syncthreads();
       if (k >= kDim - 2) {
-        if (tid == 0) {
+        if (tid == kDim * 8 - 64) {
           S.d[k] = x[k];
           S.e[k] = k + 1 < kDim ? x[k + 1] : 0.0;
           S.tau[k] = 0.0;
         }
         continue;
       }
-      const double x1 = x[lane], x2 = x[lane + 64], x0 = x[k + 1];
-      const double sig = wave_sum_f64((lane > k + 1 ? x1 * x1 : 0.0) + (lane + 64 > k + 1 ? x2 * x2 : 0.0));
-      double tau = 0.0, beta = x0;
-      if (sig > 0.0) {   // the same in every thread
-        const double nrm = sqrt(fma(x0, x0, sig));
-        beta = x0 > 0.0 ? -nrm : nrm;
-        tau = (beta - x0) / beta;
-        const double sc = 1.0 / (x0 - beta);
-        auto vof = [&](int i, double xi) { return i > k + 1 ? xi * sc : (i == k + 1 ? 1.0 : 0.0); };
-        const double vr = vof(r, x[r]);
-        double vc[16], p = 0.0;
+      // the last wavefront, which is on in every step, forms the reflector's
+      // scalars once (a root and two quotients, which sixteen wavefronts would
+      // queue for)
+      if (r >= kDim - 8) {
+        const double x0 = x[k + 1], x1 = x[lane], x2 = x[lane + 64];
+        const double sig = wave_sum_f64((lane > k + 1 ? x1 * x1 : 0.0) + (lane + 64 > k + 1 ? x2 * x2 : 0.0));
+        double beta = x0, tau = 0.0, sc = 0.0;
+        if (sig > 0.0) {
+          const double nrm = sqrt(fma(x0, x0, sig));
+          beta = x0 > 0.0 ? -nrm : nrm;
+          tau = (beta - x0) / beta;
+          sc = 1.0 / (x0 - beta);
+        }
+        if (lane == 0) {
+          par[0] = tau;
+          par[1] = sc;
+          S.d[k] = x[k];
+          S.e[k] = beta;
+          S.tau[k] = tau;
+        }
+      }
+      __syncthreads();
+      const double tau = par[0], sc = par[1];   // tau = 0: the column is reduced already
+      const bool on = rlast > k && tau != 0.0;
+      double vr = 0.0, vc[16], pr = 0.0;
+      if (on) {
+        auto vof = [&](int i) { return i > k + 1 ? x[i] * sc : (i == k + 1 ? 1.0 : 0.0); };
+        vr = vof(r);
+        double p = 0.0;
 #pragma unroll
-        for (int m = 0; m < 16; ++m) {
-          vc[m] = vof(s + 8 * m, x[s + 8 * m]);
+        for (int m = mk; m < 16; ++m) {
+          vc[m] = vof(s + 8 * m);
           p = fma(a[m], vc[m], p);
         }
         // over the row's eight threads
         p += dpp_f64<0xB1>(p);
         p += dpp_f64<0x4E>(p);
         p += dpp_f64<0x141>(p);
-        if (s == 0) {
-          ps[r] = tau * p;
-          S.V[k * kDim + r] = vr;
-        }
-        __syncthreads();
-        const double dot = wave_sum_f64(fma(ps[lane], vof(lane, x1), ps[lane + 64] * vof(lane + 64, x2)));
-        const double K = 0.5 * tau * dot;
-        const double wr = fma(-K, vr, ps[r]);
+        pr = tau * p;
+        if (s == 0) ps[r] = pr;
+      }
+      // this wavefront's share of p v
+      {
+        double t = s == 0 ? pr * vr : 0.0;
+        t = wave_sum_f64(t);
+        if (lane == 0) part[tid >> 6] = t;
+      }
+      if (s == 0) S.V[k * kDim + r] = vr;
+      __syncthreads();
+      if (on) {
+        const double K = 0.5 * tau * row16_sum_f64(part[lane & 15]);
+        const double wr = fma(-K, vr, pr);
 #pragma unroll
-        for (int m = 0; m < 16; ++m) {
+        for (int m = mk; m < 16; ++m) {
           const double wc = fma(-K, vc[m], ps[s + 8 * m]);
           a[m] = fma(-vr, wc, fma(-wr, vc[m], a[m]));
         }
-      }
-      if (tid == 0) {
-        S.d[k] = x[k];
-        S.e[k] = beta;
-        S.tau[k] = tau;
       }
     }
 }
@@ -295,14 +318,18 @@ __global__ __launch_bounds__(1024) void k_eig_tri(const double* __restrict__ raw
 // outwards from the row with the smallest twist pivot, and the reflectors in
 // reverse.  Column 127 - i of X.
 __global__ __launch_bounds__(256) void k_eig_vec(double* __restrict__ scratch) {
-  __shared__ double d[kDim], e[kDim], e2[kDim];
+  __shared__ double d[kDim], e[kDim];
+  __shared__ double2 de[kDim], ed[kDim];   // d_j with e_(j-1)^2, and with e_j^2
+  __shared__ double2 sc[kDim];             // de of the scaled form
   __shared__ double qf[4][kDim], qb[4][kDim], z[4][kDim];
   const EigScratch S = eig_scratch(scratch);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   if (threadIdx.x < kDim) {
     d[threadIdx.x] = S.d[threadIdx.x];
     e[threadIdx.x] = S.e[threadIdx.x];
-    e2[threadIdx.x] = S.e[threadIdx.x] * S.e[threadIdx.x];
+    const int up = threadIdx.x > 0 ? threadIdx.x - 1 : 0;
+    de[threadIdx.x] = make_double2(S.d[threadIdx.x], S.e[up] * S.e[up]);
+    ed[threadIdx.x] = make_double2(S.d[threadIdx.x], S.e[threadIdx.x] * S.e[threadIdx.x]);
   }
   __syncthreads();
   const int i = blockIdx.x * 4 + wave;
@@ -319,13 +346,45 @@ __global__ __launch_bounds__(256) void k_eig_vec(double* __restrict__ scratch) {
   hi += wide;
   const double tiny = 1e-290;
   auto guard = [&](double q) { return fabs(q) < tiny ? -tiny : q; };
+  // Eigenvalues below x: sign changes of the leading minors' determinants
+  // p_j = (d_j - x) p_(j-1) - e_(j-1)^2 p_(j-2), one fused multiply-add of
+  // latency per row (the quotients' recurrence has a reciprocal in it: 131 ->
+  // 112 us).  T is scaled by a power of two to a radius of one, p every eight
+  // rows: eight factors of at most 3, or down to 1e-19, stay in range.
+  const double rad = fmax(fabs(lo), fabs(hi));
+  const int ex = rad > 0.0 ? __builtin_amdgcn_frexp_exp(rad) : 0;
+  lo = ldexp(lo, -ex);
+  hi = ldexp(hi, -ex);
+  if (threadIdx.x < kDim)
+    sc[threadIdx.x] = make_double2(ldexp(de[threadIdx.x].x, -ex), ldexp(de[threadIdx.x].y, -2 * ex));
+  __syncthreads();
   for (int pass = 0; pass < 10; ++pass) {
     const double step = (hi - lo) * (1.0 / 65.0), x = fma((double)(lane + 1), step, lo);
-    double q = guard(d[0] - x);
-    int cnt = q < 0.0 ? 1 : 0;
-    for (int j = 1; j < kDim; ++j) {
-      q = guard((d[j] - x) - e2[j - 1] * rcp_f64(q));
-      cnt += q < 0.0 ? 1 : 0;
+    double p0 = 0.0, p1 = 1.0;   // p_(j-2), p_(j-1)
+    bool neg = false;            // the sign of p_(j-1); of zero, the opposite of the one before
+    int cnt = 0;
+#pragma unroll 1
+    for (int j = 0; j < kDim; j += 8) {
+      double2 t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) t[u] = sc[j + u];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const double p = fma(t[u].x - x, p1, -(t[u].y * p0));
+        const bool n = p < 0.0 || (p == 0.0 && !neg);
+        cnt += n != neg ? 1 : 0;
+        neg = n;
+        p0 = p1;
+        p1 = p;
+      }
+      const double big = fmax(fabs(p0), fabs(p1));
+      if (big == 0.0) {
+        p1 = neg ? -1.0 : 1.0;
+      } else {
+        const int e0 = __builtin_amdgcn_frexp_exp(big);
+        p0 = ldexp(p0, -e0);
+        p1 = ldexp(p1, -e0);
+      }
     }
     const uint64_t m = __ballot(cnt > i);
     const int f = m ? __ffsll((unsigned long long)m) - 1 : 64;
@@ -334,16 +393,24 @@ __global__ __launch_bounds__(256) void k_eig_vec(double* __restrict__ scratch) {
     lo = nlo;
     hi = nhi;
   }
-  const double lam = 0.5 * (lo + hi);
+  const double lam = ldexp(0.5 * (lo + hi), ex);
   if (lane < 2) {
     const bool up = lane == 1;   // from the bottom
     double q = guard((up ? d[kDim - 1] : d[0]) - lam);
     double* const out = up ? qb[wave] : qf[wave];
     out[up ? kDim - 1 : 0] = q;
-    for (int t = 1; t < kDim; ++t) {
-      const int j = up ? kDim - 1 - t : t;
-      q = guard((d[j] - lam) - e2[up ? j : j - 1] * rcp_f64(q));
-      out[j] = q;
+    const double2* const co = up ? ed : de;
+#pragma unroll 1
+    for (int t0 = 1; t0 < kDim; t0 += 8) {
+      double2 t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) t[u] = co[up ? max(kDim - 1 - t0 - u, 0) : min(t0 + u, kDim - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (t0 + u == kDim) break;
+        q = guard((t[u].x - lam) - t[u].y * rcp_f64(q));
+        out[up ? kDim - 1 - t0 - u : t0 + u] = q;
+      }
     }
   }
   __syncthreads();
@@ -372,11 +439,20 @@ __global__ __launch_bounds__(256) void k_eig_vec(double* __restrict__ scratch) {
   }
   __syncthreads();
   if (lane < 2) {
+    // lane 0 up from row k (the ratio there is 1), lane 1 down from it
+    const int dir = lane == 0 ? -1 : 1, n = lane == 0 ? k + 1 : kDim - 1 - k;
+    const int at = lane == 0 ? k : k + 1;
     double v = 1.0;
-    if (lane == 0) {
-      for (int j = k; j >= 0; --j) z[wave][j] = v = j == k ? 1.0 : v * qf[wave][j];
-    } else {
-      for (int j = k + 1; j < kDim; ++j) z[wave][j] = v = v * qf[wave][j];
+#pragma unroll 1
+    for (int t0 = 0; t0 < n; t0 += 8) {
+      double f[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) f[u] = qf[wave][at + dir * min(t0 + u, n - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        v *= f[u];
+        if (t0 + u < n) z[wave][at + dir * (t0 + u)] = v;
+      }
     }
   }
   __syncthreads();
@@ -384,8 +460,10 @@ __global__ __launch_bounds__(256) void k_eig_vec(double* __restrict__ scratch) {
   const double inv = 1.0 / sqrt(wave_sum_f64(fma(z1, z1, z2 * z2)));
   z1 *= inv;
   z2 *= inv;
-  // reflect back, four reflectors' loads in flight
-  double v1[4], v2[4], tq[4];
+  // reflect back, kAhead reflectors' loads in flight
+  constexpr int kAhead = 14;
+  static_assert((kDim - 2) % kAhead == 0, "whole rounds");
+  double v1[kAhead], v2[kAhead], tq[kAhead];
   auto fetch = [&](int kk, int b) {
     const int c = kk < 0 ? 0 : kk;
     v1[b] = S.V[c * kDim + lane];
@@ -393,16 +471,17 @@ __global__ __launch_bounds__(256) void k_eig_vec(double* __restrict__ scratch) {
     tq[b] = kk < 0 ? 0.0 : S.tau[c];
   };
 #pragma unroll
-  for (int b = 0; b < 4; ++b) fetch(kDim - 3 - b, b);
-  for (int kk = kDim - 3; kk >= 0; kk -= 4) {
+  for (int b = 0; b < kAhead; ++b) fetch(kDim - 3 - b, b);
+#pragma unroll 1
+  for (int kk = kDim - 3; kk >= 0; kk -= kAhead) {
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
+    for (int b = 0; b < kAhead; ++b) {
       if (tq[b] != 0.0) {   // uniform; no reflector was stored otherwise
         const double f = tq[b] * wave_sum_f64(fma(v1[b], z1, v2[b] * z2));
         z1 = fma(-f, v1[b], z1);
         z2 = fma(-f, v2[b], z2);
       }
-      fetch(kk - 4 - b, b);
+      fetch(kk - kAhead - b, b);
     }
   }
   S.X[lane * kDim + kDim - 1 - i] = z1;
