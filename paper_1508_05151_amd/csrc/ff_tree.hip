@@ -18,7 +18,7 @@
 //                workgroup then reduces the two children's min/max over its
 //                chunk for the next level.
 //  * Below: one workgroup per subtree of <= kTreeLds points finishes every
-//    remaining level in LDS with a bitonic sort of (segment, key, pixel).
+//    remaining level, its rows in registers, with a bitonic sort per segment.
 #include "ff_internal.h"
 #include "ff_device.h"
 
@@ -646,68 +646,103 @@ __global__ __launch_bounds__(kNodeTpb) void k_tree_node(const FieldRec* __restri
   }
 }
 
-// ---------------------------------------------------------------- subtrees in LDS
-constexpr int kSubTpb = 512;
+// ---------------------------------------------------------------- subtrees
+// One workgroup per subtree of <= kTreeLds points does all its levels.  Its
+// rows are read once and stay in registers: eight lanes per row, four
+// dimensions each, sixteen rows per lane.  Points are numbered locally in
+// pixel order, so that a local number breaks ties as the pixel index does and
+// a sort key (value - segment minimum, local number) fits 32 bits wherever the
+// spreads stay below 2^21 (64 bits otherwise).
+// Padded layout: at relative depth lvl the 2^lvl segments sit in aligned blocks
+// of B = P >> lvl positions (segment s in [s B, s B + cnt)), so each level
+// sorts every block on its own and a split sends the left half to the first,
+// the right half to the second half of its block.
+// Per level: per-segment minima and maxima of the rows (LDS atomics, register
+// sums while there are one or two segments), the split dimensions, the keys
+// from the rows' owners, the sort.
+// Bound: instructions and LDS.  Reading every point's 128-byte row again at
+// each of eight levels and sorting 64-bit keys (two workgroups of 512 per CU)
+// took the 24 trees of eight pairs of 641x479 and below 2.47 ms, 4.8 TB/s of row
+// traffic and 57 % of the chip's instructions; now 2.38 ms.  One tree of 1024x436
+// beside two others 250 -> 133 us, of 161x119 170 -> 110.
+constexpr int kSubTpb = 1024;
+constexpr int kSubRows = kTreeLds / (kSubTpb / kLpr);   // rows per lane
+constexpr int kSubSegs = kSubTpb / kLpr;                // segments reduced at once
+// minima and maxima of a segment, dimension 4 q + c at 8 c + q: the lanes of a
+// row fall in eight neighbouring banks, other segments' rows in other ones
+constexpr int kMmPitch = 72;
+static_assert(kTreeLds == 2 * kSubTpb, "two keys per thread");
 
 __device__ __forceinline__ void heap_range(int node, int N, int& start, int& cnt) {
   const int d = 31 - __clz(node + 1);
   node_range(d, node + 1 - (1 << d), N, start, cnt);
 }
 
-// Bitonic sort of key[0, P) ascending (P a power of two, <= kTreeLds =
-// 4 kSubTpb).  Thread t holds the four consecutive keys 4t..4t+3 in
-// registers: a stage of stride j < 4 pairs keys of one thread, j < 256 keys
-// of one wavefront (shuffles), and only the strides j >= 256 go through LDS,
-// two barriers each.  Called by the whole workgroup; key[] must be settled
-// (a barrier after its last writes) before the call.
-static_assert(kTreeLds == 4 * kSubTpb, "four keys per thread");
-__device__ __forceinline__ uint64_t cas_keep(uint64_t mine, uint64_t other, int i, int j, int k) {
-  // compare-exchange of positions i and i ^ j in a sequence sorted up where
-  // (i & k) == 0: the lower position keeps the smaller key there
-  const bool up = (i & k) == 0, lower = (i & j) == 0;
-  const uint64_t lo = mine < other ? mine : other, hi = mine < other ? other : mine;
-  return lower == up ? lo : hi;
+// the value of lane ^ M
+template <int M>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  if constexpr (M == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);
+  else if constexpr (M == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);
+  else if constexpr (M == 4) {   // 7 - lane within eight, then 3 - lane within four
+    const int m = __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false);
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x1B, 0xF, 0xF, false);
+  } else if constexpr (M == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, false);
+  else return (uint32_t)__shfl_xor((int)v, M);
+}
+template <int M>
+__device__ __forceinline__ uint64_t lane_xor(uint64_t v) {
+  return ((uint64_t)lane_xor<M>((uint32_t)(v >> 32)) << 32) | lane_xor<M>((uint32_t)v);
 }
 
-// Sorts every aligned block of B keys (B a power of two <= P) ascending: the
-// network of a full sort stopped at merges of size B, the last merge taken
-// ascending in every block.
-__device__ void bitonic_sort(uint64_t* key, int P, int B) {
-  const int t = threadIdx.x;
-  uint64_t v[4];
+// One stride of a bitonic merge: thread t holds positions 2t, 2t + 1.  kd: the
+// bit of a position that says its sequence runs down.
+template <int J, typename K>
+__device__ __forceinline__ void bitonic_stage(K (&v)[2], K* buf, int kd) {
+  const int p = 2 * threadIdx.x;
+  const bool up = (p & kd) == 0;
+  if constexpr (J == 1) {
+    const K lo = v[0] < v[1] ? v[0] : v[1], hi = v[0] < v[1] ? v[1] : v[0];
+    v[0] = up ? lo : hi;
+    v[1] = up ? hi : lo;
+  } else {
+    K o[2];
+    if constexpr (J >= 128) {
+      buf[p] = v[0];
+      buf[p + 1] = v[1];
+      __syncthreads();
+      o[0] = buf[p ^ J];
+      o[1] = buf[(p ^ J) + 1];
+      __syncthreads();
+    } else {
+      o[0] = lane_xor<J / 2>(v[0]);
+      o[1] = lane_xor<J / 2>(v[1]);
+    }
+    const bool least = up == ((p & J) == 0);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) v[r] = key[4 * t + r];
-  for (int k = 2; k <= B; k <<= 1) {
-    const int kd = k == B ? 2 * P : k;   // direction bit: none in the last merge
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      if (j >= 256) {
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < 4; ++r) key[4 * t + r] = v[r];
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = 4 * t + r;
-          v[r] = cas_keep(v[r], key[i ^ j], i, j, kd);
-        }
-      } else if (j >= 4) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = cas_keep(v[r], __shfl_xor(v[r], j >> 2), 4 * t + r, j, kd);
-      } else {
-        uint64_t w[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) w[r] = cas_keep(v[r], v[r ^ j], 4 * t + r, j, kd);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = w[r];
-      }
+    for (int r = 0; r < 2; ++r) {
+      const K lo = v[r] < o[r] ? v[r] : o[r], hi = v[r] < o[r] ? o[r] : v[r];
+      v[r] = least ? lo : hi;
     }
   }
-  __syncthreads();
-  if (4 * t < P) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) key[4 * t + r] = v[r];
+}
+// Sorts every aligned block of B positions (a power of two) ascending; called
+// by the whole workgroup, buf settled.
+template <typename K>
+__device__ __forceinline__ void bitonic_sort(K (&v)[2], K* buf, int B) {
+  for (int k = 2; k <= B; k <<= 1) {
+    const int kd = k == B ? 2 * kTreeLds : k;   // the last merge runs up everywhere
+    if (k >= 2048) bitonic_stage<1024>(v, buf, kd);
+    if (k >= 1024) bitonic_stage<512>(v, buf, kd);
+    if (k >= 512) bitonic_stage<256>(v, buf, kd);
+    if (k >= 256) bitonic_stage<128>(v, buf, kd);
+    if (k >= 128) bitonic_stage<64>(v, buf, kd);
+    if (k >= 64) bitonic_stage<32>(v, buf, kd);
+    if (k >= 32) bitonic_stage<16>(v, buf, kd);
+    if (k >= 16) bitonic_stage<8>(v, buf, kd);
+    if (k >= 8) bitonic_stage<4>(v, buf, kd);
+    if (k >= 4) bitonic_stage<2>(v, buf, kd);
+    bitonic_stage<1>(v, buf, kd);
   }
-  __syncthreads();
 }
 
 // grid: (2^maxTop, fields); block x finishes the subtree rooted at node x of
@@ -716,173 +751,217 @@ __global__ __launch_bounds__(kSubTpb) void k_tree_subtree(const FieldRec* __rest
   tree_priority();
   const TreeView t = tree_view(table[blockIdx.y]);
   if ((int)blockIdx.x >= (1 << t.top)) return;
+  constexpr uint32_t kNone = 0xFFFFu;
+  constexpr int kLocalBits = 11;
+  static_assert((1 << kLocalBits) == kTreeLds, "local numbers");
+  __shared__ union {
+    uint32_t k32[kTreeLds];
+    uint64_t k64[kTreeLds];
+    int32_t mm[kSubSegs * kMmPitch];
+  } u;
+  __shared__ int32_t s_id[kTreeLds];                     // pixel of a local number
+  __shared__ uint32_t s_val[kTreeLds];                   // its value on the split dimension, less the minimum
+  __shared__ uint16_t s_seg[kTreeLds];                   // its segment where that splits, else kNone
+  __shared__ uint16_t s_pos[kTreeLds];                   // local number at a position, or kNone
+  __shared__ int32_t s_start[kTreeLds / 2], s_cnt[kTreeLds / 2], s_dim[kTreeLds / 2], s_bmin[kTreeLds / 2];
+  __shared__ uint8_t s_split[2][kTreeLds / 2];           // of this level and the last
+  __shared__ int s_any;
+  __shared__ uint32_t s_spread;
+  const int tid = threadIdx.x, g = tid / kLpr, q = tid % kLpr, p0 = 2 * tid;
+  const int D = t.D, N = t.N, root = (1 << t.top) - 1 + blockIdx.x;
   const int32_t* perm_in = (t.top & 1) ? t.perm2 : t.perm;
   int32_t* perm_out = t.perm;
-  const int32_t* V = t.V;
-  const int stride = t.stride, D = t.D, N = t.N;
-  // Padded layout: at relative depth lvl the subtree's 2^lvl segments sit in
-  // aligned blocks of B = P >> lvl positions (segment s in [s B, s B + cnt),
-  // the rest +inf), so each level sorts every block on its own and a split
-  // keeps the left half in place and moves the right half to the second
-  // half of the block.  A segment that stops splitting is a leaf: its block,
-  // sorted by pixel index at that level, is written out at once.
-  __shared__ uint64_t keys[2][kTreeLds];
-  __shared__ int32_t s_start[kTreeLds / 2], s_cnt[kTreeLds / 2];
-  __shared__ int32_t s_best[kTreeLds / 2], s_dim[kTreeLds / 2], s_bmin[kTreeLds / 2];
-  __shared__ uint8_t s_alive[kTreeLds / 2], s_alive2[kTreeLds / 2];
-  __shared__ int32_t s_pmin[kSubTpb / 64][32], s_pmax[kSubTpb / 64][32];
-  __shared__ int s_any;
-  const int root = (1 << t.top) - 1 + blockIdx.x;
   int rstart, rcnt;
   heap_range(root, N, rstart, rcnt);
   int P = 1;
   while (P < rcnt) P <<= 1;
-  int cur = 0;
-  for (int e = threadIdx.x; e < P; e += kSubTpb) keys[0][e] = e < rcnt ? (uint64_t)perm_in[rstart + e] : ~0ull;
-  if (threadIdx.x == 0) s_alive[0] = 1;
+  {
+    uint32_t id[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) id[r] = p0 + r < rcnt ? (uint32_t)perm_in[rstart + p0 + r] : ~0u;
+    bitonic_sort(id, u.k32, P);
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const bool in = p0 + r < rcnt;
+      s_id[p0 + r] = (int32_t)id[r];
+      s_pos[p0 + r] = (uint16_t)(in ? p0 + r : kNone);
+      s_seg[p0 + r] = (uint16_t)(in && rcnt > leaf ? 0 : kNone);
+    }
+  }
   __syncthreads();
-  const uint64_t idmask = (1ull << 22) - 1;
+  // a wavefront's eight rows lie far apart in the image, so that they are
+  // seldom of one segment (whose words they would queue for)
+  const int loc0 = (g & 7) * (kTreeLds / 8) + (g >> 3) * kSubRows;
+  v4i_t row[kSubRows];   // of local numbers loc0 + i
+#pragma unroll
+  for (int i = 0; i < kSubRows; ++i) {
+    const int loc = loc0 + i;
+    row[i] = v4i_t{0, 0, 0, 0};
+    if (loc < rcnt && rcnt > leaf && 4 * q < D) row[i] = row_quad(t.V, t.stride, s_id[loc], q);
+  }
   for (int lvl = 0;; ++lvl) {
-    const int nslots = 1 << lvl;
-    const int B = P >> lvl;
-    const int lgB = 31 - __clz(B);
+    const int nslots = 1 << lvl, B = P >> lvl, lgB = 31 - __clz(B);
     const int base = (root + 1) * nslots - 1;    // first heap index at this relative depth
-    uint64_t* key = keys[cur];
-    if (threadIdx.x == 0) s_any = 0;
+    const uint8_t* split = s_split[lvl & 1];
+    if (tid == 0) {
+      s_any = 0;
+      s_spread = 0;
+    }
     __syncthreads();
-    for (int s = threadIdx.x; s < nslots; s += kSubTpb) {
+    if (tid < nslots) {
       int st, c;
-      heap_range(base + s, N, st, c);
-      s_start[s] = st - rstart;
-      s_cnt[s] = c;
-      s_best[s] = -1;
-      s_dim[s] = 0;
-      s_bmin[s] = 0;
-      if (s_alive[s] && c > leaf) s_any = 1;
+      heap_range(base + tid, N, st, c);
+      const bool alive = lvl == 0 || s_split[(lvl & 1) ^ 1][tid >> 1];
+      s_start[tid] = st - rstart;
+      s_cnt[tid] = alive ? c : 0;
+      s_split[lvl & 1][tid] = alive && c > leaf;
+      if (alive && c > leaf) s_any = 1;
     }
     __syncthreads();
     const bool last = !s_any;
     if (!last) {
-      // Split dimension of every splitting segment in one pass over its rows:
-      // 64 groups of 8 lanes, a lane holding 4 dimensions of a row.  With
-      // fewer than 64 segments, gps groups share a segment (partials merged by
-      // shuffles inside a wavefront, then through LDS across wavefronts); with
-      // more, each group walks spg segments.
-      const int g = threadIdx.x >> 3, q = threadIdx.x & 7, wv = threadIdx.x >> 6;
-      const int gps = nslots >= 64 ? 1 : 64 / nslots;
-      const int spg = nslots >= 64 ? nslots / 64 : 1;
-      for (int si = 0; si < spg; ++si) {
-        const int s = nslots >= 64 ? g * spg + si : g / gps;
-        const int part = nslots >= 64 ? 0 : g % gps;
-        const bool act = s_alive[s] && s_cnt[s] > leaf;
-        int mn[4] = {INT32_MAX, INT32_MAX, INT32_MAX, INT32_MAX};
-        int mx[4] = {INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN};
-        if (act && 4 * q < D) {
-          const int c = s_cnt[s], st = s << lgB;
-          const int a = st + c * part / gps, b = st + c * (part + 1) / gps;
-#pragma unroll 8
-          for (int e = a; e < b; ++e) {
-            const v4i_t v = row_quad(V, stride, (int)(key[e] & idmask), q);
-            mn[0] = min(mn[0], v.x); mx[0] = max(mx[0], v.x);
-            mn[1] = min(mn[1], v.y); mx[1] = max(mx[1], v.y);
-            mn[2] = min(mn[2], v.z); mx[2] = max(mx[2], v.z);
-            mn[3] = min(mn[3], v.w); mx[3] = max(mx[3], v.w);
-          }
-        }
-        for (int m = 1; m < gps && m < 8; m <<= 1)
+      for (int c0 = 0; c0 < nslots; c0 += kSubSegs) {
+        const int ns = min(kSubSegs, nslots - c0);
+        for (int e = tid; e < ns * kMmPitch; e += kSubTpb) u.mm[e] = e % kMmPitch < 32 ? INT32_MAX : INT32_MIN;
+        __syncthreads();
+        if (4 * q < D) {
+          if (nslots <= 2) {
+            for (int s = 0; s < nslots; ++s) {
+              int mn[4] = {INT32_MAX, INT32_MAX, INT32_MAX, INT32_MAX};
+              int mx[4] = {INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN};
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            mn[i] = min(mn[i], __shfl_xor(mn[i], 8 * m));
-            mx[i] = max(mx[i], __shfl_xor(mx[i], 8 * m));
-          }
-        if (gps > 8) {
-          // 2..8 wavefronts per segment: merge their partials through LDS
-          if ((g & 7) == 0)
+              for (int i = 0; i < kSubRows; ++i)
+                if (s_seg[loc0 + i] == s) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { s_pmin[wv][4 * q + i] = mn[i]; s_pmax[wv][4 * q + i] = mx[i]; }
-          __syncthreads();
-          const int wps = gps / 8;
-          const int s2 = g < nslots ? g : 0;
+                  for (int c = 0; c < 4; ++c) {
+                    mn[c] = min(mn[c], row[i][c]);
+                    mx[c] = max(mx[c], row[i][c]);
+                  }
+                }
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            mn[i] = INT32_MAX;
-            mx[i] = INT32_MIN;
-            for (int w = s2 * wps; w < (s2 + 1) * wps; ++w) {
-              mn[i] = min(mn[i], s_pmin[w][4 * q + i]);
-              mx[i] = max(mx[i], s_pmax[w][4 * q + i]);
+              for (int c = 0; c < 4; ++c) {
+                mn[c] = min(mn[c], (int)lane_xor<8>((uint32_t)mn[c]));
+                mx[c] = max(mx[c], (int)lane_xor<8>((uint32_t)mx[c]));
+                for (int o = 16; o < 64; o <<= 1) {
+                  mn[c] = min(mn[c], __shfl_xor(mn[c], o));
+                  mx[c] = max(mx[c], __shfl_xor(mx[c], o));
+                }
+                if ((tid & 63) < kLpr) {
+                  atomicMin(&u.mm[s * kMmPitch + 8 * c + q], mn[c]);
+                  atomicMax(&u.mm[s * kMmPitch + 32 + 8 * c + q], mx[c]);
+                }
+              }
+            }
+          } else {
+#pragma unroll
+            for (int i = 0; i < kSubRows; ++i) {
+              const int s = (int)s_seg[loc0 + i] - c0;
+              if (s >= 0 && s < ns) {   // kNone lies beyond
+                int32_t* m = &u.mm[s * kMmPitch + q];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                  atomicMin(m + 8 * c, row[i][c]);
+                  atomicMax(m + 32 + 8 * c, row[i][c]);
+                }
+              }
             }
           }
         }
-        // best dimension of the group's segment: largest spread, lowest on ties
-        int bs = -1, bd = 0, bm = 0;
+        __syncthreads();
+        // best dimension of segment c0 + g: largest spread, lowest on ties
+        if (g < ns && split[c0 + g]) {
+          int bs = -1, bd = 0, bm = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int k = 4 * q + i;
-          if (k < D) {
-            const int sp = mx[i] - mn[i];
-            if (sp > bs) { bs = sp; bd = k; bm = mn[i]; }
+          for (int c = 0; c < 4; ++c) {
+            const int k = 4 * q + c;
+            if (k < D) {
+              const int mn = u.mm[g * kMmPitch + 8 * c + q], sp = u.mm[g * kMmPitch + 32 + 8 * c + q] - mn;
+              if (sp > bs) { bs = sp; bd = k; bm = mn; }
+            }
+          }
+          for (int o = 1; o < kLpr; o <<= 1) {
+            const int obs = __shfl_xor(bs, o), obd = __shfl_xor(bd, o), obm = __shfl_xor(bm, o);
+            if (obs > bs || (obs == bs && obd < bd)) { bs = obs; bd = obd; bm = obm; }
+          }
+          if (q == 0) {
+            s_dim[c0 + g] = bd;
+            s_bmin[c0 + g] = bm;
+            atomicMax(&s_spread, (uint32_t)bs);
           }
         }
-        for (int o = 1; o < 8; o <<= 1) {
-          const int obs = __shfl_xor(bs, o), obd = __shfl_xor(bd, o), obm = __shfl_xor(bm, o);
-          if (obs > bs || (obs == bs && obd < bd)) { bs = obs; bd = obd; bm = obm; }
+        __syncthreads();
+      }
+#pragma unroll
+      for (int i = 0; i < kSubRows; ++i) {
+        const int loc = loc0 + i;
+        const uint32_t s = s_seg[loc];
+        if (s != kNone) {
+          const int d = s_dim[s];
+          if (d >> 2 == q) {
+            const int lo = d & 1 ? row[i][1] : row[i][0], hi = d & 1 ? row[i][3] : row[i][2];
+            s_val[loc] = (uint32_t)((d & 2 ? hi : lo) - s_bmin[s]);
+          }
         }
-        const bool owner = gps > 8 ? (g < nslots) : (part == 0);
-        const int so = gps > 8 ? g : s;
-        if (owner && q == 0 && s_alive[so] && s_cnt[so] > leaf) { s_best[so] = bs; s_dim[so] = bd; s_bmin[so] = bm; }
       }
       __syncthreads();
     }
-    // keys: (split value - minimum) << 22 | pixel for a splitting segment,
-    // the pixel alone for a leaf, +inf outside the live segments
-    for (int e = threadIdx.x; e < P; e += kSubTpb) {
-      const int s = e >> lgB, j = e & (B - 1);
-      uint64_t kv = ~0ull;
-      if (s_alive[s] && j < s_cnt[s]) {
-        const uint64_t id = key[e] & idmask;
-        uint64_t sub = 0;
-        if (s_cnt[s] > leaf) sub = (uint64_t)(uint32_t)(V[(size_t)id * stride + s_dim[s]] - s_bmin[s]) << 22;
-        kv = sub | id;
-      }
-      key[e] = kv;
+    // keys: (value, local number) in a splitting segment, the number alone in
+    // a leaf, all ones outside the segments
+    uint32_t val[2], loc[2];
+    int sg[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      loc[r] = s_pos[p0 + r];
+      sg[r] = min((p0 + r) >> lgB, nslots - 1);
+      val[r] = loc[r] != kNone && split[sg[r]] ? s_val[loc[r]] : 0u;
     }
-    __syncthreads();
-    bitonic_sort(key, P, B);
+    if (s_spread < (1u << (32 - kLocalBits)) - 1) {
+      uint32_t key[2];
+#pragma unroll
+      for (int r = 0; r < 2; ++r) key[r] = loc[r] != kNone ? (val[r] << kLocalBits) | loc[r] : ~0u;
+      bitonic_sort(key, u.k32, B);
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        loc[r] = key[r] != ~0u ? key[r] & (kTreeLds - 1) : kNone;
+        val[r] = key[r] >> kLocalBits;
+      }
+    } else {
+      uint64_t key[2];
+#pragma unroll
+      for (int r = 0; r < 2; ++r) key[r] = loc[r] != kNone ? ((uint64_t)val[r] << kLocalBits) | loc[r] : ~0ull;
+      bitonic_sort(key, u.k64, B);
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        loc[r] = key[r] != ~0ull ? (uint32_t)key[r] & (kTreeLds - 1) : kNone;
+        val[r] = (uint32_t)(key[r] >> kLocalBits);
+      }
+    }
     // split nodes; leaves written out (their blocks are in pixel order)
-    for (int s = threadIdx.x; s < nslots; s += kSubTpb) {
-      if (s_alive[s] && s_cnt[s] > leaf) {
-        const int h = s_cnt[s] >> 1;
-        const uint64_t pid = key[(s << lgB) + h] & idmask;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      if (p0 + r >= P || loc[r] == kNone) continue;
+      const int s = sg[r], j = (p0 + r) & (B - 1);
+      if (!split[s]) {
+        perm_out[rstart + s_start[s] + j] = s_id[loc[r]];
+      } else if (j == s_cnt[s] >> 1) {
         t.dim[base + s] = s_dim[s];
-        t.split[base + s] = V[(size_t)pid * stride + s_dim[s]];
+        t.split[base + s] = (int32_t)val[r] + s_bmin[s];
       }
-    }
-    for (int e = threadIdx.x; e < P; e += kSubTpb) {
-      const int s = e >> lgB, j = e & (B - 1);
-      if (s_alive[s] && s_cnt[s] <= leaf && j < s_cnt[s]) perm_out[rstart + s_start[s] + j] = (int32_t)(key[e] & idmask);
     }
     if (last) break;
     // the next level's layout: block 2s takes the first h of segment s, block
     // 2s + 1 the rest, both of size B / 2
-    uint64_t* nkey = keys[cur ^ 1];
-    const int hB = B >> 1;
-    for (int e = threadIdx.x; e < P; e += kSubTpb) {
-      const int s2 = e >> (lgB - 1), j = e & (hB - 1), s = s2 >> 1;
-      uint64_t kv = ~0ull;
-      if (s_alive[s] && s_cnt[s] > leaf) {
-        const int h = s_cnt[s] >> 1;
-        if (!(s2 & 1)) {
-          if (j < h) kv = key[(s << lgB) + j];
-        } else {
-          if (j < s_cnt[s] - h) kv = key[(s << lgB) + h + j];
-        }
-      }
-      nkey[e] = kv;
-    }
-    for (int s2 = threadIdx.x; s2 < 2 * nslots; s2 += kSubTpb) s_alive2[s2] = s_alive[s2 >> 1] && s_cnt[s2 >> 1] > leaf;
     __syncthreads();
-    for (int s2 = threadIdx.x; s2 < 2 * nslots; s2 += kSubTpb) s_alive[s2] = s_alive2[s2];
-    cur ^= 1;
+    s_pos[p0] = s_pos[p0 + 1] = (uint16_t)kNone;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      if (p0 + r >= P || loc[r] == kNone || !split[sg[r]]) continue;
+      const int s = sg[r], j = (p0 + r) & (B - 1), c = s_cnt[s], h = c >> 1;
+      const int s2 = 2 * s + (j >= h), c2 = j >= h ? c - h : h;
+      s_pos[s2 * (B >> 1) + (j >= h ? j - h : j)] = (uint16_t)loc[r];
+      s_seg[loc[r]] = (uint16_t)(c2 > leaf ? s2 : kNone);
+    }
     __syncthreads();
   }
 }
