@@ -637,29 +637,319 @@ struct SweepArgs {
   int inbuf;         // grid buffer read; the other one is written
 };
 
-// S = 2r+1, or 0: the field's own (up to 31); LEV: the level, or -1: any
-template <int S, int LEV>
-__global__ __launch_bounds__(64) void k_sweep(const FieldRec* __restrict__ table, SweepArgs a, RelaxQ q) {
+// LDS of a sweep's workgroup.  RM: the largest radius; even pitches: the rows
+// of a step lie a pitch -+ 1 apart, so their words fall in different banks.
+template <int RM>
+struct SweepPitch {
+  static constexpr int row = kTileW + kTileH + 2 * RM, col = (kTileH + 2 * RM + 4) & ~1;
+};
+constexpr int kPitchOwn = kTileW + 1;
+template <int RM>
+struct SweepSmem {
+  uint32_t row[(kTileH + 2 * RM + 1) * SweepPitch<RM>::row];       // source census, row-major
+  uint32_t col[(kTileW + kTileH + 2 * RM) * SweepPitch<RM>::col];  // and column-major
+  int2 own[kTileH * kPitchOwn];                                    // own values
+  int2 res[kTileH * kPitchOwn];                                    // results, on entry those of the visit before
+  int2 left[kTileH], top[kTileW + 2];                              // border values: flow, 2 cost + changed
+};
+
+// One visit of tile gt (number in the launch) of field f; returns the next
+// tile this workgroup owns, or -1.  S = 2r+1, or 0: the field's own (up to 31);
+// LEV: the level, or -1: any.  first: no earlier visit of this tile in this
+// launch.
+template <int S, int LEV, int RMS>
+__device__ __forceinline__ int sweep_visit(const FieldRec& f, const SweepArgs& a, const RelaxQ& q, SweepSmem<RMS>& sm,
+                                           int gt, bool first, int& done) {
   constexpr int RM = S ? S / 2 : kMaxRadius;
+  static_assert(RM <= RMS, "the workgroup's LDS");
   constexpr int CW = S ? S / 4 : 1;      // words of a line per lane, one more word per line left over (S = 4 CW + 1)
   constexpr bool kWide = S && LEV == 0;  // consecutive words
   static_assert(S == 0 || S % 4 == 1, "line split");
-  // even pitches: the rows of a step lie a pitch -+ 1 apart, so their words
-  // fall in different banks
-  constexpr int P1 = kTileW + kTileH + 2 * RM, P2 = (kTileH + 2 * RM + 4) & ~1;
-  constexpr int kPitchOwn = kTileW + 1;
-  __shared__ uint32_t s_row[(kTileH + 2 * RM + 1) * P1];          // source census, row-major
-  __shared__ uint32_t s_col[(kTileW + kTileH + 2 * RM) * P2];     // and column-major
-  __shared__ int2 s_own[kTileH * kPitchOwn];                      // own values
-  __shared__ int2 s_res[kTileH * kPitchOwn];                      // results, on entry those of the visit before
-  __shared__ int2 s_left[kTileH], s_top[kTileW + 2];              // border values: flow, 2 cost + changed
+  constexpr int P1 = SweepPitch<RM>::row, P2 = SweepPitch<RM>::col;
+  uint32_t *const s_row = sm.row, *const s_col = sm.col;
+  int2 *const s_own = sm.own, *const s_res = sm.res, *const s_left = sm.left, *const s_top = sm.top;
   const int lane = threadIdx.x;
   const int lev = LEV >= 0 ? LEV : a.lev;
   const int n = 1 << lev;
   const int sx = a.sx, sy = a.sy;
-  // the first visits are dealt out in turn; then queued tiles
+  const CostCtx c = ctx_of(f, lev, a.qshift);
+  const int r = S ? S / 2 : c.r;
+  const int Sd = 2 * r + 1;
+  const int Q = c.Q;
+  const int Gw = (f.Ws + n - 1) >> lev, Gh = (f.Hs + n - 1) >> lev;
+  const int g0 = f.t0[lev], tile = gt - g0;
+  const int nu = tiles_x(Gw), nv = tiles_y(Gh);
+  const int tv = tile / nu, tu = tile - tv * nu;
+  const int u0 = tu * kTileW, v0 = tv * kTileH;
+  int32_t* const cnt = reinterpret_cast<int32_t*>(f.ws + f.o_st[lev]);
+  const int have = ld_coh(cnt + tile) - a.base;   // requests this visit answers
+  const int32_t* const inF = grid_flow(f, lev, a.inbuf);
+  const int32_t* const inC = grid_cost(f, lev, a.inbuf);
+  auto gx_of = [&](int u) { return sx > 0 ? u : Gw - 1 - u; };
+  auto gy_of = [&](int v) { return sy > 0 ? v : Gh - 1 - v; };
+  auto pidx = [&](int u, int v) { return gy_of(v) * Gw + gx_of(u); };
+  // own values, four points per lane (points outside the grid: EMPTY)
+  const int lx = lane & 15, ly = lane >> 4;
+  int32_t of[4], oc[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int p = pidx(clampi(u0 + lx - k * 4 - ly, 0, Gw - 1), min(v0 + k * 4 + ly, Gh - 1));
+    of[k] = gp(inF)[p];
+    oc[k] = gp(inC)[p];
+  }
+  // a tile visited before: its results, and the border flows they came from
+  int32_t* const outF = grid_flow(f, lev, a.inbuf ^ 1);
+  int32_t* const outC = grid_cost(f, lev, a.inbuf ^ 1);
+  int32_t* const was = reinterpret_cast<int32_t*>(f.ws + f.o_seen) + tile * 32;
+  int32_t pf[4], pc[4], wasF = 0;
+  if (!first) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int p = pidx(clampi(u0 + lx - k * 4 - ly, 0, Gw - 1), min(v0 + k * 4 + ly, Gh - 1));
+      pf[k] = ld_coh(outF + p);
+      pc[k] = ld_coh(outC + p);
+    }
+    wasF = ld_coh(was + (lane & 31));
+  }
+  // the source census under the tile's patches, in ascending grid
+  // coordinates from (gxm, gym), clamped to the image in pixels; lane
+  // (ly, lx) takes the samples at rows ly + 4 k, columns lx + 16 j
+  const int TH = kTileH + 2 * r + 1, TW = kTileW + kTileH + 2 * r;
+  constexpr int NK = (kTileH + 2 * RM + 1 + 3) / 4, NJ = (kTileW + kTileH + 2 * RM + 15) / 16;
+  const int gxm = sx > 0 ? u0 - kTileH - r : Gw - kTileW - u0 - r;
+  const int gym = sy > 0 ? v0 - r - 1 : Gh - kTileH - v0 - r;
+  int scol[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) scol[j] = clampi((gxm + lx + 16 * j) * n, 0, c.Ws - 1);
+  auto stage = [&](auto K0, auto K1) {
+    uint32_t w[K1.value - K0.value][NJ];
+#pragma unroll
+    for (int k = K0.value; k < K1.value; ++k) {
+      const int row = clampi((gym + ly + 4 * k) * n, 0, c.Hs - 1) * c.Ws;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) w[k - K0.value][j] = gp(c.src)[row + scol[j]];
+    }
+#pragma unroll
+    for (int k = K0.value; k < K1.value; ++k)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int y = ly + 4 * k, x = lx + 16 * j;
+        if (y < TH && x < TW) {
+          s_row[y * P1 + x] = w[k - K0.value][j];
+          s_col[x * P2 + y] = w[k - K0.value][j];
+        }
+      }
+  };
+  stage(std::integral_constant<int, 0>{}, std::integral_constant<int, NK / 2>{});
+  // the neighbours' border values: lanes 0..15 the column left of row
+  // `lane`, lanes 16..31 the row above; and this tile's own border words,
+  // its right column and its bottom row.  Read after the request counter.
+  uint64_t* const xr = reinterpret_cast<uint64_t*>(f.ws + f.o_xr);
+  uint64_t* const xb = reinterpret_cast<uint64_t*>(f.ws + f.o_xb);
+  const bool isl = lane < 16;
+  const int bl = lane & 15;
+  const int hu = isl ? u0 - bl - 1 : u0 + bl, hv = isl ? v0 + bl : v0 - 1;
+  const bool hok = lane < 32 && hu >= 0 && hu < Gw && hv >= 0 && hv < Gh;
+  const int ou = isl ? u0 + 15 - bl : u0 + bl - 15, ov = isl ? v0 + bl : v0 + 15;
+  const bool ook = lane < 32 && ou >= 0 && ou < Gw && ov < Gh && (isl ? tu + 1 < nu : tv + 1 < nv);
+  const int handled = __builtin_amdgcn_readfirstlane(have);
+  mem_wait();
+  uint64_t hw = 0;
+  int32_t hf = kEmpty, hc = kInf;
+  if (hok) {
+    hw = ld_coh(isl ? xr + (size_t)(tu - 1) * Gh + hv : xb + (size_t)(tv - 1) * Gw + hu);
+    hf = gp(inF)[pidx(hu, hv)];
+    hc = gp(inC)[pidx(hu, hv)];
+  }
+  stage(std::integral_constant<int, NK / 2>{}, std::integral_constant<int, NK>{});
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int u = u0 + lx - k * 4 - ly;
+    const bool ok = u >= 0 && u < Gw && v0 + k * 4 + ly < Gh;
+    const int2 own = ok ? make_int2(of[k], oc[k]) : make_int2(kEmpty, kInf);
+    s_own[(k * 4 + ly) * kPitchOwn + lx] = own;
+    s_res[(k * 4 + ly) * kPitchOwn + lx] = first || !ok ? own : make_int2(pf[k], pc[k]);
+  }
+  if ((uint32_t)(hw >> 48) == a.tag) {
+    const uint32_t c16 = (uint32_t)(hw >> 32) & 0xFFFFu;
+    hf = (int32_t)(uint32_t)hw;
+    hc = c16 == 0xFFFFu ? kInf : (int32_t)c16;
+  }
+  // cost doubled, the low bit marks a value that this tile has not seen
+  // (EMPTY's cost is never used)
+  if (lane < 32) (isl ? s_left : s_top)[bl] = make_int2(hf, (int)((uint32_t)hc << 1) | (first || hf != wasF ? 1 : 0));
+  if (lane == 32) s_top[kTileW] = make_int2(kEmpty, 0);
+  __syncthreads();
+  // what the readers of this tile's border hold so far
+  const int oidx = isl ? bl * kPitchOwn + 15 : 15 * kPitchOwn + bl;
+  int2 seen = s_res[oidx];
+  asm volatile("" : "+v"(seen.x), "+v"(seen.y));   // read before the steps overwrite it
+  // ---- the steps
+  const int i = lane >> 2, j = lane & 3;
+  g_byte* const tgt = (g_byte*)(c.dst);
+  const uint32_t dT = (uint32_t)(c.dstT - c.dst);   // transposed planes after the row-major ones
+  const int Wm = c.Wd - 1, Hm = c.Hd - 1;
+  const uint32_t Wd = (uint32_t)c.Wd, Hd = (uint32_t)c.Hd;
+  const uint32_t maxMx = (uint32_t)(Wm * Q), maxMy = (uint32_t)(Hm * Q);
+  const int rn = r * n;
+  const int offX0 = -sx * (r + 1) * n, offX1 = sx * rn, offY0 = -sy * (r + 1) * n, offY1 = sy * rn;
+  const int vi = v0 + i, gyi = gy_of(vi), gx0 = gx_of(u0 - i);
+  const int js = kWide ? CW * j : j;                // the lane's first word of a line
+  const int jt = (kWide ? CW * j : j * n) - rn;     // and its place in the target's
+  const uint32_t* spv = s_row + (gyi - sy * (r + 1) - gym) * P1 + (gx0 - r - gxm) + js;
+  const uint32_t* sph = s_col + (gx0 - sx * (r + 1) - gxm) * P2 + (gyi - r - gym) + js;
+  const int eV = sy * Sd * P1, eH = sx * Sd * P2;   // from a leaving line to the entering one
+  // the last word of line j (S = 4 CW + 1)
+  const uint32_t* spt = (j < 2 ? spv + (j & 1) * eV : sph + (j & 1) * eH) + (S - 1 - js);
+  const int32_t tmul = (j & 1 ? 1 : -1) * (j >= 2 ? 65536 : 1);
+  const int tailOff = (S - 1) * n - rn - jt;
+  const int nQshift = lev + c.qshift;
+  const int pyq = gyi << nQshift;
+  int pxq = gx0 << nQshift;
+  int uL = vi < Gh ? u0 - i : -(1 << 20);
+  int2 h = s_left[i], v = i == 0 ? s_top[0] : s_left[i > 0 ? i - 1 : 0];
+  // LDS values are read a step ahead of their use
+  int2 ownN = s_own[i * kPitchOwn], oldN = s_res[i * kPitchOwn], topN = s_top[1];
+  const bool roomX = Wm >= 2 * rn, roomY = Hm >= 2 * rn;   // else every line clamps
+#pragma unroll 1
+  for (int t = 0; t < kTileW; ++t) {
+    const int2 own = ownN, old = oldN, top = topN;
+    ownN = s_own[i * kPitchOwn + t + 1];
+    oldN = s_res[i * kPitchOwn + t + 1];
+    topN = s_top[t + 2];
+    const int mxv = pxq + fx_of(v.x), myv = pyq + fy_of(v.x), mxh = pxq + fx_of(h.x), myh = pyq + fy_of(h.x);
+    // EMPTY (-32768, -32768) lies outside, so this rejects it too
+    // a point none of whose inputs changed keeps its result
+    const bool in = ((uint32_t)uL < (uint32_t)Gw) & (((v.y | h.y) & 1) != 0);
+    const bool useV = in & (v.x != own.x) & ((uint32_t)mxv <= maxMx) & ((uint32_t)myv <= maxMy);
+    const bool useH = in & (h.x != own.x) & ((uint32_t)mxh <= maxMx) & ((uint32_t)myh <= maxMy);
+    int2 res = in ? own : old;
+    if (__ballot(useV || useH)) {
+      const int Mxv = mxv >> c.qshift, Myv = myv >> c.qshift, Mxh = mxh >> c.qshift, Myh = myh >> c.qshift;
+      // every product has both factors below 2^24 (plane words <= 2^22,
+      // phase < 64, coordinates and pitches < 8192)
+      const uint32_t plv = __umul24(c.pw, (uint32_t)(((myv & c.qmask) << c.qshift) + (mxv & c.qmask)));
+      const uint32_t plh = dT + __umul24(c.pw, (uint32_t)(((myh & c.qmask) << c.qshift) + (mxh & c.qmask)));
+      uint32_t l0 = plv + __umul24(clamp0(Myv + offY0, Hm), Wd), l1 = plv + __umul24(clamp0(Myv + offY1, Hm), Wd);
+      uint32_t l2 = plh + __umul24(clamp0(Mxh + offX0, Wm), Hd), l3 = plh + __umul24(clamp0(Mxh + offX1, Wm), Hd);
+      uint32_t lea = 0, ent = 0, leaH = 0, entH = 0, tail = 0;
+      const bool clampV = (uint32_t)(Mxv - rn) > (uint32_t)(Wm - 2 * rn);
+      const bool clampH = (uint32_t)(Myh - rn) > (uint32_t)(Hm - 2 * rn);
+      if (S && roomX && roomY && __ballot((useV & clampV) | (useH & clampH)) == 0) {
+        // no sample of a candidate in use clamps; the lanes of a candidate
+        // that is not read word 0
+        l0 = useV ? l0 + (uint32_t)(Mxv + jt) : 0;
+        l1 = useV ? l1 + (uint32_t)(Mxv + jt) : 0;
+        l2 = useH ? l2 + (uint32_t)(Myh + jt) : 0;
+        l3 = useH ? l3 + (uint32_t)(Myh + jt) : 0;
+        const uint32_t lt = j < 2 ? (j & 1 ? l1 : l0) : (j & 1 ? l3 : l2);
+        uint32_t w0[CW], w1[CW], w2[CW], w3[CW];
+        load_line<CW, kWide, LEV>(tgt, l0 << 2, lev, w0);
+        load_line<CW, kWide, LEV>(tgt, l1 << 2, lev, w1);
+        load_line<CW, kWide, LEV>(tgt, l2 << 2, lev, w2);
+        load_line<CW, kWide, LEV>(tgt, l3 << 2, lev, w3);
+        const uint32_t wt = tword(tgt, lt + (uint32_t)((j < 2 ? useV : useH) ? tailOff : 0));
+#pragma unroll
+        for (int m = 0; m < CW; ++m) {
+          const int k = kWide ? m : 4 * m;
+          lea += __popc(w0[m] ^ spv[k]);
+          ent += __popc(w1[m] ^ spv[eV + k]);
+          leaH += __popc(w2[m] ^ sph[k]);
+          entH += __popc(w3[m] ^ sph[eH + k]);
+        }
+        tail = __popc(wt ^ *spt);
+        asm volatile("" : "+v"(tail));   // keeps this branch's loads in it
+      } else {
+        if (S) {
+          // all loads first: one round trip
+          uint32_t x[4][CW];
+#pragma unroll
+          for (int m = 0; m < CW; ++m) {
+            const int o = (js + (kWide ? m : 4 * m)) * n - rn;
+            const uint32_t xv = clamp0(Mxv + o, Wm), yh = clamp0(Myh + o, Hm);
+            x[0][m] = tword(tgt, l0 + xv);
+            x[1][m] = tword(tgt, l1 + xv);
+            x[2][m] = tword(tgt, l2 + yh);
+            x[3][m] = tword(tgt, l3 + yh);
+          }
+          const uint32_t lt = j < 2 ? (j & 1 ? l1 : l0) : (j & 1 ? l3 : l2);
+          const uint32_t wt = tword(tgt, lt + clamp0((j < 2 ? Mxv : Myh) + rn, j < 2 ? Wm : Hm));
+#pragma unroll
+          for (int m = 0; m < CW; ++m) {
+            const int k = kWide ? m : 4 * m;
+            lea += __popc(x[0][m] ^ spv[k]);
+            ent += __popc(x[1][m] ^ spv[eV + k]);
+            leaH += __popc(x[2][m] ^ sph[k]);
+            entH += __popc(x[3][m] ^ sph[eH + k]);
+          }
+          tail = __popc(wt ^ *spt);
+        } else {
+          for (int k = 0; k < Sd - js; k += 4) {
+            const int o = (js + k) * n - rn;
+            const uint32_t xv = clamp0(Mxv + o, Wm), yh = clamp0(Myh + o, Hm);
+            lea += __popc(tword(tgt, l0 + xv) ^ spv[k]);
+            ent += __popc(tword(tgt, l1 + xv) ^ spv[eV + k]);
+            leaH += __popc(tword(tgt, l2 + yh) ^ sph[k]);
+            entH += __popc(tword(tgt, l3 + yh) ^ sph[eH + k]);
+          }
+        }
+      }
+      // vertical sum in the low half, horizontal in the high half
+      // (|sums| < 2^15), over the row's four lanes
+      int32_t d = (int32_t)(ent - lea) + (int32_t)((entH - leaH) << 16) + __mul24((int32_t)tail, tmul);
+      d += __builtin_amdgcn_update_dpp(0, d, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
+      d += __builtin_amdgcn_update_dpp(0, d, 0x4E, 0xF, 0xF, false);   // quad_perm [2,3,0,1]
+      const int32_t dV = (int32_t)(int16_t)(uint16_t)((uint32_t)d & 0xFFFFu), dH = (d - dV) >> 16;
+      // candidate order of Eq. 2: current, vertical, horizontal; strict <
+      const int costV = (v.y >> 1) + dV, costH = (h.y >> 1) + dH;
+      if (useV && costV < res.y) res = make_int2(v.x, costV);
+      if (useH && costH < res.y) res = make_int2(h.x, costH);
+    }
+    s_res[i * kPitchOwn + t] = res;
+    // next step's candidates: horizontal the row's own result, vertical the
+    // result of the row above (four lanes down; across a 16-lane DPP row
+    // its last lane's value; the top row from the border)
+    h = make_int2(res.x, (int)((uint32_t)res.y << 1) | (first || res.x != old.x ? 1 : 0));
+    v.x = __builtin_amdgcn_update_dpp(top.x, h.x, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v.y = __builtin_amdgcn_update_dpp(top.y, h.y, 0x114, 0xF, 0xF, false);
+    v.x = __builtin_amdgcn_update_dpp(v.x, h.x, 0x142, 0xE, 0x1, false);     // row_bcast:15
+    v.y = __builtin_amdgcn_update_dpp(v.y, h.y, 0x142, 0xE, 0x1, false);
+    pxq += sx * (1 << nQshift);
+    spv += sx;
+    sph += sx * P2;
+    spt += j < 2 ? sx : sx * P2;
+    ++uL;
+  }
+  __syncthreads();
+  // ---- results out, changed border words published
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int u = u0 + lx - k * 4 - ly, v = v0 + k * 4 + ly;
+    if (u >= 0 && u < Gw && v < Gh) {
+      const int2 x = s_res[(k * 4 + ly) * kPitchOwn + lx];
+      st_coh(outF + pidx(u, v), x.x);
+      st_coh(outC + pidx(u, v), x.y);
+    }
+  }
+  if (lane < 32) st_coh(was + lane, hf);
+  const int2 now = s_res[oidx];
+  const bool chg = ook && now.x != seen.x;
+  if (chg) st_coh(isl ? xr + (size_t)tu * Gh + ov : xb + (size_t)tv * Gw + ou, xch_pack(now.x, now.y, a.tag));
+  const uint64_t cm = __ballot(chg);
+  mem_wait();
+  __syncthreads();
+  return relax_done(q, cnt, a.base, tile, nu, g0, handled, (cm & 0xFFFFu) != 0, (cm & 0x7FFF0000u) != 0,
+                    (cm & 0x80000000u) != 0, done);
+}
+
+// The visits of a workgroup: its first visits, dealt out in turn, then queued
+// tiles.
+template <typename Visit>
+__device__ __forceinline__ void sweep_tiles(const FieldRec* __restrict__ table, const SweepArgs& a, const RelaxQ& q, int lev,
+                                            Visit visit) {
+  const int lane = threadIdx.x;
   int mine = blockIdx.x, gt = mine, done = 0;
-  bool first = true;   // no earlier visit of this tile in this launch
+  bool first = true;
   do {
     // the tile's field: the last one whose first tile is not above it
     int fi = a.f0 + (a.nf == 1 ? 1 : 0);
@@ -669,275 +959,7 @@ __global__ __launch_bounds__(64) void k_sweep(const FieldRec* __restrict__ table
       fi += __popcll(__ballot(le));
     }
     fi = __builtin_amdgcn_readfirstlane(fi - 1);
-    const FieldRec& f = table[fi];
-    const CostCtx c = ctx_of(f, lev, a.qshift);
-    const int r = S ? S / 2 : c.r;
-    const int Sd = 2 * r + 1;
-    const int Q = c.Q;
-    const int Gw = (f.Ws + n - 1) >> lev, Gh = (f.Hs + n - 1) >> lev;
-    const int g0 = f.t0[lev], tile = gt - g0;
-    const int nu = tiles_x(Gw), nv = tiles_y(Gh);
-    const int tv = tile / nu, tu = tile - tv * nu;
-    const int u0 = tu * kTileW, v0 = tv * kTileH;
-    int32_t* const cnt = reinterpret_cast<int32_t*>(f.ws + f.o_st[lev]);
-    const int have = ld_coh(cnt + tile) - a.base;   // requests this visit answers
-    const int32_t* const inF = grid_flow(f, lev, a.inbuf);
-    const int32_t* const inC = grid_cost(f, lev, a.inbuf);
-    auto gx_of = [&](int u) { return sx > 0 ? u : Gw - 1 - u; };
-    auto gy_of = [&](int v) { return sy > 0 ? v : Gh - 1 - v; };
-    auto pidx = [&](int u, int v) { return gy_of(v) * Gw + gx_of(u); };
-    // own values, four points per lane (points outside the grid: EMPTY)
-    const int lx = lane & 15, ly = lane >> 4;
-    int32_t of[4], oc[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int p = pidx(clampi(u0 + lx - k * 4 - ly, 0, Gw - 1), min(v0 + k * 4 + ly, Gh - 1));
-      of[k] = gp(inF)[p];
-      oc[k] = gp(inC)[p];
-    }
-    // a tile visited before: its results, and the border flows they came from
-    int32_t* const outF = grid_flow(f, lev, a.inbuf ^ 1);
-    int32_t* const outC = grid_cost(f, lev, a.inbuf ^ 1);
-    int32_t* const was = reinterpret_cast<int32_t*>(f.ws + f.o_seen) + tile * 32;
-    int32_t pf[4], pc[4], wasF = 0;
-    if (!first) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int p = pidx(clampi(u0 + lx - k * 4 - ly, 0, Gw - 1), min(v0 + k * 4 + ly, Gh - 1));
-        pf[k] = ld_coh(outF + p);
-        pc[k] = ld_coh(outC + p);
-      }
-      wasF = ld_coh(was + (lane & 31));
-    }
-    // the source census under the tile's patches, in ascending grid
-    // coordinates from (gxm, gym), clamped to the image in pixels; lane
-    // (ly, lx) takes the samples at rows ly + 4 k, columns lx + 16 j
-    const int TH = kTileH + 2 * r + 1, TW = kTileW + kTileH + 2 * r;
-    constexpr int NK = (kTileH + 2 * RM + 1 + 3) / 4, NJ = (kTileW + kTileH + 2 * RM + 15) / 16;
-    const int gxm = sx > 0 ? u0 - kTileH - r : Gw - kTileW - u0 - r;
-    const int gym = sy > 0 ? v0 - r - 1 : Gh - kTileH - v0 - r;
-    int scol[NJ];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) scol[j] = clampi((gxm + lx + 16 * j) * n, 0, c.Ws - 1);
-    auto stage = [&](auto K0, auto K1) {
-      uint32_t w[K1.value - K0.value][NJ];
-#pragma unroll
-      for (int k = K0.value; k < K1.value; ++k) {
-        const int row = clampi((gym + ly + 4 * k) * n, 0, c.Hs - 1) * c.Ws;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) w[k - K0.value][j] = gp(c.src)[row + scol[j]];
-      }
-#pragma unroll
-      for (int k = K0.value; k < K1.value; ++k)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          const int y = ly + 4 * k, x = lx + 16 * j;
-          if (y < TH && x < TW) {
-            s_row[y * P1 + x] = w[k - K0.value][j];
-            s_col[x * P2 + y] = w[k - K0.value][j];
-          }
-        }
-    };
-    stage(std::integral_constant<int, 0>{}, std::integral_constant<int, NK / 2>{});
-    // the neighbours' border values: lanes 0..15 the column left of row
-    // `lane`, lanes 16..31 the row above; and this tile's own border words,
-    // its right column and its bottom row.  Read after the request counter.
-    uint64_t* const xr = reinterpret_cast<uint64_t*>(f.ws + f.o_xr);
-    uint64_t* const xb = reinterpret_cast<uint64_t*>(f.ws + f.o_xb);
-    const bool isl = lane < 16;
-    const int bl = lane & 15;
-    const int hu = isl ? u0 - bl - 1 : u0 + bl, hv = isl ? v0 + bl : v0 - 1;
-    const bool hok = lane < 32 && hu >= 0 && hu < Gw && hv >= 0 && hv < Gh;
-    const int ou = isl ? u0 + 15 - bl : u0 + bl - 15, ov = isl ? v0 + bl : v0 + 15;
-    const bool ook = lane < 32 && ou >= 0 && ou < Gw && ov < Gh && (isl ? tu + 1 < nu : tv + 1 < nv);
-    const int handled = __builtin_amdgcn_readfirstlane(have);
-    mem_wait();
-    uint64_t hw = 0;
-    int32_t hf = kEmpty, hc = kInf;
-    if (hok) {
-      hw = ld_coh(isl ? xr + (size_t)(tu - 1) * Gh + hv : xb + (size_t)(tv - 1) * Gw + hu);
-      hf = gp(inF)[pidx(hu, hv)];
-      hc = gp(inC)[pidx(hu, hv)];
-    }
-    stage(std::integral_constant<int, NK / 2>{}, std::integral_constant<int, NK>{});
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int u = u0 + lx - k * 4 - ly;
-      const bool ok = u >= 0 && u < Gw && v0 + k * 4 + ly < Gh;
-      const int2 own = ok ? make_int2(of[k], oc[k]) : make_int2(kEmpty, kInf);
-      s_own[(k * 4 + ly) * kPitchOwn + lx] = own;
-      s_res[(k * 4 + ly) * kPitchOwn + lx] = first || !ok ? own : make_int2(pf[k], pc[k]);
-    }
-    if ((uint32_t)(hw >> 48) == a.tag) {
-      const uint32_t c16 = (uint32_t)(hw >> 32) & 0xFFFFu;
-      hf = (int32_t)(uint32_t)hw;
-      hc = c16 == 0xFFFFu ? kInf : (int32_t)c16;
-    }
-    // cost doubled, the low bit marks a value that this tile has not seen
-    // (EMPTY's cost is never used)
-    if (lane < 32) (isl ? s_left : s_top)[bl] = make_int2(hf, (int)((uint32_t)hc << 1) | (first || hf != wasF ? 1 : 0));
-    if (lane == 32) s_top[kTileW] = make_int2(kEmpty, 0);
-    __syncthreads();
-    // what the readers of this tile's border hold so far
-    const int oidx = isl ? bl * kPitchOwn + 15 : 15 * kPitchOwn + bl;
-    int2 seen = s_res[oidx];
-    asm volatile("" : "+v"(seen.x), "+v"(seen.y));   // read before the steps overwrite it
-    // ---- the steps
-    const int i = lane >> 2, j = lane & 3;
-    g_byte* const tgt = (g_byte*)(c.dst);
-    const uint32_t dT = (uint32_t)(c.dstT - c.dst);   // transposed planes after the row-major ones
-    const int Wm = c.Wd - 1, Hm = c.Hd - 1;
-    const uint32_t Wd = (uint32_t)c.Wd, Hd = (uint32_t)c.Hd;
-    const uint32_t maxMx = (uint32_t)(Wm * Q), maxMy = (uint32_t)(Hm * Q);
-    const int rn = r * n;
-    const int offX0 = -sx * (r + 1) * n, offX1 = sx * rn, offY0 = -sy * (r + 1) * n, offY1 = sy * rn;
-    const int vi = v0 + i, gyi = gy_of(vi), gx0 = gx_of(u0 - i);
-    const int js = kWide ? CW * j : j;                // the lane's first word of a line
-    const int jt = (kWide ? CW * j : j * n) - rn;     // and its place in the target's
-    const uint32_t* spv = s_row + (gyi - sy * (r + 1) - gym) * P1 + (gx0 - r - gxm) + js;
-    const uint32_t* sph = s_col + (gx0 - sx * (r + 1) - gxm) * P2 + (gyi - r - gym) + js;
-    const int eV = sy * Sd * P1, eH = sx * Sd * P2;   // from a leaving line to the entering one
-    // the last word of line j (S = 4 CW + 1)
-    const uint32_t* spt = (j < 2 ? spv + (j & 1) * eV : sph + (j & 1) * eH) + (S - 1 - js);
-    const int32_t tmul = (j & 1 ? 1 : -1) * (j >= 2 ? 65536 : 1);
-    const int tailOff = (S - 1) * n - rn - jt;
-    const int nQshift = lev + c.qshift;
-    const int pyq = gyi << nQshift;
-    int pxq = gx0 << nQshift;
-    int uL = vi < Gh ? u0 - i : -(1 << 20);
-    int2 h = s_left[i], v = i == 0 ? s_top[0] : s_left[i > 0 ? i - 1 : 0];
-    // LDS values are read a step ahead of their use
-    int2 ownN = s_own[i * kPitchOwn], oldN = s_res[i * kPitchOwn], topN = s_top[1];
-    const bool roomX = Wm >= 2 * rn, roomY = Hm >= 2 * rn;   // else every line clamps
-#pragma unroll 1
-    for (int t = 0; t < kTileW; ++t) {
-      const int2 own = ownN, old = oldN, top = topN;
-      ownN = s_own[i * kPitchOwn + t + 1];
-      oldN = s_res[i * kPitchOwn + t + 1];
-      topN = s_top[t + 2];
-      const int mxv = pxq + fx_of(v.x), myv = pyq + fy_of(v.x), mxh = pxq + fx_of(h.x), myh = pyq + fy_of(h.x);
-      // EMPTY (-32768, -32768) lies outside, so this rejects it too
-      // a point none of whose inputs changed keeps its result
-      const bool in = ((uint32_t)uL < (uint32_t)Gw) & (((v.y | h.y) & 1) != 0);
-      const bool useV = in & (v.x != own.x) & ((uint32_t)mxv <= maxMx) & ((uint32_t)myv <= maxMy);
-      const bool useH = in & (h.x != own.x) & ((uint32_t)mxh <= maxMx) & ((uint32_t)myh <= maxMy);
-      int2 res = in ? own : old;
-      if (__ballot(useV || useH)) {
-        const int Mxv = mxv >> c.qshift, Myv = myv >> c.qshift, Mxh = mxh >> c.qshift, Myh = myh >> c.qshift;
-        // every product has both factors below 2^24 (plane words <= 2^22,
-        // phase < 64, coordinates and pitches < 8192)
-        const uint32_t plv = __umul24(c.pw, (uint32_t)(((myv & c.qmask) << c.qshift) + (mxv & c.qmask)));
-        const uint32_t plh = dT + __umul24(c.pw, (uint32_t)(((myh & c.qmask) << c.qshift) + (mxh & c.qmask)));
-        uint32_t l0 = plv + __umul24(clamp0(Myv + offY0, Hm), Wd), l1 = plv + __umul24(clamp0(Myv + offY1, Hm), Wd);
-        uint32_t l2 = plh + __umul24(clamp0(Mxh + offX0, Wm), Hd), l3 = plh + __umul24(clamp0(Mxh + offX1, Wm), Hd);
-        uint32_t lea = 0, ent = 0, leaH = 0, entH = 0, tail = 0;
-        const bool clampV = (uint32_t)(Mxv - rn) > (uint32_t)(Wm - 2 * rn);
-        const bool clampH = (uint32_t)(Myh - rn) > (uint32_t)(Hm - 2 * rn);
-        if (S && roomX && roomY && __ballot((useV & clampV) | (useH & clampH)) == 0) {
-          // no sample of a candidate in use clamps; the lanes of a candidate
-          // that is not read word 0
-          l0 = useV ? l0 + (uint32_t)(Mxv + jt) : 0;
-          l1 = useV ? l1 + (uint32_t)(Mxv + jt) : 0;
-          l2 = useH ? l2 + (uint32_t)(Myh + jt) : 0;
-          l3 = useH ? l3 + (uint32_t)(Myh + jt) : 0;
-          const uint32_t lt = j < 2 ? (j & 1 ? l1 : l0) : (j & 1 ? l3 : l2);
-          uint32_t w0[CW], w1[CW], w2[CW], w3[CW];
-          load_line<CW, kWide, LEV>(tgt, l0 << 2, lev, w0);
-          load_line<CW, kWide, LEV>(tgt, l1 << 2, lev, w1);
-          load_line<CW, kWide, LEV>(tgt, l2 << 2, lev, w2);
-          load_line<CW, kWide, LEV>(tgt, l3 << 2, lev, w3);
-          const uint32_t wt = tword(tgt, lt + (uint32_t)((j < 2 ? useV : useH) ? tailOff : 0));
-#pragma unroll
-          for (int m = 0; m < CW; ++m) {
-            const int k = kWide ? m : 4 * m;
-            lea += __popc(w0[m] ^ spv[k]);
-            ent += __popc(w1[m] ^ spv[eV + k]);
-            leaH += __popc(w2[m] ^ sph[k]);
-            entH += __popc(w3[m] ^ sph[eH + k]);
-          }
-          tail = __popc(wt ^ *spt);
-          asm volatile("" : "+v"(tail));   // keeps this branch's loads in it
-        } else {
-          if (S) {
-            // all loads first: one round trip
-            uint32_t x[4][CW];
-#pragma unroll
-            for (int m = 0; m < CW; ++m) {
-              const int o = (js + (kWide ? m : 4 * m)) * n - rn;
-              const uint32_t xv = clamp0(Mxv + o, Wm), yh = clamp0(Myh + o, Hm);
-              x[0][m] = tword(tgt, l0 + xv);
-              x[1][m] = tword(tgt, l1 + xv);
-              x[2][m] = tword(tgt, l2 + yh);
-              x[3][m] = tword(tgt, l3 + yh);
-            }
-            const uint32_t lt = j < 2 ? (j & 1 ? l1 : l0) : (j & 1 ? l3 : l2);
-            const uint32_t wt = tword(tgt, lt + clamp0((j < 2 ? Mxv : Myh) + rn, j < 2 ? Wm : Hm));
-#pragma unroll
-            for (int m = 0; m < CW; ++m) {
-              const int k = kWide ? m : 4 * m;
-              lea += __popc(x[0][m] ^ spv[k]);
-              ent += __popc(x[1][m] ^ spv[eV + k]);
-              leaH += __popc(x[2][m] ^ sph[k]);
-              entH += __popc(x[3][m] ^ sph[eH + k]);
-            }
-            tail = __popc(wt ^ *spt);
-          } else {
-            for (int k = 0; k < Sd - js; k += 4) {
-              const int o = (js + k) * n - rn;
-              const uint32_t xv = clamp0(Mxv + o, Wm), yh = clamp0(Myh + o, Hm);
-              lea += __popc(tword(tgt, l0 + xv) ^ spv[k]);
-              ent += __popc(tword(tgt, l1 + xv) ^ spv[eV + k]);
-              leaH += __popc(tword(tgt, l2 + yh) ^ sph[k]);
-              entH += __popc(tword(tgt, l3 + yh) ^ sph[eH + k]);
-            }
-          }
-        }
-        // vertical sum in the low half, horizontal in the high half
-        // (|sums| < 2^15), over the row's four lanes
-        int32_t d = (int32_t)(ent - lea) + (int32_t)((entH - leaH) << 16) + __mul24((int32_t)tail, tmul);
-        d += __builtin_amdgcn_update_dpp(0, d, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
-        d += __builtin_amdgcn_update_dpp(0, d, 0x4E, 0xF, 0xF, false);   // quad_perm [2,3,0,1]
-        const int32_t dV = (int32_t)(int16_t)(uint16_t)((uint32_t)d & 0xFFFFu), dH = (d - dV) >> 16;
-        // candidate order of Eq. 2: current, vertical, horizontal; strict <
-        const int costV = (v.y >> 1) + dV, costH = (h.y >> 1) + dH;
-        if (useV && costV < res.y) res = make_int2(v.x, costV);
-        if (useH && costH < res.y) res = make_int2(h.x, costH);
-      }
-      s_res[i * kPitchOwn + t] = res;
-      // next step's candidates: horizontal the row's own result, vertical the
-      // result of the row above (four lanes down; across a 16-lane DPP row
-      // its last lane's value; the top row from the border)
-      h = make_int2(res.x, (int)((uint32_t)res.y << 1) | (first || res.x != old.x ? 1 : 0));
-      v.x = __builtin_amdgcn_update_dpp(top.x, h.x, 0x114, 0xF, 0xF, false);   // row_shr:4
-      v.y = __builtin_amdgcn_update_dpp(top.y, h.y, 0x114, 0xF, 0xF, false);
-      v.x = __builtin_amdgcn_update_dpp(v.x, h.x, 0x142, 0xE, 0x1, false);     // row_bcast:15
-      v.y = __builtin_amdgcn_update_dpp(v.y, h.y, 0x142, 0xE, 0x1, false);
-      pxq += sx * (1 << nQshift);
-      spv += sx;
-      sph += sx * P2;
-      spt += j < 2 ? sx : sx * P2;
-      ++uL;
-    }
-    __syncthreads();
-    // ---- results out, changed border words published
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int u = u0 + lx - k * 4 - ly, v = v0 + k * 4 + ly;
-      if (u >= 0 && u < Gw && v < Gh) {
-        const int2 x = s_res[(k * 4 + ly) * kPitchOwn + lx];
-        st_coh(outF + pidx(u, v), x.x);
-        st_coh(outC + pidx(u, v), x.y);
-      }
-    }
-    if (lane < 32) st_coh(was + lane, hf);
-    const int2 now = s_res[oidx];
-    const bool chg = ook && now.x != seen.x;
-    if (chg) st_coh(isl ? xr + (size_t)tu * Gh + ov : xb + (size_t)tv * Gw + ou, xch_pack(now.x, now.y, a.tag));
-    const uint64_t cm = __ballot(chg);
-    mem_wait();
-    __syncthreads();
-    gt = relax_done(q, cnt, a.base, tile, nu, g0, handled, (cm & 0xFFFFu) != 0, (cm & 0x7FFF0000u) != 0,
-                    (cm & 0x80000000u) != 0, done);
+    gt = visit(table[fi], gt, first, done);
     first = false;
     if (gt < 0) {
       mine += q.G;
@@ -945,6 +967,27 @@ __global__ __launch_bounds__(64) void k_sweep(const FieldRec* __restrict__ table
       gt = first ? mine : relax_wait(q, done);
     }
   } while (gt >= 0);
+}
+
+// fields of one radius
+template <int S, int LEV>
+__global__ __launch_bounds__(64) void k_sweep(const FieldRec* __restrict__ table, SweepArgs a, RelaxQ q) {
+  constexpr int RM = S ? S / 2 : kMaxRadius;
+  __shared__ SweepSmem<RM> sm;
+  sweep_tiles(table, a, q, LEV >= 0 ? LEV : a.lev, [&](const FieldRec& f, int gt, bool first, int& done) {
+    return sweep_visit<S, LEV, RM>(f, a, q, sm, gt, first, done);
+  });
+}
+
+// Fields of r = 8 and of r = 6 in one launch: one chain of revisits at its end
+// instead of two (eight mixed pairs 29.5 -> 26.5 ms).
+template <int LEV>
+__global__ __launch_bounds__(64) void k_sweep_mixed(const FieldRec* __restrict__ table, SweepArgs a, RelaxQ q) {
+  __shared__ SweepSmem<8> sm;
+  sweep_tiles(table, a, q, LEV >= 0 ? LEV : a.lev, [&](const FieldRec& f, int gt, bool first, int& done) {
+    return f.r == 8 ? sweep_visit<17, LEV, 8>(f, a, q, sm, gt, first, done)
+                    : sweep_visit<13, LEV, 8>(f, a, q, sm, gt, first, done);
+  });
 }
 
 // write the grid of level lev into the full-resolution outputs (inspection
@@ -977,9 +1020,22 @@ static void launch_sweep_s(const FieldRec* table, const SweepArgs& a, const Rela
   }
 }
 
-// the paper's radii (r = 8, r2 = 6) have instances of their own
-static void launch_sweep(int r, const FieldRec* table, const SweepArgs& a, const RelaxQ& q, hipStream_t stream) {
-  if (r == 8) launch_sweep_s<17>(table, a, q, stream);
+static void launch_sweep_mixed(const FieldRec* table, const SweepArgs& a, const RelaxQ& q, hipStream_t stream) {
+  switch (a.lev) {
+    case 0: k_sweep_mixed<0><<<q.G, 64, 0, stream>>>(table, a, q); break;
+    case 1: k_sweep_mixed<1><<<q.G, 64, 0, stream>>>(table, a, q); break;
+    case 2: k_sweep_mixed<2><<<q.G, 64, 0, stream>>>(table, a, q); break;
+    case 3: k_sweep_mixed<3><<<q.G, 64, 0, stream>>>(table, a, q); break;
+    default: k_sweep_mixed<-1><<<q.G, 64, 0, stream>>>(table, a, q); break;
+  }
+}
+
+// The paper's radii (r = 8, r2 = 6) have instances of their own, and go in one
+// launch; r, rl: of the launch's first and last field.
+static bool sweep_together(int r0, int r1) { return r0 == r1 || (r0 == 8 && r1 == 6) || (r0 == 6 && r1 == 8); }
+static void launch_sweep(int r, int rl, const FieldRec* table, const SweepArgs& a, const RelaxQ& q, hipStream_t stream) {
+  if (r != rl) launch_sweep_mixed(table, a, q, stream);
+  else if (r == 8) launch_sweep_s<17>(table, a, q, stream);
   else if (r == 6) launch_sweep_s<13>(table, a, q, stream);
   else k_sweep<0, -1><<<q.G, 64, 0, stream>>>(table, a, q);
 }
@@ -1214,7 +1270,7 @@ static ff_status run_batch(const ff_field_job* jobs, int n, const ff_match_param
     maxH = std::max(maxH, recs[i].Hs);
     maxN = std::max(maxN, recs[i].Wd * recs[i].Hd);
     maxTop = std::max(maxTop, recs[i].t_top);
-    if (i > 0 && recs[i].r == recs[i - 1].r)
+    if (i > 0 && sweep_together(recs[i - 1].r, recs[i].r))
       for (int lev = 0; lev <= k; ++lev) recs[i].t0[lev] = recs[i - 1].t0[lev] + tiles_of(recs[i - 1], lev);
   }
   const int qshift = ilog2i(jobs[0].dst->subpel);
@@ -1250,12 +1306,12 @@ static ff_status run_batch(const ff_field_job* jobs, int n, const ff_match_param
   int launch = 0;
   auto sx_of = [](int i) { return ((i & 3) == 0 || (i & 3) == 3) ? 1 : -1; };
   auto sy_of = [](int i) { return ((i & 3) == 0 || (i & 3) == 2) ? 1 : -1; };
-  // sweep i of a level, one launch per patch radius
+  // sweep i of a level, one launch per patch radius (r = 8 and 6 together)
   auto sweep = [&](int lev, int i) {
     prof_mark(FF_PROF_PROPAGATE, stream, true);
     for (int f0 = 0; f0 < n;) {
       int f1 = f0;
-      while (f1 < n && recs[f1].r == recs[f0].r) ++f1;
+      while (f1 < n && (f1 == f0 || sweep_together(recs[f1 - 1].r, recs[f1].r))) ++f1;
       // request counters start at -(i + 1): every sweep of a level leaves
       // them where the next one's first visits are owed
       const SweepArgs a{f0, f1 - f0, lev, qshift, sx_of(i), sy_of(i), (uint32_t)(launch + 1), -(i + 1), buf};
@@ -1272,7 +1328,7 @@ static ff_status run_batch(const ff_field_job* jobs, int n, const ff_match_param
       q.G = std::min(q.T, f1 - f0 == 1 ? kSweepGrid / 3 : kSweepGrid);
       q.status = status;
       q.timeout = timeout;
-      launch_sweep(recs[f0].r, table, a, q, stream);
+      launch_sweep(recs[f0].r, recs[f1 - 1].r, table, a, q, stream);
       ++launch;
       f0 = f1;
     }
