@@ -778,9 +778,7 @@ class BatchMatcher:
                  use_kdtree=1, pipeline=0):
         self.shapes = list(shapes)            # (W, H) per pair
         self.C, self.r, self.r2, self.k, self.Q, self.eps = channels, r, r2, k, subpel, eps
-        # a batch keeps the GPU full of bands: pipelined sweep pairs, which
-        # add workgroups to overlap a field's sweeps, are off unless asked for
-        # (autotune() times both)
+        # band_rows and pipeline are accepted and have no effect
         self.params = ff_default_params(k=k, band_rows=band_rows, use_kdtree=use_kdtree, pipeline=pipeline)
         self.descs, self.blobs1, self.blobs2, self.out = [], [], [], []
         for (W, H) in self.shapes:
@@ -840,9 +838,9 @@ class BatchMatcher:
         return ff_read_status(self.ws)
 
     def autotune(self, imgs1, imgs2, band_rows=(8, 16, 32), pipeline=(1, 0), reps=2):
-        """Time every (band height, sweep-pair pipelining) combination on this
-        batch and keep the fastest (all give identical bytes).  Returns
-        (band_rows, pipeline, ms)."""
+        """Time every (band_rows, pipeline) combination on this batch and keep
+        the fastest (neither has an effect on the bytes or, beyond noise, on
+        the time).  Returns (band_rows, pipeline, ms)."""
         best = None
         for bh in band_rows:
             for pipe in pipeline:
