@@ -1565,10 +1565,9 @@ ff_status ff_build_kdtree(const ff_desc* d, const void* blob, int32_t radius, in
 // One wavefront follows a cycle of indices through global memory (every
 // lane the same one): every hop is one load whose address is the previous
 // load's value, so a hop costs one dependent round trip to wherever the
-// cycle's lines live.  The sweep's step
-// is such a chain (a step's result decides the next step's target
-// addresses), so this round trip times the number of wavefront steps is the
-// floor a sweep cannot go below.
+// cycle's lines live.  A visit of a sweep's tile is such a chain (a step's
+// result decides the next step's target addresses), so a visit takes at least
+// this round trip times its steps.
 namespace ff {
 __global__ void k_chase(const int32_t* __restrict__ next, int32_t mask, int32_t warm, int32_t hops,
                         int64_t* __restrict__ out) {
