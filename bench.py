@@ -10,7 +10,7 @@ l=8, eps=5).  Inputs are resident in HBM before the timed region.
 Prints one JSON line: the throughput (Mpixel/s = W*H / time per pair); the
 dominant kernel's measured rate against its roofline; every other kernel
 class against its own bound (algorithmic bytes per launch over the measured
-launch time); the level-1 propagation sweep's time per wavefront step;
+launch time); each propagation sweep's time;
 secondary workloads (the paper's fast variant, the skewed-motion recipe, the
 path through the region filter and sparsification of sections 3.4-3.5, 64
 mixed-size pairs in one batched call, the learned proposal); the path with

@@ -520,10 +520,9 @@ ff_status ff_profile_end_each(double* total_ms, int32_t* launches, double* each_
 
 /*
  * Dependent-load latency probe (measurement only; not used on the search
- * path).  A propagation sweep is a chain of wavefront steps, each step's
- * result deciding the next step's target addresses (Eq. 2 in raster order,
- * section 3.2), so one dependent memory round trip per step is a floor on
- * its time.  This call measures that round trip: one wavefront follows next[]
+ * path).  A visit of a propagation sweep's tile is a chain of steps, each
+ * step's result deciding the next step's target addresses (Eq. 2, section
+ * 3.2), so one dependent memory round trip per step is a floor on its time.  This call measures that round trip: one wavefront follows next[]
  * from index 0 for `warm` hops (bringing the cycle into the caches), then
  * for `hops` more, timed with the 100 MHz real-time counter.  Every hop is
  * one global load whose address is the previous load's value masked to
