@@ -38,7 +38,6 @@
 // (8.8 instead of 6.2 ms per 1024x436 pair).
 #pragma once
 
-#include "ff_device.h"
 #include "ff_internal.h"
 
 namespace ff {
@@ -70,6 +69,10 @@ __device__ __forceinline__ void st_coh(T* p, T v) {
 template <class T>
 __device__ __forceinline__ T add_coh(T* p, T v) {
   return __hip_atomic_fetch_add(gp(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ T swap_coh(T* p, T v) {
+  return __hip_atomic_exchange(gp(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // every memory operation of this wavefront before this point has completed
 __device__ __forceinline__ void mem_wait() {
@@ -118,12 +121,15 @@ __device__ __forceinline__ int relax_wait(const RelaxQ& q, int& done) {
   uint64_t t0 = rt_clock();
   int last = 1;
   for (int it = 0;; ++it) {
-    const int v = __builtin_amdgcn_readfirstlane(ld_coh(slot));
-    if (v != 0) {
+    if (__builtin_amdgcn_readfirstlane(ld_coh(slot)) != 0) {
       // (an abandoned launch may leave entries behind)
       if (__builtin_amdgcn_readfirstlane(ld_coh(q.status)) != 0) return -1;
-      if (lane == 0) st_coh(slot, 0);
-      return v - 1;
+      // tickets a ring apart share a slot: an entry is taken by whoever clears
+      // it, and the other one waits on for the next
+      int v = 0;
+      if (lane == 0) v = swap_coh(slot, 0);
+      v = __builtin_amdgcn_readfirstlane(v);
+      if (v != 0) return v - 1;
     }
     if ((it & 3) == 3) {
       const int p = __builtin_amdgcn_readfirstlane(ld_coh(&q.ctl->pend));

@@ -1,0 +1,47 @@
+"""The tile relaxation's scheduler (csrc/ff_relax.h) compiled for the host and
+run under a simulation of workgroups on a chip (tests/relax_host): whatever the
+order of events, every tile ends at the raster-order solution, no tile is
+visited twice at once, and the counters, the queue and the count of owed visits
+come back to rest."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def relax(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("relax") / "relax_host")
+    here = os.path.join(ROOT, "tests", "relax_host")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", here, "-I", os.path.join(ROOT, "paper_1508_05151_amd", "csrc"),
+                    "-I", os.path.join(ROOT, "include"), os.path.join(here, "relax_host.cpp"), "-o", exe], check=True)
+
+    def run(nu, nv, G, slots=10**6, seed=1, stall=0, visit=1500, timeout=2 * 10**6, slow=1, shuffle=0):
+        args = [nu, nv, G, slots, seed, stall, visit, timeout, slow, shuffle]
+        out = subprocess.run([exe] + [str(int(a)) for a in args], capture_output=True, text=True, timeout=100)
+        assert out.returncode == 0, (args, out.stdout, out.stderr)
+        w = out.stdout.split()
+        return {w[i]: int(w[i + 1]) for i in range(0, len(w), 2)}
+    return run
+
+
+def settled(r):
+    return r["status"] == 0 and r["wrong"] == 0 and r["twice"] == 0 and r["left"] == 0
+
+
+@pytest.mark.parametrize("nu,nv,G", [(1, 1, 1), (2, 1, 2), (12, 10, 120), (12, 10, 17), (40, 1, 40), (1, 30, 7)])
+def test_settles_at_the_raster_solution(relax, nu, nv, G):
+    """As many workgroups as tiles and fewer, all of them on the chip."""
+    for seed in range(3):
+        assert settled(relax(nu, nv, G, seed=seed)), seed
+
+
+def test_queue_entry_taken_once(relax):
+    """Few tiles, so that tickets a ring apart share a slot soon, short visits
+    and operations held up for much longer than a visit (a workgroup that has
+    seen an entry and has not yet taken it)."""
+    for nu, nv, seed in [(3, 2, 32), (3, 3, 3), (3, 3, 24), (3, 3, 36), (3, 3, 37), (3, 3, 60), (4, 2, 5)] + \
+            [(3, 3, s) for s in range(100, 140)]:
+        assert settled(relax(nu, nv, 100, seed=seed, stall=20000, visit=300)), (nu, nv, seed)
