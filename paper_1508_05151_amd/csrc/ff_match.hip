@@ -659,7 +659,7 @@ struct SweepSmem {
 // launch.
 template <int S, int LEV, int RMS>
 __device__ __forceinline__ int sweep_visit(const FieldRec& f, const SweepArgs& a, const RelaxQ& q, SweepSmem<RMS>& sm,
-                                           int gt, bool first, int& done) {
+                                           int gt, bool first, RelaxWg& w) {
   constexpr int RM = S ? S / 2 : kMaxRadius;
   static_assert(RM <= RMS, "the workgroup's LDS");
   constexpr int CW = S ? S / 4 : 1;      // words of a line per lane, one more word per line left over (S = 4 CW + 1)
@@ -939,7 +939,7 @@ __device__ __forceinline__ int sweep_visit(const FieldRec& f, const SweepArgs& a
   mem_wait();
   __syncthreads();
   return relax_done(q, cnt, a.base, tile, nu, g0, handled, (cm & 0xFFFFu) != 0, (cm & 0x7FFF0000u) != 0,
-                    (cm & 0x80000000u) != 0, done);
+                    (cm & 0x80000000u) != 0, w);
 }
 
 // The visits of a workgroup: its first visits, dealt out in turn, then queued
@@ -948,7 +948,8 @@ template <typename Visit>
 __device__ __forceinline__ void sweep_tiles(const FieldRec* __restrict__ table, const SweepArgs& a, const RelaxQ& q, int lev,
                                             Visit visit) {
   const int lane = threadIdx.x;
-  int mine = blockIdx.x, gt = mine, done = 0;
+  RelaxWg w = relax_begin(q, blockIdx.x);
+  int gt = w.mine;
   bool first = true;
   do {
     // the tile's field: the last one whose first tile is not above it
@@ -959,13 +960,7 @@ __device__ __forceinline__ void sweep_tiles(const FieldRec* __restrict__ table, 
       fi += __popcll(__ballot(le));
     }
     fi = __builtin_amdgcn_readfirstlane(fi - 1);
-    gt = visit(table[fi], gt, first, done);
-    first = false;
-    if (gt < 0) {
-      mine += q.G;
-      first = mine < q.T;
-      gt = first ? mine : relax_wait(q, done);
-    }
+    gt = relax_next(q, w, visit(table[fi], gt, first, w), first);
   } while (gt >= 0);
 }
 
@@ -974,8 +969,8 @@ template <int S, int LEV>
 __global__ __launch_bounds__(64) void k_sweep(const FieldRec* __restrict__ table, SweepArgs a, RelaxQ q) {
   constexpr int RM = S ? S / 2 : kMaxRadius;
   __shared__ SweepSmem<RM> sm;
-  sweep_tiles(table, a, q, LEV >= 0 ? LEV : a.lev, [&](const FieldRec& f, int gt, bool first, int& done) {
-    return sweep_visit<S, LEV, RM>(f, a, q, sm, gt, first, done);
+  sweep_tiles(table, a, q, LEV >= 0 ? LEV : a.lev, [&](const FieldRec& f, int gt, bool first, RelaxWg& w) {
+    return sweep_visit<S, LEV, RM>(f, a, q, sm, gt, first, w);
   });
 }
 
@@ -984,9 +979,9 @@ __global__ __launch_bounds__(64) void k_sweep(const FieldRec* __restrict__ table
 template <int LEV>
 __global__ __launch_bounds__(64) void k_sweep_mixed(const FieldRec* __restrict__ table, SweepArgs a, RelaxQ q) {
   __shared__ SweepSmem<8> sm;
-  sweep_tiles(table, a, q, LEV >= 0 ? LEV : a.lev, [&](const FieldRec& f, int gt, bool first, int& done) {
-    return f.r == 8 ? sweep_visit<17, LEV, 8>(f, a, q, sm, gt, first, done)
-                    : sweep_visit<13, LEV, 8>(f, a, q, sm, gt, first, done);
+  sweep_tiles(table, a, q, LEV >= 0 ? LEV : a.lev, [&](const FieldRec& f, int gt, bool first, RelaxWg& w) {
+    return f.r == 8 ? sweep_visit<17, LEV, 8>(f, a, q, sm, gt, first, w)
+                    : sweep_visit<13, LEV, 8>(f, a, q, sm, gt, first, w);
   });
 }
 
@@ -1368,13 +1363,17 @@ static ff_status run_batch(const ff_field_job* jobs, int n, const ff_match_param
 }
 
 // ---------------------------------------------------------------- no-allocation scratch
+// The limit of ff_match_field_noalloc counts three lines of scheduler words per
+// launch; the ones that count the started workgroups have room of their own.
+constexpr size_t kUncountedWords = sizeof(RelaxCtl) - 3 * 128;
+constexpr size_t kNoallocWords = 5 * 64 * kUncountedWords;   // levels x sweeps, at most
 // ff_match_field_noalloc keeps what ff_match_field keeps in its workspace
 // (status word, scheduler words, field table, kd-tree, level grids, border
 // words) in this one static array per device.  On the host its name
 // is only a stand-in symbol, not a device address: host code uses the address
 // hipGetSymbolAddress returns for the current device, looked up once per
 // device (at ff_init, else at the entry point's first call there).
-static __device__ __align__(256) char scratch[FF_NOALLOC_SCRATCH_BYTES + 8 * (size_t)kMaxPoints];
+static __device__ __align__(256) char scratch[FF_NOALLOC_SCRATCH_BYTES + 8 * (size_t)kMaxPoints + kNoallocWords];
 
 namespace {
 std::mutex g_scratch_mu;
@@ -1502,7 +1501,8 @@ ff_status ff_match_field_noalloc(const ff_desc* src, const void* src_blob, const
   const ff_field_job j = single_job(src, src_blob, dst, dst_blob, radius, p, proposal, flow, cost);
   const BatchLayout B = batch_layout(&j, 1, p);
   // a second grid buffer outside the tree's region has its own room
-  if (B.bytes - field_plan(src, dst, p).alt_bytes > (size_t)FF_NOALLOC_SCRATCH_BYTES) return FF_ERR_SIZE;
+  if (B.bytes - field_plan(src, dst, p).alt_bytes - B.launches * kUncountedWords > (size_t)FF_NOALLOC_SCRATCH_BYTES)
+    return FF_ERR_SIZE;
   st = check_job(j, p);
   if (st != FF_OK) return st;
   st = ensure_init();

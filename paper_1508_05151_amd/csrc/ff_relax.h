@@ -30,9 +30,13 @@
 // whose L2 caches are not coherent) and complete before the counter is
 // touched.
 //
-// No workgroup waits for another one in order to make progress: a waiting
-// workgroup has no tile.  It waits for one to be queued, so that a burst of
-// requests finds workgroups ready; surplus ones leave.  What every workgroup
+// A workgroup without a tile waits for one to be queued, so that a burst of
+// requests finds workgroups ready; surplus ones leave.  It waits only once
+// every workgroup of the launch has started, and leaves otherwise: it holds a
+// place on the chip, and one that has not started still owes its first visits.
+// So a launch needs one place to end, however many the chip has left for it:
+// the workgroup that starts last finds all started and drains the queue.
+// What every workgroup
 // shares is kept off the visits: with a ticket and a count of owed visits
 // touched on each of them, one memory channel set the pace of the whole chip
 // (8.8 instead of 6.2 ms per 1024x436 pair).
@@ -47,7 +51,8 @@ __host__ __device__ __forceinline__ int tiles_x(int Gw) { return (Gw + kTileH - 
 __host__ __device__ __forceinline__ int tiles_y(int Gh) { return (Gh + kTileH - 1) / kTileH; }
 constexpr int kSweepGrid = 2048;          // workgroups of a sweep that the chip holds (eight per CU, by LDS)
 
-constexpr int kRelaxIdle = 96;   // workgroups kept waiting for work; the rest leave
+constexpr int kRelaxIdle = 96;   // workgroups that wait for work, about: more only crowd the words they poll
+constexpr int kRelaxStart = 16;  // words that count the workgroups started, block b on word b % 16
 
 __device__ __forceinline__ uint64_t rt_clock() { return __builtin_amdgcn_s_memrealtime(); }
 
@@ -90,7 +95,11 @@ struct RelaxCtl {
   int32_t head, pad0[31];   // tickets drawn for queued tiles
   int32_t tail, pad1[31];   // tiles queued
   int32_t pend, pad2[31];   // (visits owed) - T; -T when the sweep has settled
+  struct {
+    int32_t n, pad[31];
+  } started[kRelaxStart];
 };
+static_assert(sizeof(RelaxCtl) == (3 + kRelaxStart) * 128, "one line per word");
 struct RelaxQ {
   RelaxCtl* ctl;
   int32_t* ring;       // queued tiles + 1, 0 where empty; empty again when the launch ends
@@ -100,16 +109,29 @@ struct RelaxQ {
   uint64_t timeout;    // its limit, in 10 ns ticks
 };
 
-// A queued tile to visit, or -1 to leave.  done: visits this workgroup has
-// answered for and not yet taken off the owed ones (kept by the workgroup:
-// one operation on the shared word per wait instead of one per visit).
-__device__ __forceinline__ int relax_wait(const RelaxQ& q, int& done) {
+// A workgroup's own words.  done: visits it has answered for and not yet taken
+// off the owed ones (one operation on the shared word per wait instead of one
+// per visit).
+struct RelaxWg {
+  int mine;   // its first visits: tiles block, block + G, ..
+  int done;
+};
+__device__ __forceinline__ RelaxWg relax_begin(const RelaxQ& q, int block) {
+  if ((threadIdx.x & 63) == 0) add_coh(&q.ctl->started[block % kRelaxStart].n, 1);
+  return {block, 0};
+}
+
+// A queued tile to visit, or -1 to leave.
+__device__ __forceinline__ int relax_wait(const RelaxQ& q, RelaxWg& w) {
   const int lane = threadIdx.x & 63;
   int old = 0;
-  if (lane == 0) old = add_coh(&q.ctl->pend, -done);
+  if (lane == 0) old = add_coh(&q.ctl->pend, -w.done);
+  const int all = (q.G + kRelaxStart - 1 - lane) / kRelaxStart;   // workgroups counted on word `lane`
+  const bool some = lane < kRelaxStart && ld_coh(&q.ctl->started[lane < kRelaxStart ? lane : 0].n) < all;
   old = __builtin_amdgcn_readfirstlane(old);
-  if (old - done == -q.T) return -1;
-  done = 0;
+  if (old - w.done == -q.T) return -1;
+  w.done = 0;
+  if (__ballot(some)) return -1;
   // enough workgroups wait already?
   const int h = __builtin_amdgcn_readfirstlane(ld_coh(&q.ctl->head));
   const int tl = __builtin_amdgcn_readfirstlane(ld_coh(&q.ctl->tail));
@@ -151,10 +173,10 @@ __device__ __forceinline__ int relax_wait(const RelaxQ& q, int& done) {
 // the field, the field's tiles starting at g0): its stores have completed.
 // handled: requests the visit answered.  to_r / to_bl / to_b: whether border
 // values that tile self + 1 / self + nu - 1 / self + nu reads have changed.
-// Returns the next tile (global number) this workgroup owns, or -1; done is
+// Returns the next tile (global number) this workgroup owns, or -1; w.done is
 // raised when the visit leaves nothing owed in its place.
 __device__ __forceinline__ int relax_done(const RelaxQ& q, int32_t* cnt, int base, int self, int nu, int g0,
-                                          int handled, bool to_r, bool to_bl, bool to_b, int& done) {
+                                          int handled, bool to_r, bool to_bl, bool to_b, RelaxWg& w) {
   const int lane = threadIdx.x & 63;
   const bool on = lane == 0 || (lane == 1 && to_r) || (lane == 2 && to_b) || (lane == 3 && to_bl);
   const int tile = self + (lane == 1 ? 1 : lane == 2 ? nu : lane == 3 ? nu - 1 : 0);
@@ -165,7 +187,7 @@ __device__ __forceinline__ int relax_done(const RelaxQ& q, int32_t* cnt, int bas
   }
   const uint64_t m = __ballot(owned);
   if (m == 0) {
-    ++done;
+    ++w.done;
     return -1;
   }
   const int first = __ffsll((unsigned long long)m) - 1;
@@ -174,8 +196,8 @@ __device__ __forceinline__ int relax_done(const RelaxQ& q, int32_t* cnt, int bas
     // the visits are owed before anyone can make them
     const int k = __popcll(rest);
     int pos = 0;
-    const int pay = k - done;   // what is owed less what was answered for
-    done = 0;
+    const int pay = k - w.done;   // what is owed less what was answered for
+    w.done = 0;
     if (lane < 2) pos = add_coh(lane == 0 ? &q.ctl->tail : &q.ctl->pend, lane == 0 ? k : pay);
     mem_wait();
     pos = __builtin_amdgcn_readfirstlane(pos) + __popcll(rest & ((1ull << lane) - 1));
@@ -199,6 +221,19 @@ __device__ __forceinline__ int relax_done(const RelaxQ& q, int32_t* cnt, int bas
     }
   }
   return g0 + __builtin_amdgcn_readlane(tile, first);
+}
+
+// The tile after a visit that left the workgroup with tile `next`, or none
+// (-1): that one, its next first visit, or a queued tile; -1 to leave.  first:
+// no earlier visit of the tile in this launch.
+__device__ __forceinline__ int relax_next(const RelaxQ& q, RelaxWg& w, int next, bool& first) {
+  first = false;
+  if (next >= 0) return next;
+  if (w.mine < q.T) {
+    w.mine += q.G;
+    first = w.mine < q.T;
+  }
+  return first ? w.mine : relax_wait(q, w);
 }
 
 // Border words: flow | cost | launch tag

@@ -558,7 +558,9 @@ __global__ __launch_bounds__(256, SG <= 5 ? 3 : 2) void k_sift_sweep(const SiftR
   __shared__ int s_next, s_first;
   const int tid = threadIdx.x, lev = a.lev, n = 1 << lev, sx = a.sx, sy = a.sy;
   constexpr int kPO = kTileW + 1;
-  int mine = blockIdx.x, gt = mine, done = 0;
+  RelaxWg w{(int)blockIdx.x, 0};   // the first wavefront's
+  if (tid < 64) w = relax_begin(q, blockIdx.x);
+  int gt = blockIdx.x;
   bool first = true;   // no earlier visit of this tile in this launch
   do {
     // the tile's field: the last one whose first tile is not above it
@@ -660,14 +662,10 @@ __global__ __launch_bounds__(256, SG <= 5 ? 3 : 2) void k_sift_sweep(const SiftR
     mem_wait();
     __syncthreads();
     if (tid < 64) {
-      int next = relax_done(q, cnt, a.base, tile, nu, g0, handled, (cm & 0xFFFFu) != 0, (cm & 0x7FFF0000u) != 0,
-                            (cm & 0x80000000u) != 0, done);
-      bool fresh = false;
-      if (next < 0) {
-        mine += q.G;
-        fresh = mine < q.T;
-        next = fresh ? mine : relax_wait(q, done);
-      }
+      const int own = relax_done(q, cnt, a.base, tile, nu, g0, handled, (cm & 0xFFFFu) != 0, (cm & 0x7FFF0000u) != 0,
+                                 (cm & 0x80000000u) != 0, w);
+      bool fresh;
+      const int next = relax_next(q, w, own, fresh);
       if (tid == 0) {
         s_next = next;
         s_first = fresh;

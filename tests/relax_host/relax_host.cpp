@@ -100,8 +100,7 @@ int solve(int t, int l, int d, int u) {
 }
 
 // as the sweeps' visits: counter, borders, work, results, words, requests
-template <class Done>
-int visit(int t, bool first, Done& done) {
+int visit(int t, bool first, ff::RelaxWg& w) {
   using namespace ff;
   const int lane = threadIdx.x, base = -1;
   const int handled = __builtin_amdgcn_readfirstlane(ld_coh(&P.cnt[t]) - base);
@@ -127,22 +126,16 @@ int visit(int t, bool first, Done& done) {
   changed = __builtin_amdgcn_readfirstlane(changed);
   const bool right = t % P.nu + 1 < P.nu, down = t + P.nu < P.T;
   return relax_done(P.q, P.cnt.data(), base, t, P.nu, 0, handled, changed && right, changed && down && t % P.nu > 0,
-                    changed && down, done);
+                    changed && down, w);
 }
 
 void lane_main() {
   using namespace ff;
-  int mine = wg->block, gt = mine, done = 0;
+  RelaxWg w = relax_begin(P.q, wg->block);
+  int gt = w.mine;
   bool first = true;
-  do {
-    gt = visit(gt, first, done);
-    first = false;
-    if (gt < 0) {
-      mine += P.q.G;
-      first = mine < P.q.T;
-      gt = first ? mine : relax_wait(P.q, done);
-    }
-  } while (gt >= 0);
+  do gt = relax_next(P.q, w, visit(gt, first, w), first);
+  while (gt >= 0);
   leave(kDone);
 }
 

@@ -45,3 +45,13 @@ def test_queue_entry_taken_once(relax):
     for nu, nv, seed in [(3, 2, 32), (3, 3, 3), (3, 3, 24), (3, 3, 36), (3, 3, 37), (3, 3, 60), (4, 2, 5)] + \
             [(3, 3, s) for s in range(100, 140)]:
         assert settled(relax(nu, nv, 100, seed=seed, stall=20000, visit=300)), (nu, nv, seed)
+
+
+@pytest.mark.parametrize("slots", [1, 2, 7, 40, 96, 110])
+def test_settles_whatever_places_it_gets(relax, slots):
+    """More workgroups than the chip has places for them: those without a tile
+    make room for those not yet started, in whichever order these start."""
+    for seed in range(3):
+        for shuffle in (0, 1):
+            assert settled(relax(16, 9, 144, slots=slots, seed=seed, shuffle=shuffle)), (seed, shuffle)
+            assert settled(relax(16, 9, 120, slots=slots, seed=seed, stall=300, shuffle=shuffle)), (seed, shuffle)
