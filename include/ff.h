@@ -109,11 +109,14 @@ typedef struct {
                          and results are identical for every value */
   int32_t pipeline;   /* 0 or 1 (default): accepted likewise, no effect on
                          results or schedule */
-  int32_t watchdog_us; /* 0 (default): a workgroup that waits for work while no
-                          other one finishes any gives up after 2 s and the
-                          call reports FF_ERR_DEVICE; > 0: that limit in
-                          microseconds (a tiny value forces the error path in
-                          tests) */
+  int32_t watchdog_us; /* 0 (default): a workgroup that waits for work while it
+                          sees no other one finish any gives up after 2 s and
+                          the call reports FF_ERR_DEVICE; > 0: that limit in
+                          microseconds.  Workgroups show their progress at
+                          least every 32 visits of a tile (about a millisecond
+                          on a busy chip), so a limit of some milliseconds
+                          does not end a call that is at work; a tiny one does
+                          (it forces the error path in tests) */
   uint64_t seed;      /* Philox key */
 } ff_match_params;
 

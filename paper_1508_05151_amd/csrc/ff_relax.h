@@ -94,7 +94,8 @@ __device__ __forceinline__ void mem_wait() {
 struct RelaxCtl {
   int32_t head, pad0[31];   // tickets drawn for queued tiles
   int32_t tail, pad1[31];   // tiles queued
-  int32_t pend, pad2[31];   // (visits owed) - T; -T when the sweep has settled
+  int32_t pend;             // (visits owed) - T; -T when the sweep has settled
+  int32_t beat, pad2[30];   // raised by every kBeatVisits-th visit of a workgroup
   struct {
     int32_t n, pad[31];
   } started[kRelaxStart];
@@ -109,16 +110,24 @@ struct RelaxQ {
   uint64_t timeout;    // its limit, in 10 ns ticks
 };
 
+// The watchdog: a waiting workgroup gives up when neither pend nor beat has
+// changed for the limit.  pend changes when a workgroup waits or queues tiles;
+// one that goes from tile to tile without either (its first visits, a chain of
+// single revisits) raises beat every kBeatVisits of them.  So it fires on a
+// sweep at work only if that many visits take longer than the limit.
+constexpr int kBeatVisits = 32;
+
 // A workgroup's own words.  done: visits it has answered for and not yet taken
 // off the owed ones (one operation on the shared word per wait instead of one
 // per visit).
 struct RelaxWg {
-  int mine;   // its first visits: tiles block, block + G, ..
+  int mine;     // its first visits: tiles block, block + G, ..
   int done;
+  int visits;
 };
 __device__ __forceinline__ RelaxWg relax_begin(const RelaxQ& q, int block) {
   if ((threadIdx.x & 63) == 0) add_coh(&q.ctl->started[block % kRelaxStart].n, 1);
-  return {block, 0};
+  return {block, 0, 0};
 }
 
 // A queued tile to visit, or -1 to leave.
@@ -141,7 +150,7 @@ __device__ __forceinline__ int relax_wait(const RelaxQ& q, RelaxWg& w) {
   pos = __builtin_amdgcn_readfirstlane(pos);
   int32_t* const slot = q.ring + pos % q.cap;
   uint64_t t0 = rt_clock();
-  int last = 1;
+  uint64_t last = ~0ull;
   for (int it = 0;; ++it) {
     if (__builtin_amdgcn_readfirstlane(ld_coh(slot)) != 0) {
       // (an abandoned launch may leave entries behind)
@@ -154,11 +163,13 @@ __device__ __forceinline__ int relax_wait(const RelaxQ& q, RelaxWg& w) {
       if (v != 0) return v - 1;
     }
     if ((it & 3) == 3) {
-      const int p = __builtin_amdgcn_readfirstlane(ld_coh(&q.ctl->pend));
+      const uint64_t pb = ld_coh(reinterpret_cast<const uint64_t*>(&q.ctl->pend));
+      const int p = __builtin_amdgcn_readfirstlane((int)(uint32_t)pb);
+      const int b = __builtin_amdgcn_readfirstlane((int)(uint32_t)(pb >> 32));
       if (p == -q.T || __builtin_amdgcn_readfirstlane(ld_coh(q.status)) != 0) return -1;
-      // the watchdog runs only while no visit ends anywhere
-      if (p != last) {
-        last = p;
+      const uint64_t seen = ((uint64_t)(uint32_t)b << 32) | (uint32_t)p;
+      if (seen != last) {
+        last = seen;
         t0 = rt_clock();
       } else if (rt_clock() - t0 > q.timeout) {
         if (lane == 0) st_coh(q.status, (int32_t)FF_ERR_DEVICE);
@@ -185,6 +196,7 @@ __device__ __forceinline__ int relax_done(const RelaxQ& q, int32_t* cnt, int bas
     const int old = add_coh(cnt + tile, lane == 0 ? -handled : 1);
     owned = lane == 0 ? old - handled != base : old == base;
   }
+  if (++w.visits % kBeatVisits == 0 && lane == 0) add_coh(&q.ctl->beat, 1);
   const uint64_t m = __ballot(owned);
   if (m == 0) {
     ++w.done;

@@ -558,7 +558,7 @@ __global__ __launch_bounds__(256, SG <= 5 ? 3 : 2) void k_sift_sweep(const SiftR
   __shared__ int s_next, s_first;
   const int tid = threadIdx.x, lev = a.lev, n = 1 << lev, sx = a.sx, sy = a.sy;
   constexpr int kPO = kTileW + 1;
-  RelaxWg w{(int)blockIdx.x, 0};   // the first wavefront's
+  RelaxWg w{};   // the first wavefront's
   if (tid < 64) w = relax_begin(q, blockIdx.x);
   int gt = blockIdx.x;
   bool first = true;   // no earlier visit of this tile in this launch

@@ -51,7 +51,21 @@ def test_queue_entry_taken_once(relax):
 def test_settles_whatever_places_it_gets(relax, slots):
     """More workgroups than the chip has places for them: those without a tile
     make room for those not yet started, in whichever order these start."""
-    for seed in range(3):
+    for seed in range(2):
         for shuffle in (0, 1):
             assert settled(relax(16, 9, 144, slots=slots, seed=seed, shuffle=shuffle)), (seed, shuffle)
             assert settled(relax(16, 9, 120, slots=slots, seed=seed, stall=300, shuffle=shuffle)), (seed, shuffle)
+
+
+@pytest.mark.parametrize("nu,visits", [(160, 40), (220, 64)])
+def test_watchdog_spares_a_chain_of_visits(relax, nu, visits):
+    """One row whose change runs through every tile, one revisit after the
+    other in one workgroup while the others wait; a limit shorter than the
+    chain and longer than the visits between two signs of progress."""
+    r = relax(nu, 1, nu, visit=2000, timeout=visits * 2300, slow=3)
+    assert settled(r) and r["visits"] > nu + visits, r
+
+
+def test_watchdog_fires_on_a_short_limit(relax):
+    """The same with a limit of a few visits: the sweep is given up."""
+    assert relax(60, 1, 60, visit=2000, timeout=5 * 2300, slow=20)["status"] == -6
