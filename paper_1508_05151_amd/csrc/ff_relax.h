@@ -136,7 +136,7 @@ __device__ __forceinline__ int relax_wait(const RelaxQ& q, RelaxWg& w) {
   int old = 0;
   if (lane == 0) old = add_coh(&q.ctl->pend, -w.done);
   const int all = (q.G + kRelaxStart - 1 - lane) / kRelaxStart;   // workgroups counted on word `lane`
-  const bool some = lane < kRelaxStart && ld_coh(&q.ctl->started[lane < kRelaxStart ? lane : 0].n) < all;
+  const bool some = lane < kRelaxStart && ld_coh(&q.ctl->started[lane].n) < all;
   old = __builtin_amdgcn_readfirstlane(old);
   if (old - w.done == -q.T) return -1;
   w.done = 0;
@@ -153,13 +153,14 @@ __device__ __forceinline__ int relax_wait(const RelaxQ& q, RelaxWg& w) {
   uint64_t last = ~0ull;
   for (int it = 0;; ++it) {
     if (__builtin_amdgcn_readfirstlane(ld_coh(slot)) != 0) {
-      // (an abandoned launch may leave entries behind)
-      if (__builtin_amdgcn_readfirstlane(ld_coh(q.status)) != 0) return -1;
       // tickets a ring apart share a slot: an entry is taken by whoever clears
       // it, and the other one waits on for the next
       int v = 0;
       if (lane == 0) v = swap_coh(slot, 0);
+      const int st = ld_coh(q.status);
       v = __builtin_amdgcn_readfirstlane(v);
+      // (an abandoned launch may leave entries behind)
+      if (__builtin_amdgcn_readfirstlane(st) != 0) return -1;
       if (v != 0) return v - 1;
     }
     if ((it & 3) == 3) {
