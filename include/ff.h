@@ -170,7 +170,8 @@ ff_status ff_match_field(const ff_desc* src, const void* src_blob, const ff_desc
  * vectors exist (ff_compute_lab_wht) while the census planes are still being
  * computed.  A following ff_match_field with the same arguments, the same
  * workspace and p->use_kdtree = 2 seeds from it instead of building it; its
- * results equal a call with use_kdtree = 1.  p->use_kdtree must be nonzero.
+ * results equal a call with use_kdtree = 1 (of p, only leaf has to be the same;
+ * the workspace has to be large enough for both).  p->use_kdtree must be nonzero.
  * The blobs need only their WHT regions at this point.
  */
 ff_status ff_match_field_tree(const ff_desc* src, const void* src_blob, const ff_desc* dst, const void* dst_blob,

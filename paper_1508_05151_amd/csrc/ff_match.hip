@@ -1157,16 +1157,9 @@ static BatchLayout batch_layout(const ff_field_job* jobs, int n, const ff_match_
   int groups = 0;
   for (int i = 0; i < n; ++i)
     if (i == 0 || jobs[B.order[i]].radius != jobs[B.order[i - 1]].radius) ++groups;
+  // the fields come before what depends on the number of sweeps: a tree left in
+  // the workspace is found there by a call with another k or n_prop as well
   size_t off = kStatusBytes;
-  B.off_ctl = off;
-  B.launches = (p->k + 1) * p->n_prop * groups;
-  off += (size_t)B.launches * sizeof(RelaxCtl);
-  B.off_ring = off;
-  for (int i = 0; i < n; ++i)   // tiles of the finest level over all fields: every launch has fewer
-    B.cap += tiles_x(jobs[i].src->width) * tiles_y(jobs[i].src->height);
-  off += (size_t)B.cap * 4;
-  B.ctl_words = (off - B.off_ctl) / 4;
-  off = align_up(off, 256);
   B.off_table = off;
   off = align_up(off + (size_t)n * sizeof(FieldRec), 256);
   B.off_field.resize(n);
@@ -1175,7 +1168,15 @@ static BatchLayout batch_layout(const ff_field_job* jobs, int n, const ff_match_
     B.off_field[i] = off;
     off = align_up(off + field_plan(j.src, j.dst, p).bytes, 256);
   }
-  B.bytes = off;
+  B.off_ctl = off;
+  B.launches = (p->k + 1) * p->n_prop * groups;
+  off += (size_t)B.launches * sizeof(RelaxCtl);
+  B.off_ring = off;
+  for (int i = 0; i < n; ++i)   // tiles of the finest level over all fields: every launch has fewer
+    B.cap += tiles_x(jobs[i].src->width) * tiles_y(jobs[i].src->height);
+  off += (size_t)B.cap * 4;
+  B.ctl_words = (off - B.off_ctl) / 4;
+  B.bytes = align_up(off, 256);
   return B;
 }
 
