@@ -453,14 +453,14 @@ ff_status ff_match_sift(const ff_sift_job* jobs, int32_t n_jobs, const ff_match_
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * search as ff_match_field, with the same arguments minus the workspace, and
  * identical outputs.  Its scratch (what ff_match_field keeps in the
- * workspace) is one static device array per GPU (FF_NOALLOC_SCRATCH_BYTES
- * and that second buffer),
- * held until the process ends; the call allocates nothing (no hipMalloc, no
- * host heap).  ff_init() looks the array up on the current device; call it
+ * workspace) is one static device array per GPU (FF_NOALLOC_SCRATCH_BYTES and
+ * 640 KB of scheduler words), held until the process ends; the call allocates
+ * nothing (no hipMalloc, no host heap).  ff_init() looks the array up on the current device; call it
  * before the first use inside a capture.
  *  - Limit: FF_ERR_SIZE if ff_match_workspace_bytes() of the same arguments,
- *    less the second grid buffer where a source much larger than the target
- *    needs one of its own, exceeds FF_NOALLOC_SCRATCH_BYTES (64 MiB: fields of up to about 1.7 Mpx
+ *    less 2 KB per sweep and, where the source is much larger than the target,
+ *    less what its second grid buffer needs beside the kd-tree's own scratch,
+ *    exceeds FF_NOALLOC_SCRATCH_BYTES (64 MiB: fields of up to about 1.7 Mpx
  *    at k = 3 and leaf 8, e.g. 1024x436, 1242x375, 1280x720, 1600x1000; not
  *    1920x1080).  Checked before anything is enqueued.
  *  - Every call on one GPU uses that GPU's single array and the array keeps

@@ -1042,7 +1042,7 @@ struct FieldPlan {
   size_t off_grid[5], off_st[5];
   size_t off_alt, off_xr, off_xb, off_seen;
   size_t clear_words;     // from off_st[0]: counters and border words
-  size_t alt_bytes;       // of an off_alt outside the tree's region, else 0
+  size_t alt_past;        // what the buffer at off_alt needs past the tree's region
   size_t bytes;
 };
 
@@ -1054,6 +1054,13 @@ static FieldPlan field_plan(const ff_desc* src, const ff_desc* dst, const ff_mat
     P.tree = tree_layout(dst->width * dst->height, p->leaf, 0);
     off = P.tree.bytes;
   }
+  // the second grid buffer: what the tree build needs beside the finished
+  // tree (which seeding reads) is free once the tree stands; a source too
+  // large for it reaches past its end
+  P.off_alt = P.has_tree ? P.tree.off_perm2 : 0;
+  const size_t alt_end = align_up(P.off_alt + (size_t)src->width * src->height * 8, 256);
+  P.alt_past = alt_end > off ? alt_end - off : 0;
+  off += P.alt_past;
   for (int lev = 1; lev <= p->k; ++lev) {
     const int n = 1 << lev;
     const size_t G = (size_t)((src->width + n - 1) / n) * ((src->height + n - 1) / n);
@@ -1076,18 +1083,6 @@ static FieldPlan field_plan(const ff_desc* src, const ff_desc* dst, const ff_mat
   P.clear_words = (off - clear0) / 4;
   P.off_seen = off;
   off += (size_t)tiles_x(src->width) * tiles_y(src->height) * 32 * 4;
-  // the second grid buffer: what the tree build needs beside the finished
-  // tree (which seeding reads) is free once the tree stands; a source that
-  // does not fit there gets a region of its own, the field's last
-  const size_t alt = (size_t)src->width * src->height * 8;
-  if (P.has_tree && P.tree.bytes - P.tree.off_perm2 >= alt) {
-    P.off_alt = P.tree.off_perm2;
-  } else {
-    off = align_up(off, 256);
-    P.off_alt = off;
-    P.alt_bytes = align_up(alt, 256);
-    off += alt;
-  }
   P.bytes = align_up(off, 256);
   return P;
 }
@@ -1364,17 +1359,21 @@ static ff_status run_batch(const ff_field_job* jobs, int n, const ff_match_param
 }
 
 // ---------------------------------------------------------------- no-allocation scratch
-// The limit of ff_match_field_noalloc counts three lines of scheduler words per
-// launch; the ones that count the started workgroups have room of their own.
+// The limit of ff_match_field_noalloc counts neither what the second grid
+// buffer needs past the tree's region nor, of the scheduler words, the ones that
+// count the started workgroups.  The latter have room of their own; with the
+// former the limit is still kept: a source so large leaves the tree little of
+// it (64.0 MiB at most, over sizes, leaves and depths that the limit lets by).
 constexpr size_t kUncountedWords = sizeof(RelaxCtl) - 3 * 128;
 constexpr size_t kNoallocWords = 5 * 64 * kUncountedWords;   // levels x sweeps, at most
+constexpr size_t kNoallocBytes = FF_NOALLOC_SCRATCH_BYTES + kNoallocWords;
 // ff_match_field_noalloc keeps what ff_match_field keeps in its workspace
 // (status word, scheduler words, field table, kd-tree, level grids, border
 // words) in this one static array per device.  On the host its name
 // is only a stand-in symbol, not a device address: host code uses the address
 // hipGetSymbolAddress returns for the current device, looked up once per
 // device (at ff_init, else at the entry point's first call there).
-static __device__ __align__(256) char scratch[FF_NOALLOC_SCRATCH_BYTES + 8 * (size_t)kMaxPoints + kNoallocWords];
+static __device__ __align__(256) char scratch[kNoallocBytes];
 
 namespace {
 std::mutex g_scratch_mu;
@@ -1501,9 +1500,8 @@ ff_status ff_match_field_noalloc(const ff_desc* src, const void* src_blob, const
   if (st != FF_OK) return st;
   const ff_field_job j = single_job(src, src_blob, dst, dst_blob, radius, p, proposal, flow, cost);
   const BatchLayout B = batch_layout(&j, 1, p);
-  // a second grid buffer outside the tree's region has its own room
-  if (B.bytes - field_plan(src, dst, p).alt_bytes - B.launches * kUncountedWords > (size_t)FF_NOALLOC_SCRATCH_BYTES)
-    return FF_ERR_SIZE;
+  const size_t counted = B.bytes - field_plan(src, dst, p).alt_past - B.launches * kUncountedWords;
+  if (counted > FF_NOALLOC_SCRATCH_BYTES || B.bytes > kNoallocBytes) return FF_ERR_SIZE;
   st = check_job(j, p);
   if (st != FF_OK) return st;
   st = ensure_init();
