@@ -1028,6 +1028,13 @@ static void launch_sweep_mixed(const FieldRec* table, const SweepArgs& a, const 
 // The paper's radii (r = 8, r2 = 6) have instances of their own, and go in one
 // launch; r, rl: of the launch's first and last field.
 static bool sweep_together(int r0, int r1) { return r0 == r1 || (r0 == 8 && r1 == 6) || (r0 == 6 && r1 == 8); }
+// Workgroups of such a launch that the chip holds, by LDS (160 KB per CU): eight
+// per CU with 17.9 KB (r = 8; r = 6 alone has less, and no use for more), five
+// of the instance for any radius, which has LDS for the largest one.
+constexpr int kSweepGrid = 256 * 8;
+static int sweep_places(int r0, int r1) {
+  return (r0 == 8 || r0 == 6) && (r1 == 8 || r1 == 6) ? kSweepGrid : 256 * 5;
+}
 static void launch_sweep(int r, int rl, const FieldRec* table, const SweepArgs& a, const RelaxQ& q, hipStream_t stream) {
   if (r != rl) launch_sweep_mixed(table, a, q, stream);
   else if (r == 8) launch_sweep_s<17>(table, a, q, stream);
@@ -1312,11 +1319,16 @@ static ff_status run_batch(const ff_field_job* jobs, int n, const ff_match_param
       q.cap = B.cap;
       q.T = recs[f1 - 1].t0[lev] + tiles_of(recs[f1 - 1], lev);
       // One field: a pair's three fields are matched side by side on streams
-      // of their own, so each takes a third of what the chip holds.  (With the
-      // whole: 1024x436 6.75 against 6.3-6.4 ms a pair, 1920x1080 22.1 against
-      // 20.0; a 641x479 field alone 2.48 against 2.53.)  Several in one call:
-      // the whole (eight pairs 29.0 ms, with 1,024 the same, with 512 32.5).
-      q.G = std::min(q.T, f1 - f0 == 1 ? kSweepGrid / 3 : kSweepGrid);
+      // of their own, so each takes a third of the places of the r = 8 and 6
+      // instances (1024x436 6.23 -> 5.74 ms a pair, 1920x1080 21.6 -> 19.2; a
+      // 641x479 field alone 2.30 -> 2.34).  As many with any other radius: with
+      // a third of that instance's places a pair of r = 5 and 3 takes 5.30 for
+      // 5.45 ms (641x479) and 7.18 for 7.27 (1024x436), but a field of r = 5
+      // alone 4.07 for 4.03 and 5.25 for 5.08.
+      // Several in one call: all places (eight fields of 641x479: r = 3 8.8,
+      // r = 5 10.4, r = 15 22.9 ms; with the 2,048 of the others 10.0, 11.7 and
+      // 25.3: workgroups that start late hold first visits back).
+      q.G = std::min(q.T, f1 - f0 == 1 ? kSweepGrid / 3 : sweep_places(recs[f0].r, recs[f1 - 1].r));
       q.status = status;
       q.timeout = timeout;
       launch_sweep(recs[f0].r, recs[f1 - 1].r, table, a, q, stream);

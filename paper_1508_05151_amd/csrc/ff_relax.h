@@ -49,7 +49,6 @@ namespace ff {
 constexpr int kTileH = 16, kTileW = 16;   // rows, columns
 __host__ __device__ __forceinline__ int tiles_x(int Gw) { return (Gw + kTileH - 1 + kTileW - 1) / kTileW; }
 __host__ __device__ __forceinline__ int tiles_y(int Gh) { return (Gh + kTileH - 1) / kTileH; }
-constexpr int kSweepGrid = 2048;          // workgroups of a sweep that the chip holds (eight per CU, by LDS)
 
 constexpr int kRelaxIdle = 96;   // workgroups that wait for work, about: more only crowd the words they poll
 constexpr int kRelaxStart = 16;  // words that count the workgroups started, block b on word b % 16
