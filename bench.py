@@ -65,9 +65,22 @@ def propagate_ops_per_pair(W, H, k, radii, n_prop=4):
     return sum(n_prop * pts * 2 * 2 * (2 * r + 1) * 2 for r in radii)
 
 
+def sweep_launches_per_field(k, n_prop=4):
+    """Launches of the propagation class per field: one per sweep."""
+    return n_prop * (k + 1)
+
+
+def sweep_ops_per_launch(W, H, k, radii, n_prop=4):
+    """Algorithmic integer ops of one sweep launch, on average over a pair's
+    (the numerator of the roofline)."""
+    return propagate_ops_per_pair(W, H, k, radii, n_prop) / (len(radii) * sweep_launches_per_field(k, n_prop))
+
+
 def per_point_ops_in_sweep_launches(W, H, k, radii, n_prop=4, n_rs=3):
-    """Algorithmic integer ops of the per-point stages that run inside
-    launches of a sweep pair, for a schedule that pairs them: two
+    """Algorithmic integer ops of the per-point stages inside the launches of
+    a schedule that pairs sweeps.  The library has none such now: every sweep,
+    search and entry is a launch of its own, and no figure of the benchmark
+    includes this count.  In that schedule two
     sweeps of one level with the same horizontal direction hold the random
     search between them (all grid points), and a level's last sweep paired
     with the next level's first holds that level's entry (the carried points,
@@ -325,9 +338,9 @@ def main():
     ap.add_argument("--outlier-pairs", type=int, default=8,
                     help="outliers mode: layered 1024x436 pairs (seeds 1000..)")
     ap.add_argument("--band-rows", type=int, default=16, choices=(8, 16, 32),
-                    help="propagation band height of the headline pair (results are identical for every value)")
+                    help="accepted, without effect (sweeps are split into tiles of a fixed size)")
     ap.add_argument("--pipeline", type=int, default=1, choices=(0, 1),
-                    help="pipelined sweep pairs on the headline pair (results are identical)")
+                    help="accepted, without effect (every sweep is a launch of its own)")
     ap.add_argument("--calib-copy-mib", type=int, default=0,
                     help="also run one plain device-to-device copy of this many MiB (the reference dispatch "
                          "for scaling hardware byte counters)")
@@ -423,7 +436,7 @@ def main():
     # timed region: K whole-path steps; the dominant kernel class is bracketed
     # with HIP events on the streams it runs on (library profiling hook), and
     # each of its launches is timed
-    per_field = 4 * (K + 1)
+    per_field = sweep_launches_per_field(K)
     ff.ff_profile_begin("propagate", 3 * per_field * args.steps + 8)
     ms_per_step, per_step, out = time_steps(run, torch, args.steps)
     tot, nl, each = ff.ff_profile_end(each=3 * per_field * args.steps)
@@ -432,7 +445,8 @@ def main():
 
     # dominant kernel against its roofline (integer VALU: census terms)
     avg_launch_ms = tot / max(nl, 1)
-    ops_per_launch = propagate_ops_per_pair(W, H, K, (R, R, R2)) / (nl / args.steps)
+    assert nl == 3 * per_field * args.steps, nl
+    ops_per_launch = sweep_ops_per_launch(W, H, K, (R, R, R2))
     achieved = ops_per_launch / (avg_launch_ms / 1000.0) / 1e12
     roof = {"bound": "alu", "achieved": round(achieved, 4), "peak": round(INT_PEAK_TOPS, 2), "unit": "TOP/s",
             "frac": round(achieved / INT_PEAK_TOPS, 5),
@@ -787,7 +801,6 @@ def bench_batch(args, ff, prs, torch, dev, steps=None):
     m = ff.BatchMatcher(shapes)
     m.run(i1, i2, seeds=seeds)
     torch.cuda.synchronize()
-    best_bh, best_pipe, tune_ms = m.autotune(i1, i2)
     s = torch.cuda.Stream()
     s.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(s):
@@ -834,9 +847,7 @@ def bench_batch(args, ff, prs, torch, dev, steps=None):
         "dtype": "int32", "data": "synthetic",
         "config": {"workload": f"{len(prs)} layered pairs of mixed sizes (320x240 to 1242x375, 2-8 layers, seeds "
                                f"3000..{3000 + len(prs) - 1}), {total_px} px per batch; descriptors, all fields in "
-                               f"one ff_match_batch call, filters; whole batch replayed from one HIP graph",
-                   "band_rows": best_bh, "pipelined_sweep_pairs": bool(best_pipe),
-                   "autotune": "band height x sweep-pair pipelining, fastest of 6 on this batch"},
+                               f"one ff_match_batch call, filters; whole batch replayed from one HIP graph"},
         "one_pair_per_launch": {"ms_per_batch": round(ms_single, 3),
                                 "Mpixel_per_s": round(total_px / (ms_single / 1000.0) / 1e6, 3),
                                 "pairs_per_s": round(len(prs) / (ms_single / 1000.0), 2)},
