@@ -621,15 +621,17 @@ __global__ __launch_bounds__(256) void k_random_search_tile(const FieldRec* __re
 // lie in different phase planes and mostly miss both caches: 0.62 us per step
 // with the chip idle, 1.3 us with every CU at work, of which instructions are
 // 0.25 us.  A visit is 16 steps and about 4 us around them.  Measured on
-// 1024x436 (three fields at once) a level-1 sweep takes 0.30 ms on average
-// where one wavefront per band of 16 rows, every band waiting for the one
-// above, took 1.15 ms; a pair 6.2 ms against 10.3, one 641x479 field 2.7
-// against 6.7, eight mixed pairs in one call 31.8 against 41.4.
+// 1024x436 (three fields at once) the four level-1 sweeps take 0.63, 0.32, 0.23
+// and 0.19 ms where one wavefront per band of 16 rows, every band waiting for
+// the one above, took 1.15 ms each.  By this alone a pair took 6.2 ms for 10.3,
+// one 641x479 field 2.7 for 6.7, eight mixed pairs in one call 31.8 for 41.4;
+// with the searches, trees and launch counts since, 5.4 to 5.6, 2.5 and 26.
+// 64 mixed pairs (a full chip throughout): 209 -> 194 ms with all of it.
 // Tile size (modelled from the visits each needs on that pair): 16 x 8, 8 x 16
 // and 8 x 8 points need 1.5 to 2 times the visits for the same chain, 16 x 32
 // has a longer one.
 struct SweepArgs {
-  int f0, nf;        // fields of this launch (one patch radius)
+  int f0, nf;        // fields of this launch
   int lev, qshift;
   int sx, sy;
   uint32_t tag;      // of this launch, in the border words

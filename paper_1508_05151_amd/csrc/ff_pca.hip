@@ -7,7 +7,9 @@
 // to tridiagonal form by Householder reflections with C in its registers
 // (k_eig_tri); one wavefront per eigenvalue then brackets it by 64-way
 // multisection of the Sturm count, takes its vector from the twisted
-// factorisation and reflects it back (k_eig_vec); one step of the first-order
+// factorisation (Fernando, "On computing an eigenvector of a tridiagonal
+// matrix", 1997; Parlett and Dhillon, "Fernando's solution to Wilkinson's
+// problem", 1997) and reflects it back (k_eig_vec); one step of the first-order
 // correction of Ogita and Aishima ("Iterative refinement for symmetric
 // eigenvalue decomposition", 2018) makes the basis orthogonal and the vectors
 // accurate to rounding (k_eig_w, k_eig_s, k_eig_correct).  The step squares

@@ -436,9 +436,11 @@ __global__ __launch_bounds__(256) void k_sift_rs(const SiftRec* __restrict__ tab
 // Bound: at level 0 the loads and integer work of the visits (2.7 visits per
 // tile), on coarser levels the chain of visits.  A colour pair is weighted
 // and summed by one packed dot product per weight.  Measured on the 1242x375
-// gray pair (F, B1, B2 in one launch): level-0 sweep 1.11 ms where bands of
-// 4 rows, each waiting for the one above, took 5.1; all 16 sweeps 8.0 ms
-// against 34, the pair 19.3 against 46.0; a 161x119 pair 5.6 against 9.1.
+// gray pair (F, B1, B2 in one launch): level-0 sweep 0.69 ms where bands of
+// 4 rows, each waiting for the one above, took 5.1; all 16 sweeps 5.8 ms
+// against 34.  By the tiles alone the pair took 19.3 for 46.0 ms and a 161x119
+// pair 5.6 for 9.1; with the searches, PCA and workgroup counts since, 10.9 and
+// 2.5.
 
 // Signed share of a lane in its line's sum: samples q, q + 4, ... of the line
 // whose sample k lies at p + (dx0 + k kx, dy0 + k ky) around the source point
