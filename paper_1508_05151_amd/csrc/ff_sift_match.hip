@@ -559,9 +559,10 @@ __global__ __launch_bounds__(256, SG <= 5 ? 3 : 2) void k_sift_sweep(const SiftR
   __shared__ STile s;
   __shared__ int s_next, s_first;
   const int tid = threadIdx.x, lev = a.lev, n = 1 << lev, sx = a.sx, sy = a.sy;
+  const bool wave0 = __builtin_amdgcn_readfirstlane(tid >> 6) == 0;
   constexpr int kPO = kTileW + 1;
   RelaxWg w{};   // the first wavefront's
-  if (tid < 64) w = relax_begin(q, blockIdx.x);
+  if (wave0) w = relax_begin(q, blockIdx.x);
   int gt = blockIdx.x;
   bool first = true;   // no earlier visit of this tile in this launch
   do {
@@ -609,7 +610,7 @@ __global__ __launch_bounds__(256, SG <= 5 ? 3 : 2) void k_sift_sweep(const SiftR
     const ptrdiff_t oat = isl ? (ptrdiff_t)((size_t)tu * Gh + ov) : (ptrdiff_t)((size_t)nu * Gh + (size_t)tv * Gw + ou);
     const int handled = __builtin_amdgcn_readfirstlane(have);
     int32_t hf = kEmpty, hc = kInf;
-    if (tid < 64) {
+    if (wave0) {
       mem_wait();   // the request counter is read before the borders
       if (tid < 32) {
         int32_t wasF = 0;
@@ -650,7 +651,7 @@ __global__ __launch_bounds__(256, SG <= 5 ? 3 : 2) void k_sift_sweep(const SiftR
       st_coh(outC + pp, x.y);
     }
     uint64_t cm = 0;
-    if (tid < 64) {
+    if (wave0) {
       const int2 now = s.res[oidx < kTileH * kPO ? oidx : 0];
       const bool chg = ook && now.x != seen;
       if (tid < 32) {
@@ -663,7 +664,7 @@ __global__ __launch_bounds__(256, SG <= 5 ? 3 : 2) void k_sift_sweep(const SiftR
     }
     mem_wait();
     __syncthreads();
-    if (tid < 64) {
+    if (wave0) {
       const int own = relax_done(q, cnt, a.base, tile, nu, g0, handled, (cm & 0xFFFFu) != 0, (cm & 0x7FFF0000u) != 0,
                                  (cm & 0x80000000u) != 0, w);
       bool fresh;
