@@ -36,10 +36,11 @@
 // place on the chip, and one that has not started still owes its first visits.
 // So a launch needs one place to end, however many the chip has left for it:
 // the workgroup that starts last finds all started and drains the queue.
-// What every workgroup
-// shares is kept off the visits: with a ticket and a count of owed visits
-// touched on each of them, one memory channel set the pace of the whole chip
-// (8.8 instead of 6.2 ms per 1024x436 pair).
+// What every workgroup shares is kept off the visits: with a ticket and a count
+// of owed visits touched on each of them, one memory channel set the pace of
+// the whole chip (8.8 instead of 6.2 ms per 1024x436 pair).  The words that
+// count starts are sixteen for the same reason (eight pairs: 1 % slower with 32;
+// SIFT 161x119: 1 % slower with one per 32 workgroups).
 #pragma once
 
 #include "ff_internal.h"
@@ -214,8 +215,9 @@ __device__ __forceinline__ int relax_done(const RelaxQ& q, int32_t* cnt, int bas
     mem_wait();
     pos = __builtin_amdgcn_readfirstlane(pos) + __popcll(rest & ((1ull << lane) - 1));
     if ((rest >> lane) & 1) {
-      // an entry this far behind has been taken by a running workgroup that
-      // is about to clear it
+      // an entry still there is one that a running workgroup holds a ticket
+      // for and is about to take: no more than T tiles are queued at a time, so
+      // later entries have been taken
       int32_t* const slot = q.ring + pos % q.cap;
       const uint64_t t0 = rt_clock();
       for (;;) {
